@@ -46,7 +46,7 @@ __global__ __launch_bounds__(256) void grouped_gemm_f32_kernel(const float* __re
     if (nt == 0) return;
     const int tile = blockIdx.x % nt, nb = blockIdx.x / nt;  // row tiles vary fastest
     if (nb * 16 >= Nout) return;
-    const int e = tile_expert[tile], row0 = tile_row0[tile], rows = tile_rows[tile];
+    const int e = tile_expert[tile], row0 = tile_row0[tile], rows = tile_rows[tile] & kTileRowsMask;
     const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
     const int n0 = nb * 16;
     const float* b0 = B0 + (size_t)e * Nout * K;
@@ -97,7 +97,8 @@ __host__ __device__ constexpr int waitcnt_vm(int n) { return (n & 15) | (7 << 4)
 // from B1_FROM on.  The loads are MUBUF loads with an LDS destination: unlike the global (FLAT-encoded)
 // form, the compiler does not count them against the LDS counter, so the operand reads of the matrix
 // loop keep fine-grained waits; the K advance goes into the scalar offset.
-template <int LOADS, int A_LOADS, int B1_FROM>
+// B_POLICY: cache policy of the weight loads.
+template <int LOADS, int A_LOADS, int B1_FROM, int B_POLICY>
 struct Fills {
     static constexpr int kALoads = A_LOADS;
     __amdgpu_buffer_rsrc_t a, b0, b1;
@@ -105,7 +106,10 @@ struct Fills {
     __device__ __forceinline__ void one(int i, uint8_t* lds_dst, uint32_t k_bytes) const {
         // i is a compile-time constant after unrolling
         const __amdgpu_buffer_rsrc_t r = i < A_LOADS ? a : (i >= B1_FROM ? b1 : b0);
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lptr_t)lds_dst, 16, voff[i], k_bytes, 0, 0);
+        if (i < A_LOADS)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lptr_t)lds_dst, 16, voff[i], k_bytes, 0, 0);
+        else
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lptr_t)lds_dst, 16, voff[i], k_bytes, 0, B_POLICY);
     }
 };
 
@@ -137,7 +141,9 @@ __device__ __forceinline__ void mfma_16x16x32(f32x4& c, const bf16x8& a, const b
 // Loads complete in order, so "all but the last B_LOADS" at barrier kt means the activations and weights of
 // slab kt+1 have landed while the weights of slab kt+2 may still be in flight.  LIVE = number of 16-row
 // activation sub-tiles that are multiplied (the rest lie past the expert's last row).
-template <int BM, int BN, int NW, int TM, int TN, int WTN, bool SWIGLU, int LOADS, class FillsT>
+// STREAM: the walk over K starts at slab k0 + k_start and wraps around at the end of the block's share (see
+// TileConfig16); otherwise k_start is 0.
+template <int BM, int BN, int NW, int TM, int TN, int WTN, bool SWIGLU, int LOADS, bool STREAM, class FillsT>
 struct PipelinedLoop16 {
     static constexpr int BK = 64;
     static constexpr int A_SLOT = BM * 128, B_SLOT = BN * 128, B_BASE = 2 * A_SLOT;
@@ -148,13 +154,20 @@ struct PipelinedLoop16 {
     int a_lane, b_lane;  // byte offset, inside a slot, of this lane's piece of the wave's first row (k-step 0)
     int KT, wv;  // slabs this block multiplies, wave index
     int k0;      // first of them (0 unless the item is cut along K)
+    int k_start;  // STREAM: slab of the share the walk begins with, below KT
 
     // byte offset of weight sub-tile i relative to the wave's first weight row: with SwiGLU the second half
     // of the sub-tiles are the up-projection rows of the same hidden columns
     static __device__ __forceinline__ constexpr int b_tile(int i) {
         return SWIGLU ? ((i / (TN / 2)) * (BN / 2) + (i % (TN / 2)) * 16) * 128 : i * 16 * 128;
     }
-    __device__ __forceinline__ uint32_t k_bytes(int kt) const { return (uint32_t)(kt + k0) * (BK * 2); }
+    __device__ __forceinline__ uint32_t k_bytes(int kt) const {
+        if (STREAM) {
+            kt += k_start;
+            kt = kt < KT ? kt : kt - KT;
+        }
+        return (uint32_t)(kt + k0) * (BK * 2);
+    }
     __device__ __forceinline__ void fill_a(int i, int kt) const {
         fills.one(i, smem + (kt & 1) * A_SLOT + (wv + NW * i) * 1024, k_bytes(kt));
     }
@@ -308,17 +321,29 @@ struct SplitUnit {
 //
 // Two shapes are used: 256 x 256 with 2 x 2 waves (128 x 128 per wave) for full-height row tiles, and
 // 64 x 256 with 1 x 4 waves (64 x 64 per wave) for the short remainders, where the work is weight streaming.
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool SWIGLU>
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool SWIGLU, bool STREAM>
 struct TileConfig16 {
     static constexpr int kBM = BM, kBN = BN;
     static constexpr int kNCols = SWIGLU ? BN / 2 : BN;
     static constexpr int kThreads = 64 * WAVES_M * WAVES_N;
     static constexpr int kLdsBytes = 2 * BM * 128 + 3 * BN * 128;
+    // STREAM: the block's weight rows are read by no other block while they are in the L2: an expert's only row tile,
+    // short or partly filled, and the short tiles that run after all big ones.  Two things bound such a stream, measured
+    // on a read-only kernel with the same fills (256 rows of 128 bytes per slab, 3 GiB):
+    //   - blocks that walk K in step all read at the same offset of a power-of-two row pitch, i.e. from a few memory
+    //     channels: 4.9 TB/s at K = 4096, 5.0 at 2048; with the walk of the blocks starting at different slabs 6.3, 6.0;
+    //   - keeping lines that nobody reads again: with the non-temporal policy on top 7.0, 6.9 (K = 1408, whose pitch
+    //     spreads over the channels by itself: 6.3 -> 7.1).
+    // Whole layers, before -> after: 64 experts x 4096 x 1408 with 37 tokens 392 -> 346 us, with 256 tokens 431 -> 380;
+    // 8 experts x 4096 x 14336 with 16 tokens 503 -> 445; 60 x 2048 x 1408 with 1531 tokens 253 -> 228.
+    // Other tiles share their weight rows with the blocks that run beside them at the same K: neither applies (the
+    // policy on the short tiles of the joint list, whose experts' big tiles run beside them: 1 % slower).
+    static constexpr int kWeightPolicy = STREAM ? 2 : 0;  // bit 1: non-temporal
 
     static __device__ __forceinline__ void run(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B0,
                                                const uint16_t* __restrict__ B1, uint16_t* __restrict__ C,
                                                const int32_t* __restrict__ gather, int e, int row0, int rows, int n0,
-                                               int K, int Nout, uint8_t* smem, const SplitUnit& split) {
+                                               int K, int Nout, bool alone, uint8_t* smem, const SplitUnit& split) {
     constexpr int NW = WAVES_M * WAVES_N;
     constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;
     constexpr int TM = WTM / 16, TN = WTN / 16;
@@ -338,7 +363,7 @@ struct TileConfig16 {
     // 32-bit byte offsets suffice whatever the tensor size; with a gather list the window is the whole
     // unpermuted input, whose size the host checks.
     constexpr int kRsrcFlags = 0x00020000;  // raw buffer of 32-bit words, no swizzle (gfx9 descriptor word 3)
-    using FillsT = Fills<LOADS, A_LOADS, B1_FROM>;
+    using FillsT = Fills<LOADS, A_LOADS, B1_FROM, kWeightPolicy>;
     FillsT fills;
     fills.a = __builtin_amdgcn_make_buffer_rsrc((void*)(gather ? A : A + (size_t)row0 * K), 0, -1, kRsrcFlags);
     fills.b0 = __builtin_amdgcn_make_buffer_rsrc((void*)(B0 + ((size_t)e * Nout + n0) * K), 0, -1, kRsrcFlags);
@@ -381,13 +406,16 @@ struct TileConfig16 {
     int live = (rows - wm * WTM + 31) / 32 * 2;
     live = __builtin_amdgcn_readfirstlane(live < 0 ? 0 : (live > TM ? TM : live));
 
-    using Loop = PipelinedLoop16<BM, BN, NW, TM, TN, WTN, SWIGLU, LOADS, FillsT>;
+    using Loop = PipelinedLoop16<BM, BN, NW, TM, TN, WTN, SWIGLU, LOADS, STREAM, FillsT>;
     static_assert(Loop::LDS_BYTES == kLdsBytes, "LDS size");
     // this block's share of the K slabs: all of them, or slice `split.slice` of `split.slices`
     const int slabs_all = K / 64;
     const int k_first = split.slices > 1 ? (int)((long long)split.slice * slabs_all / split.slices) : 0;
     const int k_end = split.slices > 1 ? (int)((long long)(split.slice + 1) * slabs_all / split.slices) : slabs_all;
-    Loop loop{smem, fills, a_lane, b_lane, k_end - k_first, __builtin_amdgcn_readfirstlane(wv), k_first};
+    // The start of the walk depends on the output columns alone and only moves where the expert has a single tile, so
+    // a row's sums run in the same order whatever other experts share the launch.
+    const int k_start = STREAM && alone ? (int)((long long)n0 * (k_end - k_first) / Nout) : 0;
+    Loop loop{smem, fills, a_lane, b_lane, k_end - k_first, __builtin_amdgcn_readfirstlane(wv), k_first, k_start};
     if (live == TM) {
         switch (loop.wv & 3) {
             case 0: loop.template run<TM, 0>(acc); break;
@@ -532,7 +560,7 @@ __device__ inline void decode_item(int logical, int nt, int col_group, int& tile
 // ones (longest first).  The last split_hdr[0] big items of an XCD's share run as split_hdr[1] units each; the
 // units follow the XCD's whole items in launch order, slice by slice, so that the units that run together read
 // the same K range of the tiles they share.
-template <class Big, class Small, bool SWIGLU>
+template <class Big, class BigAlone, class Small, class SmallShared, bool SWIGLU>
 __global__ __launch_bounds__(Big::kThreads) void ffn_gemm_bf16_kernel(
     const uint16_t* __restrict__ A, const uint16_t* __restrict__ B0, const uint16_t* __restrict__ B1,
     uint16_t* __restrict__ C, const int32_t* __restrict__ gather, const TileListArgs L, int K, int Nout,
@@ -577,11 +605,16 @@ __global__ __launch_bounds__(Big::kThreads) void ffn_gemm_bf16_kernel(
         }
         decode_item(logical, nt, col_group_big, tile, nb);
         const int rows = L.u_rows[tile];
-        if (rows >= kShortTileFlag)
-            Small::run(A, B0, B1, C, gather, L.u_expert[tile], L.u_row0[tile], rows - kShortTileFlag, nb * Small::kNCols,
-                       K, Nout, smem, one);
+        const int e = L.u_expert[tile], row0 = L.u_row0[tile], n0 = nb * Big::kNCols, n_rows = rows & kTileRowsMask;
+        const bool is_short = rows & kShortTileFlag, alone = rows & kAloneTileFlag;
+        if (is_short && alone)
+            Small::run(A, B0, B1, C, gather, e, row0, n_rows, n0, K, Nout, true, smem, one);
+        else if (is_short)  // its expert's big tiles run beside it and read the same weights
+            SmallShared::run(A, B0, B1, C, gather, e, row0, n_rows, n0, K, Nout, false, smem, one);
+        else if (alone)
+            BigAlone::run(A, B0, B1, C, gather, e, row0, n_rows, n0, K, Nout, true, smem, one);
         else
-            Big::run(A, B0, B1, C, gather, L.u_expert[tile], L.u_row0[tile], rows, nb * Big::kNCols, K, Nout, smem, one);
+            Big::run(A, B0, B1, C, gather, e, row0, n_rows, n0, K, Nout, false, smem, one);
         return;
     }
     const int nt_b = *L.b_count, nt_s = *L.s_count;
@@ -596,7 +629,12 @@ __global__ __launch_bounds__(Big::kThreads) void ffn_gemm_bf16_kernel(
         const int logical = xcd * chunk_b + slot;
         if (logical >= total_b) return;
         decode_item(logical, nt_b, col_group_big, tile, nb);
-        Big::run(A, B0, B1, C, gather, b_expert[tile], b_row0[tile], b_rows[tile], nb * Big::kNCols, K, Nout, smem, one);
+        const int rows = b_rows[tile];
+        if (rows & kAloneTileFlag)
+            BigAlone::run(A, B0, B1, C, gather, b_expert[tile], b_row0[tile], rows & kTileRowsMask, nb * Big::kNCols, K, Nout,
+                          true, smem, one);
+        else
+            Big::run(A, B0, B1, C, gather, b_expert[tile], b_row0[tile], rows, nb * Big::kNCols, K, Nout, false, smem, one);
         return;
     }
     slot -= whole;
@@ -610,10 +648,10 @@ __global__ __launch_bounds__(Big::kThreads) void ffn_gemm_bf16_kernel(
         const int logical = xcd * chunk_b + whole + idx;
         if (logical >= total_b) return;
         decode_item(logical, nt_b, col_group_big, tile, nb);
-        const int first = piece * Small::kBM, left = b_rows[tile] - first;
+        const int first = piece * Small::kBM, left = (b_rows[tile] & kTileRowsMask) - first;
         if (left <= 0) return;
         Small::run(A, B0, B1, C, gather, b_expert[tile], b_row0[tile] + first, left < Small::kBM ? left : Small::kBM,
-                   nb * Small::kNCols, K, Nout, smem, one);
+                   nb * Small::kNCols, K, Nout, b_rows[tile] & kAloneTileFlag, smem, one);
         return;
     }
     slot -= in_rows * kRowPieces;
@@ -621,8 +659,8 @@ __global__ __launch_bounds__(Big::kThreads) void ffn_gemm_bf16_kernel(
         const int logical = xcd * chunk_s + slot;
         if (logical >= total_s) return;
         decode_item(logical, nt_s, col_group_small, tile, nb);
-        Small::run(A, B0, B1, C, gather, s_expert[tile], s_row0[tile], s_rows[tile], nb * Small::kNCols, K, Nout, smem,
-                   one);
+        Small::run(A, B0, B1, C, gather, s_expert[tile], s_row0[tile], s_rows[tile] & kTileRowsMask, nb * Small::kNCols, K,
+                   Nout, s_rows[tile] & kAloneTileFlag, smem, one);
         return;
     }
     slot -= whole_s;
@@ -635,7 +673,8 @@ __global__ __launch_bounds__(Big::kThreads) void ffn_gemm_bf16_kernel(
         const SplitUnit su{slices, slice, cut,
                            split_partial + (size_t)(xcd * per_xcd + idx) * ((size_t)Big::kBM * Big::kBN),
                            split_counter + xcd * per_xcd + idx};
-        Big::run(A, B0, B1, C, gather, b_expert[tile], b_row0[tile], b_rows[tile], nb * Big::kNCols, K, Nout, smem, su);
+        Big::run(A, B0, B1, C, gather, b_expert[tile], b_row0[tile], b_rows[tile] & kTileRowsMask, nb * Big::kNCols, K,
+                 Nout, false, smem, su);
         return;
     }
     slot -= units;
@@ -649,8 +688,8 @@ __global__ __launch_bounds__(Big::kThreads) void ffn_gemm_bf16_kernel(
         const SplitUnit su{slices_s, slice, cut_s,
                            region + (size_t)(xcd * per_xcd + idx) * ((size_t)Small::kBM * Small::kBN),
                            split_counter + kFfnSplitUnits + xcd * per_xcd + idx};
-        Small::run(A, B0, B1, C, gather, s_expert[tile], s_row0[tile], s_rows[tile], nb * Small::kNCols, K, Nout, smem,
-                   su);
+        Small::run(A, B0, B1, C, gather, s_expert[tile], s_row0[tile], s_rows[tile] & kTileRowsMask, nb * Small::kNCols, K,
+                   Nout, s_rows[tile] & kAloneTileFlag, smem, su);
     }
 }
 
@@ -668,12 +707,12 @@ static int column_group(int nb_total) {
     return 1;
 }
 
-template <class Big, class Small, bool SWIGLU>
+template <class Big, class BigAlone, class Small, class SmallShared, bool SWIGLU>
 static void launch_bf16(const void* A, const void* B0, const void* B1, void* C, const int32_t* gather,
                         const FfnWorkspace& ws, int K, int Nout, const int32_t* split_hdr, int32_t* split_counter,
                         hipStream_t st) {
     constexpr int lds = Big::kLdsBytes > Small::kLdsBytes ? Big::kLdsBytes : Small::kLdsBytes;
-    auto kern = ffn_gemm_bf16_kernel<Big, Small, SWIGLU>;
+    auto kern = ffn_gemm_bf16_kernel<Big, BigAlone, Small, SmallShared, SWIGLU>;
     static std::atomic<uint64_t> configured{0};
     once_per_device(configured, [&] {
         (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -686,7 +725,9 @@ static void launch_bf16(const void* A, const void* B0, const void* B1, void* C, 
         std::max(2 * kFfnSplitUnits, kFfnJointPoolRounds * compute_units()) + 16;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(Big::kThreads), lds, st, (const uint16_t*)A,
                        (const uint16_t*)B0, (const uint16_t*)B1, (uint16_t*)C, gather, tile_list_args(ws, true), K, Nout,
-                       column_group(nb_b), column_group(nb_s), split_hdr, ws.split_partial, split_counter);
+                       // short items: all column blocks of a tile in a row, so that those that run together start
+                       // their walks over K at different slabs (they share activation rows only)
+                       column_group(nb_b), nb_s, split_hdr, ws.split_partial, split_counter);
 }
 
 // The arguments of the tile schedule for a descriptor and its workspace layout (host side).
@@ -760,18 +801,22 @@ hipError_t launch_grouped_ffn(const moe_desc_t& d, const Sizes& s, const FfnWork
         // full-height row tiles: 256 x 256 blocks; short remainders: 64 x 256 blocks; four waves each
         {
             ProfileScope prof(MOE_KERNEL_FFN_GATE_UP, st);
-            launch_bf16<TileConfig16<kFfnTileM, 256, 2, 2, true>, TileConfig16<kFfnTileSmall, 256, 1, 4, true>,
+            launch_bf16<TileConfig16<kFfnTileM, 256, 2, 2, true, false>, TileConfig16<kFfnTileM, 256, 2, 2, true, true>,
+                        TileConfig16<kFfnTileSmall, 256, 1, 4, true, true>,
+                        TileConfig16<kFfnTileSmall, 256, 1, 4, true, false>,
                         true>(xp, w_gate, w_up, ws.hidden, row_token, ws, K1, N1, split_gu, ws.split_counter, st);
         }
         ProfileScope prof(MOE_KERNEL_FFN_DOWN, st);
         if (bn_down == 256)
-            launch_bf16<TileConfig16<kFfnTileM, 256, 2, 2, false>,
-                        TileConfig16<kFfnTileSmall, 256, 1, 4, false>, false>(ws.hidden, w_down, nullptr, yp, nullptr,
+            launch_bf16<TileConfig16<kFfnTileM, 256, 2, 2, false, false>, TileConfig16<kFfnTileM, 256, 2, 2, false, true>,
+                        TileConfig16<kFfnTileSmall, 256, 1, 4, false, true>,
+                        TileConfig16<kFfnTileSmall, 256, 1, 4, false, false>, false>(ws.hidden, w_down, nullptr, yp, nullptr,
                                                                                     ws, K2, N2, split_dn,
                                                                                     ws.split_counter + 2 * kFfnSplitUnits, st);
         else
-            launch_bf16<TileConfig16<kFfnTileM, 128, 2, 2, false>,
-                        TileConfig16<kFfnTileSmall, 128, 1, 4, false>, false>(ws.hidden, w_down, nullptr, yp, nullptr,
+            launch_bf16<TileConfig16<kFfnTileM, 128, 2, 2, false, false>, TileConfig16<kFfnTileM, 128, 2, 2, false, true>,
+                        TileConfig16<kFfnTileSmall, 128, 1, 4, false, true>,
+                        TileConfig16<kFfnTileSmall, 128, 1, 4, false, false>, false>(ws.hidden, w_down, nullptr, yp, nullptr,
                                                                                     ws, K2, N2, split_dn,
                                                                                     ws.split_counter + 2 * kFfnSplitUnits, st);
     } else {

@@ -44,7 +44,10 @@ struct TileListArgs {
     int32_t *u_expert, *u_row0, *u_rows, *u_count;
     int u_max;
 };
-constexpr int kShortTileFlag = 1 << 16;  // above every tile height
+// Flags beside a tile's row count (tile heights are far below them).
+constexpr int kShortTileFlag = 1 << 16;  // joint list: a short tile
+constexpr int kAloneTileFlag = 1 << 17;  // its expert's only tile
+constexpr int kTileRowsMask = kShortTileFlag - 1;
 
 struct ExpertTiles {
     int lo, rows, nb, ns;
@@ -176,18 +179,19 @@ __device__ inline void build_ffn_schedule(const int32_t* expert_offset, const Ff
         nt_b += __shfl(ib, kWave - 1, kWave);
         nt_s += __shfl(is, kWave - 1, kWave);
         const int start_u = start_b + start_s;
+        const int flag = x.nb + x.ns == 1 ? kAloneTileFlag : 0;
         for (int i = 0; i < x.nb; ++i) {
             const int idx = start_b + i;
             const int left = x.rows - i * big;
             if (idx < L.b_max) {
                 L.b_expert[idx] = e;
                 L.b_row0[idx] = x.lo + i * big;
-                L.b_rows[idx] = left < big ? left : big;
+                L.b_rows[idx] = (left < big ? left : big) | flag;
             }
             if (start_u + i < L.u_max) {
                 L.u_expert[start_u + i] = e;
                 L.u_row0[start_u + i] = x.lo + i * big;
-                L.u_rows[start_u + i] = left < big ? left : big;
+                L.u_rows[start_u + i] = (left < big ? left : big) | flag;
             }
         }
         const int full = x.rows >> big_sh, rem = x.rows - (full << big_sh);
@@ -197,14 +201,14 @@ __device__ inline void build_ffn_schedule(const int32_t* expert_offset, const Ff
                 L.s_expert[idx] = e;
                 L.s_row0[idx] = x.lo + full * big + i * small;
                 const int left = rem - i * small;
-                L.s_rows[idx] = left < small ? left : small;
+                L.s_rows[idx] = (left < small ? left : small) | flag;
             }
             const int ui = start_u + x.nb + i;
             if (ui < L.u_max) {
                 L.u_expert[ui] = e;
                 L.u_row0[ui] = x.lo + full * big + i * small;
                 const int left = rem - i * small;
-                L.u_rows[ui] = (left < small ? left : small) + kShortTileFlag;
+                L.u_rows[ui] = (left < small ? left : small) | kShortTileFlag | flag;
             }
         }
     }

@@ -600,6 +600,32 @@ def test_ffn_joint_tile_list(orc, d, h, counts):
     assert torch.equal(fused.y, buf.y)
 
 
+@pytest.mark.parametrize("d,h", [(128, 128), (384, 640), (1024, 256)])
+def test_ffn_single_tile_experts(orc, d, h):
+    """Experts with one row tile stream their weights with a walk over K that starts at another slab for every column
+    block: short and partly filled big tiles at their edges, beside experts with several tiles, from two slabs of K
+    up.  Every token against the oracle (Eq. 2), and the same bits with the gather fused into the first GEMM."""
+    counts = [1, 63, 64, 65, 130, 255, 256, 257, 320, 321, 0, 33]
+    e, n = len(counts), sum(counts)
+    w = synth.scaled(W["olmoe"], name="alone", n_tokens=n, d_model=d, n_experts=e, top_k=1, d_hidden=h, device_groups=1)
+    layer = DeviceLayer(w)
+    owner = np.repeat(np.arange(e), counts)
+    np.random.default_rng(35).shuffle(owner)
+    logits = np.zeros((n, e), np.float32)
+    logits[np.arange(n), owner] = 6.0
+    ref = orc.route_and_drop(logits, 1, 1, NONE, GLOBAL, 1.0)
+    np.testing.assert_array_equal(ref.plan.expert_count, counts)
+    desc = layer.desc(NONE, GLOBAL, 1.0)
+    buf = run_layer(layer, desc, logits)
+    y_ref = orc.layer_output(layer.x_host, ref.scores, ref.keep, layer.host_gate, layer.host_up, layer.host_down)
+    assert_output_close(to_host_f64(buf.y), y_ref, TOL[w.dtype], "single-tile experts")
+    fused = capmoe.LayerBuffers(desc)
+    capmoe.layer_forward(fused, layer.x, layer.w_router, layer.bias, layer.w_gate, layer.w_up, layer.w_down,
+                         torch.from_numpy(logits).cuda(), fused_dispatch=True)
+    torch.cuda.synchronize()
+    assert torch.equal(fused.y, buf.y)
+
+
 def test_ffn_leftover_items_in_row_pieces(orc):
     """A GEMM too short in K to be cut there, with one big item per XCD left over after a full round (66 big
     tiles x 4 column blocks = 33 items per XCD): the leftover items run as four 64-row blocks each, the last of them
