@@ -19,7 +19,7 @@ constexpr int kWave = 64;
 constexpr int kFfnTileM = 256;      // bf16 MFMA kernels, compute-bound tiles
 constexpr int kFfnTileSmall = 64;   // bf16 MFMA kernels, tail of an expert with at most 64 rows left
 constexpr int kFfnSmallMax = 64;    // a remainder of up to this many rows is one small tile (larger: a partly filled big tile)
-constexpr int kFfnTileMF32 = 16;    // fp32 fallback kernels (tiny layers)
+constexpr int kFfnTileMF32 = 64;    // fp32 kernels
 
 inline size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
@@ -155,6 +155,11 @@ hipError_t launch_combine(const moe_desc_t& d, const Sizes& s, const void* yp, c
 hipError_t launch_grouped_ffn(const moe_desc_t& d, const Sizes& s, const FfnWorkspace& ws, const void* xp,
                               const int32_t* row_token, const int32_t* expert_offset, const void* w_gate,
                               const void* w_up, const void* w_down, void* yp, bool schedule_ready, hipStream_t st);
+// the two products of the fp32 FFN on the tile schedule in ws (launch_grouped_ffn calls them)
+void launch_ffn_gate_up_f32(const moe_desc_t& d, const Sizes& s, const FfnWorkspace& ws, const void* xp,
+                            const int32_t* row_token, const void* w_gate, const void* w_up, hipStream_t st);
+void launch_ffn_down_f32(const moe_desc_t& d, const Sizes& s, const FfnWorkspace& ws, const void* w_down, void* yp,
+                         hipStream_t st);
 // schedule != nullptr (launch_capacity_drop): the drop also builds the tile schedule of the expert GEMMs;
 // schedule_ready (launch_grouped_ffn): it has been built that way, no schedule kernel is launched
 FfnScheduleArgs ffn_schedule_args(const moe_desc_t& d, const FfnWorkspace& ws, int cus);

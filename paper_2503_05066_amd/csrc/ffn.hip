@@ -13,6 +13,7 @@
 // tiles (the bulk of the flops), 64 x 256 blocks of 1 x 4 waves with 64 x 64 wave tiles for the short
 // remainders (weight streaming).  The weight rows feed the MFMA's first operand and the activation
 // rows the second, so a lane ends up with 4 consecutive output columns of one row.
+// The fp32 kernels are in ffn_f32.hip.
 #include <type_traits>
 
 #include "common.h"
@@ -27,50 +28,6 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(64) void ffn_schedule_kernel(const int32_t* __restrict__ expert_offset, FfnScheduleArgs args) {
     build_ffn_schedule(expert_offset, args);
-}
-
-// ---------------------------------------------------------------------------------------------
-// fp32 path (small layers): one 16x16 output tile per block, K walked in slabs of 16.
-// ---------------------------------------------------------------------------------------------
-template <bool SWIGLU>
-__global__ __launch_bounds__(256) void grouped_gemm_f32_kernel(const float* __restrict__ A,
-                                                               const float* __restrict__ B0,
-                                                               const float* __restrict__ B1, float* __restrict__ C,
-                                                               const int32_t* __restrict__ tile_expert,
-                                                               const int32_t* __restrict__ tile_row0,
-                                                               const int32_t* __restrict__ tile_rows,
-                                                               const int32_t* __restrict__ n_tiles,
-                                                               const int32_t* __restrict__ gather, int K, int Nout) {
-    __shared__ float as[16][17], b0s[16][17], b1s[16][17];
-    const int nt = *n_tiles;
-    if (nt == 0) return;
-    const int tile = blockIdx.x % nt, nb = blockIdx.x / nt;  // row tiles vary fastest
-    if (nb * 16 >= Nout) return;
-    const int e = tile_expert[tile], row0 = tile_row0[tile], rows = tile_rows[tile] & kTileRowsMask;
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    const int n0 = nb * 16;
-    const float* b0 = B0 + (size_t)e * Nout * K;
-    const float* b1 = SWIGLU ? B1 + (size_t)e * Nout * K : nullptr;
-    float acc0 = 0.f, acc1 = 0.f;
-    const int arow = ty < rows ? (gather ? gather[row0 + ty] : row0 + ty) : 0;
-    for (int k0 = 0; k0 < K; k0 += 16) {
-        const int kk = k0 + tx;
-        as[ty][tx] = (ty < rows && kk < K) ? A[(size_t)arow * K + kk] : 0.f;
-        b0s[ty][tx] = (n0 + ty < Nout && kk < K) ? b0[(size_t)(n0 + ty) * K + kk] : 0.f;
-        if (SWIGLU) b1s[ty][tx] = (n0 + ty < Nout && kk < K) ? b1[(size_t)(n0 + ty) * K + kk] : 0.f;
-        __syncthreads();
-#pragma unroll
-        for (int c = 0; c < 16; ++c) {
-            acc0 = fmaf(as[ty][c], b0s[tx][c], acc0);
-            if (SWIGLU) acc1 = fmaf(as[ty][c], b1s[tx][c], acc1);
-        }
-        __syncthreads();
-    }
-    if (ty < rows && n0 + tx < Nout) {
-        float out = acc0;
-        if (SWIGLU) out = acc0 / (1.0f + expf(-acc0)) * acc1;
-        C[(size_t)(row0 + ty) * Nout + n0 + tx] = out;
-    }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -787,7 +744,6 @@ void ffn_schedule_on_host(const moe_desc_t& d, const FfnWorkspace& ws, const int
 hipError_t launch_grouped_ffn(const moe_desc_t& d, const Sizes& s, const FfnWorkspace& ws, const void* xp,
                               const int32_t* row_token, const int32_t* expert_offset, const void* w_gate,
                               const void* w_up, const void* w_down, void* yp, bool schedule_ready, hipStream_t st) {
-    (void)s;
     const int K1 = d.d_model, N1 = d.d_hidden, K2 = d.d_hidden, N2 = d.d_model;
     const bool bf16 = d.dtype == MOE_DTYPE_BF16;
     const int bn_down = N2 % 256 == 0 ? 256 : 128;  // d is a multiple of 128 at least: output columns per block
@@ -820,17 +776,8 @@ hipError_t launch_grouped_ffn(const moe_desc_t& d, const Sizes& s, const FfnWork
                                                                                     ws, K2, N2, split_dn,
                                                                                     ws.split_counter + 2 * kFfnSplitUnits, st);
     } else {
-        const dim3 g1(((N1 + 15) / 16) * ws.big.max_tiles), g2(((N2 + 15) / 16) * ws.big.max_tiles);
-        {
-            ProfileScope prof(MOE_KERNEL_FFN_GATE_UP, st);
-            hipLaunchKernelGGL((grouped_gemm_f32_kernel<true>), g1, dim3(256), 0, st, (const float*)xp,
-                               (const float*)w_gate, (const float*)w_up, (float*)ws.hidden, ws.big.expert, ws.big.row0,
-                               ws.big.rows, ws.big.count, row_token, K1, N1);
-        }
-        ProfileScope prof(MOE_KERNEL_FFN_DOWN, st);
-        hipLaunchKernelGGL((grouped_gemm_f32_kernel<false>), g2, dim3(256), 0, st, (const float*)ws.hidden,
-                           (const float*)w_down, (const float*)nullptr, (float*)yp, ws.big.expert, ws.big.row0,
-                           ws.big.rows, ws.big.count, (const int32_t*)nullptr, K2, N2);
+        launch_ffn_gate_up_f32(d, s, ws, xp, row_token, w_gate, w_up, st);
+        launch_ffn_down_f32(d, s, ws, w_down, yp, st);
     }
     return hipGetLastError();
 }

@@ -626,6 +626,37 @@ def test_ffn_single_tile_experts(orc, d, h):
     assert torch.equal(fused.y, buf.y)
 
 
+@pytest.mark.parametrize("d,h,counts", [
+    (4, 1, [1, 0, 5]),                                    # less than one K slab in both products, a single hidden column
+    (64, 33, [16, 17, 64, 65, 1, 0, 31, 48, 49, 130]),    # edges of sub-tiles and tiles; the down product has K = 33
+    (100, 97, [32, 33, 63, 128, 129, 2]),                 # rows whose pitch is no multiple of 16 bytes
+    (160, 250, [300, 7, 200]),                            # several tiles per expert: four-wave blocks
+    (36, 1000, [3, 40, 0, 90, 64, 64]),
+    (1024, 31, [3, 1, 12]),
+])
+def test_ffn_fp32_shapes(orc, d, h, counts):
+    """The fp32 expert products at the edges of their tiles, column blocks and K slabs, permuted rows and fused gather.
+    Both products are fp32 sums of at most 1024 terms: their relative error in the 2-norm is about sqrt(K) 2^-24 < 2e-6."""
+    e, n = len(counts), sum(counts)
+    w = synth.scaled(W["tiny"], name="f32 shapes", n_tokens=n, d_model=d, n_experts=e, top_k=1, d_hidden=h, device_groups=1)
+    layer = DeviceLayer(w)
+    owner = np.repeat(np.arange(e), counts)
+    np.random.default_rng(36).shuffle(owner)
+    logits = np.zeros((n, e), np.float32)
+    logits[np.arange(n), owner] = 6.0
+    ref = orc.route_and_drop(logits, 1, 1, NONE, GLOBAL, 1.0)
+    np.testing.assert_array_equal(ref.plan.expert_count, counts)
+    desc = layer.desc(NONE, GLOBAL, 1.0)
+    buf = run_layer(layer, desc, logits)
+    y_ref = orc.layer_output(layer.x_host, ref.scores, ref.keep, layer.host_gate, layer.host_up, layer.host_down)
+    assert_output_close(to_host_f64(buf.y), y_ref, 1e-5, "fp32 shapes")
+    fused = capmoe.LayerBuffers(desc)
+    capmoe.layer_forward(fused, layer.x, layer.w_router, layer.bias, layer.w_gate, layer.w_up, layer.w_down,
+                         torch.from_numpy(logits).cuda(), fused_dispatch=True)
+    torch.cuda.synchronize()
+    assert torch.equal(fused.y, buf.y)
+
+
 def test_ffn_leftover_items_in_row_pieces(orc):
     """A GEMM too short in K to be cut there, with one big item per XCD left over after a full round (66 big
     tiles x 4 column blocks = 33 items per XCD): the leftover items run as four 64-row blocks each, the last of them
