@@ -5,31 +5,27 @@
 // implementation of the same sequence.
 #include <hip/hip_bf16.h>
 
+#include <type_traits>
+
 #include "common.h"
 
 namespace capmoe {
 
 // ---------------------------------------------------------------------------------------------
-// Router logits: a skinny GEMM [N,d] x [d,E], fp32 accumulation.
+// Router logits of bf16 activations whose width the matrix-core kernel does not take (router_mfma.hip: multiples of
+// 32): a skinny GEMM [N,d] x [d,E], fp32 accumulation.
 // One block computes 64 tokens x all experts; K is walked in slabs of 32 staged in LDS.
 // Thread (ty,tx) of a 16x16 block owns tokens ty*4..+3 and experts tx + 16*i.
 // ---------------------------------------------------------------------------------------------
-template <typename T>
-__device__ inline float load_as_float(const T* p);
-template <>
-__device__ inline float load_as_float<float>(const float* p) {
-    return *p;
-}
-template <>
-__device__ inline float load_as_float<__hip_bfloat16>(const __hip_bfloat16* p) {
+__device__ inline float load_as_float(const __hip_bfloat16* p) {
     return __uint_as_float((uint32_t)(*(const uint16_t*)p) << 16);
 }
 
 constexpr int kRtTokens = 64;
 constexpr int kRtSlab = 32;
 
-template <typename T, int EPT>
-__global__ __launch_bounds__(256) void router_logits_kernel(const T* __restrict__ x, const float* __restrict__ w,
+template <int EPT>
+__global__ __launch_bounds__(256) void router_logits_kernel(const __hip_bfloat16* __restrict__ x, const float* __restrict__ w,
                                                             const float* __restrict__ bias,
                                                             float* __restrict__ logits, int N, int d, int E) {
     extern __shared__ float smem[];
@@ -50,7 +46,7 @@ __global__ __launch_bounds__(256) void router_logits_kernel(const T* __restrict_
         for (int idx = tid; idx < kRtTokens * kRtSlab; idx += 256) {
             const int r = idx >> 5, c = idx & 31;
             const int t = t0 + r, kk = k0 + c;
-            xs[r * (kRtSlab + 1) + c] = (t < N && kk < d) ? load_as_float<T>(x + (size_t)t * d + kk) : 0.f;
+            xs[r * (kRtSlab + 1) + c] = (t < N && kk < d) ? load_as_float(x + (size_t)t * d + kk) : 0.f;
         }
         for (int idx = tid; idx < e_rows * kRtSlab; idx += 256) {
             const int r = idx >> 5, c = idx & 31;
@@ -84,39 +80,166 @@ __global__ __launch_bounds__(256) void router_logits_kernel(const T* __restrict_
     }
 }
 
-template <typename T, int EPT>
-static void launch_rl(const T* x, const float* w, const float* bias, float* logits, int N, int d, int E,
+template <int EPT>
+static void launch_rl(const __hip_bfloat16* x, const float* w, const float* bias, float* logits, int N, int d, int E,
                       hipStream_t st) {
     const int grid = (N + kRtTokens - 1) / kRtTokens;
     const size_t lds = sizeof(float) * (kRtSlab + 1) * (kRtTokens + 16 * EPT);
-    hipLaunchKernelGGL((router_logits_kernel<T, EPT>), dim3(grid), dim3(256), lds, st, x, w, bias, logits, N, d, E);
+    hipLaunchKernelGGL((router_logits_kernel<EPT>), dim3(grid), dim3(256), lds, st, x, w, bias, logits, N, d, E);
 }
 
-template <typename T>
-static void dispatch_rl(const T* x, const float* w, const float* bias, float* logits, int N, int d, int E,
+static void dispatch_rl(const __hip_bfloat16* x, const float* w, const float* bias, float* logits, int N, int d, int E,
                         hipStream_t st) {
     const int ept = (E + 15) / 16;
     if (ept <= 1)
-        launch_rl<T, 1>(x, w, bias, logits, N, d, E, st);
+        launch_rl<1>(x, w, bias, logits, N, d, E, st);
     else if (ept <= 2)
-        launch_rl<T, 2>(x, w, bias, logits, N, d, E, st);
+        launch_rl<2>(x, w, bias, logits, N, d, E, st);
     else if (ept <= 4)
-        launch_rl<T, 4>(x, w, bias, logits, N, d, E, st);
+        launch_rl<4>(x, w, bias, logits, N, d, E, st);
     else if (ept <= 8)
-        launch_rl<T, 8>(x, w, bias, logits, N, d, E, st);
+        launch_rl<8>(x, w, bias, logits, N, d, E, st);
     else if (ept <= 16)
-        launch_rl<T, 16>(x, w, bias, logits, N, d, E, st);
+        launch_rl<16>(x, w, bias, logits, N, d, E, st);
     else
-        launch_rl<T, 32>(x, w, bias, logits, N, d, E, st);
+        launch_rl<32>(x, w, bias, logits, N, d, E, st);
+}
+
+// ---------------------------------------------------------------------------------------------
+// fp32 activations on the matrix cores.  v_mfma_f32_16x16x4_f32 adds its four products as a chain of fused
+// multiply-adds in ascending k (measured bit for bit, subnormal products included), so a logit is the same chain over
+// the whole of K, in order, as one thread adding product after product: K is not split, whatever the size of the batch.
+//
+// The chain is what bounds it (32 cycles per four k; 1024 k 3.4 us) as long as the slabs arrive in time: WT x WE waves take
+// 16 tokens x 16 experts each, slabs of 64 k are fetched as whole cache lines, wait R deep in registers and pass through
+// one of two LDS buffers (rows of 68 words: the reads of an instruction, 16 rows x 4 words, then fall into 64 banks).
+// 1024 tokens x 1024, 16 experts: 138 -> MEAS us against 64 x 16 outputs per block on vector instructions.
+// ---------------------------------------------------------------------------------------------
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4), aligned(4))) float f32x4u;  // x may start at any float
+
+constexpr int kRfSlab = 64;   // k per LDS buffer
+constexpr int kRfPitch = 68;  // words of a row in LDS
+
+template <int WT, int WE>
+__global__ __launch_bounds__(64 * WT * WE) void router_logits_f32_kernel(const float* __restrict__ x,
+                                                                         const float* __restrict__ w,
+                                                                         const float* __restrict__ bias,
+                                                                         float* __restrict__ logits, int N, int d, int E) {
+    constexpr int kThreads = 64 * WT * WE, kRows = 16 * (WT + WE);  // token rows, then expert rows
+    constexpr int kLoads = kRows * (kRfSlab / 4) / kThreads;        // 16-byte pieces a thread fetches per slab
+    constexpr int R = 4;
+    static_assert(kRows * (kRfSlab / 4) % kThreads == 0, "whole rounds of loads");
+    __shared__ __attribute__((aligned(16))) float buf[2][kRows * kRfPitch];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int lr = lane & 15, p = lane >> 4;
+    const int t0 = blockIdx.x * 16 * WT, e0 = blockIdx.y * 16 * WE;
+    const float* src[kLoads];
+    int dst[kLoads], kc[kLoads];
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+        const int idx = tid + kThreads * i, r = idx / (kRfSlab / 4);
+        kc[i] = idx % (kRfSlab / 4) * 4;
+        dst[i] = r * kRfPitch + kc[i];
+        // rows past the last token or expert repeat it and are not stored
+        const int t = t0 + r < N ? t0 + r : N - 1, e = e0 + r - 16 * WT < E ? e0 + r - 16 * WT : E - 1;
+        src[i] = (r < 16 * WT ? x + (size_t)t * d : w + (size_t)e * d) + kc[i];
+    }
+    const int full = d / kRfSlab, rest = d - full * kRfSlab;  // rest: a multiple of four
+    f32x4 ring[R][kLoads];
+    auto request = [&](int u, int s) {  // past the last whole slab: that one again
+        const int at = (s < full ? s : full - 1) * kRfSlab;
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) ring[u][i] = *(const f32x4u*)(src[i] + at);
+    };
+    const float* a_row = &buf[0][(16 * WT + (wv % WE) * 16 + lr) * kRfPitch + p];  // experts: the first operand
+    const float* b_row = &buf[0][(wv / WE * 16 + lr) * kRfPitch + p];
+    constexpr int kBuf = kRows * kRfPitch;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    f32x4 last[kLoads];  // what d leaves after its whole slabs (a piece lies inside a row or past its end)
+    if (rest > 0) {
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i)
+            last[i] = *(const f32x4u*)(src[i] + (kc[i] < rest ? full * kRfSlab : full * kRfSlab - kc[i] + rest - 4));
+    }
+    if (full > 0) {
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            __builtin_amdgcn_sched_barrier(0);
+            request(u, u);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        // buffer s & 1 was last read two slabs ago, and every wave has passed a barrier since
+        auto slab = [&](auto u_c, auto refill_c, int s) {
+            constexpr int u = decltype(u_c)::value;
+            float* here = &buf[0][(u & 1) * kBuf];
+#pragma unroll
+            for (int i = 0; i < kLoads; ++i) *(f32x4*)(here + dst[i]) = ring[u][i];
+            __builtin_amdgcn_sched_barrier(0);
+            if (decltype(refill_c)::value) request(u, s + R);
+            __builtin_amdgcn_sched_barrier(0);
+            __syncthreads();
+            const float *a = a_row + (u & 1) * kBuf, *b = b_row + (u & 1) * kBuf;
+            float av[kRfSlab / 4], bv[kRfSlab / 4];
+#pragma unroll
+            for (int q = 0; q < kRfSlab / 4; ++q) {
+                av[q] = a[4 * q];
+                bv[q] = b[4 * q];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < kRfSlab / 4; ++q) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[q], bv[q], acc, 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        const std::integral_constant<int, 0> c0{};
+        const std::integral_constant<int, 1> c1{};
+        const std::integral_constant<int, 2> c2{};
+        const std::integral_constant<int, 3> c3{};
+        int s = 0;
+        for (; s + R <= full; s += R) {  // no branch inside: the compiler's wait counts stay exact
+            slab(c0, std::true_type{}, s);
+            slab(c1, std::true_type{}, s + 1);
+            slab(c2, std::true_type{}, s + 2);
+            slab(c3, std::true_type{}, s + 3);
+        }
+        if (s < full) slab(c0, std::false_type{}, s);
+        if (s + 1 < full) slab(c1, std::false_type{}, s + 1);
+        if (s + 2 < full) slab(c2, std::false_type{}, s + 2);
+    }
+    if (rest > 0) {
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) *(f32x4*)(&buf[0][(full & 1) * kBuf + dst[i]]) = last[i];
+        __syncthreads();
+        for (int q = 0; q < rest / 4; ++q)
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a_row[(full & 1) * kBuf + 4 * q], b_row[(full & 1) * kBuf + 4 * q], acc,
+                                                       0, 0, 0);
+    }
+    // lane: four consecutive experts of token lr
+    const int t = t0 + wv / WE * 16 + lr, e = e0 + wv % WE * 16 + 4 * p;
+    if (t < N) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (e + v < E) logits[(size_t)t * E + e + v] = acc[v] + (bias ? bias[e + v] : 0.f);
+    }
+}
+
+static void launch_router_f32(const float* x, const float* w, const float* bias, float* logits, int N, int d, int E,
+                              hipStream_t st) {
+    if (E <= 16)
+        hipLaunchKernelGGL((router_logits_f32_kernel<1, 1>), dim3((N + 15) / 16), dim3(64), 0, st, x, w, bias, logits, N, d,
+                           E);
+    else
+        hipLaunchKernelGGL((router_logits_f32_kernel<2, 2>), dim3((N + 31) / 32, (E + 31) / 32), dim3(256), 0, st, x, w, bias,
+                           logits, N, d, E);
 }
 
 hipError_t launch_router_logits(const moe_desc_t& d, const void* x, const float* w, const float* bias, float* logits,
                                 hipStream_t st) {
     ProfileScope prof(MOE_KERNEL_ROUTER_LOGITS, st);
     if (d.dtype == MOE_DTYPE_BF16)
-        dispatch_rl<__hip_bfloat16>((const __hip_bfloat16*)x, w, bias, logits, d.n_tokens, d.d_model, d.n_experts, st);
+        dispatch_rl((const __hip_bfloat16*)x, w, bias, logits, d.n_tokens, d.d_model, d.n_experts, st);
     else
-        dispatch_rl<float>((const float*)x, w, bias, logits, d.n_tokens, d.d_model, d.n_experts, st);
+        launch_router_f32((const float*)x, w, bias, logits, d.n_tokens, d.d_model, d.n_experts, st);
     return hipGetLastError();
 }
 

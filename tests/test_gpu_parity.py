@@ -117,6 +117,33 @@ def test_router_logits_shapes(orc, n, d, e):
     assert np.abs(got - ref).max() <= 1e-4 * np.abs(ref).max()
 
 
+@pytest.mark.parametrize("n,d,e", [
+    (1, 4, 1), (15, 60, 16), (16, 64, 17), (33, 68, 8),        # below, at and above one K slab; edges of both tilings
+    (31, 252, 33), (64, 256, 32), (70, 320, 100), (32, 324, 16),  # the ring of four slabs: not full, full, once around
+    (130, 1024, 10),
+])
+def test_router_logits_fp32_chain(n, d, e):
+    """A logit of fp32 activations is the chain of fused multiply-adds over ascending k, rounded once per product: bit for
+    bit, so that equal inputs route alike whatever the batch they come in.  The reference chain adds in 64-bit
+    significands, which hold every product exactly."""
+    rng = np.random.default_rng(n * 1000 + d + e)
+    x, wr = rng.standard_normal((n, d)).astype(np.float32), rng.standard_normal((e, d)).astype(np.float32)
+    b = rng.standard_normal(e).astype(np.float32)
+    ref = np.zeros((n, e), np.float32)
+    for k in range(d):
+        prod = x[:, None, k].astype(np.longdouble) * wr[None, :, k].astype(np.longdouble)
+        ref = (ref.astype(np.longdouble) + prod).astype(np.float32)
+    ref = ref + b
+    desc = capmoe.make_desc(n, d, e, 1, 8, 1, NONE, LOCAL, 1.0, synth.DTYPE_F32)
+    buf = capmoe.LayerBuffers(desc)
+    storage = torch.zeros(n * d + 1, device="cuda")
+    for x_dev in (torch.from_numpy(x).cuda(), storage[1:].view(n, d).copy_(torch.from_numpy(x))):   # also from an odd float
+        capmoe.moe_route_topk(desc, x_dev, torch.from_numpy(wr).cuda(), torch.from_numpy(b).cuda(), 0, buf.logits,
+                              buf.scores, buf.topk_idx, buf.topk_score, buf.workspace)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(buf.logits.cpu().numpy().view(np.uint32), ref.view(np.uint32))
+
+
 # ------------------------------------------------------------------------------------------------
 # scores, top-k and the dispatch plan, bit-exact from identical logits
 # ------------------------------------------------------------------------------------------------
