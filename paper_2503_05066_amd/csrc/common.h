@@ -155,6 +155,10 @@ hipError_t launch_combine(const moe_desc_t& d, const Sizes& s, const void* yp, c
 hipError_t launch_grouped_ffn(const moe_desc_t& d, const Sizes& s, const FfnWorkspace& ws, const void* xp,
                               const int32_t* row_token, const int32_t* expert_offset, const void* w_gate,
                               const void* w_up, const void* w_down, void* yp, bool schedule_ready, hipStream_t st);
+// the two products of the bf16 FFN for batches whose tiles have few rows (launch_grouped_ffn asks and calls)
+bool ffn_is_thin(const moe_desc_t& d, const Sizes& s);
+void launch_ffn_thin(const moe_desc_t& d, const Sizes& s, const FfnWorkspace& ws, const void* xp, const int32_t* row_token,
+                     const void* w_gate, const void* w_up, const void* w_down, void* yp, hipStream_t st);
 // the two products of the fp32 FFN on the tile schedule in ws (launch_grouped_ffn calls them)
 void launch_ffn_gate_up_f32(const moe_desc_t& d, const Sizes& s, const FfnWorkspace& ws, const void* xp,
                             const int32_t* row_token, const void* w_gate, const void* w_up, hipStream_t st);

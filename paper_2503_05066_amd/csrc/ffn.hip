@@ -13,7 +13,7 @@
 // tiles (the bulk of the flops), 64 x 256 blocks of 1 x 4 waves with 64 x 64 wave tiles for the short
 // remainders (weight streaming).  The weight rows feed the MFMA's first operand and the activation
 // rows the second, so a lane ends up with 4 consecutive output columns of one row.
-// The fp32 kernels are in ffn_f32.hip.
+// The fp32 kernels are in ffn_f32.hip, those of the smallest bf16 batches in ffn_thin.hip.
 #include <type_traits>
 
 #include "common.h"
@@ -751,7 +751,9 @@ hipError_t launch_grouped_ffn(const moe_desc_t& d, const Sizes& s, const FfnWork
         ProfileScope prof(MOE_KERNEL_FFN_SCHEDULE, st);
         hipLaunchKernelGGL(ffn_schedule_kernel, dim3(1), dim3(64), 0, st, expert_offset, ffn_schedule_args(d, ws, compute_units()));
     }
-    if (bf16) {
+    if (ffn_is_thin(d, s)) {
+        launch_ffn_thin(d, s, ws, xp, row_token, w_gate, w_up, w_down, yp, st);
+    } else if (bf16) {
         const int32_t* split_gu = ws.split_hdr;
         const int32_t* split_dn = ws.split_hdr + kFfnSplitHdr;
         // full-height row tiles: 256 x 256 blocks; short remainders: 64 x 256 blocks; four waves each
