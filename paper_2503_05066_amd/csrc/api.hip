@@ -79,6 +79,9 @@ DropWorkspace drop_workspace(const moe_desc_t& d, const Sizes& s, void* base) {
     off += align256(segs * 4);
     w.seg_need = (int32_t*)(p + off);
     off += align256(segs * 4);
+    const size_t big = drop_big_state_bytes(d, s);
+    w.big_state = big > 0 ? p + off : nullptr;
+    off += align256(big);
     w.bytes = off;
     return w;
 }

@@ -46,8 +46,10 @@ struct DropWorkspace {
     uint8_t* slot_t;    // [E,N]  slot of the pair in the token's candidate list
     uint32_t* seg_tau;  // [B*E]  threshold key of the segment
     int32_t* seg_need;  // [B*E]  how many candidates equal to the threshold are kept
+    void* big_state;    // histograms of segments that many blocks share, or null (drop.hip)
     size_t bytes;
 };
+size_t drop_big_state_bytes(const moe_desc_t& d, const Sizes& s);
 DropWorkspace drop_workspace(const moe_desc_t& d, const Sizes& s, void* base);
 
 // Workspace layout of moe_route_topk (bf16 activations: router GEMM on the matrix cores, split over K).

@@ -46,7 +46,16 @@ __global__ __launch_bounds__(256) void drop_prepare_kernel(const float* __restri
                                                            int32_t* __restrict__ pair_row, int N, int E, int k, int S,
                                                            int expanded, int group_tokens, int group_experts,
                                                            int metric, int seg_tokens,
-                                                           const uint8_t* __restrict__ token_class, uint32_t seed) {
+                                                           const uint8_t* __restrict__ token_class, uint32_t seed,
+                                                           uint32_t* __restrict__ clear, long long clear_words,
+                                                           int32_t* __restrict__ clear_count,
+                                                           int32_t* __restrict__ clear_need, int segs) {
+    // what the launches that share segments among blocks add to (clear_words == 0: nothing)
+    if (clear_words > 0) {
+        for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < clear_words; i += (long long)gridDim.x * 256)
+            clear[i] = 0u;
+        for (int i = blockIdx.x * 256 + threadIdx.x; i < segs; i += gridDim.x * 256) clear_count[i] = clear_need[i] = 0;
+    }
     extern __shared__ uint32_t lds[];
     const int ld = E | 1;                                  // odd row pitch: conflict-free transposed reads
     uint32_t* key_s = lds;                                 // [kPrepTokens][ld] score bits, then keys
@@ -168,8 +177,6 @@ __device__ __forceinline__ void static_for(F&& f) {
 // ---------------------------------------------------------------------------------------------
 // 2. threshold per segment
 // ---------------------------------------------------------------------------------------------
-constexpr int kSelectCache = 32768;  // keys of a segment kept in LDS (up to 128 KB); longer segments re-read L2
-
 // One block per capacity segment: `span` experts (1, or the E/G experts of a device when the
 // capacity is a device budget) over seg_tokens tokens.  The keys of expert e0+r form run r.
 // Outputs, per (block, expert): the threshold, how many keys equal to it survive, the kept count.
@@ -178,17 +185,15 @@ constexpr int kSelectCache = 32768;  // keys of a segment kept in LDS (up to 128
 // NT threads: 256 for short segments, 1024 for long ones (a segment is one block's work, and its
 // passes over the keys are chains of load latencies that only more loads in flight shorten).
 // VEC keys per load: 4 when every run starts on a 16-byte boundary (N and seg_tokens multiples of 4).
-// HELD: the segment has at most NT * VEC * kSelectBatch<NT> keys (65536 keys of 8192 tokens x 8 experts, Random metric:
-// 43 -> 34 us; 3000 tokens 9.5 -> 6.9; held segments use no LDS cache).
-template <int NT>
-constexpr int kSelectBatch = NT > 256 ? 16 : 8;
-template <int NT, int VEC, bool HELD>
+// The threads keep the segment's keys in registers, VEC * BATCH each, and only the first pass loads
+// them (from L2 or LDS in every pass: 65536 keys of 8192 tokens x 8 experts 43 -> 34 us, 3000 tokens 9.5 -> 6.9).
+// Longer segments: drop_big_hist_kernel and what follows it.
+template <int NT, int VEC, int BATCH>
 __global__ __launch_bounds__(NT) void drop_select_kernel(const uint32_t* __restrict__ key_t,
                                                           uint32_t* __restrict__ seg_tau,
                                                           int32_t* __restrict__ seg_need,
                                                           int32_t* __restrict__ seg_count, int N, int E, int seg_tokens,
                                                           int span, int cap) {
-    extern __shared__ __attribute__((aligned(16))) uint32_t cache[];
     __shared__ int hist[256];
     __shared__ int gt_s[kMaxExperts], eq_s[kMaxExperts];
     __shared__ int red[NT / kWave];
@@ -199,73 +204,49 @@ __global__ __launch_bounds__(NT) void drop_select_kernel(const uint32_t* __restr
     const uint32_t* keys = key_t + (size_t)e0 * N + (size_t)b * seg_tokens;  // run r starts at keys + r*N
     const int tid = threadIdx.x;
     const int n_keys = span * seg_tokens;
-    const bool cached = !HELD && n_keys <= kSelectCache;
+    if (cap == 0) {  // nothing passes
+        for (int r = tid; r < span; r += NT) {
+            seg_tau[b * E + e0 + r] = 0xffffffffu;
+            seg_need[b * E + e0 + r] = seg_count[b * E + e0 + r] = 0;
+        }
+        return;
+    }
 
-    // Every pass walks all keys of the segment, key i = run i / seg_tokens, token i % seg_tokens: a thread
-    // requests kBatch loads of VEC keys before it uses any, then calls f(run, token, key) key by key (in
-    // ascending i per thread).
-    // HELD: one batch covers the segment, and the threads keep its keys in registers.
-    constexpr int kBatch = kSelectBatch<NT>;
+    // Every pass walks all keys of the segment, key i = run i / seg_tokens, token i % seg_tokens, and calls
+    // f(run, token, key) key by key, in ascending i per thread.
     struct alignas(4 * VEC) KeyVec {
         uint32_t c[VEC];
     };
-    uint32_t held[HELD ? kBatch * VEC : 1];
-    if constexpr (HELD)
-        static_for<kBatch>([&](auto uc) __attribute__((always_inline)) {
+    uint32_t held[BATCH * VEC];
+    static_for<BATCH>([&](auto uc) __attribute__((always_inline)) {
+        constexpr int u = decltype(uc)::value;
+        const int i = tid * VEC + NT * VEC * u;  // VEC divides seg_tokens: the keys of a load share a run
+        const int run = span == 1 ? 0 : i / seg_tokens;
+        // no branch, so that all loads are under way together; past the end: key 0, not used
+        const size_t at = i < n_keys ? (size_t)run * N + (i - run * seg_tokens) : 0;
+        const KeyVec v = *(const KeyVec*)(keys + at);
+        static_for<VEC>([&](auto cc) __attribute__((always_inline)) {
+            held[u * VEC + decltype(cc)::value] = v.c[decltype(cc)::value];
+        });
+    });
+    auto for_each_key = [&](auto&& f) __attribute__((always_inline)) {
+        static_for<BATCH>([&](auto uc) __attribute__((always_inline)) {
             constexpr int u = decltype(uc)::value;
             const int i = tid * VEC + NT * VEC * u, run = span == 1 ? 0 : i / seg_tokens;
-            const size_t at = i < n_keys ? (size_t)run * N + (i - run * seg_tokens) : 0;  // (key 0 of the segment)
-            const KeyVec v = *(const KeyVec*)(keys + at);
-            static_for<VEC>([&](auto cc) __attribute__((always_inline)) {
-                held[u * VEC + decltype(cc)::value] = v.c[decltype(cc)::value];
-            });
+            if (i < n_keys)
+                static_for<VEC>([&](auto cc) __attribute__((always_inline)) {
+                    constexpr int c = decltype(cc)::value;
+                    f(run, i - run * seg_tokens + c, held[u * VEC + c]);
+                });
         });
-    auto for_each_key = [&](bool from_cache, auto&& f) __attribute__((always_inline)) {
-        if constexpr (HELD) {
-            static_for<kBatch>([&](auto uc) __attribute__((always_inline)) {
-                constexpr int u = decltype(uc)::value;
-                const int i = tid * VEC + NT * VEC * u, run = span == 1 ? 0 : i / seg_tokens;
-                if (i < n_keys)
-                    static_for<VEC>([&](auto cc) __attribute__((always_inline)) {
-                        constexpr int c = decltype(cc)::value;
-                        f(run, i - run * seg_tokens + c, held[u * VEC + c]);
-                    });
-            });
-            return;
-        }
-        for (int i0 = tid * VEC; i0 < n_keys; i0 += NT * VEC * kBatch) {
-            KeyVec kx[kBatch];
-            int run[kBatch], tok[kBatch];
-#pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                const int i = i0 + NT * VEC * u;  // VEC divides seg_tokens: the keys of a load share a run
-                run[u] = span == 1 ? 0 : i / seg_tokens;  // (a division is as much work as four keys)
-                tok[u] = i - run[u] * seg_tokens;
-                if (i >= n_keys) {
-#pragma unroll
-                    for (int c = 0; c < VEC; ++c) kx[u].c[c] = 0u;
-                } else if (from_cache) {
-                    kx[u] = *(const KeyVec*)(cache + i);
-                } else {
-                    kx[u] = *(const KeyVec*)(keys + (size_t)run[u] * N + tok[u]);
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < kBatch; ++u)
-                if (i0 + NT * VEC * u < n_keys) {
-#pragma unroll
-                    for (int c = 0; c < VEC; ++c) f(run[u], tok[u] + c, kx[u].c[c]);
-                }
-        }
     };
 
-    // load the keys; the histogram of their top byte (the first radix pass) is taken on the way
+    // the histogram of the keys' top byte (the first radix pass)
     if (tid < 256) hist[tid] = 0;
     for (int r = tid; r < span; r += NT) gt_s[r] = eq_s[r] = 0;
     __syncthreads();
     int mine = 0;
-    for_each_key(false, [&](int r, int tl, uint32_t key) {
-        if (cached) cache[r * seg_tokens + tl] = key;
+    for_each_key([&](int, int, uint32_t key) {
         if (key != 0u) {  // non-candidates (key 0) never matter
             ++mine;
             atomicAdd(&hist[key >> 24], 1);
@@ -276,9 +257,7 @@ __global__ __launch_bounds__(NT) void drop_select_kernel(const uint32_t* __restr
     // threshold: keys above tau are kept, `rem` of the keys equal to tau are kept
     uint32_t tau = 0;  // every candidate (key >= 1) passes
     int rem = 0;
-    if (cap == 0) {
-        tau = 0xffffffffu;  // nothing passes
-    } else if (n_cand > cap) {
+    if (n_cand > cap) {
         // cap-th largest key, most significant byte first
         uint32_t prefix = 0;
         rem = cap;
@@ -290,7 +269,7 @@ __global__ __launch_bounds__(NT) void drop_select_kernel(const uint32_t* __restr
                 auto count_digit = [&](int, int, uint32_t key) {
                     if (key != 0u && (key & hi_mask) == prefix) atomicAdd(&hist[(key >> shift) & 255u], 1);
                 };
-                for_each_key(cached, count_digit);
+                for_each_key(count_digit);
                 __syncthreads();
             }
             // thread i < 256 owns digit 255 - i: an exclusive scan over threads counts the keys with a larger
@@ -314,14 +293,14 @@ __global__ __launch_bounds__(NT) void drop_select_kernel(const uint32_t* __restr
             const int seg = b * E + e0;
             seg_tau[seg] = tau;
             seg_need[seg] = rem;
-            seg_count[seg] = cap == 0 ? 0 : (n_cand > cap ? cap : n_cand);
+            seg_count[seg] = n_cand > cap ? cap : n_cand;
         }
         return;
     }
     // per expert: keys above the threshold and keys equal to it (a thread's keys change run rarely)
     auto count_runs = [&](int tie_token, int tie_run) __attribute__((always_inline)) {
         int run = -1, gt = 0, eq = 0;
-        for_each_key(cached, [&](int r, int tl, uint32_t key) {
+        for_each_key([&](int r, int tl, uint32_t key) {
             if (r != run) {
                 if (gt) atomicAdd(&gt_s[run], gt);
                 if (eq) atomicAdd(&eq_s[run], eq);
@@ -346,7 +325,7 @@ __global__ __launch_bounds__(NT) void drop_select_kernel(const uint32_t* __restr
         const int per = (seg_tokens + NT - 1) / NT;
         const int tb = tid * per < seg_tokens ? tid * per : seg_tokens;
         const int te = tb + per < seg_tokens ? tb + per : seg_tokens;
-        auto key_at = [&](int r, int tl) { return cached ? cache[r * seg_tokens + tl] : keys[(size_t)r * N + tl]; };
+        auto key_at = [&](int r, int tl) { return keys[(size_t)r * N + tl]; };
         int c = 0;
         for (int tl = tb; tl < te; ++tl)
             for (int r = 0; r < span; ++r) c += key_at(r, tl) == tau;
@@ -374,6 +353,206 @@ __global__ __launch_bounds__(NT) void drop_select_kernel(const uint32_t* __restr
         seg_need[seg] = eq_s[tid];  // inside an expert the granted keys are its first ones in token order
         seg_count[seg] = gt_s[tid] + eq_s[tid];
     }
+}
+
+// ---------------------------------------------------------------------------------------------
+// 2b. threshold of segments that one block would walk for long
+// ---------------------------------------------------------------------------------------------
+// A device budget makes one segment of all keys of a device's experts, a million and more with a single device.  One block
+// needs a pass over them per radix digit and another for the counts, at one compute unit's bandwidth.  Here many
+// blocks share a segment: three launches build the histograms of an 11, 11 and 10 bit digit (every block first picks the
+// digit before it from the histogram of the launch before), one counts per expert, one small one settles ties.  Integer
+// atomics throughout: the same numbers run to run.  Which segments come here: launch_capacity_drop.
+constexpr int kBigChunk = 8192;   // keys (or tokens of a run) of a block
+constexpr int kBigBins = 2048;    // of a level
+struct BigState {                 // of a segment; cleared by drop_prepare_kernel
+    uint32_t hist[3][kBigBins];
+    uint32_t prefix[2];           // digits picked after the first and the second level
+    int32_t rem[3];               // keys of the prefix still to keep; after the last level: of the threshold
+    int32_t eq_total;             // keys equal to the threshold
+    int32_t first_eq, last_eq;    // seg_tokens - the lowest token with such a key, 1 + the highest
+    int32_t pad[4];
+};
+static_assert(sizeof(BigState) % 16 == 0, "whole words");
+
+// The digit of `hist` in which the rem-th key from above lies, for the whole block of 256 threads: *digit, and in *left how
+// many of that digit's keys are kept.  All counts together are *total; with fewer than rem keys *digit stays -1.
+__device__ inline void pick_digit(const uint32_t* hist, int rem, int* digit, int* left, int* total, int* red) {
+    __shared__ int sh_digit, sh_left;
+    constexpr int kPer = kBigBins / 256;
+    if (threadIdx.x == 0) sh_digit = -1;
+    int h[kPer], sum = 0;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {  // thread i owns the digits from kBigBins - 1 - kPer * i downwards
+        h[j] = (int)hist[kBigBins - 1 - (threadIdx.x * kPer + j)];
+        sum += h[j];
+    }
+    int above = block_exclusive_scan_256(sum, red, total);  // its barriers order the reset before the writes
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        if (above < rem && above + h[j] >= rem) {  // one digit of one thread at most
+            sh_digit = kBigBins - 1 - (threadIdx.x * kPer + j);
+            sh_left = rem - above;
+        }
+        above += h[j];
+    }
+    __syncthreads();
+    *digit = sh_digit;
+    *left = sh_left;
+    __syncthreads();
+}
+
+template <int VEC>
+struct alignas(4 * VEC) BigVec {
+    uint32_t c[VEC];
+};
+
+// LEVEL: digit counted here, 0 (bits 31-21), 1 (20-10) or 2 (9-0)
+template <int LEVEL, int VEC>
+__global__ __launch_bounds__(256) void drop_big_hist_kernel(const uint32_t* __restrict__ key_t, BigState* __restrict__ state,
+                                                            int N, int E, int seg_tokens, int span, int cap, int chunks) {
+    __shared__ int hist[kBigBins];
+    __shared__ int red[4];
+    const int ds = blockIdx.x / chunks, chunk = blockIdx.x - ds * chunks, groups = E / span;
+    const int b = ds / groups, e0 = (ds - b * groups) * span, tid = threadIdx.x;
+    const uint32_t* keys = key_t + (size_t)e0 * N + (size_t)b * seg_tokens;
+    const long long n_keys = (long long)span * seg_tokens;
+    BigState* st = state + ds;
+    constexpr int kLoads = kBigChunk / 256 / VEC;
+    BigVec<VEC> v[kLoads];
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u) {  // requested before the pick waits
+        const long long i = (long long)chunk * kBigChunk + (tid + 256 * u) * VEC;
+        const int run = (int)(i / seg_tokens);  // VEC divides seg_tokens: the keys of a load share a run
+        if (i < n_keys) {
+            v[u] = *(const BigVec<VEC>*)(keys + (size_t)run * N + (i - (long long)run * seg_tokens));
+        } else {
+#pragma unroll
+            for (int c = 0; c < VEC; ++c) v[u].c[c] = 0u;
+        }
+    }
+    for (int i = tid; i < kBigBins; i += 256) hist[i] = 0;
+    uint32_t prefix = 0;
+    if (LEVEL > 0) {
+        int digit, left, total;
+        const int rem = LEVEL == 1 ? cap : st->rem[0];
+        if (LEVEL == 2 && rem == 0) return;  // every candidate passes: nothing to pick
+        pick_digit(st->hist[LEVEL - 1], rem, &digit, &left, &total, red);
+        if (LEVEL == 1 && total <= cap) return;  // rem stays 0
+        prefix = LEVEL == 1 ? (uint32_t)digit << 21 : st->prefix[0] | ((uint32_t)digit << 10);
+        if (chunk == 0 && tid == 0) {
+            st->prefix[LEVEL - 1] = prefix;
+            st->rem[LEVEL - 1] = left;
+        }
+    }
+    __syncthreads();
+    constexpr uint32_t kMask = LEVEL == 0 ? 0u : (LEVEL == 1 ? 0xffe00000u : 0xfffffc00u);
+    constexpr int kShift = LEVEL == 0 ? 21 : (LEVEL == 1 ? 10 : 0);
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u)
+#pragma unroll
+        for (int c = 0; c < VEC; ++c) {
+            const uint32_t key = v[u].c[c];  // non-candidates (key 0) never matter
+            if (key != 0u && (key & kMask) == prefix) atomicAdd(&hist[(key >> kShift) & (LEVEL == 2 ? 1023u : 2047u)], 1);
+        }
+    __syncthreads();
+    for (int i = tid; i < kBigBins; i += 256)
+        if (hist[i]) atomicAdd(&st->hist[LEVEL][i], (uint32_t)hist[i]);
+}
+
+// Keys above and equal to the threshold, per expert: sums in seg_count and seg_need (cleared before).
+__global__ __launch_bounds__(256) void drop_big_count_kernel(const uint32_t* __restrict__ key_t, BigState* __restrict__ state,
+                                                             uint32_t* __restrict__ seg_tau, int32_t* __restrict__ seg_need,
+                                                             int32_t* __restrict__ seg_count, int N, int E, int seg_tokens,
+                                                             int span, int parts) {
+    __shared__ int red[4];
+    __shared__ int lo, hi;
+    const int seg = blockIdx.x / parts, part = blockIdx.x - seg * parts;
+    const int b = seg / E, e = seg - b * E, ds = b * (E / span) + e / span, tid = threadIdx.x;
+    const uint32_t* keys = key_t + (size_t)e * N + (size_t)b * seg_tokens;
+    BigState* st = state + ds;
+    uint32_t tau = 0;  // every candidate (key >= 1) passes
+    if (tid == 0) lo = hi = 0;
+    if (st->rem[0] > 0) {
+        int digit, left, total;
+        pick_digit(st->hist[2], st->rem[1], &digit, &left, &total, red);
+        tau = st->prefix[1] | (uint32_t)digit;
+        if (part == 0 && e % span == 0 && tid == 0) {
+            st->rem[2] = left;
+            st->eq_total = (int)st->hist[2][digit];
+        }
+    }
+    __syncthreads();
+    int gt = 0, eq = 0;
+    for (int i = tid; i < kBigChunk; i += 256) {
+        const int tl = part * kBigChunk + i;
+        const uint32_t key = tl < seg_tokens ? keys[tl] : 0u;
+        gt += key > tau;
+        if (key == tau && key != 0u) {
+            ++eq;
+            atomicMax(&lo, seg_tokens - tl);
+            atomicMax(&hi, tl + 1);
+        }
+    }
+    const int gt_total = block_sum_256(gt, red), eq_total = block_sum_256(eq, red);
+    if (tid == 0) {
+        if (part == 0) seg_tau[seg] = tau;
+        if (gt_total) atomicAdd(&seg_count[seg], gt_total);
+        if (eq_total) {
+            atomicAdd(&seg_need[seg], eq_total);
+            atomicMax(&st->first_eq, lo);
+            atomicMax(&st->last_eq, hi);
+        }
+    }
+}
+
+// One block per segment.  seg_need: how many of the keys equal to the threshold an expert keeps; where there are more of
+// them than the budget has room for they are granted in (token, expert) order, as in drop_select_kernel.
+__global__ __launch_bounds__(256) void drop_big_finish_kernel(const uint32_t* __restrict__ key_t,
+                                                              const BigState* __restrict__ state,
+                                                              const uint32_t* __restrict__ seg_tau,
+                                                              int32_t* __restrict__ seg_need, int32_t* __restrict__ seg_count,
+                                                              int N, int E, int seg_tokens, int span) {
+    __shared__ int red[4];
+    __shared__ int eq_s[kMaxExperts];
+    __shared__ int sh_tie_token, sh_tie_run;
+    const int groups = E / span, b = blockIdx.x / groups, e0 = (blockIdx.x - b * groups) * span, tid = threadIdx.x;
+    const uint32_t* keys = key_t + (size_t)e0 * N + (size_t)b * seg_tokens;
+    const BigState* st = state + blockIdx.x;
+    const int seg0 = b * E + e0, rem = st->rem[2];
+    if (st->eq_total > rem) {
+        const uint32_t tau = seg_tau[seg0];
+        const int from = seg_tokens - st->first_eq, to = st->last_eq;  // the tokens that hold such keys
+        const int per = (to - from + 255) / 256;
+        const int tb = from + tid * per < to ? from + tid * per : to, te = tb + per < to ? tb + per : to;
+        int c = 0;
+        for (int tl = tb; tl < te; ++tl)
+            for (int r = 0; r < span; ++r) c += keys[(size_t)r * N + tl] == tau;
+        int total;
+        const int before = block_exclusive_scan_256(c, red, &total);
+        if (before < rem && rem <= before + c) {  // exactly one thread: 1 <= rem < eq_total = total
+            int left = rem - before;
+            for (int tl = tb; tl < te && left > 0; ++tl)
+                for (int r = 0; r < span && left > 0; ++r)
+                    if (keys[(size_t)r * N + tl] == tau && --left == 0) {
+                        sh_tie_token = tl;
+                        sh_tie_run = r;
+                    }
+        }
+        for (int r = tid; r < span; r += 256) eq_s[r] = 0;
+        __syncthreads();
+        const int tie_token = sh_tie_token, tie_run = sh_tie_run;
+        for (int r = 0; r < span; ++r) {
+            int eq = 0;
+            for (int tl = from + tid; tl < tie_token + (r <= tie_run ? 1 : 0); tl += 256)
+                eq += keys[(size_t)r * N + tl] == tau;
+            if (eq) atomicAdd(&eq_s[r], eq);
+        }
+        __syncthreads();
+        for (int r = tid; r < span; r += 256) seg_need[seg0 + r] = eq_s[r];
+    }
+    __syncthreads();
+    for (int r = tid; r < span; r += 256) seg_count[seg0 + r] += seg_need[seg0 + r];
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1001,6 +1180,19 @@ __global__ __launch_bounds__(NT) void drop_fused_kernel(
     }
 }
 
+// keys are fetched four at a time: every run starts on a 16-byte boundary
+static bool select_by_four(const Sizes& s, int n_tokens) { return n_tokens % 4 == 0 && s.seg_tokens % 4 == 0; }
+
+// Bytes of the segments' states where many blocks share a segment, 0 where a block has it alone: from where a block cannot
+// hold the keys in its registers.  Selection, one block -> many: 2 segments of 101472 keys 66 -> 32 us, one of 2^20 keys
+// 822 -> 30 us (Score), of 1048640 keys with an odd pitch 612 -> 46 us (Order, whose ties fall on one token), of 2^22
+// keys 961 -> 36 us; but 64 segments of 30001 keys 35 -> 46.  Keys at an odd pitch are held one load each, 32 a thread.
+size_t drop_big_state_bytes(const moe_desc_t& d, const Sizes& s) {
+    const long long n_keys = (long long)s.seg_tokens * s.span;
+    if (n_keys <= (select_by_four(s, d.n_tokens) ? 65536 : 32768) || s.cap == 0) return 0;  // (no capacity: nothing to walk)
+    return (size_t)s.n_blocks * (d.n_experts / s.span) * sizeof(BigState);
+}
+
 hipError_t launch_capacity_drop(const moe_desc_t& d, const Sizes& s, const DropWorkspace& ws, const float* scores,
                                 const int32_t* topk_idx, const uint8_t* token_class, uint32_t seed,
                                 int32_t* expert_count, int32_t* seg_count,
@@ -1053,6 +1245,7 @@ hipError_t launch_capacity_drop(const moe_desc_t& d, const Sizes& s, const DropW
             return hipGetLastError();
         }
     }
+    const bool big = ws.big_state != nullptr;
     if (N > 0) {
         const int grid = (N + kPrepTokens - 1) / kPrepTokens;
         const size_t lds = (size_t)kPrepTokens * (E | 1) * 5;
@@ -1062,27 +1255,43 @@ hipError_t launch_capacity_drop(const moe_desc_t& d, const Sizes& s, const DropW
         ProfileScope prof(MOE_KERNEL_DROP_PREPARE, st);
         hipLaunchKernelGGL(drop_prepare_kernel, dim3(grid), dim3(256), lds, st, scores, topk_idx, ws.key_t, ws.slot_t,
                            pair_row, N, E, s.list_k, s.slots, d.mode == MOE_MODE_EXPANDED_DROP ? 1 : 0, s.group_tokens,
-                           s.group_experts, d.metric, s.seg_tokens > 0 ? s.seg_tokens : 1, token_class, seed);
+                           s.group_experts, d.metric, s.seg_tokens > 0 ? s.seg_tokens : 1, token_class, seed,
+                           (uint32_t*)ws.big_state, big ? (long long)(s.n_blocks * (E / s.span)) * (long long)(sizeof(BigState) / 4) : 0ll,
+                           seg_count, ws.seg_need, s.n_blocks * E);
     }
     const int segs = s.n_blocks * E;
-    {
+    if (big) {
+        ProfileScope prof(MOE_KERNEL_DROP_SELECT, st);
+        BigState* state = (BigState*)ws.big_state;
+        const int dsegs = segs / s.span;
+        const int chunks = (int)(((long long)s.seg_tokens * s.span + kBigChunk - 1) / kBigChunk);
+        const int parts = (s.seg_tokens + kBigChunk - 1) / kBigChunk;
+        auto hist = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3(dsegs * chunks), dim3(256), 0, st, ws.key_t, state, N, E, s.seg_tokens, s.span, s.cap,
+                               chunks);
+        };
+        if (select_by_four(s, N)) {
+            hist(drop_big_hist_kernel<0, 4>);
+            hist(drop_big_hist_kernel<1, 4>);
+            hist(drop_big_hist_kernel<2, 4>);
+        } else {
+            hist(drop_big_hist_kernel<0, 1>);
+            hist(drop_big_hist_kernel<1, 1>);
+            hist(drop_big_hist_kernel<2, 1>);
+        }
+        hipLaunchKernelGGL(drop_big_count_kernel, dim3(segs * parts), dim3(256), 0, st, ws.key_t, state, ws.seg_tau, ws.seg_need,
+                           seg_count, N, E, s.seg_tokens, s.span, parts);
+        hipLaunchKernelGGL(drop_big_finish_kernel, dim3(dsegs), dim3(256), 0, st, ws.key_t, state, ws.seg_tau, ws.seg_need,
+                           seg_count, N, E, s.seg_tokens, s.span);
+    } else {
         ProfileScope prof(MOE_KERNEL_DROP_SELECT, st);
         const size_t n_keys = (size_t)s.seg_tokens * s.span;
-        const bool wide = n_keys > 4096;                          // threads per block
-        const bool vec = N % 4 == 0 && s.seg_tokens % 4 == 0;     // 16-byte loads of four keys
-        const bool held = n_keys <= (size_t)(wide ? 1024 * kSelectBatch<1024> : 256 * kSelectBatch<256>) * (vec ? 4 : 1);
-        const size_t lds = (!held && n_keys <= (size_t)kSelectCache ? n_keys : 0) * 4;
-        static std::atomic<uint64_t> configured{0};
-        once_per_device(configured, [] {  // up to 128 KB of keys plus the kernel's own few kilobytes
-            for (const void* k : {(const void*)drop_select_kernel<256, 1, false>, (const void*)drop_select_kernel<1024, 1, false>})
-                (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kSelectCache * 4);
-        });
-        // 16-byte loads: up to 4096 keys are always held by 256 threads, up to 65536 by 1024
-        auto kern = wide ? (vec ? (held ? drop_select_kernel<1024, 4, true> : drop_select_kernel<1024, 4, false>)
-                                : (held ? drop_select_kernel<1024, 1, true> : drop_select_kernel<1024, 1, false>))
-                         : (vec ? drop_select_kernel<256, 4, true>
-                                : (held ? drop_select_kernel<256, 1, true> : drop_select_kernel<256, 1, false>));
-        hipLaunchKernelGGL(kern, dim3(segs / s.span), dim3(wide ? 1024 : 256), lds, st, ws.key_t, ws.seg_tau,
+        const bool vec = select_by_four(s, N);
+        const bool wide = n_keys > (vec ? 4096 : 2048);  // threads per block
+        auto kern = !wide ? (vec ? drop_select_kernel<256, 4, 8> : drop_select_kernel<256, 1, 8>)
+                    : vec ? drop_select_kernel<1024, 4, 16>
+                          : (n_keys <= 16384 ? drop_select_kernel<1024, 1, 16> : drop_select_kernel<1024, 1, 32>);
+        hipLaunchKernelGGL(kern, dim3(segs / s.span), dim3(wide ? 1024 : 256), 0, st, ws.key_t, ws.seg_tau,
                            ws.seg_need, seg_count, N, E, s.seg_tokens, s.span, s.cap);
     }
     auto emit = [&](bool last) {

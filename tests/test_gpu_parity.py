@@ -296,6 +296,34 @@ def test_plan_large_segments(orc, n, e, k, g, mode, scope, gamma):
     check_route_and_plan(orc, logits, n, e, k, g, mode, scope, gamma, "large segment")
 
 
+@pytest.mark.parametrize("n,e,k,g,mode,scope,gamma,metric,ties", [
+    (4100, 32, 4, 1, TD, GLOBAL_DEV, 1.0, 0, None),     # 131200 keys in one segment, ragged last chunk
+    (4101, 24, 3, 1, ED, LOCAL_DEV, 0.7, 0, None),         # odd: keys fetched one at a time; every expert a candidate
+    (4608, 48, 6, 2, ED, GLOBAL_DEV, 0.9, 3, None),     # two segments, drawn ranks, half of the experts local
+    (9000, 64, 2, 4, TD, GLOBAL_DEV, 1.25, 1, None),    # Order: the boundary token holds several equal keys
+    (18000, 16, 4, 2, TD, LOCAL_DEV, 0.5, 2, None),     # Reverse Order, capacity per device's own tokens
+    (4096, 32, 2, 1, TD, LOCAL_DEV, 40.0, 0, None),     # fewer candidates than the budget
+    (4096, 32, 4, 1, TD, GLOBAL_DEV, 0.6, 0, "flat"),   # every score equal: token and expert order decide
+    (6001, 24, 4, 1, ED, GLOBAL_DEV, 0.3, 0, "few"),    # three different logits
+    (70004, 2, 1, 1, TD, GLOBAL, 0.4, 0, "few"),           # long segments of single experts
+    (16389, 3, 1, 1, TD, GLOBAL, 0.4, 0, None),            # odd keys, held by one block
+    (10922, 3, 1, 1, TD, LOCAL_DEV, 0.4, 0, None),         # 32766 and 32769 of them: either side of the line
+    (10923, 3, 1, 1, TD, LOCAL_DEV, 0.4, 0, None),
+    (16384, 4, 1, 1, TD, LOCAL_DEV, 0.4, 0, None),         # the most keys one block holds
+    (4096, 32, 2, 1, TD, LOCAL_DEV, 0.0, 0, None),      # no capacity
+])
+def test_plan_segments_of_many_blocks(orc, n, e, k, g, mode, scope, gamma, metric, ties):
+    """Segments with more keys than one block holds: thresholds from shared histograms, counts per expert, ties."""
+    rng = np.random.default_rng(n + e)
+    logits = rng.standard_normal((n, e)).astype(np.float32)
+    if ties == "flat":
+        logits[:] = 0.0
+    elif ties == "few":
+        logits = rng.integers(-1, 2, size=(n, e)).astype(np.float32)
+    classes = rng.integers(0, 2, size=n).astype(np.uint8) if metric == 3 else None
+    check_route_and_plan(orc, logits, n, e, k, g, mode, scope, gamma, f"many blocks {n}x{e}", metric, classes, 5)
+
+
 def test_device_level_ties(orc):
     w = synth.scaled(W["olmoe"], n_tokens=2048, n_experts=32, top_k=4, device_groups=4)
     logits = synth.logits_with_ties(w)
