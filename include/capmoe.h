@@ -277,7 +277,8 @@ int moe_profile_attach(moe_profile_t* table);
  *                   [2], [3] the same for the short items, [4] 1 if the GEMM walks the joint tile list,
  *                   [5] work items at the end of that list that the XCDs share out by a counter,
  *                   [6] big work items per XCD that run as four 64-row blocks, [7] 0.
- *                   All zero for desc->dtype == fp32, whose kernels use none of this.
+ *                   All zero for desc->dtype == fp32, whose kernels use none of this; the kernels of bf16 batches
+ *                   with few rows per expert use the tiles but not the header.
  * Errors: MOE_ERR_INVALID_ARG for null pointers, negative counts, more rows than max_rows.
  */
 int moe_ffn_schedule_query(const moe_desc_t* desc, const int32_t* expert_count, int compute_units, int32_t* tiles,

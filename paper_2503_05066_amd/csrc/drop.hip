@@ -8,7 +8,8 @@
 //                     the score's bit pattern (Score metric), the token's position (Order, Reverse
 //                     Order) or a hashed draw (Random), below an optional 2-bit token class.
 //   2. drop_select    per segment: the cap-th largest key by a 4-pass radix select over LDS
-//                     histograms (the threshold tau of Eq. 8) and how many keys equal to it survive.
+//                     histograms (the threshold tau of Eq. 8) and how many keys equal to it survive
+//                     (drop_big_*: the same for segments that many blocks share).
 //   3. drop_emit      per segment (a block per 4096 tokens of it): ordered compaction of the survivors,
 //                     which yields rows in ascending token order and gives ties at the threshold to
 //                     the lower token index.
