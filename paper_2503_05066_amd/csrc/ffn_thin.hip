@@ -193,8 +193,10 @@ struct ThinTile {
     }
 };
 
-// Every tile is in the list of short tiles (at most 64 rows).  A tile of more than 32 rows is done in two passes of its
-// blocks over the same weights.
+// expert_offset is the caller's: an expert of a plan from elsewhere may have more rows than the capacity leaves it, and then
+// has big tiles too.  So the blocks walk the joint list, as often around as it takes: with the plans of this library's own
+// drop once, because no expert has a second tile there.  A tile of more than 32 rows is done in passes of its blocks over
+// the same weights.
 template <bool SWIGLU>
 __global__ __launch_bounds__(64 * kThinWaves, 2) void ffn_thin_kernel(
     const uint16_t* __restrict__ A, const uint16_t* __restrict__ B0, const uint16_t* __restrict__ B1,
@@ -202,22 +204,23 @@ __global__ __launch_bounds__(64 * kThinWaves, 2) void ffn_thin_kernel(
     const int32_t* __restrict__ tile_row0, const int32_t* __restrict__ tile_rows, const int32_t* __restrict__ n_tiles, int K,
     int Nout, int col_blocks) {
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
-    const int tile = blockIdx.x / col_blocks, nb = blockIdx.x - tile * col_blocks;
-    if (tile >= *n_tiles) return;
-    const int e = tile_expert[tile], row0 = tile_row0[tile], rows = tile_rows[tile] & kTileRowsMask;
-    const int n0 = nb * ThinTile<1, SWIGLU>::kCols;
-    for (int at = 0; at < rows; at += kThinPiece) {
-        if (at > 0) __syncthreads();  // the first wave reads the others' sums out of their rings
-        const int left = rows - at;
-        if (left <= 16)
-            ThinTile<1, SWIGLU>::run(A, B0, B1, C, gather, e, row0 + at, left, n0, K, Nout, smem);
-        else
-            ThinTile<2, SWIGLU>::run(A, B0, B1, C, gather, e, row0 + at, left < kThinPiece ? left : kThinPiece, n0, K, Nout,
-                                     smem);
+    const int first = blockIdx.x / col_blocks, n0 = (blockIdx.x - first * col_blocks) * ThinTile<1, SWIGLU>::kCols;
+    const int step = gridDim.x / col_blocks, nt = *n_tiles;
+    for (int tile = first; tile < nt; tile += step) {
+        const int e = tile_expert[tile], row0 = tile_row0[tile], rows = tile_rows[tile] & kTileRowsMask;
+        for (int at = 0; at < rows; at += kThinPiece) {
+            if (tile > first || at > 0) __syncthreads();  // the first wave reads the others' sums out of their rings
+            const int left = rows - at;
+            if (left <= 16)
+                ThinTile<1, SWIGLU>::run(A, B0, B1, C, gather, e, row0 + at, left, n0, K, Nout, smem);
+            else
+                ThinTile<2, SWIGLU>::run(A, B0, B1, C, gather, e, row0 + at, left < kThinPiece ? left : kThinPiece, n0, K, Nout,
+                                         smem);
+        }
     }
 }
 
-// most rows an expert can have
+// most rows the capacity leaves an expert
 static long long rows_bound(const moe_desc_t& d, const Sizes& s) {
     const long long kept = (long long)s.n_blocks * s.cap;
     return kept < d.n_tokens ? kept : d.n_tokens;
@@ -247,8 +250,8 @@ static void launch_thin(const Sizes& s, int experts, const void* A, const void* 
     const int col_blocks = Nout / ThinTile<1, SWIGLU>::kCols;
     const long long tiles = s.max_rows < experts ? s.max_rows : experts;
     hipLaunchKernelGGL(kern, dim3((unsigned)(tiles * col_blocks)), dim3(64 * kThinWaves), lds, st, (const uint16_t*)A, (const uint16_t*)B0,
-                       (const uint16_t*)B1, (uint16_t*)C, gather, ws.small.expert, ws.small.row0, ws.small.rows,
-                       ws.small.count, K, Nout, col_blocks);
+                       (const uint16_t*)B1, (uint16_t*)C, gather, ws.all.expert, ws.all.row0, ws.all.rows,
+                       ws.all.count, K, Nout, col_blocks);
 }
 
 void launch_ffn_thin(const moe_desc_t& d, const Sizes& s, const FfnWorkspace& ws, const void* xp, const int32_t* row_token,

@@ -738,6 +738,43 @@ def test_ffn_few_rows(orc, d, h, counts):
     assert torch.equal(fused.y, buf.y)
 
 
+@pytest.mark.parametrize("counts", [
+    {0: 100, 1: 3, 5: 65, 31: 1},                  # above the capacity of a descriptor whose experts have 64 rows at most
+    {3: 321, 7: 64, 8: 65, 20: 30},                # several full tiles and a remainder on one expert
+    {e: 16 for e in range(32)},                    # every expert its average
+    {31: 512},                                     # all rows on one expert
+])
+def test_ffn_plans_of_the_caller(orc, counts):
+    """expert_offset is the caller's: an expert may hold more rows than the descriptor's own capacity would leave it (rows
+    exchanged between devices, an edited plan), as long as all of them fit max_rows.  64 tokens, top-8 of 32 experts: a
+    descriptor whose experts have few rows.  Every row against the oracle's SwiGLU, rows past the plan untouched."""
+    e, n, k, d, h = 32, 64, 8, 256, 384
+    w = synth.scaled(W["olmoe"], name="caller's plan", n_tokens=n, d_model=d, n_experts=e, top_k=k, d_hidden=h,
+                     device_groups=1)
+    layer = DeviceLayer(w)
+    desc = layer.desc(NONE, GLOBAL, 1.0)
+    max_rows, rows = capmoe.moe_query(desc)[2], sum(counts.values())
+    assert rows <= max_rows == n * k
+    per_expert = [counts.get(j, 0) for j in range(e)]
+    offset = torch.from_numpy(np.concatenate([[0], np.cumsum(per_expert)]).astype(np.int32)).cuda()
+    row_token = np.random.default_rng(38).integers(0, n, size=max_rows).astype(np.int32)
+    tokens = torch.from_numpy(row_token).cuda()
+    xp = layer.x[tokens.long()].contiguous()
+    workspace = torch.empty(capmoe.moe_query(desc)[3], dtype=torch.uint8, device="cuda")
+    separate = torch.full((max_rows, d), 7.0, dtype=torch.bfloat16, device="cuda")
+    fused = separate.clone()
+    capmoe.moe_grouped_ffn(desc, xp, offset, layer.w_gate, layer.w_up, layer.w_down, separate, workspace)
+    capmoe.moe_dispatch_ffn(desc, layer.x, offset, tokens, layer.w_gate, layer.w_up, layer.w_down, fused, workspace)
+    torch.cuda.synchronize()
+    # the oracle's layer with one expert per row and weight one is that expert's FFN
+    keep = np.zeros((rows, e), np.uint8)
+    keep[np.arange(rows), np.repeat(np.arange(e), per_expert)] = 1
+    ref = orc.layer_output(layer.x_host[row_token[:rows]], keep.astype(np.float32), keep, layer.host_gate, layer.host_up,
+                           layer.host_down)
+    assert_output_close(to_host_f64(separate[:rows]), ref, TOL[w.dtype], "caller's plan")
+    assert (separate[rows:] == 7.0).all() and torch.equal(separate, fused)
+
+
 def test_ffn_leftover_items_in_row_pieces(orc):
     """A GEMM too short in K to be cut there, with one big item per XCD left over after a full round (66 big
     tiles x 4 column blocks = 33 items per XCD): the leftover items run as four 64-row blocks each, the last of them
