@@ -284,8 +284,9 @@ struct TileConfig16 {
     static constexpr int kNCols = SWIGLU ? BN / 2 : BN;
     static constexpr int kThreads = 64 * WAVES_M * WAVES_N;
     static constexpr int kLdsBytes = 2 * BM * 128 + 3 * BN * 128;
-    // STREAM: the block's weight rows are read by no other block while they are in the L2: an expert's only row tile,
-    // short or partly filled, and the short tiles that run after all big ones.  Two things bound such a stream, measured
+    // STREAM (layers whose weights do not fit the memory-side cache, see launch_grouped_ffn): an expert's only row tile, short
+    // or partly filled, whose weight rows no other block reads, and the short tiles, row pieces and cut short items that run
+    // after the big ones.  Two things bound such a stream, measured
     // on a read-only kernel with the same fills (256 rows of 128 bytes per slab, 3 GiB):
     //   - blocks that walk K in step all read at the same offset of a power-of-two row pitch, i.e. from a few memory
     //     channels: 4.9 TB/s at K = 4096, 5.0 at 2048; with the walk of the blocks starting at different slabs 6.3, 6.0;
@@ -517,7 +518,10 @@ __device__ inline void decode_item(int logical, int nt, int col_group, int& tile
 // ones (longest first).  The last split_hdr[0] big items of an XCD's share run as split_hdr[1] units each; the
 // units follow the XCD's whole items in launch order, slice by slice, so that the units that run together read
 // the same K range of the tiles they share.
-template <class Big, class BigAlone, class Small, class SmallShared, bool SWIGLU>
+//
+// Big, Small: tiles whose weight rows other blocks read beside them; BigStream, SmallStream: tiles that stream them (the same
+// two classes where the weights are to stay in the caches, see launch_grouped_ffn).
+template <class Big, class BigStream, class Small, class SmallStream, bool SWIGLU>
 __global__ __launch_bounds__(Big::kThreads) void ffn_gemm_bf16_kernel(
     const uint16_t* __restrict__ A, const uint16_t* __restrict__ B0, const uint16_t* __restrict__ B1,
     uint16_t* __restrict__ C, const int32_t* __restrict__ gather, const TileListArgs L, int K, int Nout,
@@ -525,6 +529,7 @@ __global__ __launch_bounds__(Big::kThreads) void ffn_gemm_bf16_kernel(
     int32_t* split_counter) {
     static_assert(Big::kThreads == Small::kThreads, "one block size");
     static_assert(Big::kNCols == Small::kNCols, "one column-block width: the joint list is decoded with it");
+    constexpr bool kStream = !std::is_same_v<Big, BigStream>;
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
     const int32_t* __restrict__ b_expert = L.b_expert;
     const int32_t* __restrict__ b_row0 = L.b_row0;
@@ -563,13 +568,13 @@ __global__ __launch_bounds__(Big::kThreads) void ffn_gemm_bf16_kernel(
         decode_item(logical, nt, col_group_big, tile, nb);
         const int rows = L.u_rows[tile];
         const int e = L.u_expert[tile], row0 = L.u_row0[tile], n0 = nb * Big::kNCols, n_rows = rows & kTileRowsMask;
-        const bool is_short = rows & kShortTileFlag, alone = rows & kAloneTileFlag;
+        const bool is_short = rows & kShortTileFlag, alone = kStream && (rows & kAloneTileFlag);
         if (is_short && alone)
-            Small::run(A, B0, B1, C, gather, e, row0, n_rows, n0, K, Nout, true, smem, one);
+            SmallStream::run(A, B0, B1, C, gather, e, row0, n_rows, n0, K, Nout, true, smem, one);
         else if (is_short)  // its expert's big tiles run beside it and read the same weights
-            SmallShared::run(A, B0, B1, C, gather, e, row0, n_rows, n0, K, Nout, false, smem, one);
+            Small::run(A, B0, B1, C, gather, e, row0, n_rows, n0, K, Nout, false, smem, one);
         else if (alone)
-            BigAlone::run(A, B0, B1, C, gather, e, row0, n_rows, n0, K, Nout, true, smem, one);
+            BigStream::run(A, B0, B1, C, gather, e, row0, n_rows, n0, K, Nout, true, smem, one);
         else
             Big::run(A, B0, B1, C, gather, e, row0, n_rows, n0, K, Nout, false, smem, one);
         return;
@@ -587,11 +592,12 @@ __global__ __launch_bounds__(Big::kThreads) void ffn_gemm_bf16_kernel(
         if (logical >= total_b) return;
         decode_item(logical, nt_b, col_group_big, tile, nb);
         const int rows = b_rows[tile];
-        if (rows & kAloneTileFlag)
-            BigAlone::run(A, B0, B1, C, gather, b_expert[tile], b_row0[tile], rows & kTileRowsMask, nb * Big::kNCols, K, Nout,
-                          true, smem, one);
+        if (kStream && (rows & kAloneTileFlag))
+            BigStream::run(A, B0, B1, C, gather, b_expert[tile], b_row0[tile], rows & kTileRowsMask, nb * Big::kNCols, K, Nout,
+                           true, smem, one);
         else
-            Big::run(A, B0, B1, C, gather, b_expert[tile], b_row0[tile], rows, nb * Big::kNCols, K, Nout, false, smem, one);
+            Big::run(A, B0, B1, C, gather, b_expert[tile], b_row0[tile], rows & kTileRowsMask, nb * Big::kNCols, K, Nout, false,
+                     smem, one);
         return;
     }
     slot -= whole;
@@ -607,8 +613,8 @@ __global__ __launch_bounds__(Big::kThreads) void ffn_gemm_bf16_kernel(
         decode_item(logical, nt_b, col_group_big, tile, nb);
         const int first = piece * Small::kBM, left = (b_rows[tile] & kTileRowsMask) - first;
         if (left <= 0) return;
-        Small::run(A, B0, B1, C, gather, b_expert[tile], b_row0[tile] + first, left < Small::kBM ? left : Small::kBM,
-                   nb * Small::kNCols, K, Nout, b_rows[tile] & kAloneTileFlag, smem, one);
+        SmallStream::run(A, B0, B1, C, gather, b_expert[tile], b_row0[tile] + first, left < Small::kBM ? left : Small::kBM,
+                         nb * Small::kNCols, K, Nout, b_rows[tile] & kAloneTileFlag, smem, one);
         return;
     }
     slot -= in_rows * kRowPieces;
@@ -616,15 +622,15 @@ __global__ __launch_bounds__(Big::kThreads) void ffn_gemm_bf16_kernel(
         const int logical = xcd * chunk_s + slot;
         if (logical >= total_s) return;
         decode_item(logical, nt_s, col_group_small, tile, nb);
-        const bool alone = s_rows[tile] & kAloneTileFlag;
+        const bool alone = kStream && (s_rows[tile] & kAloneTileFlag);
         // with less than a round of big items those of the same expert run beside it and read the same weights (314 tokens,
         // all at 8 experts x 3840 x 640: 169 -> 155 us)
-        if (!alone && chunk_b <= per_xcd)
-            SmallShared::run(A, B0, B1, C, gather, s_expert[tile], s_row0[tile], s_rows[tile] & kTileRowsMask,
-                             nb * Small::kNCols, K, Nout, false, smem, one);
-        else
+        if (!kStream || (!alone && chunk_b <= per_xcd))
             Small::run(A, B0, B1, C, gather, s_expert[tile], s_row0[tile], s_rows[tile] & kTileRowsMask, nb * Small::kNCols,
-                       K, Nout, alone, smem, one);
+                       K, Nout, false, smem, one);
+        else
+            SmallStream::run(A, B0, B1, C, gather, s_expert[tile], s_row0[tile], s_rows[tile] & kTileRowsMask,
+                             nb * Small::kNCols, K, Nout, alone, smem, one);
         return;
     }
     slot -= whole_s;
@@ -652,8 +658,8 @@ __global__ __launch_bounds__(Big::kThreads) void ffn_gemm_bf16_kernel(
         const SplitUnit su{slices_s, slice, cut_s,
                            region + (size_t)(xcd * per_xcd + idx) * ((size_t)Small::kBM * Small::kBN),
                            split_counter + kFfnSplitUnits + xcd * per_xcd + idx};
-        Small::run(A, B0, B1, C, gather, s_expert[tile], s_row0[tile], s_rows[tile] & kTileRowsMask, nb * Small::kNCols, K,
-                   Nout, s_rows[tile] & kAloneTileFlag, smem, su);
+        SmallStream::run(A, B0, B1, C, gather, s_expert[tile], s_row0[tile], s_rows[tile] & kTileRowsMask, nb * Small::kNCols,
+                         K, Nout, s_rows[tile] & kAloneTileFlag, smem, su);
     }
 }
 
@@ -671,12 +677,12 @@ static int column_group(int nb_total) {
     return 1;
 }
 
-template <class Big, class BigAlone, class Small, class SmallShared, bool SWIGLU>
-static void launch_bf16(const void* A, const void* B0, const void* B1, void* C, const int32_t* gather,
+template <class Big, class BigStream, class Small, class SmallStream, bool SWIGLU>
+static void launch_bf16_tiles(const void* A, const void* B0, const void* B1, void* C, const int32_t* gather,
                         const FfnWorkspace& ws, int K, int Nout, const int32_t* split_hdr, int32_t* split_counter,
                         hipStream_t st) {
     constexpr int lds = Big::kLdsBytes > Small::kLdsBytes ? Big::kLdsBytes : Small::kLdsBytes;
-    auto kern = ffn_gemm_bf16_kernel<Big, BigAlone, Small, SmallShared, SWIGLU>;
+    auto kern = ffn_gemm_bf16_kernel<Big, BigStream, Small, SmallStream, SWIGLU>;
     static std::atomic<uint64_t> configured{0};
     once_per_device(configured, [&] {
         (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -689,9 +695,25 @@ static void launch_bf16(const void* A, const void* B0, const void* B1, void* C, 
         std::max(2 * kFfnSplitUnits, kFfnJointPoolRounds * compute_units()) + 16;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(Big::kThreads), lds, st, (const uint16_t*)A,
                        (const uint16_t*)B0, (const uint16_t*)B1, (uint16_t*)C, gather, tile_list_args(ws, true), K, Nout,
-                       // short items: all column blocks of a tile in a row, so that those that run together start
-                       // their walks over K at different slabs (they share activation rows only)
-                       column_group(nb_b), nb_s, split_hdr, ws.split_partial, split_counter);
+                       // short items that stream: all column blocks of a tile in a row, so that those that run together
+                       // start their walks over K at different slabs (they share activation rows only)
+                       column_group(nb_b), std::is_same_v<Big, BigStream> ? column_group(nb_s) : nb_s, split_hdr,
+                       ws.split_partial, split_counter);
+}
+
+// BN: weight rows of a block
+template <int BN, bool SWIGLU>
+static void launch_bf16(bool stream, const void* A, const void* B0, const void* B1, void* C, const int32_t* gather,
+                        const FfnWorkspace& ws, int K, int Nout, const int32_t* split_hdr, int32_t* split_counter,
+                        hipStream_t st) {
+    using Big = TileConfig16<kFfnTileM, BN, 2, 2, SWIGLU, false>;
+    using Small = TileConfig16<kFfnTileSmall, BN, 1, 4, SWIGLU, false>;
+    if (stream)
+        launch_bf16_tiles<Big, TileConfig16<kFfnTileM, BN, 2, 2, SWIGLU, true>, Small,
+                          TileConfig16<kFfnTileSmall, BN, 1, 4, SWIGLU, true>, SWIGLU>(A, B0, B1, C, gather, ws, K, Nout,
+                                                                                       split_hdr, split_counter, st);
+    else
+        launch_bf16_tiles<Big, Big, Small, Small, SWIGLU>(A, B0, B1, C, gather, ws, K, Nout, split_hdr, split_counter, st);
 }
 
 // The arguments of the tile schedule for a descriptor and its workspace layout (host side).
@@ -763,27 +785,22 @@ hipError_t launch_grouped_ffn(const moe_desc_t& d, const Sizes& s, const FfnWork
     } else if (bf16) {
         const int32_t* split_gu = ws.split_hdr;
         const int32_t* split_dn = ws.split_hdr + kFfnSplitHdr;
+        int32_t* tickets_dn = ws.split_counter + 2 * kFfnSplitUnits;
+        // Weights that fit the memory-side cache are read from there by the layer's next pass unless they were fetched
+        // with the streaming policy: 37 tokens, 2 x 3584 x 1408 (61 MB) 50 us a pass, streaming 69; 412, 16 x 2944 x 768
+        // (217 MB) 84 and 95; 256, 16 x 4096 x 1024 (403 MB) 125 and 120; 37, 64 x 4096 x 1408 (2.2 GB) 350 and 273.
+        constexpr uint64_t kMemorySideCache = 256ull << 20;
+        const bool stream = 3ull * d.n_experts * d.d_model * d.d_hidden * s.elem > kMemorySideCache;
         // full-height row tiles: 256 x 256 blocks; short remainders: 64 x 256 blocks; four waves each
         {
             ProfileScope prof(MOE_KERNEL_FFN_GATE_UP, st);
-            launch_bf16<TileConfig16<kFfnTileM, 256, 2, 2, true, false>, TileConfig16<kFfnTileM, 256, 2, 2, true, true>,
-                        TileConfig16<kFfnTileSmall, 256, 1, 4, true, true>,
-                        TileConfig16<kFfnTileSmall, 256, 1, 4, true, false>,
-                        true>(xp, w_gate, w_up, ws.hidden, row_token, ws, K1, N1, split_gu, ws.split_counter, st);
+            launch_bf16<256, true>(stream, xp, w_gate, w_up, ws.hidden, row_token, ws, K1, N1, split_gu, ws.split_counter, st);
         }
         ProfileScope prof(MOE_KERNEL_FFN_DOWN, st);
         if (bn_down == 256)
-            launch_bf16<TileConfig16<kFfnTileM, 256, 2, 2, false, false>, TileConfig16<kFfnTileM, 256, 2, 2, false, true>,
-                        TileConfig16<kFfnTileSmall, 256, 1, 4, false, true>,
-                        TileConfig16<kFfnTileSmall, 256, 1, 4, false, false>, false>(ws.hidden, w_down, nullptr, yp, nullptr,
-                                                                                    ws, K2, N2, split_dn,
-                                                                                    ws.split_counter + 2 * kFfnSplitUnits, st);
+            launch_bf16<256, false>(stream, ws.hidden, w_down, nullptr, yp, nullptr, ws, K2, N2, split_dn, tickets_dn, st);
         else
-            launch_bf16<TileConfig16<kFfnTileM, 128, 2, 2, false, false>, TileConfig16<kFfnTileM, 128, 2, 2, false, true>,
-                        TileConfig16<kFfnTileSmall, 128, 1, 4, false, true>,
-                        TileConfig16<kFfnTileSmall, 128, 1, 4, false, false>, false>(ws.hidden, w_down, nullptr, yp, nullptr,
-                                                                                    ws, K2, N2, split_dn,
-                                                                                    ws.split_counter + 2 * kFfnSplitUnits, st);
+            launch_bf16<128, false>(stream, ws.hidden, w_down, nullptr, yp, nullptr, ws, K2, N2, split_dn, tickets_dn, st);
     } else {
         launch_ffn_gate_up_f32(d, s, ws, xp, row_token, w_gate, w_up, st);
         launch_ffn_down_f32(d, s, ws, w_down, yp, st);

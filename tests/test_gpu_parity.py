@@ -681,6 +681,32 @@ def test_ffn_single_tile_experts(orc, d, h):
     assert torch.equal(fused.y, buf.y)
 
 
+@pytest.mark.parametrize("d,h", [(2048, 1920), (1920, 2048)])
+def test_ffn_single_tile_experts_of_a_large_layer(orc, d, h):
+    """As above with more expert weights (283 MB) than the memory-side cache holds, where such experts stream them: the first
+    and the last row of every row tile against the oracle, and the same bits with the fused gather."""
+    counts = [1, 63, 64, 65, 130, 255, 256, 257, 320, 321, 0, 33]
+    e, n = len(counts), sum(counts)
+    w = synth.scaled(W["olmoe"], name="alone, large", n_tokens=n, d_model=d, n_experts=e, top_k=1, d_hidden=h, device_groups=1)
+    layer = DeviceLayer(w)
+    owner = np.repeat(np.arange(e), counts)
+    np.random.default_rng(39).shuffle(owner)
+    logits = np.zeros((n, e), np.float32)
+    logits[np.arange(n), owner] = 6.0
+    ref = orc.route_and_drop(logits, 1, 1, NONE, GLOBAL, 1.0)
+    desc = layer.desc(NONE, GLOBAL, 1.0)
+    buf = run_layer(layer, desc, logits)
+    tokens = sorted({int(np.flatnonzero(owner == j)[r]) for j in range(e) if counts[j]
+                     for first in range(0, counts[j], 64) for r in (first, min(first + 63, counts[j] - 1))})
+    y_ref = orc.layer_output(layer.x_host, ref.scores, ref.keep, layer.host_gate, layer.host_up, layer.host_down, tokens)
+    assert_output_close(to_host_f64(buf.y)[tokens], y_ref, TOL[w.dtype], "single-tile experts of a large layer")
+    fused = capmoe.LayerBuffers(desc)
+    capmoe.layer_forward(fused, layer.x, layer.w_router, layer.bias, layer.w_gate, layer.w_up, layer.w_down,
+                         torch.from_numpy(logits).cuda(), fused_dispatch=True)
+    torch.cuda.synchronize()
+    assert torch.isfinite(buf.y.float()).all() and torch.equal(fused.y, buf.y)
+
+
 @pytest.mark.parametrize("d,h,counts", [
     (4, 1, [1, 0, 5]),                                    # less than one K slab in both products, a single hidden column
     (64, 33, [16, 17, 64, 65, 1, 0, 31, 48, 49, 130]),    # edges of sub-tiles and tiles; the down product has K = 33
