@@ -67,8 +67,9 @@ struct TileF32 {
         f32x4 xr[R][NA], wr[R][NB];
         const int slabs = K / kF32Slab, tail = K - slabs * kF32Slab;
         // Column blocks start their walks over K at different slabs: in step, they all read at the same offset of the row
-        // pitch, from few memory channels when that is a power of two.  The start depends on the columns alone.
-        const int turn = (int)((long long)n0 * slabs / Nout);
+        // pitch, from few memory channels when that is a power of two.  The start depends on the columns alone, the same for the
+        // 64 columns of a wide block and of the narrow blocks in its place: a row's bits do not depend on its batch.
+        const int turn = (int)((long long)(n0 & ~63) * slabs / Nout);
         // element offset of slab s; past the last slab: that one again
         auto slab_at = [&](int s) {
             s = (s < slabs ? s : slabs - 1) + turn;

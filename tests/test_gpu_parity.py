@@ -801,6 +801,23 @@ def test_ffn_plans_of_the_caller(orc, counts):
     assert (separate[rows:] == 7.0).all() and torch.equal(separate, fused)
 
 
+@pytest.mark.parametrize("d,h", [(512, 1000), (100, 97), (1024, 256)])
+def test_ffn_fp32_rows_do_not_depend_on_the_batch(d, h):
+    """An fp32 token gets the same bits alone, in a batch of few rows (narrow column blocks) and in a larger one (wide ones)."""
+    e, k = 8, 2
+    big = synth.scaled(W["tiny"], name="batch", n_tokens=400, d_model=d, n_experts=e, top_k=k, d_hidden=h, device_groups=1)
+    layer = DeviceLayer(big, host_weights=False)
+    outs = {}
+    for n in (400, 40, 1):
+        desc = capmoe.make_desc(n, d, e, k, h, 1, NONE, GLOBAL, 1.0, synth.DTYPE_F32)
+        buf = capmoe.LayerBuffers(desc)
+        capmoe.layer_forward(buf, layer.x[:n].contiguous(), layer.w_router, layer.bias, layer.w_gate, layer.w_up,
+                             layer.w_down)
+        torch.cuda.synchronize()
+        outs[n] = buf.y
+    assert torch.equal(outs[40], outs[400][:40]) and torch.equal(outs[1], outs[400][:1])
+
+
 def test_ffn_leftover_items_in_row_pieces(orc):
     """A GEMM too short in K to be cut there, with one big item per XCD left over after a full round (66 big
     tiles x 4 column blocks = 33 items per XCD): the leftover items run as four 64-row blocks each, the last of them
