@@ -242,38 +242,43 @@ struct TileF32 {
 
 // Work items: row tiles (fastest) x column blocks; every XCD (block id mod 8) takes a contiguous eighth, so that the tiles of
 // an expert that read the same weight rows run side by side on one L2.  Of a 64-row tile's four sub-tiles only those that
-// hold rows are multiplied.
-template <int NW, int TN, bool SWIGLU>
+// hold rows are multiplied: one after the other (PIECES == 1), or each by a block of its own (4).
+template <int NW, int TN, bool SWIGLU, int PIECES>
 __global__ __launch_bounds__(64 * NW, NW < 4 ? 2 : 3) void ffn_gemm_f32_kernel(
     const float* __restrict__ A, const float* __restrict__ B0, const float* __restrict__ B1, float* __restrict__ C,
     const int32_t* __restrict__ tile_expert, const int32_t* __restrict__ tile_row0, const int32_t* __restrict__ tile_rows,
     const int32_t* __restrict__ n_tiles, const int32_t* __restrict__ gather, int K, int Nout, int col_blocks) {
-    __shared__ __attribute__((aligned(16))) uint8_t smem[2 * TileF32<NW, 4, TN, SWIGLU>::kBuf];
-    const int nt = *n_tiles;
+    static_assert(kFfnTileMF32 == 64 && (PIECES == 1 || PIECES == 4), "four sub-tiles");
+    __shared__ __attribute__((aligned(16))) uint8_t smem[2 * TileF32<NW, 4 / PIECES, TN, SWIGLU>::kBuf];
+    const int nt = *n_tiles * PIECES;
     const long long total = (long long)nt * col_blocks, chunk = (total + 7) >> 3;
     const long long slot = blockIdx.x >> 3, logical = (blockIdx.x & 7) * chunk + slot;
     if (slot >= chunk || logical >= total) return;
-    const int nb = (int)(logical / nt), tile = (int)(logical - (long long)nb * nt);
-    const int e = tile_expert[tile], row0 = tile_row0[tile], rows = tile_rows[tile] & kTileRowsMask;
+    const int nb = (int)(logical / nt), item = (int)(logical - (long long)nb * nt), tile = item / PIECES;
+    const int first = 16 * (item % PIECES);  // of the tile's rows
+    const int e = tile_expert[tile], row0 = tile_row0[tile] + first, rows = (tile_rows[tile] & kTileRowsMask) - first;
     const int n0 = nb * (SWIGLU ? 16 : 16 * TN) * NW;
-    static_assert(kFfnTileMF32 == 64, "four sub-tiles");
-    if (rows <= 16)
+    if (PIECES > 1) {
+        if (rows > 0)
+            TileF32<NW, 1, TN, SWIGLU>::run(A, B0, B1, C, gather, e, row0, rows < 16 ? rows : 16, n0, K, Nout, smem);
+    } else if (rows <= 16) {
         TileF32<NW, 1, TN, SWIGLU>::run(A, B0, B1, C, gather, e, row0, rows, n0, K, Nout, smem);
-    else if (rows <= 32)
+    } else if (rows <= 32) {
         TileF32<NW, 2, TN, SWIGLU>::run(A, B0, B1, C, gather, e, row0, rows, n0, K, Nout, smem);
-    else if (rows <= 48)
+    } else if (rows <= 48) {
         TileF32<NW, 3, TN, SWIGLU>::run(A, B0, B1, C, gather, e, row0, rows, n0, K, Nout, smem);
-    else
+    } else {
         TileF32<NW, 4, TN, SWIGLU>::run(A, B0, B1, C, gather, e, row0, rows, n0, K, Nout, smem);
+    }
 }
 
-template <int NW, bool SWIGLU>
+template <int NW, int PIECES, bool SWIGLU>
 static void launch_gemm_f32(const void* A, const void* B0, const void* B1, void* C, const int32_t* gather,
                             const FfnWorkspace& ws, int K, int Nout, hipStream_t st) {
     constexpr int TN = SWIGLU ? 2 : 1, kCols = 16 * NW;
     const int col_blocks = (Nout + kCols - 1) / kCols;
-    const long long grid = ((long long)col_blocks * ws.big.max_tiles + 7) / 8 * 8;
-    hipLaunchKernelGGL((ffn_gemm_f32_kernel<NW, TN, SWIGLU>), dim3((unsigned)grid), dim3(64 * NW), 0, st, (const float*)A,
+    const long long grid = ((long long)col_blocks * ws.big.max_tiles * PIECES + 7) / 8 * 8;
+    hipLaunchKernelGGL((ffn_gemm_f32_kernel<NW, TN, SWIGLU, PIECES>), dim3((unsigned)grid), dim3(64 * NW), 0, st, (const float*)A,
                        (const float*)B0, (const float*)B1, (float*)C, ws.big.expert, ws.big.row0, ws.big.rows, ws.big.count,
                        gather, K, Nout, col_blocks);
 }
@@ -286,11 +291,17 @@ static void choose_gemm_f32(const moe_desc_t& d, const Sizes& s, const void* A, 
     // 8 experts x 1024 x 1024 37 -> 34 us, 16 x 1024 x 2048 66 -> 57, 64 x 600 x 300 23 -> 20; but 400 tokens,
     // 8 x 512 x 1000 (100 rows per expert) 43 -> 46, 1000 tokens 63 -> 92.
     const long long tiles = (s.max_rows < d.n_experts ? s.max_rows : d.n_experts) + s.max_rows / kFfnTileMF32;
-    const bool narrow = s.max_rows <= 32ll * d.n_experts && tiles * ((Nout + 63) / 64) < 1024;
-    if (!narrow)
-        launch_gemm_f32<4, SWIGLU>(A, B0, B1, C, gather, ws, K, Nout, st);
+    const long long wide_blocks = tiles * ((Nout + 63) / 64);
+    // Few blocks are few chains of matrix instructions: a wave per sub-tile of 16 rows shortens them.  Products of up to half
+    // the chip's wide blocks, whole tiles -> sub-tiles, gate/up + down: 429 tokens, 8 x 84 x 7 16.6 -> 14.4 us; 1000 top-2,
+    // 8 x 64 x 128 (39 and 78 blocks) 16.2 -> 14.6; but 2000, 8 x 128 x 100 (140) 20 -> 24, 1024, 8 x 256 x 256 (160) 25 -> 29,
+    // and with a handful of rows per expert most pieces are empty (131 tokens, 32 x 312 x 6 14.9 -> 15.3).
+    if (wide_blocks <= 128 && s.max_rows > 8ll * d.n_experts)
+        launch_gemm_f32<1, 4, SWIGLU>(A, B0, B1, C, gather, ws, K, Nout, st);
+    else if (s.max_rows <= 32ll * d.n_experts && wide_blocks < 1024)
+        launch_gemm_f32<1, 1, SWIGLU>(A, B0, B1, C, gather, ws, K, Nout, st);
     else
-        launch_gemm_f32<1, SWIGLU>(A, B0, B1, C, gather, ws, K, Nout, st);
+        launch_gemm_f32<4, 1, SWIGLU>(A, B0, B1, C, gather, ws, K, Nout, st);
 }
 
 void launch_ffn_gate_up_f32(const moe_desc_t& d, const Sizes& s, const FfnWorkspace& ws, const void* xp,

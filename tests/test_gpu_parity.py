@@ -714,6 +714,7 @@ def test_ffn_single_tile_experts_of_a_large_layer(orc, d, h):
     (160, 250, [300, 7, 200]),                            # several tiles per expert: four-wave blocks
     (36, 1000, [3, 40, 0, 90, 64, 64]),
     (1024, 31, [3, 1, 12]),
+    (84, 7, [16, 17, 100, 0, 31, 160, 33, 72]),           # a block per 16-row piece: whole, ragged and empty ones
 ])
 def test_ffn_fp32_shapes(orc, d, h, counts):
     """The fp32 expert products at the edges of their tiles, column blocks and K slabs, permuted rows and fused gather.
