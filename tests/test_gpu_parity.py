@@ -324,6 +324,19 @@ def test_plan_segments_of_many_blocks(orc, n, e, k, g, mode, scope, gamma, metri
     check_route_and_plan(orc, logits, n, e, k, g, mode, scope, gamma, f"many blocks {n}x{e}", metric, classes, 5)
 
 
+@pytest.mark.parametrize("n,e,k,g,mode,scope,gamma", [
+    (32768, 6, 2, 1, TD, GLOBAL, 0.7),      # eight parts of a segment: the blocks of a part share an XCD
+    (36864, 6, 2, 8, ED, LOCAL, 0.7),       # two parts, eight blocks of tokens
+    (65536, 3, 1, 1, TD, GLOBAL, 0.7),      # sixteen parts: the parts of a segment are neighbours
+    (73728, 2, 1, 2, TD, LOCAL, 0.7),       # nine parts of each of two blocks
+])
+def test_plan_block_orders_of_the_emit(orc, n, e, k, g, mode, scope, gamma):
+    if e % g:
+        e *= g
+    logits = np.random.default_rng(n + e).standard_normal((n, e)).astype(np.float32)
+    check_route_and_plan(orc, logits, n, e, k, g, mode, scope, gamma, f"emit order {n}x{e}")
+
+
 def test_device_level_ties(orc):
     w = synth.scaled(W["olmoe"], n_tokens=2048, n_experts=32, top_k=4, device_groups=4)
     logits = synth.logits_with_ties(w)
