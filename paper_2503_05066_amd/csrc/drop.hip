@@ -51,8 +51,8 @@ __global__ __launch_bounds__(256) void drop_prepare_kernel(const float* __restri
                                                            uint32_t* __restrict__ clear, long long clear_words,
                                                            int32_t* __restrict__ clear_count,
                                                            int32_t* __restrict__ clear_need, int segs) {
-    // what the launches that share segments among blocks add to (clear_words == 0: nothing)
-    if (clear_words > 0) {
+    // what the launches that share segments among blocks add to (clear_count == nullptr: there are none)
+    if (clear_count) {
         for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < clear_words; i += (long long)gridDim.x * 256)
             clear[i] = 0u;
         for (int i = blockIdx.x * 256 + threadIdx.x; i < segs; i += gridDim.x * 256) clear_count[i] = clear_need[i] = 0;
@@ -188,7 +188,7 @@ __device__ __forceinline__ void static_for(F&& f) {
 // VEC keys per load: 4 when every run starts on a 16-byte boundary (N and seg_tokens multiples of 4).
 // The threads keep the segment's keys in registers, VEC * BATCH each, and only the first pass loads
 // them (from L2 or LDS in every pass: 65536 keys of 8192 tokens x 8 experts 43 -> 34 us, 3000 tokens 9.5 -> 6.9).
-// Longer segments: drop_big_hist_kernel and what follows it.
+// Longer segments: see select_form.
 template <int NT, int VEC, int BATCH>
 __global__ __launch_bounds__(NT) void drop_select_kernel(const uint32_t* __restrict__ key_t,
                                                           uint32_t* __restrict__ seg_tau,
@@ -363,7 +363,7 @@ __global__ __launch_bounds__(NT) void drop_select_kernel(const uint32_t* __restr
 // needs a pass over them per radix digit and another for the counts, at one compute unit's bandwidth.  Here many
 // blocks share a segment: three launches build the histograms of an 11, 11 and 10 bit digit (every block first picks the
 // digit before it from the histogram of the launch before), one counts per expert, one small one settles ties.  Integer
-// atomics throughout: the same numbers run to run.  Which segments come here: launch_capacity_drop.
+// atomics throughout: the same numbers run to run.  Which segments come here: select_form.
 constexpr int kBigChunk = 8192;   // keys (or tokens of a run) of a block
 constexpr int kBigBins = 2048;    // of a level
 struct BigState {                 // of a segment; cleared by drop_prepare_kernel
@@ -371,9 +371,10 @@ struct BigState {                 // of a segment; cleared by drop_prepare_kerne
     uint32_t prefix[2];           // digits picked after the first and the second level
     int32_t rem[3];               // keys of the prefix still to keep; after the last level: of the threshold
     int32_t eq_total;             // keys equal to the threshold
-    int32_t first_eq, last_eq;    // seg_tokens - the lowest token with such a key, 1 + the highest
-    int32_t pad[4];
+    int32_t pad[2];
 };
+constexpr int kBigPiece = 1024;   // tokens of an entry in the table of equal keys, see drop_big_count_kernel
+static int big_pieces(int seg_tokens) { return (seg_tokens + kBigPiece - 1) / kBigPiece; }
 static_assert(sizeof(BigState) % 16 == 0, "whole words");
 
 // The digit of `hist` in which the rem-th key from above lies, for the whole block of 256 threads: *digit, and in *left how
@@ -461,20 +462,21 @@ __global__ __launch_bounds__(256) void drop_big_hist_kernel(const uint32_t* __re
         if (hist[i]) atomicAdd(&st->hist[LEVEL][i], (uint32_t)hist[i]);
 }
 
-// Keys above and equal to the threshold, per expert: sums in seg_count and seg_need (cleared before).
+// Keys above and equal to the threshold, per expert: sums in seg_count and seg_need (cleared before), and for budgets over
+// several experts the number of equal keys of every kBigPiece tokens in eq_table [expert segment][piece].  A wave takes a
+// piece at a time.
 __global__ __launch_bounds__(256) void drop_big_count_kernel(const uint32_t* __restrict__ key_t, BigState* __restrict__ state,
-                                                             uint32_t* __restrict__ seg_tau, int32_t* __restrict__ seg_need,
-                                                             int32_t* __restrict__ seg_count, int N, int E, int seg_tokens,
-                                                             int span, int parts) {
+                                                             int32_t* __restrict__ eq_table, uint32_t* __restrict__ seg_tau,
+                                                             int32_t* __restrict__ seg_need, int32_t* __restrict__ seg_count,
+                                                             int N, int E, int seg_tokens, int span, int parts, int pieces) {
     __shared__ int red[4];
-    __shared__ int lo, hi;
     const int seg = blockIdx.x / parts, part = blockIdx.x - seg * parts;
-    const int b = seg / E, e = seg - b * E, ds = b * (E / span) + e / span, tid = threadIdx.x;
+    const int b = seg / E, e = seg - b * E, ds = b * (E / span) + e / span, tid = threadIdx.x, lane = tid & 63;
     const uint32_t* keys = key_t + (size_t)e * N + (size_t)b * seg_tokens;
     BigState* st = state + ds;
     uint32_t tau = 0;  // every candidate (key >= 1) passes
-    if (tid == 0) lo = hi = 0;
-    if (st->rem[0] > 0) {
+    const bool threshold = st->rem[0] > 0;
+    if (threshold) {
         int digit, left, total;
         pick_digit(st->hist[2], st->rem[1], &digit, &left, &total, red);
         tau = st->prefix[1] | (uint32_t)digit;
@@ -483,77 +485,115 @@ __global__ __launch_bounds__(256) void drop_big_count_kernel(const uint32_t* __r
             st->eq_total = (int)st->hist[2][digit];
         }
     }
-    __syncthreads();
-    int gt = 0, eq = 0;
-    for (int i = tid; i < kBigChunk; i += 256) {
-        const int tl = part * kBigChunk + i;
-        const uint32_t key = tl < seg_tokens ? keys[tl] : 0u;
-        gt += key > tau;
-        if (key == tau && key != 0u) {
-            ++eq;
-            atomicMax(&lo, seg_tokens - tl);
-            atomicMax(&hi, tl + 1);
+    int gt = 0, eq = 0;  // of this wave
+    for (int q = tid >> 6; q < kBigChunk / kBigPiece; q += 4) {
+        const int piece = part * (kBigChunk / kBigPiece) + q, t0 = piece * kBigPiece + lane;
+        if (piece >= pieces) break;
+        constexpr int kLoads = kBigPiece / kWave;
+        uint32_t key[kLoads];
+#pragma unroll
+        for (int j = 0; j < kLoads; ++j) key[j] = t0 + kWave * j < seg_tokens ? keys[t0 + kWave * j] : 0u;
+        int here = 0;
+#pragma unroll
+        for (int j = 0; j < kLoads; ++j) {
+            gt += __popcll(__ballot(key[j] > tau));
+            here += __popcll(__ballot(key[j] == tau && key[j] != 0u));
         }
+        if (threshold && span > 1 && lane == 0) eq_table[(size_t)seg * pieces + piece] = here;
+        eq += here;
     }
-    const int gt_total = block_sum_256(gt, red), eq_total = block_sum_256(eq, red);
+    const int gt_total = block_sum_256(lane == 0 ? gt : 0, red), eq_total = block_sum_256(lane == 0 ? eq : 0, red);
     if (tid == 0) {
         if (part == 0) seg_tau[seg] = tau;
         if (gt_total) atomicAdd(&seg_count[seg], gt_total);
-        if (eq_total) {
-            atomicAdd(&seg_need[seg], eq_total);
-            atomicMax(&st->first_eq, lo);
-            atomicMax(&st->last_eq, hi);
-        }
+        if (eq_total) atomicAdd(&seg_need[seg], eq_total);
     }
 }
 
-// One block per segment.  seg_need: how many of the keys equal to the threshold an expert keeps; where there are more of
-// them than the budget has room for they are granted in (token, expert) order, as in drop_select_kernel.
-__global__ __launch_bounds__(256) void drop_big_finish_kernel(const uint32_t* __restrict__ key_t,
-                                                              const BigState* __restrict__ state,
-                                                              const uint32_t* __restrict__ seg_tau,
-                                                              int32_t* __restrict__ seg_need, int32_t* __restrict__ seg_count,
-                                                              int N, int E, int seg_tokens, int span) {
-    __shared__ int red[4];
-    __shared__ int eq_s[kMaxExperts];
-    __shared__ int sh_tie_token, sh_tie_run;
+// One block per segment.  seg_need: how many of the keys equal to the threshold an expert keeps.  Where a budget over several
+// experts has room for a part of them they are granted in (token, expert) order, as in drop_select_kernel: the table tells
+// the piece of tokens in which the budget ends, a thread per token of that piece the pair.
+constexpr int kFinishThreads = kBigPiece;
+__global__ __launch_bounds__(kFinishThreads) void drop_big_finish_kernel(const uint32_t* __restrict__ key_t,
+                                                                         const BigState* __restrict__ state,
+                                                                         const int32_t* __restrict__ eq_table,
+                                                                         const uint32_t* __restrict__ seg_tau,
+                                                                         int32_t* __restrict__ seg_need,
+                                                                         int32_t* __restrict__ seg_count, int N, int E,
+                                                                         int seg_tokens, int span, int pieces) {
+    __shared__ int red[kFinishThreads / kWave];
+    __shared__ int need_s[kMaxExperts];
+    __shared__ int sh_piece, sh_left, sh_tie_token, sh_tie_run;
     const int groups = E / span, b = blockIdx.x / groups, e0 = (blockIdx.x - b * groups) * span, tid = threadIdx.x;
+    const int lane = tid & 63, wv = tid >> 6;
     const uint32_t* keys = key_t + (size_t)e0 * N + (size_t)b * seg_tokens;
     const BigState* st = state + blockIdx.x;
     const int seg0 = b * E + e0, rem = st->rem[2];
-    if (st->eq_total > rem) {
-        const uint32_t tau = seg_tau[seg0];
-        const int from = seg_tokens - st->first_eq, to = st->last_eq;  // the tokens that hold such keys
-        const int per = (to - from + 255) / 256;
-        const int tb = from + tid * per < to ? from + tid * per : to, te = tb + per < to ? tb + per : to;
-        int c = 0;
-        for (int tl = tb; tl < te; ++tl)
-            for (int r = 0; r < span; ++r) c += keys[(size_t)r * N + tl] == tau;
-        int total;
-        const int before = block_exclusive_scan_256(c, red, &total);
-        if (before < rem && rem <= before + c) {  // exactly one thread: 1 <= rem < eq_total = total
-            int left = rem - before;
-            for (int tl = tb; tl < te && left > 0; ++tl)
-                for (int r = 0; r < span && left > 0; ++r)
-                    if (keys[(size_t)r * N + tl] == tau && --left == 0) {
-                        sh_tie_token = tl;
-                        sh_tie_run = r;
-                    }
-        }
-        for (int r = tid; r < span; r += 256) eq_s[r] = 0;
-        __syncthreads();
-        const int tie_token = sh_tie_token, tie_run = sh_tie_run;
-        for (int r = 0; r < span; ++r) {
-            int eq = 0;
-            for (int tl = from + tid; tl < tie_token + (r <= tie_run ? 1 : 0); tl += 256)
-                eq += keys[(size_t)r * N + tl] == tau;
-            if (eq) atomicAdd(&eq_s[r], eq);
-        }
-        __syncthreads();
-        for (int r = tid; r < span; r += 256) seg_need[seg0 + r] = eq_s[r];
-    }
+    for (int r = tid; r < span; r += kFinishThreads) need_s[r] = span == 1 && seg_need[seg0] > rem ? rem : seg_need[seg0 + r];
     __syncthreads();
-    for (int r = tid; r < span; r += 256) seg_count[seg0 + r] += seg_need[seg0 + r];
+    if (span > 1 && st->eq_total > rem) {
+        const uint32_t tau = seg_tau[seg0];
+        const int32_t* table = eq_table + (size_t)seg0 * pieces;
+        // the piece: a thread adds up a run of consecutive ones
+        const int per = (pieces + kFinishThreads - 1) / kFinishThreads;
+        const int pb = tid * per < pieces ? tid * per : pieces, pe = pb + per < pieces ? pb + per : pieces;
+        int c = 0, total;
+        for (int p = pb; p < pe; ++p)
+#pragma unroll 8
+            for (int r = 0; r < span; ++r) c += table[(size_t)r * pieces + p];
+        int before = block_exclusive_scan<kFinishThreads>(c, red, &total);
+        if (before < rem && rem <= before + c) {  // exactly one thread: 1 <= rem < eq_total = total
+            for (int p = pb; p < pe; ++p) {
+                int here = 0;
+                for (int r = 0; r < span; ++r) here += table[(size_t)r * pieces + p];
+                if (before < rem && rem <= before + here) {
+                    sh_piece = p;
+                    sh_left = rem - before;
+                }
+                before += here;
+            }
+        }
+        for (int r = tid; r < span; r += kFinishThreads) need_s[r] = 0;
+        __syncthreads();
+        // the pair
+        const int piece = sh_piece, left = sh_left, t = piece * kBigPiece + tid;
+        c = 0;
+        if (t < seg_tokens)
+#pragma unroll 8
+            for (int r = 0; r < span; ++r) c += keys[(size_t)r * N + t] == tau;
+        before = block_exclusive_scan<kFinishThreads>(c, red, &total);
+        if (before < left && left <= before + c) {
+            int open = left - before;
+            for (int r = 0; r < span; ++r)
+                if (keys[(size_t)r * N + t] == tau && --open == 0) {
+                    sh_tie_token = t;
+                    sh_tie_run = r;
+                }
+        }
+        __syncthreads();
+        // what each expert keeps: its pieces before that one, its tokens before the pair
+        const int tie_token = sh_tie_token, tie_run = sh_tie_run;
+        for (int r0 = 0; r0 < span; r0 += 8) {
+            uint32_t key[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) key[u] = r0 + u < span && t <= tie_token ? keys[(size_t)(r0 + u) * N + t] : 0u;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int n = __popcll(__ballot(key[u] == tau && (t < tie_token || r0 + u <= tie_run)));
+                if (lane == 0 && n) atomicAdd(&need_s[r0 + u], n);
+            }
+        }
+        for (int r = wv; r < span; r += kFinishThreads / kWave) {
+            int n = 0;
+            for (int p = lane; p < piece; p += kWave) n += table[(size_t)r * pieces + p];
+            if (n) atomicAdd(&need_s[r], n);
+        }
+        __syncthreads();
+    }
+    for (int r = tid; r < span; r += kFinishThreads) {
+        seg_need[seg0 + r] = need_s[r];
+        seg_count[seg0 + r] += need_s[r];
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1185,14 +1225,21 @@ __global__ __launch_bounds__(NT) void drop_fused_kernel(
 // keys are fetched four at a time: every run starts on a 16-byte boundary
 static bool select_by_four(const Sizes& s, int n_tokens) { return n_tokens % 4 == 0 && s.seg_tokens % 4 == 0; }
 
-// Bytes of the segments' states where many blocks share a segment, 0 where a block has it alone: from where a block cannot
-// hold the keys in its registers.  Selection, one block -> many: 2 segments of 101472 keys 66 -> 32 us, one of 2^20 keys
-// 822 -> 30 us (Score), of 1048640 keys with an odd pitch 612 -> 46 us (Order, whose ties fall on one token), of 2^22
-// keys 961 -> 36 us; but 64 segments of 30001 keys 35 -> 46.  Keys at an odd pitch are held one load each, 32 a thread.
-size_t drop_big_state_bytes(const moe_desc_t& d, const Sizes& s) {
+// How the segments' thresholds are found.
+enum class Select { kHeld, kShared };
+static Select select_form(const moe_desc_t& d, const Sizes& s) {
     const long long n_keys = (long long)s.seg_tokens * s.span;
-    if (n_keys <= (select_by_four(s, d.n_tokens) ? 65536 : 32768) || s.cap == 0) return 0;  // (no capacity: nothing to walk)
-    return (size_t)s.n_blocks * (d.n_experts / s.span) * sizeof(BigState);
+    // A block holds the keys in its registers (at an odd pitch one load each, 32 a thread); no capacity: nothing to walk.
+    // Selection, one block -> many: 2 segments of 101472 keys 66 -> 32 us, one of 2^20 keys 822 -> 30 us (Score), of 1048640
+    // keys with an odd pitch 612 -> 46 us, of 2^22 keys 961 -> 36 us; but 64 segments of 30001 keys 35 -> 46.
+    if (n_keys <= (select_by_four(s, d.n_tokens) ? 65536 : 32768) || s.cap == 0) return Select::kHeld;
+    return Select::kShared;
+}
+
+size_t drop_big_state_bytes(const moe_desc_t& d, const Sizes& s) {
+    if (select_form(d, s) != Select::kShared) return 0;
+    const size_t segs = (size_t)s.n_blocks * d.n_experts;
+    return segs / s.span * sizeof(BigState) + (s.span > 1 ? segs * big_pieces(s.seg_tokens) * sizeof(int32_t) : 0);
 }
 
 hipError_t launch_capacity_drop(const moe_desc_t& d, const Sizes& s, const DropWorkspace& ws, const float* scores,
@@ -1247,7 +1294,10 @@ hipError_t launch_capacity_drop(const moe_desc_t& d, const Sizes& s, const DropW
             return hipGetLastError();
         }
     }
-    const bool big = ws.big_state != nullptr;
+    const Select form = select_form(d, s);
+    const bool many = form == Select::kShared;  // blocks per segment
+    const int segs = s.n_blocks * E, dsegs = segs / s.span;
+    BigState* state = form == Select::kShared ? (BigState*)ws.big_state : nullptr;
     if (N > 0) {
         const int grid = (N + kPrepTokens - 1) / kPrepTokens;
         const size_t lds = (size_t)kPrepTokens * (E | 1) * 5;
@@ -1258,33 +1308,33 @@ hipError_t launch_capacity_drop(const moe_desc_t& d, const Sizes& s, const DropW
         hipLaunchKernelGGL(drop_prepare_kernel, dim3(grid), dim3(256), lds, st, scores, topk_idx, ws.key_t, ws.slot_t,
                            pair_row, N, E, s.list_k, s.slots, d.mode == MOE_MODE_EXPANDED_DROP ? 1 : 0, s.group_tokens,
                            s.group_experts, d.metric, s.seg_tokens > 0 ? s.seg_tokens : 1, token_class, seed,
-                           (uint32_t*)ws.big_state, big ? (long long)(s.n_blocks * (E / s.span)) * (long long)(sizeof(BigState) / 4) : 0ll,
-                           seg_count, ws.seg_need, s.n_blocks * E);
+                           (uint32_t*)state, state ? (long long)dsegs * (long long)(sizeof(BigState) / 4) : 0ll,
+                           many ? seg_count : nullptr, ws.seg_need, segs);
     }
-    const int segs = s.n_blocks * E;
-    if (big) {
+    if (many) {
         ProfileScope prof(MOE_KERNEL_DROP_SELECT, st);
-        BigState* state = (BigState*)ws.big_state;
-        const int dsegs = segs / s.span;
         const int chunks = (int)(((long long)s.seg_tokens * s.span + kBigChunk - 1) / kBigChunk);
         const int parts = (s.seg_tokens + kBigChunk - 1) / kBigChunk;
         auto hist = [&](auto kern) {
             hipLaunchKernelGGL(kern, dim3(dsegs * chunks), dim3(256), 0, st, ws.key_t, state, N, E, s.seg_tokens, s.span, s.cap,
                                chunks);
         };
-        if (select_by_four(s, N)) {
+        if (state && select_by_four(s, N)) {
             hist(drop_big_hist_kernel<0, 4>);
             hist(drop_big_hist_kernel<1, 4>);
             hist(drop_big_hist_kernel<2, 4>);
-        } else {
+        } else if (state) {
             hist(drop_big_hist_kernel<0, 1>);
             hist(drop_big_hist_kernel<1, 1>);
             hist(drop_big_hist_kernel<2, 1>);
         }
-        hipLaunchKernelGGL(drop_big_count_kernel, dim3(segs * parts), dim3(256), 0, st, ws.key_t, state, ws.seg_tau, ws.seg_need,
-                           seg_count, N, E, s.seg_tokens, s.span, parts);
-        hipLaunchKernelGGL(drop_big_finish_kernel, dim3(dsegs), dim3(256), 0, st, ws.key_t, state, ws.seg_tau, ws.seg_need,
-                           seg_count, N, E, s.seg_tokens, s.span);
+        const int pieces = big_pieces(s.seg_tokens);
+        int32_t* eq_table = state ? (int32_t*)(state + dsegs) : nullptr;  // (several experts under a budget)
+        hipLaunchKernelGGL(drop_big_count_kernel, dim3(segs * parts), dim3(256), 0, st, ws.key_t, state, eq_table, ws.seg_tau,
+                           ws.seg_need, seg_count, N, E, s.seg_tokens, s.span, parts, pieces);
+        if (state)
+            hipLaunchKernelGGL(drop_big_finish_kernel, dim3(dsegs), dim3(kFinishThreads), 0, st, ws.key_t, state, eq_table,
+                               ws.seg_tau, ws.seg_need, seg_count, N, E, s.seg_tokens, s.span, pieces);
     } else {
         ProfileScope prof(MOE_KERNEL_DROP_SELECT, st);
         const size_t n_keys = (size_t)s.seg_tokens * s.span;
@@ -1293,7 +1343,7 @@ hipError_t launch_capacity_drop(const moe_desc_t& d, const Sizes& s, const DropW
         auto kern = !wide ? (vec ? drop_select_kernel<256, 4, 8> : drop_select_kernel<256, 1, 8>)
                     : vec ? drop_select_kernel<1024, 4, 16>
                           : (n_keys <= 16384 ? drop_select_kernel<1024, 1, 16> : drop_select_kernel<1024, 1, 32>);
-        hipLaunchKernelGGL(kern, dim3(segs / s.span), dim3(wide ? 1024 : 256), 0, st, ws.key_t, ws.seg_tau,
+        hipLaunchKernelGGL(kern, dim3(dsegs), dim3(wide ? 1024 : 256), 0, st, ws.key_t, ws.seg_tau,
                            ws.seg_need, seg_count, N, E, s.seg_tokens, s.span, s.cap);
     }
     auto emit = [&](bool last) {

@@ -337,6 +337,38 @@ def test_plan_block_orders_of_the_emit(orc, n, e, k, g, mode, scope, gamma):
     check_route_and_plan(orc, logits, n, e, k, g, mode, scope, gamma, f"emit order {n}x{e}")
 
 
+def tied_logits(rng, n, e, ties):
+    logits = rng.standard_normal((n, e)).astype(np.float32)
+    if ties == "flat":
+        logits[:] = 0.0
+    elif ties == "few":
+        logits = rng.integers(-1, 2, size=(n, e)).astype(np.float32)
+    elif ties == "pad":      # a quarter of the tokens alike, all over the batch
+        logits[rng.random(n) < 0.25] = logits[0]
+    elif ties == "padend":   # the same at its end
+        logits[n - n // 4:] = logits[0]
+    return logits
+
+
+@pytest.mark.parametrize("n,e,k,g,mode,scope,gamma,metric,ties", [
+    (6144, 32, 4, 1, TD, GLOBAL_DEV, 0.5, 0, "flat"),     # the budget ends with the last pair of a piece of 1024 tokens
+    (6145, 32, 4, 1, ED, GLOBAL_DEV, 0.5, 0, "flat"),     # inside one; odd pitch, every expert a candidate
+    (20000, 16, 2, 2, ED, LOCAL_DEV, 0.4, 0, "pad"),
+    (20002, 16, 2, 2, ED, LOCAL_DEV, 0.4, 0, "padend"),
+    (9000, 64, 2, 4, ED, GLOBAL_DEV, 0.6, 0, "few"),
+    (700, 200, 8, 1, ED, GLOBAL_DEV, 0.3, 0, "few"),      # a single ragged piece, more experts than a wave
+    (5000, 32, 4, 1, ED, GLOBAL_DEV, 0.7, 1, None),       # Order: every key of a token is equal
+    (70004, 3, 2, 1, TD, GLOBAL, 0.4, 0, "pad"),          # single experts: the first equal keys in token order
+    (41001, 2, 1, 1, TD, GLOBAL, 0.4, 0, "flat"),
+])
+def test_plan_ties_in_segments_of_many_blocks(orc, n, e, k, g, mode, scope, gamma, metric, ties):
+    """More keys equal the threshold than a segment has room for, spread over all of it."""
+    logits = tied_logits(np.random.default_rng(n + e), n, e, ties)
+    check_route_and_plan(orc, logits, n, e, k, g, mode, scope, gamma, f"ties {n}x{e} {ties}", metric)
+    check_route_and_plan(orc, logits, n, e, k, g, mode, scope, gamma, f"ties {n}x{e} {ties}, at most k", metric, None, 0,
+                         min(2, e - k), True)
+
+
 def test_device_level_ties(orc):
     w = synth.scaled(W["olmoe"], n_tokens=2048, n_experts=32, top_k=4, device_groups=4)
     logits = synth.logits_with_ties(w)
