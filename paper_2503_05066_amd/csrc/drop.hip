@@ -464,7 +464,7 @@ __global__ __launch_bounds__(256) void drop_big_hist_kernel(const uint32_t* __re
 
 // Keys above and equal to the threshold, per expert: sums in seg_count and seg_need (cleared before), and for budgets over
 // several experts the number of equal keys of every kBigPiece tokens in eq_table [expert segment][piece].  A wave takes a
-// piece at a time.
+// piece at a time.  state == nullptr: there is room for every key, the counts are all there is to find.
 __global__ __launch_bounds__(256) void drop_big_count_kernel(const uint32_t* __restrict__ key_t, BigState* __restrict__ state,
                                                              int32_t* __restrict__ eq_table, uint32_t* __restrict__ seg_tau,
                                                              int32_t* __restrict__ seg_need, int32_t* __restrict__ seg_count,
@@ -475,7 +475,7 @@ __global__ __launch_bounds__(256) void drop_big_count_kernel(const uint32_t* __r
     const uint32_t* keys = key_t + (size_t)e * N + (size_t)b * seg_tokens;
     BigState* st = state + ds;
     uint32_t tau = 0;  // every candidate (key >= 1) passes
-    const bool threshold = st->rem[0] > 0;
+    const bool threshold = state && st->rem[0] > 0;
     if (threshold) {
         int digit, left, total;
         pick_digit(st->hist[2], st->rem[1], &digit, &left, &total, red);
@@ -1226,13 +1226,15 @@ __global__ __launch_bounds__(NT) void drop_fused_kernel(
 static bool select_by_four(const Sizes& s, int n_tokens) { return n_tokens % 4 == 0 && s.seg_tokens % 4 == 0; }
 
 // How the segments' thresholds are found.
-enum class Select { kHeld, kShared };
+enum class Select { kHeld, kShared, kCount };
 static Select select_form(const moe_desc_t& d, const Sizes& s) {
     const long long n_keys = (long long)s.seg_tokens * s.span;
     // A block holds the keys in its registers (at an odd pitch one load each, 32 a thread); no capacity: nothing to walk.
     // Selection, one block -> many: 2 segments of 101472 keys 66 -> 32 us, one of 2^20 keys 822 -> 30 us (Score), of 1048640
     // keys with an odd pitch 612 -> 46 us, of 2^22 keys 961 -> 36 us; but 64 segments of 30001 keys 35 -> 46.
     if (n_keys <= (select_by_four(s, d.n_tokens) ? 65536 : 32768) || s.cap == 0) return Select::kHeld;
+    // Room for every key: there is no threshold to find.
+    if (s.cap >= n_keys) return Select::kCount;
     return Select::kShared;
 }
 
@@ -1295,7 +1297,7 @@ hipError_t launch_capacity_drop(const moe_desc_t& d, const Sizes& s, const DropW
         }
     }
     const Select form = select_form(d, s);
-    const bool many = form == Select::kShared;  // blocks per segment
+    const bool many = form == Select::kShared || form == Select::kCount;  // blocks per segment
     const int segs = s.n_blocks * E, dsegs = segs / s.span;
     BigState* state = form == Select::kShared ? (BigState*)ws.big_state : nullptr;
     if (N > 0) {

@@ -369,6 +369,19 @@ def test_plan_ties_in_segments_of_many_blocks(orc, n, e, k, g, mode, scope, gamm
                          min(2, e - k), True)
 
 
+@pytest.mark.parametrize("n,e,k,g,mode,scope,gamma", [
+    (65540, 4, 2, 1, NONE, GLOBAL, 1.0),        # no drop
+    (4500, 32, 4, 1, NONE, GLOBAL_DEV, 1.0),
+    (33333, 3, 2, 1, TD, GLOBAL, math.inf),     # odd pitch
+    (4097, 32, 3, 1, ED, LOCAL_DEV, 50.0),      # a budget that holds every key of the segment
+])
+def test_plan_long_segments_with_room_for_all(orc, n, e, k, g, mode, scope, gamma):
+    """Segments of many blocks whose capacity every candidate fits: counts only."""
+    logits = np.random.default_rng(n + e).standard_normal((n, e)).astype(np.float32)
+    check_route_and_plan(orc, logits, n, e, k, g, mode, scope, gamma, f"room for all {n}x{e}")
+    check_route_and_plan(orc, logits, n, e, k, g, mode, scope, gamma, f"room for all {n}x{e}, at most k", 0, None, 0, 1, True)
+
+
 def test_device_level_ties(orc):
     w = synth.scaled(W["olmoe"], n_tokens=2048, n_experts=32, top_k=4, device_groups=4)
     logits = synth.logits_with_ties(w)
