@@ -9,7 +9,7 @@
 //                     Order) or a hashed draw (Random), below an optional 2-bit token class.
 //   2. drop_select    per segment: the cap-th largest key by a 4-pass radix select over LDS
 //                     histograms (the threshold tau of Eq. 8) and how many keys equal to it survive
-//                     (drop_big_*: the same for segments that many blocks share).
+//                     (drop_big_*: the same for segments that many blocks share; which form: select_form).
 //   3. drop_emit      per segment (a block per 4096 tokens of it): ordered compaction of the survivors,
 //                     which yields rows in ascending token order and gives ties at the threshold to
 //                     the lower token index.
@@ -189,7 +189,8 @@ __device__ __forceinline__ void static_for(F&& f) {
 // The threads keep the segment's keys in registers, VEC * BATCH each, and only the first pass loads
 // them (from L2 or LDS in every pass: 65536 keys of 8192 tokens x 8 experts 43 -> 34 us, 3000 tokens 9.5 -> 6.9).
 // Longer segments: see select_form.
-template <int NT, int VEC, int BATCH>
+// HELD == false: longer segments, read from L2 in every pass, BATCH loads at a time.
+template <int NT, int VEC, int BATCH, bool HELD>
 __global__ __launch_bounds__(NT) void drop_select_kernel(const uint32_t* __restrict__ key_t,
                                                           uint32_t* __restrict__ seg_tau,
                                                           int32_t* __restrict__ seg_need,
@@ -218,28 +219,40 @@ __global__ __launch_bounds__(NT) void drop_select_kernel(const uint32_t* __restr
     struct alignas(4 * VEC) KeyVec {
         uint32_t c[VEC];
     };
-    uint32_t held[BATCH * VEC];
-    static_for<BATCH>([&](auto uc) __attribute__((always_inline)) {
-        constexpr int u = decltype(uc)::value;
-        const int i = tid * VEC + NT * VEC * u;  // VEC divides seg_tokens: the keys of a load share a run
-        const int run = span == 1 ? 0 : i / seg_tokens;
-        // no branch, so that all loads are under way together; past the end: key 0, not used
-        const size_t at = i < n_keys ? (size_t)run * N + (i - run * seg_tokens) : 0;
-        const KeyVec v = *(const KeyVec*)(keys + at);
-        static_for<VEC>([&](auto cc) __attribute__((always_inline)) {
-            held[u * VEC + decltype(cc)::value] = v.c[decltype(cc)::value];
+    // VEC divides seg_tokens: the keys of a load share a run
+    auto run_of = [&](int i) __attribute__((always_inline)) { return span == 1 ? 0 : i / seg_tokens; };
+    // no branch, so that all loads are under way together; past the end: key 0, not used
+    auto load = [&](int i) __attribute__((always_inline)) {
+        const int run = run_of(i);
+        return *(const KeyVec*)(keys + (i < n_keys ? (size_t)run * N + (i - run * seg_tokens) : 0));
+    };
+    KeyVec held[BATCH];
+    auto load_batch = [&](int i0) __attribute__((always_inline)) {
+        static_for<BATCH>([&](auto uc) __attribute__((always_inline)) {
+            held[decltype(uc)::value] = load(i0 + NT * VEC * decltype(uc)::value);
         });
-    });
-    auto for_each_key = [&](auto&& f) __attribute__((always_inline)) {
+    };
+    auto walk_batch = [&](int i0, auto&& f) __attribute__((always_inline)) {
         static_for<BATCH>([&](auto uc) __attribute__((always_inline)) {
             constexpr int u = decltype(uc)::value;
-            const int i = tid * VEC + NT * VEC * u, run = span == 1 ? 0 : i / seg_tokens;
+            const int i = i0 + NT * VEC * u, run = run_of(i);
             if (i < n_keys)
                 static_for<VEC>([&](auto cc) __attribute__((always_inline)) {
                     constexpr int c = decltype(cc)::value;
-                    f(run, i - run * seg_tokens + c, held[u * VEC + c]);
+                    f(run, i - run * seg_tokens + c, held[u].c[c]);
                 });
         });
+    };
+    if (HELD) load_batch(tid * VEC);
+    auto for_each_key = [&](auto&& f) __attribute__((always_inline)) {
+        if (HELD) {
+            walk_batch(tid * VEC, f);
+        } else {
+            for (int i0 = tid * VEC; i0 < n_keys; i0 += NT * VEC * BATCH) {
+                load_batch(i0);
+                walk_batch(i0, f);
+            }
+        }
     };
 
     // the histogram of the keys' top byte (the first radix pass)
@@ -1226,16 +1239,20 @@ __global__ __launch_bounds__(NT) void drop_fused_kernel(
 static bool select_by_four(const Sizes& s, int n_tokens) { return n_tokens % 4 == 0 && s.seg_tokens % 4 == 0; }
 
 // How the segments' thresholds are found.
-enum class Select { kHeld, kShared, kCount };
+enum class Select { kHeld, kLoop, kShared, kCount };
 static Select select_form(const moe_desc_t& d, const Sizes& s) {
     const long long n_keys = (long long)s.seg_tokens * s.span;
     // A block holds the keys in its registers (at an odd pitch one load each, 32 a thread); no capacity: nothing to walk.
-    // Selection, one block -> many: 2 segments of 101472 keys 66 -> 32 us, one of 2^20 keys 822 -> 30 us (Score), of 1048640
-    // keys with an odd pitch 612 -> 46 us, of 2^22 keys 961 -> 36 us; but 64 segments of 30001 keys 35 -> 46.
     if (n_keys <= (select_by_four(s, d.n_tokens) ? 65536 : 32768) || s.cap == 0) return Select::kHeld;
     // Room for every key: there is no threshold to find.
     if (s.cap >= n_keys) return Select::kCount;
-    return Select::kShared;
+    // One block reads its segment from L2 five times, however many others do; shared segments cost five launches and four
+    // passes over all keys at the chip's bandwidth.  One block -> shared: 4 segments of 262144 keys 100 -> 26 us, 64 of
+    // 65540 32 -> 31, of 262144 91 -> 64; but 128 of 65540 32 -> 40, of 131072 53 -> 60, 256 of 262144 132 -> 195; at an odd
+    // pitch 4 of 32771 30 -> 37, 64 of 40001 37 -> 43, of 50001 46 -> 41.  Budgets over several experts (the walk divides
+    // by the run length, and ties need a search): 256 of 66560 70 -> 67, 64 of 131104 198 -> 58.
+    const int segs = s.n_blocks * (d.n_experts / s.span);
+    return s.span > 1 || (n_keys > 40960 && segs <= 64) ? Select::kShared : Select::kLoop;
 }
 
 size_t drop_big_state_bytes(const moe_desc_t& d, const Sizes& s) {
@@ -1342,9 +1359,11 @@ hipError_t launch_capacity_drop(const moe_desc_t& d, const Sizes& s, const DropW
         const size_t n_keys = (size_t)s.seg_tokens * s.span;
         const bool vec = select_by_four(s, N);
         const bool wide = n_keys > (vec ? 4096 : 2048);  // threads per block
-        auto kern = !wide ? (vec ? drop_select_kernel<256, 4, 8> : drop_select_kernel<256, 1, 8>)
-                    : vec ? drop_select_kernel<1024, 4, 16>
-                          : (n_keys <= 16384 ? drop_select_kernel<1024, 1, 16> : drop_select_kernel<1024, 1, 32>);
+        auto kern = !wide ? (vec ? drop_select_kernel<256, 4, 8, true> : drop_select_kernel<256, 1, 8, true>)
+                    : form == Select::kLoop
+                        ? (vec ? drop_select_kernel<1024, 4, 16, false> : drop_select_kernel<1024, 1, 16, false>)
+                    : vec ? drop_select_kernel<1024, 4, 16, true>
+                          : (n_keys <= 16384 ? drop_select_kernel<1024, 1, 16, true> : drop_select_kernel<1024, 1, 32, true>);
         hipLaunchKernelGGL(kern, dim3(dsegs), dim3(wide ? 1024 : 256), 0, st, ws.key_t, ws.seg_tau,
                            ws.seg_need, seg_count, N, E, s.seg_tokens, s.span, s.cap);
     }

@@ -382,6 +382,23 @@ def test_plan_long_segments_with_room_for_all(orc, n, e, k, g, mode, scope, gamm
     check_route_and_plan(orc, logits, n, e, k, g, mode, scope, gamma, f"room for all {n}x{e}, at most k", 0, None, 0, 1, True)
 
 
+@pytest.mark.parametrize("n,e,k,g,mode,scope,gamma,ties", [
+    (65540, 66, 2, 1, TD, GLOBAL, 0.5, None),       # more segments than are shared among blocks
+    (65540, 66, 2, 1, TD, GLOBAL, 0.5, "few"),
+    (131088, 34, 2, 2, ED, LOCAL, 0.5, "pad"),      # 68 of them in two blocks of tokens
+    (32771, 3, 1, 1, TD, GLOBAL, 0.4, None),        # odd pitch: a few, just too long to be held
+    (40961, 2, 1, 1, TD, GLOBAL, 0.4, None),        # and either side of where blocks share them
+    (40959, 2, 1, 1, TD, GLOBAL, 0.4, "flat"),
+    (41001, 65, 3, 1, TD, GLOBAL, 0.7, None),
+])
+def test_plan_segments_read_in_every_pass(orc, n, e, k, g, mode, scope, gamma, ties):
+    """Long segments of single experts that one block each selects from."""
+    logits = tied_logits(np.random.default_rng(n + e), n, e, ties)
+    check_route_and_plan(orc, logits, n, e, k, g, mode, scope, gamma, f"re-read {n}x{e} {ties}")
+    if n < 65540:
+        check_route_and_plan(orc, logits, n, e, k, g, mode, scope, gamma, f"re-read {n}x{e}, at most k", 0, None, 0, 1, True)
+
+
 def test_device_level_ties(orc):
     w = synth.scaled(W["olmoe"], n_tokens=2048, n_experts=32, top_k=4, device_groups=4)
     logits = synth.logits_with_ties(w)
