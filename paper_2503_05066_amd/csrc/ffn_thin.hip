@@ -43,7 +43,8 @@ __device__ __forceinline__ void count_down(F&& f) {
 // One block: up to 16 * TM rows of an expert times 32 weight rows: 32 output columns, or the gate and up rows of 16
 // hidden columns.  The waves split K and share nothing until the end: each keeps a ring of its own in LDS, filled by
 // direct loads (the layout and the piece swizzle of ffn.hip), waits for its own slabs only and needs no barrier.
-template <int TM, bool SWIGLU>
+// ONCE: the block's only pass over its weights, whose lines then need not be kept.
+template <int TM, bool SWIGLU, bool ONCE>
 struct ThinTile {
     static constexpr int kRows = 16 * TM;
     static constexpr int kCols = SWIGLU ? kThinWeightRows / 2 : kThinWeightRows;
@@ -96,7 +97,7 @@ struct ThinTile {
                 if (act)
                     __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lptr_t)(dst + i * 1024), 16, voff[i], k_bytes, 0, 0);
                 else
-                    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lptr_t)(dst + i * 1024), 16, voff[i], k_bytes, 0, 2);
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lptr_t)(dst + i * 1024), 16, voff[i], k_bytes, 0, ONCE ? 2 : 0);
             }
         };
         const int piece = lr * 128 + ((p ^ ((lr >> 1) & 7)) << 4);  // this lane's operand piece of a sub-tile, first half slab
@@ -196,7 +197,8 @@ struct ThinTile {
 // expert_offset is the caller's: an expert of a plan from elsewhere may have more rows than the capacity leaves it, and then
 // has big tiles too.  So the blocks walk the joint list, as often around as it takes: with the plans of this library's own
 // drop once, because no expert has a second tile there.  A tile of more than 32 rows is done in passes of its blocks over
-// the same weights.
+// the same weights, which stay in the L2 for them (64 tokens top-6, 64 x 4096 x 1408, 56 rows on one expert 210 -> 187 us,
+// 64 top-2, 8 x 4096 x 1024, 53 rows 53 -> 47).
 template <bool SWIGLU>
 __global__ __launch_bounds__(64 * kThinWaves, 2) void ffn_thin_kernel(
     const uint16_t* __restrict__ A, const uint16_t* __restrict__ B0, const uint16_t* __restrict__ B1,
@@ -204,18 +206,20 @@ __global__ __launch_bounds__(64 * kThinWaves, 2) void ffn_thin_kernel(
     const int32_t* __restrict__ tile_row0, const int32_t* __restrict__ tile_rows, const int32_t* __restrict__ n_tiles, int K,
     int Nout, int col_blocks) {
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
-    const int first = blockIdx.x / col_blocks, n0 = (blockIdx.x - first * col_blocks) * ThinTile<1, SWIGLU>::kCols;
+    const int first = blockIdx.x / col_blocks, n0 = (blockIdx.x - first * col_blocks) * ThinTile<1, SWIGLU, true>::kCols;
     const int step = gridDim.x / col_blocks, nt = *n_tiles;
     for (int tile = first; tile < nt; tile += step) {
         const int e = tile_expert[tile], row0 = tile_row0[tile], rows = tile_rows[tile] & kTileRowsMask;
         for (int at = 0; at < rows; at += kThinPiece) {
             if (tile > first || at > 0) __syncthreads();  // the first wave reads the others' sums out of their rings
             const int left = rows - at;
-            if (left <= 16)
-                ThinTile<1, SWIGLU>::run(A, B0, B1, C, gather, e, row0 + at, left, n0, K, Nout, smem);
+            if (rows > kThinPiece)
+                ThinTile<2, SWIGLU, false>::run(A, B0, B1, C, gather, e, row0 + at, left < kThinPiece ? left : kThinPiece, n0, K,
+                                                Nout, smem);
+            else if (rows > 16)
+                ThinTile<2, SWIGLU, true>::run(A, B0, B1, C, gather, e, row0, rows, n0, K, Nout, smem);
             else
-                ThinTile<2, SWIGLU>::run(A, B0, B1, C, gather, e, row0 + at, left < kThinPiece ? left : kThinPiece, n0, K, Nout,
-                                         smem);
+                ThinTile<1, SWIGLU, true>::run(A, B0, B1, C, gather, e, row0, rows, n0, K, Nout, smem);
         }
     }
 }
@@ -247,7 +251,7 @@ static void launch_thin(const Sizes& s, int experts, const void* A, const void* 
     once_per_device(configured, [&] {
         (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     });
-    const int col_blocks = Nout / ThinTile<1, SWIGLU>::kCols;
+    const int col_blocks = Nout / ThinTile<1, SWIGLU, true>::kCols;
     const long long tiles = s.max_rows < experts ? s.max_rows : experts;
     hipLaunchKernelGGL(kern, dim3((unsigned)(tiles * col_blocks)), dim3(64 * kThinWaves), lds, st, (const uint16_t*)A, (const uint16_t*)B0,
                        (const uint16_t*)B1, (uint16_t*)C, gather, ws.all.expert, ws.all.row0, ws.all.rows,
