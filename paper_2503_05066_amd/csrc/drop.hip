@@ -1358,8 +1358,11 @@ hipError_t launch_capacity_drop(const moe_desc_t& d, const Sizes& s, const DropW
         ProfileScope prof(MOE_KERNEL_DROP_SELECT, st);
         const size_t n_keys = (size_t)s.seg_tokens * s.span;
         const bool vec = select_by_four(s, N);
-        const bool wide = n_keys > (vec ? 4096 : 2048);  // threads per block
-        auto kern = !wide ? (vec ? drop_select_kernel<256, 4, 8, true> : drop_select_kernel<256, 1, 8, true>)
+        // Threads per block: short segments are often many (1024 of 3190 keys at an odd pitch: 36 us with 1024 threads,
+        // 11 with 256).
+        const bool wide = n_keys > 4096;
+        auto kern = !wide ? (vec ? drop_select_kernel<256, 4, 8, true>
+                                 : (n_keys <= 2048 ? drop_select_kernel<256, 1, 8, true> : drop_select_kernel<256, 1, 16, true>))
                     : form == Select::kLoop
                         ? (vec ? drop_select_kernel<1024, 4, 16, false> : drop_select_kernel<1024, 1, 16, false>)
                     : vec ? drop_select_kernel<1024, 4, 16, true>

@@ -311,6 +311,11 @@ def test_plan_large_segments(orc, n, e, k, g, mode, scope, gamma):
     (10923, 3, 1, 1, TD, LOCAL_DEV, 0.4, 0, None),
     (16384, 4, 1, 1, TD, LOCAL_DEV, 0.4, 0, None),         # the most keys one block holds
     (4096, 32, 2, 1, TD, LOCAL_DEV, 0.0, 0, None),      # no capacity
+    (683, 3, 1, 1, TD, GLOBAL_DEV, 0.5, 0, None),          # short segments at an odd pitch: the most keys of each form
+    (2049, 1, 1, 1, ED, LOCAL_DEV, 0.5, 0, None),
+    (1365, 3, 2, 1, ED, LOCAL_DEV, 0.6, 1, None),
+    (585, 7, 2, 1, TD, GLOBAL_DEV, 0.6, 0, "few"),
+    (587, 7, 2, 1, TD, GLOBAL_DEV, 0.6, 0, "few"),
 ])
 def test_plan_segments_of_many_blocks(orc, n, e, k, g, mode, scope, gamma, metric, ties):
     """Segments with more keys than one block holds: thresholds from shared histograms, counts per expert, ties."""
