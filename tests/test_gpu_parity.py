@@ -761,9 +761,9 @@ def test_ffn_single_tile_experts(orc, d, h):
     assert torch.equal(fused.y, buf.y)
 
 
-@pytest.mark.parametrize("d,h", [(2048, 1920), (1920, 2048)])
+@pytest.mark.parametrize("d,h", [(2048, 2432), (2432, 2048)])
 def test_ffn_single_tile_experts_of_a_large_layer(orc, d, h):
-    """As above with more expert weights (283 MB) than the memory-side cache holds, where such experts stream them: the first
+    """As above with more expert weights (359 MB) than the memory-side cache holds, where such experts stream them: the first
     and the last row of every row tile against the oracle, and the same bits with the fused gather."""
     counts = [1, 63, 64, 65, 130, 255, 256, 257, 320, 321, 0, 33]
     e, n = len(counts), sum(counts)
