@@ -56,7 +56,9 @@ struct ThinTile {
                                                const uint16_t* __restrict__ B1, uint16_t* __restrict__ C,
                                                const int32_t* __restrict__ gather, int e, int row0, int rows, int n0, int K,
                                                int Nout, uint8_t* smem) {
-        const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));  // what follows from it is computed here, not for all three shapes at the block's start
+        const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
         const int lr = lane & 15, p = lane >> 4;
 
         constexpr int kRsrcFlags = 0x00020000;  // raw buffer of 32-bit words, no swizzle
