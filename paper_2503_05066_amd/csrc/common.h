@@ -157,6 +157,7 @@ hipError_t launch_combine(const moe_desc_t& d, const Sizes& s, const void* yp, c
 hipError_t launch_grouped_ffn(const moe_desc_t& d, const Sizes& s, const FfnWorkspace& ws, const void* xp,
                               const int32_t* row_token, const int32_t* expert_offset, const void* w_gate,
                               const void* w_up, const void* w_down, void* yp, bool schedule_ready, hipStream_t st);
+bool ffn_weights_stream(const moe_desc_t& d, const Sizes& s);  // the weights of the bf16 products are fetched without keeping them
 // the two products of the bf16 FFN for batches whose tiles have few rows (launch_grouped_ffn asks and calls)
 bool ffn_is_thin(const moe_desc_t& d, const Sizes& s);
 void launch_ffn_thin(const moe_desc_t& d, const Sizes& s, const FfnWorkspace& ws, const void* xp, const int32_t* row_token,

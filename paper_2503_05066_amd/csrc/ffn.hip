@@ -284,7 +284,7 @@ struct TileConfig16 {
     static constexpr int kNCols = SWIGLU ? BN / 2 : BN;
     static constexpr int kThreads = 64 * WAVES_M * WAVES_N;
     static constexpr int kLdsBytes = 2 * BM * 128 + 3 * BN * 128;
-    // STREAM (layers whose weights the memory-side cache does not keep, see launch_grouped_ffn): an expert's only row tile, short
+    // STREAM (layers whose weights the memory-side cache does not keep, see ffn_weights_stream): an expert's only row tile, short
     // or partly filled, whose weight rows no other block reads, and the short tiles, row pieces and cut short items that run
     // after the big ones.  Two things bound such a stream, measured
     // on a read-only kernel with the same fills (256 rows of 128 bytes per slab, 3 GiB):
@@ -520,7 +520,7 @@ __device__ inline void decode_item(int logical, int nt, int col_group, int& tile
 // the same K range of the tiles they share.
 //
 // Big, Small: tiles whose weight rows other blocks read beside them; BigStream, SmallStream: tiles that stream them (the same
-// two classes where the weights are to stay in the caches, see launch_grouped_ffn).
+// two classes where the weights are to stay in the caches, see ffn_weights_stream).
 template <class Big, class BigStream, class Small, class SmallStream, bool SWIGLU>
 __global__ __launch_bounds__(Big::kThreads) void ffn_gemm_bf16_kernel(
     const uint16_t* __restrict__ A, const uint16_t* __restrict__ B0, const uint16_t* __restrict__ B1,
@@ -767,6 +767,17 @@ void ffn_schedule_on_host(const moe_desc_t& d, const FfnWorkspace& ws, const int
     }
 }
 
+// Whether the expert weights are fetched with the streaming policy.  Weights that fit the memory-side cache (256 MB) are read
+// from there by the layer's next pass unless they were: 37 tokens, 2 x 3584 x 1408 (61 MB) 50 us a pass, streaming 69; 412,
+// 16 x 2944 x 768 (217 MB) 84 and 95; few rows: 16, 1 x 1024 x 14336 (88 MB) 34 and 46, 60 top-8, 32 x 1024 x 1024 (201 MB)
+// 42 and 46 (from HBM 47 and 46, 48 and 46).  While they do not exceed it by much, most of what a pass uses still is there:
+// 91 tokens top-1, 96 x 2048 x 256 (302 MB) 37 and 46 (50 and 47 from HBM).  256 tokens, 16 x 4096 x 1024 (403 MB) 125 and 120,
+// 1000, 16 x 2048 x 2048 (403 MB) 134 and 119; 37, 64 x 4096 x 1408 (2.2 GB) 306 and 273.
+bool ffn_weights_stream(const moe_desc_t& d, const Sizes& s) {
+    constexpr uint64_t kKeptWeights = 320ull << 20;
+    return 3ull * d.n_experts * d.d_model * d.d_hidden * s.elem > kKeptWeights;
+}
+
 // row_token == nullptr: xp holds the permuted rows.  Otherwise xp is the unpermuted x and row r of the
 // plan is fetched from x[row_token[r]] (dispatch fused into the first GEMM's operand fetch).
 // schedule_ready: the tile schedule is in the workspace already (built by the drop), no schedule kernel is launched.
@@ -786,13 +797,7 @@ hipError_t launch_grouped_ffn(const moe_desc_t& d, const Sizes& s, const FfnWork
         const int32_t* split_gu = ws.split_hdr;
         const int32_t* split_dn = ws.split_hdr + kFfnSplitHdr;
         int32_t* tickets_dn = ws.split_counter + 2 * kFfnSplitUnits;
-        // Weights that fit the memory-side cache (256 MB) are read from there by the layer's next pass unless they were
-        // fetched with the streaming policy: 37 tokens, 2 x 3584 x 1408 (61 MB) 50 us a pass, streaming 69; 412, 16 x 2944 x
-        // 768 (217 MB) 84 and 95; and while they do not exceed it by much, most of what a pass uses still is: 91 tokens top-1,
-        // 96 x 2048 x 256 (302 MB) 37 and 46 (50 and 47 from HBM).  256 tokens, 16 x 4096 x 1024 (403 MB) 125 and 120, 1000,
-        // 16 x 2048 x 2048 (403 MB) 134 and 119; 37, 64 x 4096 x 1408 (2.2 GB) 350 and 273.
-        constexpr uint64_t kKeptWeights = 320ull << 20;
-        const bool stream = 3ull * d.n_experts * d.d_model * d.d_hidden * s.elem > kKeptWeights;
+        const bool stream = ffn_weights_stream(d, s);
         // full-height row tiles: 256 x 256 blocks; short remainders: 64 x 256 blocks; four waves each
         {
             ProfileScope prof(MOE_KERNEL_FFN_GATE_UP, st);

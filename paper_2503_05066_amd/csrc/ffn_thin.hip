@@ -43,7 +43,7 @@ __device__ __forceinline__ void count_down(F&& f) {
 // One block: up to 16 * TM rows of an expert times 32 weight rows: 32 output columns, or the gate and up rows of 16
 // hidden columns.  The waves split K and share nothing until the end: each keeps a ring of its own in LDS, filled by
 // direct loads (the layout and the piece swizzle of ffn.hip), waits for its own slabs only and needs no barrier.
-// ONCE: the block's only pass over its weights, whose lines then need not be kept.
+// ONCE: the weights' lines need not be kept.
 template <int TM, bool SWIGLU, bool ONCE>
 struct ThinTile {
     static constexpr int kRows = 16 * TM;
@@ -201,14 +201,14 @@ struct ThinTile {
 // drop once, because no expert has a second tile there.  A tile of more than 32 rows is done in passes of its blocks over
 // the same weights, which stay in the L2 for them (64 tokens top-6, 64 x 4096 x 1408, 56 rows on one expert 210 -> 187 us,
 // 64 top-2, 8 x 4096 x 1024, 53 rows 53 -> 47).
-template <bool SWIGLU>
+template <bool SWIGLU, bool STREAM>
 __global__ __launch_bounds__(64 * kThinWaves, 2) void ffn_thin_kernel(
     const uint16_t* __restrict__ A, const uint16_t* __restrict__ B0, const uint16_t* __restrict__ B1,
     uint16_t* __restrict__ C, const int32_t* __restrict__ gather, const int32_t* __restrict__ tile_expert,
     const int32_t* __restrict__ tile_row0, const int32_t* __restrict__ tile_rows, const int32_t* __restrict__ n_tiles, int K,
     int Nout, int col_blocks) {
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
-    const int first = blockIdx.x / col_blocks, n0 = (blockIdx.x - first * col_blocks) * ThinTile<1, SWIGLU, true>::kCols;
+    const int first = blockIdx.x / col_blocks, n0 = (blockIdx.x - first * col_blocks) * ThinTile<1, SWIGLU, STREAM>::kCols;
     const int step = gridDim.x / col_blocks, nt = *n_tiles;
     for (int tile = first; tile < nt; tile += step) {
         const int e = tile_expert[tile], row0 = tile_row0[tile], rows = tile_rows[tile] & kTileRowsMask;
@@ -219,9 +219,9 @@ __global__ __launch_bounds__(64 * kThinWaves, 2) void ffn_thin_kernel(
                 ThinTile<2, SWIGLU, false>::run(A, B0, B1, C, gather, e, row0 + at, left < kThinPiece ? left : kThinPiece, n0, K,
                                                 Nout, smem);
             else if (rows > 16)
-                ThinTile<2, SWIGLU, true>::run(A, B0, B1, C, gather, e, row0, rows, n0, K, Nout, smem);
+                ThinTile<2, SWIGLU, STREAM>::run(A, B0, B1, C, gather, e, row0, rows, n0, K, Nout, smem);
             else
-                ThinTile<1, SWIGLU, true>::run(A, B0, B1, C, gather, e, row0, rows, n0, K, Nout, smem);
+                ThinTile<1, SWIGLU, STREAM>::run(A, B0, B1, C, gather, e, row0, rows, n0, K, Nout, smem);
         }
     }
 }
@@ -244,30 +244,39 @@ bool ffn_is_thin(const moe_desc_t& d, const Sizes& s) {
     return s.max_rows <= 24ll * d.n_experts && (long long)d.n_experts * (d.d_hidden / 128) <= 128;
 }
 
-template <bool SWIGLU>
+template <bool SWIGLU, bool STREAM>
 static void launch_thin(const Sizes& s, int experts, const void* A, const void* B0, const void* B1, void* C,
                         const int32_t* gather, const FfnWorkspace& ws, int K, int Nout, hipStream_t st) {
     constexpr int lds = kThinWaves * kThinRingBytes;
-    auto kern = ffn_thin_kernel<SWIGLU>;
+    auto kern = ffn_thin_kernel<SWIGLU, STREAM>;
     static std::atomic<uint64_t> configured{0};
     once_per_device(configured, [&] {
         (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     });
-    const int col_blocks = Nout / ThinTile<1, SWIGLU, true>::kCols;
+    const int col_blocks = Nout / ThinTile<1, SWIGLU, STREAM>::kCols;
     const long long tiles = s.max_rows < experts ? s.max_rows : experts;
     hipLaunchKernelGGL(kern, dim3((unsigned)(tiles * col_blocks)), dim3(64 * kThinWaves), lds, st, (const uint16_t*)A, (const uint16_t*)B0,
                        (const uint16_t*)B1, (uint16_t*)C, gather, ws.all.expert, ws.all.row0, ws.all.rows,
                        ws.all.count, K, Nout, col_blocks);
 }
 
-void launch_ffn_thin(const moe_desc_t& d, const Sizes& s, const FfnWorkspace& ws, const void* xp, const int32_t* row_token,
-                     const void* w_gate, const void* w_up, const void* w_down, void* yp, hipStream_t st) {
+template <bool STREAM>
+static void launch_both(const moe_desc_t& d, const Sizes& s, const FfnWorkspace& ws, const void* xp, const int32_t* row_token,
+                        const void* w_gate, const void* w_up, const void* w_down, void* yp, hipStream_t st) {
     {
         ProfileScope prof(MOE_KERNEL_FFN_GATE_UP, st);
-        launch_thin<true>(s, d.n_experts, xp, w_gate, w_up, ws.hidden, row_token, ws, d.d_model, d.d_hidden, st);
+        launch_thin<true, STREAM>(s, d.n_experts, xp, w_gate, w_up, ws.hidden, row_token, ws, d.d_model, d.d_hidden, st);
     }
     ProfileScope prof(MOE_KERNEL_FFN_DOWN, st);
-    launch_thin<false>(s, d.n_experts, ws.hidden, w_down, nullptr, yp, nullptr, ws, d.d_hidden, d.d_model, st);
+    launch_thin<false, STREAM>(s, d.n_experts, ws.hidden, w_down, nullptr, yp, nullptr, ws, d.d_hidden, d.d_model, st);
+}
+
+void launch_ffn_thin(const moe_desc_t& d, const Sizes& s, const FfnWorkspace& ws, const void* xp, const int32_t* row_token,
+                     const void* w_gate, const void* w_up, const void* w_down, void* yp, hipStream_t st) {
+    if (ffn_weights_stream(d, s))
+        launch_both<true>(d, s, ws, xp, row_token, w_gate, w_up, w_down, yp, st);
+    else
+        launch_both<false>(d, s, ws, xp, row_token, w_gate, w_up, w_down, yp, st);
 }
 
 }  // namespace capmoe

@@ -845,6 +845,23 @@ def test_ffn_few_rows(orc, d, h, counts):
     assert torch.equal(fused.y, buf.y)
 
 
+@pytest.mark.parametrize("d,h,counts", [(2048, 3584, [1, 0, 16, 17, 0, 0, 30, 0]), (3584, 2048, [0, 33, 0, 15, 0, 0, 1, 2])])
+def test_ffn_few_rows_of_a_large_layer(orc, d, h, counts):
+    """As above with expert weights (352 MB) beyond what the memory-side cache keeps, which are streamed."""
+    e, n = len(counts), sum(counts)
+    w = synth.scaled(W["olmoe"], name="few rows, large", n_tokens=n, d_model=d, n_experts=e, top_k=1, d_hidden=h,
+                     device_groups=1)
+    layer = DeviceLayer(w)
+    owner = np.repeat(np.arange(e), counts)
+    np.random.default_rng(40).shuffle(owner)
+    logits = np.zeros((n, e), np.float32)
+    logits[np.arange(n), owner] = 6.0
+    ref = orc.route_and_drop(logits, 1, 1, NONE, GLOBAL, 1.0)
+    buf = run_layer(layer, layer.desc(NONE, GLOBAL, 1.0), logits)
+    y_ref = orc.layer_output(layer.x_host, ref.scores, ref.keep, layer.host_gate, layer.host_up, layer.host_down)
+    assert_output_close(to_host_f64(buf.y), y_ref, TOL[w.dtype], "few rows of a large layer")
+
+
 @pytest.mark.parametrize("counts", [
     {0: 100, 1: 3, 5: 65, 31: 1},                  # above the capacity of a descriptor whose experts have 64 rows at most
     {3: 321, 7: 64, 8: 65, 20: 30},                # several full tiles and a remainder on one expert
