@@ -199,6 +199,10 @@ int moe_dispatch(const moe_desc_t* desc, const void* x, const int32_t* expert_of
  *   w_gate, w_up [E,h,d], w_down [E,d,h] in desc->dtype.  bf16: fp32 accumulation on the matrix
  *   cores, the hidden activation is rounded to bf16 once; d and h must be multiples of 128.
  *   yp [P_max,d]; rows >= P untouched.
+ * expert_offset may come from elsewhere (rows exchanged between devices, an edited plan): any ascending offsets from 0 with
+ * P <= P_max, whatever capacity the descriptor states.
+ * The same plan and descriptor give the same bits.  fp32: the bits of a row depend on nothing else in the batch.  bf16: the
+ * order of a row's fp32 sums, and so its last bit, may differ with the number of rows of its expert and of the batch.
  */
 int moe_grouped_ffn(const moe_desc_t* desc, const void* xp, const int32_t* expert_offset, const void* w_gate,
                     const void* w_up, const void* w_down, void* yp, void* workspace, size_t workspace_bytes,
@@ -242,7 +246,8 @@ int moe_layer_forward(const moe_desc_t* desc, const void* x, const float* w_rout
  * moe_profile_attach(NULL).  While a table is attached to the calling thread, every launch of kernel id k by
  * that thread increments launches[k] and, where start[k] / stop[k] are not NULL, records those hipEvent_t
  * (passed as void*) before / after the launch on the launch stream: hipEventElapsedTime(start, stop) is then
- * that launch's duration, and launches[k] == 0 tells that the call sequence never ran the kernel.
+ * that launch's duration, and launches[k] == 0 tells that the call sequence never ran the kernel.  The launches that
+ * together select the thresholds of long segments (MOE_KERNEL_DROP_SELECT) are counted and timed as one.
  */
 enum {
     MOE_KERNEL_ROUTER_LOGITS = 0,

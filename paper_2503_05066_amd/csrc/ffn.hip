@@ -370,8 +370,9 @@ struct TileConfig16 {
     const int slabs_all = K / 64;
     const int k_first = split.slices > 1 ? (int)((long long)split.slice * slabs_all / split.slices) : 0;
     const int k_end = split.slices > 1 ? (int)((long long)(split.slice + 1) * slabs_all / split.slices) : slabs_all;
-    // The start of the walk depends on the output columns alone and only moves where the expert has a single tile, so
-    // a row's sums run in the same order whatever other experts share the launch.
+    // The start of the walk depends on the output columns alone and only moves where the expert has a single tile: in a
+    // GEMM that is not cut along K a row's sums run in the same order whatever other experts share the launch.  (Which
+    // items are cut follows from the tiles of all experts.)
     const int k_start = STREAM && alone ? (int)((long long)n0 * (k_end - k_first) / Nout) : 0;
     Loop loop{smem, fills, a_lane, b_lane, k_end - k_first, __builtin_amdgcn_readfirstlane(wv), k_first, k_start};
     if (live == TM) {

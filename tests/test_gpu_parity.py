@@ -199,8 +199,8 @@ def test_plan_edge_shapes(orc, n, e, k, g, mode, scope, gamma):
     check_route_and_plan(orc, logits, n, e, k, g, mode, scope, gamma, "edge shape")
 
 
-# Segments longer than what a block keeps in LDS (32768 keys): the selection re-reads its keys (or keeps the
-# candidates only) and the compaction of a segment is spread over one block per 4096 tokens.
+# Segments around and beyond what a block holds in its registers (65536 keys, 32768 at an odd pitch): the selection re-reads
+# its keys or shares them among blocks, and the compaction of a segment is spread over one block per 4096 tokens.
 @pytest.mark.parametrize("n,e,k,g,mode,scope,gamma,flat", [
     (70001, 8, 2, 1, TD, GLOBAL, 1.0, False),     # token count not a multiple of 4: scalar key loads
     (65536, 4, 1, 1, TD, GLOBAL, 0.7, False),     # 16-byte key loads
@@ -208,7 +208,7 @@ def test_plan_edge_shapes(orc, n, e, k, g, mode, scope, gamma):
     (49152, 16, 4, 4, ED, GLOBAL, 1.0, False),
     (40000, 16, 2, 4, TD, 3, 1.0, False),         # device budgets over 4 x 40000 keys
     (40000, 16, 2, 4, ED, 3, 0.6, True),
-    (36864, 6, 6, 1, TD, GLOBAL, 0.5, False),     # every expert is a candidate of every token: more candidates than LDS holds
+    (36864, 6, 6, 1, TD, GLOBAL, 0.5, False),     # every expert is a candidate of every token
 ])
 def test_plan_long_segments(orc, n, e, k, g, mode, scope, gamma, flat):
     rng = np.random.default_rng(n + e)
@@ -286,7 +286,7 @@ def test_plan_device_level_capacity(orc, name, mode, scope, gamma, metric):
 @pytest.mark.parametrize("n,e,k,g,mode,scope,gamma", [
     (256, 256, 8, 2, ED, LOCAL, 1.0),          # 136 candidate slots per token
     (256, 256, 8, 1, TD, 3, 1.0),              # one budget over all 256 experts: 65536 keys in one segment
-    (2048, 64, 6, 2, ED, 2, 0.7),              # 32 experts x 1024 tokens under one budget: the largest cached segment
+    (2048, 64, 6, 2, ED, 2, 0.7),              # 32 experts x 1024 tokens under one budget
     (4100, 16, 2, 4, TD, 2, 1.0),              # ragged blocks of 1025 tokens
     (64, 8, 2, 8, TD, 3, 1.5),                 # one expert per device: device budget = expert capacity
 ])
@@ -585,7 +585,13 @@ def test_one_call_entry_matches_separate_calls():
              (synth.scaled(W["olmoe"], name="reduced", n_tokens=9000, d_model=128, n_experts=8, top_k=2, d_hidden=256,
                            device_groups=1), TD, GLOBAL, 1.0, 0, False),
              (synth.scaled(W["olmoe"], name="reduced", n_tokens=9000, d_model=128, n_experts=12, top_k=3, d_hidden=128,
-                           device_groups=3), ED, GLOBAL, 0.9, 3, True)]
+                           device_groups=3), ED, GLOBAL, 0.9, 3, True),
+             # a budget over 131200 keys, shared among blocks: its workspace, with the schedule from the drop and (many
+             # experts, one row per token) without
+             (synth.scaled(W["olmoe"], name="reduced", n_tokens=4100, d_model=128, n_experts=32, top_k=4, d_hidden=128,
+                           device_groups=1), TD, GLOBAL_DEV, 0.7, 0, False),
+             (synth.scaled(W["olmoe"], name="reduced", n_tokens=2052, d_model=128, n_experts=128, top_k=1, d_hidden=128,
+                           device_groups=1), TD, GLOBAL_DEV, 0.7, 1, True)]
     for w, mode, scope, gamma, m, limit in cases:
         layer = DeviceLayer(w, host_weights=False)
         desc = layer.desc(mode, scope, gamma)
@@ -795,6 +801,9 @@ def test_ffn_single_tile_experts_of_a_large_layer(orc, d, h):
     (36, 1000, [3, 40, 0, 90, 64, 64]),
     (1024, 31, [3, 1, 12]),
     (84, 7, [16, 17, 100, 0, 31, 160, 33, 72]),           # a block per 16-row piece: whole, ragged and empty ones
+    (100, 97, [17, 33, 50, 64] + [0] * 20 + [3]),         # few rows on average: one-wave blocks of two, three and four sub-tiles
+    (1024, 250, [17, 33, 50, 64] + [0] * 20 + [3]),
+    (260, 1030, [20, 40, 60] + [5] * 13),                 # the same where many column blocks keep the tiles whole
 ])
 def test_ffn_fp32_shapes(orc, d, h, counts):
     """The fp32 expert products at the edges of their tiles, column blocks and K slabs, permuted rows and fused gather.
@@ -820,7 +829,8 @@ def test_ffn_fp32_shapes(orc, d, h, counts):
 
 
 @pytest.mark.parametrize("d,h", [(128, 128), (384, 640), (1024, 256), (256, 2048)])
-@pytest.mark.parametrize("counts", [[1], [16, 0, 1, 15], [17, 1, 0, 30, 16], [33, 0, 0, 31], [0, 64, 0, 0]])
+@pytest.mark.parametrize("counts", [[1], [16, 0, 1, 15], [17, 1, 0, 30, 16], [33, 0, 0, 31], [0, 64, 0, 0],
+                                    [30, 34, 0]])    # 21 rows on average: the narrow products only
 def test_ffn_few_rows(orc, d, h, counts):
     """Batches of at most 64 tokens: one and two sub-tiles of 16 rows, tiles done in two passes, waves without a K slab
     (d = 128 has two slabs for four waves).  Every token against the oracle (Eq. 2), and the same bits with the gather
