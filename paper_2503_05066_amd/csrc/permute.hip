@@ -1,6 +1,8 @@
 // Permutation into expert-major order and the weighted sum of Eq. (2).  Both are pure
 // memory movement: every lane moves 16-byte pieces, consecutive lanes touch consecutive
 // pieces of a row.
+#include <algorithm>
+
 #include "common.h"
 
 namespace capmoe {
@@ -28,14 +30,102 @@ __device__ inline void accumulate_bf16x8(float* acc, const uint4& v, float w) {
     }
 }
 
-__device__ inline uint32_t f32_to_bf16_rne(float f) {
-    const uint32_t u = __float_as_uint(f);
-    return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;  // inputs are finite
+// two floats -> two bf16 (round to nearest even) in one word: the hardware conversion
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+__device__ inline uint32_t combine_pack(float lo, float hi) {
+    const f32x2 v = {lo, hi};
+    const bf16x2 b = __builtin_convertvector(v, bf16x2);
+    return *(const uint32_t*)&b;
 }
 
 // y[t,:] = sum over the token's slots (ascending) of row_weight[r] * yp[r,:], fp32 accumulation.
-template <bool BF16>
+//
+// A wave takes U pieces per lane (64 * U consecutive ones) of one token: lane s fetches slot s and its weight, a ballot
+// tells which slots hold a row, and the rows are then fetched eight pieces a lane at a time from wave-uniform addresses.
+// The bytes bound it; what kept a thread per piece from them was three dependent loads per eight slots, taken or not, and
+// every slot's index in every lane.  16384 tokens of 24 slots, 46 k rows x 2048 62 -> 41 us (6.2 TB/s), 8192 x 4096 29 -> 23,
+// 4096 x 2048 15.1 -> 12.7, 3000 tokens of 32 slots 21 -> 17, 1 token 2.8 -> 2.2.
+template <bool BF16, int U>
 __global__ __launch_bounds__(256) void combine_kernel(const uint4* __restrict__ yp,
+                                                      const float* __restrict__ row_weight,
+                                                      const int32_t* __restrict__ pair_row, uint4* __restrict__ y,
+                                                      long long units, int parts, int pieces, int S) {
+    constexpr int kRows = U == 1 ? 8 : 4;  // rows in flight
+    constexpr int kVals = BF16 ? 8 : 4;
+    const int lane = threadIdx.x & 63;
+    for (long long unit = (long long)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); unit < units;
+         unit += (long long)gridDim.x * 4) {
+        const long long t = unit / parts;
+        const int c0 = (int)(unit - t * parts) * (64 * U) + lane;
+        int col[U];  // a piece past the row's end: its last one, fetched but not stored
+#pragma unroll
+        for (int u = 0; u < U; ++u) col[u] = c0 + 64 * u < pieces ? c0 + 64 * u : pieces - 1;
+        float acc[U][kVals];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int i = 0; i < kVals; ++i) acc[u][i] = 0.f;
+        for (int s0 = 0; s0 < S; s0 += 64) {
+            const int r = s0 + lane < S ? pair_row[t * S + s0 + lane] : -1;
+            const int w = r >= 0 ? __float_as_int(row_weight[r]) : 0;
+            uint64_t left = __ballot(r >= 0);
+            while (left) {
+                uint4 v[kRows][U];
+                float wj[kRows];
+                int n = 0, slot = 0;
+#pragma unroll
+                for (int j = 0; j < kRows; ++j) {
+                    if (left) {  // past the last row: that one again
+                        slot = __builtin_ctzll(left);
+                        left &= left - 1;
+                        ++n;
+                    }
+                    const uint4* row = yp + (long long)__builtin_amdgcn_readlane(r, slot) * pieces;
+                    wj[j] = __int_as_float(__builtin_amdgcn_readlane(w, slot));
+#pragma unroll
+                    for (int u = 0; u < U; ++u) v[j][u] = row[col[u]];
+                }
+                // all of them are requested before any is used (the compiler otherwise moves each load behind the branch below)
+#pragma unroll
+                for (int j = 0; j < kRows; ++j)
+#pragma unroll
+                    for (int u = 0; u < U; ++u) asm volatile("" : "+v"(v[j][u].x), "+v"(v[j][u].y), "+v"(v[j][u].z), "+v"(v[j][u].w));
+#pragma unroll
+                for (int j = 0; j < kRows; ++j) {
+                    if (j >= n) break;
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        if (BF16) {
+                            accumulate_bf16x8(acc[u], v[j][u], wj[j]);
+                        } else {
+                            acc[u][0] = fmaf(wj[j], __uint_as_float(v[j][u].x), acc[u][0]);
+                            acc[u][1] = fmaf(wj[j], __uint_as_float(v[j][u].y), acc[u][1]);
+                            acc[u][2] = fmaf(wj[j], __uint_as_float(v[j][u].z), acc[u][2]);
+                            acc[u][3] = fmaf(wj[j], __uint_as_float(v[j][u].w), acc[u][3]);
+                        }
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (c0 + 64 * u >= pieces) continue;
+            uint4 o;
+            if (BF16)
+                o = make_uint4(combine_pack(acc[u][0], acc[u][1]), combine_pack(acc[u][2], acc[u][3]),
+                               combine_pack(acc[u][4 % kVals], acc[u][5 % kVals]), combine_pack(acc[u][6 % kVals], acc[u][7 % kVals]));
+            else
+                o = make_uint4(__float_as_uint(acc[u][0]), __float_as_uint(acc[u][1]), __float_as_uint(acc[u][2]),
+                               __float_as_uint(acc[u][3]));
+            y[t * pieces + c0 + 64 * u] = o;
+        }
+    }
+}
+
+// The same for rows shorter than a wave: a thread takes one piece, so that a wave serves several tokens (see choose_combine).
+template <bool BF16>
+__global__ __launch_bounds__(256) void combine_narrow_kernel(const uint4* __restrict__ yp,
                                                       const float* __restrict__ row_weight,
                                                       const int32_t* __restrict__ pair_row, uint4* __restrict__ y,
                                                       long long items, int pieces, int S) {
@@ -71,10 +161,8 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint4* __restrict__ 
         }
         uint4 o;
         if (BF16) {
-            o.x = f32_to_bf16_rne(acc[0]) | (f32_to_bf16_rne(acc[1]) << 16);
-            o.y = f32_to_bf16_rne(acc[2]) | (f32_to_bf16_rne(acc[3]) << 16);
-            o.z = f32_to_bf16_rne(acc[4]) | (f32_to_bf16_rne(acc[5]) << 16);
-            o.w = f32_to_bf16_rne(acc[6]) | (f32_to_bf16_rne(acc[7]) << 16);
+            o = make_uint4(combine_pack(acc[0], acc[1]), combine_pack(acc[2], acc[3]), combine_pack(acc[4], acc[5]),
+                           combine_pack(acc[6], acc[7]));
         } else {
             o.x = __float_as_uint(acc[0]);
             o.y = __float_as_uint(acc[1]);
@@ -103,17 +191,43 @@ hipError_t launch_dispatch(const moe_desc_t& d, const Sizes& s, const void* x, c
     return hipGetLastError();
 }
 
+constexpr long long kMaxBlocks = 1 << 22;  // a launch has fewer than 2^32 threads; the kernel strides over the rest
+
+template <bool BF16, int U>
+static void launch_combine_units(const void* yp, const float* row_weight, const int32_t* pair_row, void* y, int tokens,
+                                 int pieces, int slots, hipStream_t st) {
+    const int parts = (pieces + 64 * U - 1) / (64 * U);
+    const long long units = (long long)tokens * parts;
+    hipLaunchKernelGGL((combine_kernel<BF16, U>), dim3((unsigned)std::min<long long>((units + 3) / 4, kMaxBlocks)), dim3(256), 0,
+                       st, (const uint4*)yp, row_weight, pair_row, (uint4*)y, units, parts, pieces, slots);
+}
+
+template <bool BF16>
+static void choose_combine(const moe_desc_t& d, const Sizes& s, const void* yp, const float* row_weight, const int32_t* pair_row,
+                           void* y, hipStream_t st) {
+    const int pieces = (int)((size_t)d.d_model * s.elem / 16);
+    // Two pieces per lane from four rounds of waves on (a compute unit holds 32): their lists are fetched half as often.  One
+    // piece -> two: 65536 units 44 -> 41 and 35 -> 23 us; 16384 12.7 -> 13.0, 4 of them 2.2 -> 3.4 (four pieces: never better).
+    const long long units = (long long)d.n_tokens * ((pieces + 63) / 64);
+    // Short rows of many tokens: a wave for each token is many rounds of mostly idle lanes.  A wave per token -> a thread per
+    // piece, eight slots: 65536 tokens of 128 bytes 20 -> 7 us, of 256 22 -> 11, of 512 24 -> 17, of 1024 32 -> 31; 16384 of 256 equal.
+    if (pieces < 64 && d.n_tokens > 16384) {
+        const long long items = (long long)d.n_tokens * pieces;
+        hipLaunchKernelGGL((combine_narrow_kernel<BF16>), dim3(grid_for(items)), dim3(256), 0, st, (const uint4*)yp, row_weight,
+                           pair_row, (uint4*)y, items, pieces, s.slots);
+    } else if (units >= 32768 && pieces > 64)
+        launch_combine_units<BF16, 2>(yp, row_weight, pair_row, y, d.n_tokens, pieces, s.slots, st);
+    else
+        launch_combine_units<BF16, 1>(yp, row_weight, pair_row, y, d.n_tokens, pieces, s.slots, st);
+}
+
 hipError_t launch_combine(const moe_desc_t& d, const Sizes& s, const void* yp, const float* row_weight,
                           const int32_t* pair_row, void* y, hipStream_t st) {
-    const int pieces = (int)((size_t)d.d_model * s.elem / 16);
-    const long long items = (long long)d.n_tokens * pieces;
     ProfileScope prof(MOE_KERNEL_COMBINE, st);
     if (d.dtype == MOE_DTYPE_BF16)
-        hipLaunchKernelGGL((combine_kernel<true>), dim3(grid_for(items)), dim3(256), 0, st, (const uint4*)yp, row_weight,
-                           pair_row, (uint4*)y, items, pieces, s.slots);
+        choose_combine<true>(d, s, yp, row_weight, pair_row, y, st);
     else
-        hipLaunchKernelGGL((combine_kernel<false>), dim3(grid_for(items)), dim3(256), 0, st, (const uint4*)yp,
-                           row_weight, pair_row, (uint4*)y, items, pieces, s.slots);
+        choose_combine<false>(d, s, yp, row_weight, pair_row, y, st);
     return hipGetLastError();
 }
 
