@@ -273,6 +273,8 @@ __device__ inline float wave_max(float v) {
     return v;
 }
 
+constexpr uint32_t kNoNumber = 0x3fffffffu;  // above every score
+
 template <int EPL>
 __global__ __launch_bounds__(256) void softmax_topk_kernel(float* __restrict__ logits,
                                                            const float* __restrict__ partial, int ksplit,
@@ -347,7 +349,10 @@ __global__ __launch_bounds__(256) void softmax_topk_kernel(float* __restrict__ l
         // Repeated wave-wide arg-max costs k rounds of cross-lane steps; this is a few ballots per bit.
         uint32_t bits[EPL];
 #pragma unroll
-        for (int i = 0; i < EPL; ++i) bits[i] = __float_as_uint(v[i] < 0.0f ? 0.0f : v[i]);
+        for (int i = 0; i < EPL; ++i) {
+            bits[i] = __float_as_uint(v[i] < 0.0f ? 0.0f : v[i]);
+            if (sum != sum) bits[i] = kNoNumber;  // a token without numbers: its scores are all the same
+        }
         uint32_t tau = 0;
         for (int bit = 29; bit >= 0; --bit) {
             const uint32_t cand = tau | (1u << bit);
@@ -394,16 +399,271 @@ __global__ __launch_bounds__(256) void softmax_topk_kernel(float* __restrict__ l
         for (int i = 0; i < EPL; ++i)
             if (bits[i] != 0xffffffffu) {
                 topk_idx[(size_t)t * k + place[i]] = lane + kWave * i;
-                topk_score[(size_t)t * k + place[i]] = __uint_as_float(bits[i]);
+                topk_score[(size_t)t * k + place[i]] = sum != sum ? sum : __uint_as_float(bits[i]);
             }
         __builtin_amdgcn_wave_barrier();  // the list is rewritten for the wave's next token only after these reads
     }
+}
+
+// ---------------------------------------------------------------------------------------------
+// The same for batches that fill the chip with four lanes per token: lane q of a token's four owns experts 16 i + 4 q .. + 3.
+// Vector instructions are what bounds softmax and top-k (the bytes take 8 us where they took 38), and with a wave per token
+// the sum's chain, the search and the ranking of the winners serve one token each; here they serve sixteen.
+// 65536 tokens, 64 experts, top-8 38 -> 15.5 us (2.4 TB/s), 16384, 128 experts 18 -> 12.6.  The same bits as above.
+// ---------------------------------------------------------------------------------------------
+template <int CTRL>
+__device__ inline int quad_perm(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true);
+}
+__device__ inline int quad_xor1(int v) { return quad_perm<0xB1>(v); }
+__device__ inline int quad_xor2(int v) { return quad_perm<0x4E>(v); }
+__device__ inline int quad_sum(int v) {
+    v += quad_xor1(v);
+    return v + quad_xor2(v);
+}
+template <int LANE>
+__device__ inline float quad_from(float v) {  // the value of the quad's lane LANE
+    return __int_as_float(quad_perm<LANE * 0x55>(__float_as_int(v)));
+}
+
+constexpr int kQuadTokens = 64;  // tokens of a block
+
+// C: 16 * C experts at most; VEC: four experts per load (E % 4 == 0); FULL: exactly 16 * C experts
+template <int C, bool VEC, bool FULL>
+__global__ __launch_bounds__(256) void softmax_topk_quad_kernel(float* __restrict__ logits, const float* __restrict__ partial,
+                                                                int ksplit, const float* __restrict__ bias,
+                                                                float* __restrict__ scores, int32_t* __restrict__ topk_idx,
+                                                                float* __restrict__ topk_score, int N, int experts, int k) {
+    extern __shared__ unsigned long long quad_lists[];  // [64 tokens][k + 1]: keys of the winners
+    constexpr int V = 4 * C;
+    const int E = FULL ? 16 * C : experts;
+    const int lane = threadIdx.x & 63, q = lane & 3;
+    unsigned long long* list = quad_lists + (size_t)(threadIdx.x >> 2) * (k + 1);
+    const int t = blockIdx.x * kQuadTokens + (threadIdx.x >> 2);
+    const bool live = t < N;
+    const size_t row = (size_t)(live ? t : N - 1) * E;  // past the last token: that one again, not stored
+    if (blockIdx.x * kQuadTokens + (threadIdx.x & ~63) / 4 >= N) return;  // nothing for this wave
+    auto expert = [&](int i) { return 16 * (i / 4) + 4 * q + i % 4; };
+    auto valid = [&](int i) -> int { return FULL || expert(i) < E; };
+    // four values of a row of E floats
+    auto fetch = [&](const float* p, int c, float* out, float none) {
+        const int e = 16 * c + 4 * q;
+        float x[4];
+        if (VEC) {
+            *(f32x4*)x = *(const f32x4u*)(p + (FULL || e < E ? e : E - 4));
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) x[j] = p[e + j < E ? e + j : E - 1];
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) out[j] = FULL || e + j < E ? x[j] : none;
+    };
+    auto store = [&](float* p, int c, const float* in) {
+        const int e = 16 * c + 4 * q;
+        if (VEC) {
+            if (FULL || e < E) *(f32x4u*)(p + e) = f32x4{in[0], in[1], in[2], in[3]};
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (e + j < E) p[e + j] = in[j];
+        }
+    };
+    float v[V];
+    if (partial) {
+        // the router GEMM left one partial sum per K slice: they are added in slice order, a few slices in flight
+        constexpr int kAhead = C >= 8 ? 2 : 4;
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            if (bias)
+                fetch(bias, c, v + 4 * c, 0.0f);
+            else
+                v[4 * c] = v[4 * c + 1] = v[4 * c + 2] = v[4 * c + 3] = 0.0f;
+        }
+        for (int s0 = 0; s0 < ksplit; s0 += kAhead) {
+            float p[kAhead][V];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                const int s = s0 + u < ksplit ? s0 + u : ksplit - 1;
+#pragma unroll
+                for (int c = 0; c < C; ++c) fetch(partial + (size_t)s * N * E + row, c, p[u] + 4 * c, 0.0f);
+            }
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u)
+                if (s0 + u < ksplit)
+#pragma unroll
+                    for (int i = 0; i < V; ++i) v[i] = __fadd_rn(v[i], p[u][i]);
+        }
+        if (live)
+#pragma unroll
+            for (int c = 0; c < C; ++c) store(logits + row, c, v + 4 * c);
+#pragma unroll
+        for (int i = 0; i < V; ++i) v[i] = valid(i) ? v[i] : -INFINITY;
+    } else {
+#pragma unroll
+        for (int c = 0; c < C; ++c) fetch(logits + row, c, v + 4 * c, -INFINITY);
+    }
+    float m = v[0];
+#pragma unroll
+    for (int i = 1; i < V; ++i) m = fmaxf(m, v[i]);
+    m = fmaxf(m, __int_as_float(quad_xor1(__float_as_int(m))));
+    m = fmaxf(m, __int_as_float(quad_xor2(__float_as_int(m))));
+#pragma unroll
+    for (int i = 0; i < V; ++i) v[i] = valid(i) ? exp_nonpositive(__fsub_rn(v[i], m)) : 0.0f;
+    // ascending expert order: the sum goes round the four lanes, four experts at each (the entries past E are +0)
+    float sum = 0.0f;
+    auto add4 = [&](float s, int c) {
+        return __fadd_rn(__fadd_rn(__fadd_rn(__fadd_rn(s, v[4 * c]), v[4 * c + 1]), v[4 * c + 2]), v[4 * c + 3]);
+    };
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        sum = add4(c == 0 ? 0.0f : quad_from<3>(sum), c);
+        sum = add4(quad_from<0>(sum), c);
+        sum = add4(quad_from<1>(sum), c);
+        sum = add4(quad_from<2>(sum), c);
+    }
+    sum = quad_from<3>(sum);
+    uint32_t bits[V];
+    // IEEE quotients by one divisor: with y = 1 / sum rounded, two steps of q + (a - sum q) y from q = a y give a / sum rounded
+    // (Markstein) as long as no remainder falls below the smallest number; others take the general division.
+    uint32_t least = 0xffffffffu;
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+        const uint32_t b = __float_as_uint(v[i]) - 1u;  // zero is above all
+        least = b < least ? b : least;
+    }
+    if (__any((least < __float_as_uint(0x1p-99f)) | (sum != sum))) {
+#pragma unroll
+        for (int i = 0; i < V; ++i) v[i] = __fdiv_rn(v[i], sum);
+    } else {
+        const float y = __fdiv_rn(1.0f, sum);
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+            float r = __fmul_rn(v[i], y);
+            r = __builtin_fmaf(__builtin_fmaf(-sum, r, v[i]), y, r);
+            v[i] = __builtin_fmaf(__builtin_fmaf(-sum, r, v[i]), y, r);
+        }
+    }
+    if (live)
+#pragma unroll
+        for (int c = 0; c < C; ++c) store(scores + row, c, v + 4 * c);
+#pragma unroll
+    for (int i = 0; i < V; ++i) bits[i] = sum != sum ? kNoNumber : __float_as_uint(v[i]);
+#pragma unroll
+    for (int i = 0; i < V; ++i) bits[i] = valid(i) ? bits[i] : 0u;  // never above a threshold
+    // the k-th largest pattern, as in the kernel above; a token whose search has ended keeps its threshold
+    uint32_t tau = 0;
+    bool found = false;
+    for (int bit = 29; bit >= 0; --bit) {
+        const uint32_t cand = tau | (1u << bit);
+        int cnt = 0;  // minus the number: all patterns are below 2^30
+#pragma unroll
+        for (int i = 0; i < V; ++i) cnt += (int)(cand - 1u - bits[i]) >> 31;
+        cnt = -quad_sum(cnt);
+        if (!found) {
+            if (cnt >= k) tau = cand;
+            if (cnt == k) {
+                tau = cand - 1u;
+                found = true;
+            }
+        }
+        if (__all(found)) break;
+    }
+    int n_gt = 0, n_eq = 0;
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+        n_gt += bits[i] > tau ? 1 : 0;
+        n_eq += (int)(valid(i) & (bits[i] == tau));
+    }
+    const int own_gt = n_gt;
+    n_gt = quad_sum(n_gt);
+    const int need = k - n_gt, eq_all = quad_sum(n_eq);  // of the patterns equal to tau, the `need` lowest experts win
+    int limit = need > 0 ? E : 0, own = own_gt + (need > 0 ? n_eq : 0);
+    if (__any(need > 0 && need < eq_all)) {  // equal scores at the threshold: below which expert do `need` of them lie
+        int low = 0;
+        for (int b = kMaxExperts / 2; b > 0; b >>= 1) {
+            int c = 0;
+#pragma unroll
+            for (int i = 0; i < V; ++i) c += (int)(valid(i) & (bits[i] == tau) & (expert(i) < low + b));
+            if (quad_sum(c) <= need) low += b;
+        }
+        if (need > 0 && need < eq_all) {
+            limit = low;
+            own = own_gt;
+#pragma unroll
+            for (int i = 0; i < V; ++i) own += (int)(valid(i) & (bits[i] == tau) & (expert(i) < limit));
+        }
+    }
+    int at = own;  // inclusive prefix over the four lanes, then exclusive
+    const int from1 = quad_perm<0x90>(at);  // lanes 0 0 1 2
+    at += q >= 1 ? from1 : 0;
+    const int from2 = quad_perm<0x40>(at);  // lanes 0 0 0 1
+    at += q >= 2 ? from2 : 0;
+    at -= own;
+    // winners by a key that orders them: larger score first, then lower expert id
+    typedef unsigned long long u64;
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+        const bool win = (bits[i] > tau) | ((bits[i] == tau) & (expert(i) < limit));
+        if (win) list[at] = (u64)bits[i] << 32 | (uint32_t)(kMaxExperts - 1 - expert(i));
+        at += win ? 1 : 0;
+    }
+    if (q == 0) list[k] = 0;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();  // LDS operations of one wave complete in order
+    // every winner's place is the number of larger keys; two winners at a time, eight of the list per round
+    for (int j = q; j < k; j += 8) {
+        const int j1 = j + 4 < k ? j + 4 : j;
+        const u64 mine[2] = {list[j], list[j1]};
+        int place[2] = {0, 0};
+        for (int i0 = 0; i0 < k; i0 += 8) {
+            u64 w[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) w[i] = list[i0 + i < k ? i0 + i : k];  // entry k: below every winner
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+#pragma unroll
+                for (int u = 0; u < 2; ++u) place[u] += w[i] > mine[u] ? 1 : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            if (live & (j + 4 * u < k)) {
+                topk_idx[(size_t)t * k + place[u]] = kMaxExperts - 1 - (int32_t)(uint32_t)mine[u];
+                topk_score[(size_t)t * k + place[u]] = sum != sum ? sum : __uint_as_float((uint32_t)(mine[u] >> 32));
+            }
+    }
+}
+
+template <int C>
+static void launch_quad(float* logits, const float* partial, int ksplit, const float* bias, float* scores, int32_t* topk_idx,
+                        float* topk_score, int N, int E, int k, hipStream_t st) {
+    const size_t lds = (size_t)kQuadTokens * (k + 1) * sizeof(unsigned long long);
+    auto kern = E == 16 * C ? softmax_topk_quad_kernel<C, true, true>
+                            : (E % 4 == 0 ? softmax_topk_quad_kernel<C, true, false> : softmax_topk_quad_kernel<C, false, false>);
+    hipLaunchKernelGGL(kern, dim3((N + kQuadTokens - 1) / kQuadTokens), dim3(256), lds, st, logits, partial, ksplit, bias, scores,
+                       topk_idx, topk_score, N, E, k);
 }
 
 hipError_t launch_softmax_topk(const moe_desc_t& d, float* logits, const float* partial, int ksplit, const float* bias,
                                float* scores, int32_t* topk_idx, float* topk_score, hipStream_t st) {
     ProfileScope prof(MOE_KERNEL_SOFTMAX_TOPK, st);
     const int N = d.n_tokens, E = d.n_experts, k = d.top_k + d.overselect;
+    // Four lanes per token from where a wave per token is many rounds of waves: below, the shorter chain of the wave per token
+    // wins (us, wave -> quad, 64 experts top-8: 8192 tokens 7.3 -> 7.6, 12288 9.2 -> 8.0, 16384 11.7 -> 8.4, 65536 37.5 -> 15.5;
+    // 128 top-8: 8192 10.6 -> 11.6, 12288 13.7 -> 11.6; 8 top-2: 4096 4.3 -> 4.6, 12288 7.4 -> 5.1; 64 top-64: 16384 17.3 -> 18.7,
+    // 32768 30.8 -> 23.3).
+    if (N >= (k <= 32 ? 12288 : 20480)) {
+        if (E <= 16)
+            launch_quad<1>(logits, partial, ksplit, bias, scores, topk_idx, topk_score, N, E, k, st);
+        else if (E <= 32)
+            launch_quad<2>(logits, partial, ksplit, bias, scores, topk_idx, topk_score, N, E, k, st);
+        else if (E <= 64)
+            launch_quad<4>(logits, partial, ksplit, bias, scores, topk_idx, topk_score, N, E, k, st);
+        else if (E <= 128)
+            launch_quad<8>(logits, partial, ksplit, bias, scores, topk_idx, topk_score, N, E, k, st);
+        else
+            launch_quad<16>(logits, partial, ksplit, bias, scores, topk_idx, topk_score, N, E, k, st);
+        return hipGetLastError();
+    }
     int grid = (N + 3) / 4;
     if (grid > 2048) grid = 2048;
     const int epl = (E + kWave - 1) / kWave;

@@ -47,3 +47,70 @@ def test_combine(n, d, slots, dtype):
     bound = slots * 2.0 ** -24 * mass + (2.0 ** -8 * ref.abs() if dtype == "bf16" else 0.0)
     assert bool(((y.double() - ref).abs() <= bound).all())
     assert bool((y[(pair_row < 0).all(dim=1)] == 0).all())
+
+
+# ------------------------------------------------------------------------------------------------
+# softmax and top-k of long batches (four lanes per token): the same bits as in batches of 64 tokens, which take the kernel
+# that the parity tests compare with the oracle
+# ------------------------------------------------------------------------------------------------
+def _route(logits, k, x=None, w=None, bias=None):
+    n, e = logits.shape
+    desc = capmoe.make_desc(n, 8 if x is None else x.shape[1], e, k, 128, 1, capmoe.MODE_NONE)
+    out = [torch.empty((n, e), device="cuda"), torch.empty((n, k), dtype=torch.int32, device="cuda"),
+           torch.empty((n, k), device="cuda")]
+    ws = torch.empty(max(capmoe.moe_query(desc)[3], 256), dtype=torch.uint8, device="cuda")
+    capmoe.moe_route_topk(desc, x, w, bias, x is None, logits, *out, ws)
+    return out
+
+
+def _assert_same_as_short_batches(logits, k, out):
+    for t0 in list(range(0, 1024, 64)) + [logits.shape[0] - 65]:
+        part = slice(t0, t0 + 64 + (t0 > 1024))
+        for a, b in zip(out, _route(logits[part].clone(), k)):
+            assert torch.equal(a[part].view(torch.int32), b.view(torch.int32)), (t0, k)
+
+
+@pytest.mark.parametrize("n,e,k", [(12288, 1, 1), (12289, 8, 2), (12300, 16, 16), (12351, 17, 3), (12288, 30, 6), (12288, 32, 32),
+                                   (20480, 33, 33), (12290, 60, 4), (12288, 61, 7), (12291, 64, 8), (20481, 64, 64),
+                                   (12288, 100, 5), (12288, 128, 8), (12288, 130, 9), (20480, 256, 64), (12289, 255, 1)])
+@pytest.mark.parametrize("kind", ["normal", "ties", "wide"])
+def test_softmax_topk_long_batches(n, e, k, kind):
+    gen = torch.Generator(device="cuda").manual_seed(n + e)
+    logits = torch.randn((n, e), generator=gen, device="cuda") * 2
+    if kind == "ties":      # rows of equal scores, and equal scores at the threshold
+        logits = logits.round() * 0.5
+        logits[::7] = 0.0
+    elif kind == "wide":    # scores down to the smallest, and exact zeros
+        logits *= 20.0
+        logits[::2, e // 2] += 70.0
+    _assert_same_as_short_batches(logits, k, _route(logits, k))
+
+
+@pytest.mark.parametrize("n,d,e,k", [(12288, 256, 64, 6), (16385, 128, 61, 4), (12500, 512, 128, 8), (13000, 1024, 8, 2)])
+def test_softmax_topk_long_batches_adds_router_slices(n, d, e, k):
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    x = torch.randn((n, d), generator=gen, device="cuda").to(torch.bfloat16)
+    w = torch.randn((e, d), generator=gen, device="cuda") * d ** -0.5
+    bias = torch.randn(e, generator=gen, device="cuda")
+    logits = torch.empty((n, e), device="cuda")
+    out = _route(logits, k, x, w, bias)
+    ref = x.double() @ w.double().T + bias.double()
+    # fp32 sums of d exact products: at most d + 2 roundings of partial sums that the mass bounds
+    mass = x.double().abs() @ w.double().abs().T + bias.double().abs()
+    assert bool(((logits.double() - ref).abs() <= (d + 2) * 2.0 ** -24 * mass).all())
+    _assert_same_as_short_batches(logits, k, out)
+
+
+@pytest.mark.parametrize("n", [130, 12288])
+def test_tokens_without_numbers(n):
+    e, k = 64, 8
+    logits = torch.randn((n, e), generator=torch.Generator(device="cuda").manual_seed(n), device="cuda")
+    clean = _route(logits.clone(), k)
+    broken = torch.zeros(n, dtype=torch.bool, device="cuda")
+    broken[1::5] = True
+    logits[1::10, 3], logits[6::10] = float("nan"), float("-inf")
+    scores, idx, score = _route(logits, k)
+    assert bool(scores[broken].isnan().all()) and bool(score[broken].isnan().all())
+    assert torch.equal(idx[broken], torch.arange(k, dtype=torch.int32, device="cuda").expand(int(broken.sum()), k))
+    for a, b in zip((scores, idx, score), clean):
+        assert torch.equal(a[~broken], b[~broken])
