@@ -7,8 +7,8 @@
 //                     expert-major so that a capacity segment is one contiguous run.  The rank is
 //                     the score's bit pattern (Score metric), the token's position (Order, Reverse
 //                     Order) or a hashed draw (Random), below an optional 2-bit token class.
-//   2. drop_select    per segment: the cap-th largest key by a 4-pass radix select over LDS
-//                     histograms (the threshold tau of Eq. 8) and how many keys equal to it survive
+//   2. drop_select    per segment: the cap-th largest key by histograms in LDS of the range
+//                     the keys lie in (the threshold tau of Eq. 8) and how many keys equal to it survive
 //                     (drop_big_*: the same for segments that many blocks share; which form: select_form).
 //   3. drop_emit      per segment (a block per 4096 tokens of it): ordered compaction of the survivors,
 //                     which yields rows in ascending token order and gives ties at the threshold to
@@ -176,6 +176,87 @@ __device__ __forceinline__ void static_for(F&& f) {
 }
 
 // ---------------------------------------------------------------------------------------------
+// the threshold of a block's keys
+// ---------------------------------------------------------------------------------------------
+// The rem-th largest of the non-zero keys, which lie in [lo, hi]: kept are the keys above the threshold that is returned, and the
+// first `rem` (as it is left) of those equal to it.  Each step spreads what is left of the range over kBins bins, finds the bin
+// with that key and goes on inside it; it ends when the bin is one key wide or all of it is kept (no key equal to the threshold is, then).
+// The bins divide the range in which the keys lie: gating scores share a few exponents, and counted by fixed digits, most lanes of
+// a wave meet in one counter (us against four passes of eight bits: 64 segments of 65536 drawn ranks 34 -> 25, the whole drop by score
+// 90 -> 65; 1024 segments of 2048 keys 12.3 -> 9.3; the whole drop of 4096 tokens, 64 experts, all scores equal 30 -> 16).
+// walk(f) calls f(key) for every key of the calling thread; hist: kBins words of LDS, zero; sh: three.  Called by the whole block after a barrier.
+template <int NT>
+constexpr int kSelectBins = NT >= 1024 ? 2048 : 1024;
+template <int NT, class Walk>
+__device__ __forceinline__ uint32_t select_threshold(uint32_t lo, uint32_t hi, int& rem, int* hist, int* red, int* sh, Walk&& walk) {
+    constexpr int kBins = kSelectBins<NT>, kPer = kBins / NT;
+    const int tid = threadIdx.x;
+    for (;;) {
+        const uint32_t range = hi - lo;
+        if (range == 0u) return lo;
+        const int width = 32 - __clz(range), shift = width > __builtin_ctz(kBins) ? width - __builtin_ctz(kBins) : 0;
+        walk([&](uint32_t key) __attribute__((always_inline)) {
+            if (key - lo <= range) atomicAdd(&hist[(key - lo) >> shift], 1);  // (below lo wraps around; key 0 is below)
+        });
+        __syncthreads();
+        // thread i owns the bins from kBins - 1 - kPer * i downwards: a scan over the threads counts the keys of higher bins
+        int h[kPer], sum = 0, total;
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            h[j] = hist[kBins - 1 - (tid * kPer + j)];
+            sum += h[j];
+        }
+        int above = block_exclusive_scan<NT>(sum, red, &total);
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            if (above < rem && above + h[j] >= rem) {  // exactly one bin of one thread
+                sh[0] = kBins - 1 - (tid * kPer + j);
+                sh[1] = rem - above;
+                sh[2] = h[j];
+            }
+            above += h[j];
+            hist[kBins - 1 - (tid * kPer + j)] = 0;
+        }
+        __syncthreads();
+        lo += (uint32_t)sh[0] << shift;
+        rem = sh[1];
+        const bool all = sh[2] == rem;
+        if (shift == 0) return lo;
+        if (all) {
+            rem = 0;
+            return lo - 1u;
+        }
+        const uint32_t top = lo + ((1u << shift) - 1u);
+        hi = hi < top ? hi : top;
+    }
+}
+
+// minimum and maximum of the block's candidate keys and their number, for all threads (lo > hi without any)
+template <int NT>
+__device__ __forceinline__ void key_extent(uint32_t& lo, uint32_t& hi, int& count, uint32_t (*red)[3]) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        const uint32_t a = __shfl_xor(lo, off, kWave), b = __shfl_xor(hi, off, kWave);
+        lo = a < lo ? a : lo;
+        hi = b > hi ? b : hi;
+        count += __shfl_xor(count, off, kWave);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        red[threadIdx.x >> 6][0] = lo;
+        red[threadIdx.x >> 6][1] = hi;
+        red[threadIdx.x >> 6][2] = (uint32_t)count;
+    }
+    __syncthreads();
+    count = 0;
+#pragma unroll
+    for (int w = 0; w < NT / kWave; ++w) {
+        lo = red[w][0] < lo ? red[w][0] : lo;
+        hi = red[w][1] > hi ? red[w][1] : hi;
+        count += (int)red[w][2];
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
 // 2. threshold per segment
 // ---------------------------------------------------------------------------------------------
 // One block per capacity segment: `span` experts (1, or the E/G experts of a device when the
@@ -196,11 +277,10 @@ __global__ __launch_bounds__(NT) void drop_select_kernel(const uint32_t* __restr
                                                           int32_t* __restrict__ seg_need,
                                                           int32_t* __restrict__ seg_count, int N, int E, int seg_tokens,
                                                           int span, int cap) {
-    __shared__ int hist[256];
+    __shared__ int hist[kSelectBins<NT>];
     __shared__ int gt_s[kMaxExperts], eq_s[kMaxExperts];
-    __shared__ int red[NT / kWave];
-    __shared__ uint32_t sh_prefix;
-    __shared__ int sh_rem;
+    __shared__ int red[NT / kWave], sh_bin[3];
+    __shared__ uint32_t extent[NT / kWave][3];
     const int groups = E / span;
     const int b = blockIdx.x / groups, e0 = (blockIdx.x - b * groups) * span;
     const uint32_t* keys = key_t + (size_t)e0 * N + (size_t)b * seg_tokens;  // run r starts at keys + r*N
@@ -255,52 +335,26 @@ __global__ __launch_bounds__(NT) void drop_select_kernel(const uint32_t* __restr
         }
     };
 
-    // the histogram of the keys' top byte (the first radix pass)
-    if (tid < 256) hist[tid] = 0;
+    for (int i = tid; i < kSelectBins<NT>; i += NT) hist[i] = 0;
     for (int r = tid; r < span; r += NT) gt_s[r] = eq_s[r] = 0;
-    __syncthreads();
-    int mine = 0;
+    uint32_t lo = 0xffffffffu, hi = 0u;
+    int n_cand = 0;
     for_each_key([&](int, int, uint32_t key) {
         if (key != 0u) {  // non-candidates (key 0) never matter
-            ++mine;
-            atomicAdd(&hist[key >> 24], 1);
+            ++n_cand;
+            lo = key < lo ? key : lo;
+            hi = key > hi ? key : hi;
         }
     });
-    const int n_cand = block_sum<NT>(mine, red);  // its barriers also order the LDS writes before the reads
+    key_extent<NT>(lo, hi, n_cand, extent);  // its barrier also orders the LDS writes before the reads
 
     // threshold: keys above tau are kept, `rem` of the keys equal to tau are kept
     uint32_t tau = 0;  // every candidate (key >= 1) passes
     int rem = 0;
     if (n_cand > cap) {
-        // cap-th largest key, most significant byte first
-        uint32_t prefix = 0;
         rem = cap;
-        for (int shift = 24; shift >= 0; shift -= 8) {
-            if (shift != 24) {
-                if (tid < 256) hist[tid] = 0;
-                __syncthreads();
-                const uint32_t hi_mask = 0xffffffffu << (shift + 8);
-                auto count_digit = [&](int, int, uint32_t key) {
-                    if (key != 0u && (key & hi_mask) == prefix) atomicAdd(&hist[(key >> shift) & 255u], 1);
-                };
-                for_each_key(count_digit);
-                __syncthreads();
-            }
-            // thread i < 256 owns digit 255 - i: an exclusive scan over threads counts the keys with a larger
-            // digit; the digit where that count first reaches `rem` holds the cap-th key
-            const int mine_d = 255 - tid;
-            const int h = tid < 256 ? hist[mine_d] : 0;
-            int total;
-            const int above = block_exclusive_scan<NT>(h, red, &total);
-            if (tid < 256 && above + h >= rem && above < rem) {  // exactly one thread
-                sh_prefix = prefix | ((uint32_t)mine_d << shift);
-                sh_rem = rem - above;
-            }
-            __syncthreads();
-            prefix = sh_prefix;
-            rem = sh_rem;
-        }
-        tau = prefix;
+        tau = select_threshold<NT>(lo, hi, rem, hist, red, sh_bin,
+                                   [&](auto&& f) __attribute__((always_inline)) { for_each_key([&](int, int, uint32_t key) { f(key); }); });
     }
     if (span == 1) {  // one expert: the counts follow from the selection itself
         if (tid == 0) {
@@ -331,7 +385,7 @@ __global__ __launch_bounds__(NT) void drop_select_kernel(const uint32_t* __restr
     __syncthreads();
     int eq_total = 0;
     for (int r = 0; r < span; ++r) eq_total += eq_s[r];
-    if (eq_total > rem) {
+    if (rem > 0 && eq_total > rem) {
         // More keys equal the threshold than the budget has room for: they are granted in
         // (token, expert) order.  A thread owns a run of consecutive tokens; the thread in whose
         // run the budget ends finds the last granted pair (token tie_token, expert run tie_run).
@@ -364,8 +418,9 @@ __global__ __launch_bounds__(NT) void drop_select_kernel(const uint32_t* __restr
     if (tid < span) {
         const int seg = b * E + e0 + tid;
         seg_tau[seg] = tau;
-        seg_need[seg] = eq_s[tid];  // inside an expert the granted keys are its first ones in token order
-        seg_count[seg] = gt_s[tid] + eq_s[tid];
+        const int granted = rem > 0 ? eq_s[tid] : 0;
+        seg_need[seg] = granted;  // inside an expert the granted keys are its first ones in token order
+        seg_count[seg] = gt_s[tid] + granted;
     }
 }
 
@@ -961,11 +1016,9 @@ __global__ __launch_bounds__(NT) void drop_fused_kernel(
     __shared__ uint32_t key_s[kMaxTok + kMaxTok / 16];
     __shared__ uint8_t slot_s[kMaxTok];
     __shared__ int cand[kFusedCounters];
-    __shared__ int hist[256];
-    __shared__ int red[kWaves];
-    __shared__ int red3[kWaves][3];
-    __shared__ uint32_t sh_prefix;
-    __shared__ int sh_rem;
+    __shared__ int hist[kSelectBins<NT>];
+    __shared__ int red[kWaves], sh_bin[3];
+    __shared__ uint32_t red5[kWaves][5];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int seg = blockIdx.x, b = seg / E, e = seg - b * E;
     const int segs = n_blocks * E;
@@ -979,7 +1032,7 @@ __global__ __launch_bounds__(NT) void drop_fused_kernel(
     auto pad = [](int i) { return i + (i >> 4); };
 
     for (int i = tid; i < copies * pitch; i += NT) cand[i] = 0;
-    if (tid < 256) hist[tid] = 0;
+    for (int i = tid; i < kSelectBins<NT>; i += NT) hist[i] = 0;
     if (scheduler)
         for (int i = tid; i < kMaxExperts; i += NT) sched_tot[i] = 0;
     __syncthreads();
@@ -1042,6 +1095,7 @@ __global__ __launch_bounds__(NT) void drop_fused_kernel(
     __syncthreads();
 
     // ---- keys and slots of this block's segment ----
+    uint32_t key_lo = 0xffffffffu, key_hi = 0u;
     if (!scheduler) {
         constexpr int kPer = 8;
         const int g_e = e / group_experts;  // device of this expert
@@ -1079,7 +1133,10 @@ __global__ __launch_bounds__(NT) void drop_fused_kernel(
                 below += lower < 0 ? 0 : (lower > group_experts ? group_experts : lower);
             }
             const uint32_t key = c[j] ? rank[j] + 1u : 0u;
-            if (c[j]) atomicAdd(&hist[key >> 24], 1);
+            if (c[j]) {
+                key_lo = key < key_lo ? key : key_lo;
+                key_hi = key > key_hi ? key : key_hi;
+            }
             key_s[pad(tl)] = key;
             slot_s[tl] = (uint8_t)below;
             if (e == 0) {  // slots beyond the token's candidate count stay unused
@@ -1113,26 +1170,33 @@ __global__ __launch_bounds__(NT) void drop_fused_kernel(
         build_schedule_from_totals(sched_tot, sched_off, sched);
         return;
     }
-    // block sums of the three (one pair of barriers)
+    // block sums of the three and the extent of the keys (one barrier)
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
         before += __shfl_xor(before, off, kWave);
         own_total += __shfl_xor(own_total, off, kWave);
         n_cand += __shfl_xor(n_cand, off, kWave);
+        const uint32_t a = __shfl_xor(key_lo, off, kWave), z = __shfl_xor(key_hi, off, kWave);
+        key_lo = a < key_lo ? a : key_lo;
+        key_hi = z > key_hi ? z : key_hi;
     }
     if (lane == 0) {
-        red3[wv][0] = before;
-        red3[wv][1] = own_total;
-        red3[wv][2] = n_cand;
+        red5[wv][0] = (uint32_t)before;
+        red5[wv][1] = (uint32_t)own_total;
+        red5[wv][2] = (uint32_t)n_cand;
+        red5[wv][3] = key_lo;
+        red5[wv][4] = key_hi;
     }
     __syncthreads();
     int row0 = 0, total;
     own_total = n_cand = 0;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
-        row0 += red3[w][0];
-        own_total += red3[w][1];
-        n_cand += red3[w][2];
+        row0 += (int)red5[w][0];
+        own_total += (int)red5[w][1];
+        n_cand += (int)red5[w][2];
+        key_lo = red5[w][3] < key_lo ? red5[w][3] : key_lo;
+        key_hi = red5[w][4] > key_hi ? red5[w][4] : key_hi;
     }
     if (tid == 0) {
         seg_count[seg] = n_cand < cap ? n_cand : cap;
@@ -1149,52 +1213,10 @@ __global__ __launch_bounds__(NT) void drop_fused_kernel(
     if (cap == 0) {
         tau = 0xffffffffu;  // nothing passes
     } else if (n_cand > cap) {
-        // cap-th largest key, most significant byte first; the histogram of the top byte is already there
-        uint32_t prefix = 0;
         need = cap;
-        for (int shift = 24; shift >= 0; shift -= 8) {
-            if (shift != 24) {
-                __syncthreads();
-                if (tid < 256) hist[tid] = 0;
-                __syncthreads();
-                const uint32_t hi_mask = 0xffffffffu << (shift + 8);
-                for (int tl = tid; tl < seg_tokens; tl += NT) {
-                    const uint32_t kx = key_s[pad(tl)];
-                    if (kx != 0u && (kx & hi_mask) == prefix) atomicAdd(&hist[(kx >> shift) & 255u], 1);
-                }
-                __syncthreads();
-            }
-            // the first wave owns the digits, lane l the four digits 255-4l .. 252-4l: a scan over its lanes
-            // counts the keys with a larger digit; the digit where that count first reaches `need` holds the
-            // cap-th key
-            if (wv == 0) {
-                int h[4], sum = 0;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    h[u] = hist[255 - 4 * lane - u];
-                    sum += h[u];
-                }
-                int incl = sum;
-#pragma unroll
-                for (int off = 1; off < kWave; off <<= 1) {
-                    const int o = __shfl_up(incl, off, kWave);
-                    if (lane >= off) incl += o;
-                }
-                int above = incl - sum;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    if (above < need && above + h[u] >= need) {  // exactly one lane and digit
-                        sh_prefix = prefix | ((uint32_t)(255 - 4 * lane - u) << shift);
-                        sh_rem = need - above;
-                    }
-                    above += h[u];
-                }
-            }
-            __syncthreads();
-            prefix = sh_prefix;
-            need = sh_rem;
-        }
-        tau = prefix;
+        tau = select_threshold<NT>(key_lo, key_hi, need, hist, red, sh_bin, [&](auto&& f) __attribute__((always_inline)) {
+            for (int tl = tid; tl < seg_tokens; tl += NT) f(key_s[pad(tl)]);
+        });
     }
 
     // ---- ordered compaction: rows in ascending token order, ties at the threshold to the lower tokens ----

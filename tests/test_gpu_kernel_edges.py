@@ -114,3 +114,50 @@ def test_tokens_without_numbers(n):
     assert torch.equal(idx[broken], torch.arange(k, dtype=torch.int32, device="cuda").expand(int(broken.sum()), k))
     for a, b in zip((scores, idx, score), clean):
         assert torch.equal(a[~broken], b[~broken])
+
+
+# ------------------------------------------------------------------------------------------------
+# thresholds of the drop: ranges of keys that are one key, a few, a power of two wide and the whole word; bins kept whole and cut
+# ------------------------------------------------------------------------------------------------
+def _scores_of_range(rng, n, e, width):
+    """Scores whose bit patterns lie within `width` of each other, everything listed: the capacity alone cuts."""
+    base = np.uint32(0x3d000000)
+    return (base + rng.integers(0, width, (n, e)).astype(np.uint32)).view(np.float32)
+
+
+@pytest.mark.parametrize("n,groups,scope", [(63, 1, 0), (2048, 1, 0), (2049, 1, 0), (8192, 1, 0), (8196, 1, 0), (12003, 1, 0),
+                                            (2048, 2, 3), (24000, 4, 2), (65544, 1, 1)])
+@pytest.mark.parametrize("width", [1, 2, 1024, 2048, 2049, 1 << 21, 1 << 24])
+def test_drop_threshold_of_key_ranges(n, groups, scope, width):
+    """The kept pairs against a sort of (key, token, expert): expert-level and device-level capacities."""
+    n -= n % groups
+    e, k, gamma = 4, 4, 0.6
+    rng = np.random.default_rng(n + width)
+    scores = _scores_of_range(rng, n, e, width)
+    desc = capmoe.make_desc(n, 4, e, k, 8, groups, capmoe.MODE_TOKEN_DROP, scope, gamma, capmoe.DTYPE_F32)
+    cap, slots, rows, workspace = capmoe.moe_query(desc)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    idx = np.broadcast_to(np.arange(e, dtype=np.int32), (n, e))
+    out = {name: torch.full(shape, -7, dtype=dt, device="cuda") for name, shape, dt in (
+        ("expert_count", (e,), torch.int32), ("seg_count", (groups * e,), torch.int32), ("expert_offset", (e + 1,), torch.int32),
+        ("row_token", (rows,), torch.int32), ("row_weight", (rows,), torch.float32), ("pair_row", (n, slots), torch.int32))}
+    ws = torch.empty(max(workspace, 256), dtype=torch.uint8, device="cuda")
+    capmoe.moe_capacity_drop(desc, dev(scores), dev(idx), out["expert_count"], out["seg_count"], out["expert_offset"],
+                             out["row_token"], out["row_weight"], out["pair_row"], ws)
+    torch.cuda.synchronize()
+    blocks = groups if scope in (0, 2) else 1
+    span = e // groups if scope in (2, 3) else 1
+    keep = np.zeros((n, e), bool)
+    per = n // blocks
+    bits = scores.view(np.uint32).astype(np.int64)
+    for b in range(blocks):
+        for g in range(e // span):
+            t, x = np.meshgrid(np.arange(b * per, (b + 1) * per), np.arange(g * span, (g + 1) * span), indexing="ij")
+            t, x = t.ravel(), x.ravel()
+            best = np.lexsort((x, t, -bits[t, x]))[:cap]   # larger score, then lower token, then lower expert
+            keep[t[best], x[best]] = True
+    tokens = np.concatenate([np.flatnonzero(keep[:, x]) for x in range(e)])
+    counts = keep.sum(axis=0)
+    np.testing.assert_array_equal(out["expert_count"].cpu().numpy(), counts)
+    np.testing.assert_array_equal(out["row_token"].cpu().numpy()[: counts.sum()], tokens)
+    assert np.array_equal(out["pair_row"].cpu().numpy() >= 0, keep)
