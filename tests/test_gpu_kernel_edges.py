@@ -126,10 +126,12 @@ def _scores_of_range(rng, n, e, width):
 
 
 @pytest.mark.parametrize("n,groups,scope", [(63, 1, 0), (2048, 1, 0), (2049, 1, 0), (8192, 1, 0), (8196, 1, 0), (12003, 1, 0),
-                                            (2048, 2, 3), (24000, 4, 2), (65544, 1, 1)])
+                                            (2048, 2, 3), (24000, 4, 2), (65544, 1, 1), (30, 2, 2), (32, 2, 2), (34, 2, 2),
+                                            (8192, 2, 2), (8224, 2, 2), (8226, 2, 2)])
 @pytest.mark.parametrize("width", [1, 2, 1024, 2048, 2049, 1 << 21, 1 << 24])
 def test_drop_threshold_of_key_ranges(n, groups, scope, width):
-    """The kept pairs against a sort of (key, token, expert): expert-level and device-level capacities."""
+    """The kept pairs against a sort of (key, token, expert): expert-level and device-level capacities; runs of 16 tokens that are
+    whole, cut short and at odd addresses, segments of one, two and many chunks of 4096 tokens."""
     n -= n % groups
     e, k, gamma = 4, 4, 0.6
     rng = np.random.default_rng(n + width)
