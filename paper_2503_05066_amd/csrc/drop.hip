@@ -1297,6 +1297,190 @@ __global__ __launch_bounds__(NT) void drop_fused_kernel(
     }
 }
 
+// ---------------------------------------------------------------------------------------------
+// 6. the same for a few tokens: a wave per segment
+// ---------------------------------------------------------------------------------------------
+// Decoding steps: segments of at most 128 tokens.  What bounds them is the chain of steps, each a barrier or a latency of the
+// kernel above; here a wave holds its segment (lane l the tokens l and l + 64), ranks its keys against each other
+// instead of looking for a threshold, and the only thing the waves of a block share is the number of candidates of every segment.
+// us, alone: 1 token, 64 experts 6.8 -> 4.4; 16 tokens, 8 experts 8.8 -> 3.7; 37, 64 experts 9.1 -> 5.6; 256 on 8 devices, Expanded
+// Drop 12.3 -> 7.7; 128 tokens, 8 experts 8.8 -> 7.9.
+constexpr int kSmallSegTokens = 128;
+constexpr int kSmallTokens = 512;  // of the batch: every block reads all lists
+constexpr int kSmallSegs = 1024;
+
+// HALVES: tokens of a lane
+template <bool EXPANDED, int HALVES>
+__global__ __launch_bounds__(256) void drop_small_kernel(
+    const float* __restrict__ scores, const int32_t* __restrict__ topk_idx, const uint8_t* __restrict__ token_class,
+    uint32_t seed, int32_t* __restrict__ expert_count, int32_t* __restrict__ seg_count,
+    int32_t* __restrict__ expert_offset, int32_t* __restrict__ row_token, float* __restrict__ row_weight,
+    int32_t* __restrict__ pair_row, int N, int E, int k, int S, int group_tokens, int group_experts, int metric,
+    int seg_tokens, int n_blocks, int cap, FfnScheduleArgs sched) {
+    __shared__ int cand[kSmallSegs];
+    __shared__ int sched_tot[kMaxExperts], sched_off[kMaxExperts + 1];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int segs = n_blocks * E;
+    const bool scheduler = sched.enabled && blockIdx.x == gridDim.x - 1;  // the last block builds the GEMMs' tile schedule
+    const int seg = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool mine = !scheduler && seg < segs;
+    const int b = mine ? seg / E : 0, e = mine ? seg - b * E : 0;
+    for (int i = tid; i < segs; i += 256) cand[i] = 0;
+    if (scheduler)
+        for (int i = tid; i < kMaxExperts; i += 256) sched_tot[i] = 0;
+
+    // ---- this segment's scores and lists: listed experts below e and in all, e itself (under Expanded Drop without the experts of the
+    // token's own device, which are candidates anyway) ----
+    uint32_t bits[HALVES], key[HALVES];
+    int below[HALVES], listed[HALVES];
+#pragma unroll
+    for (int q = 0; q < HALVES; ++q) {
+        const int tl = lane + 64 * q, t = b * seg_tokens + tl;
+        const bool live = mine && tl < seg_tokens;
+        const size_t row = live ? t : 0;  // past the segment: the first token's, not used
+        bits[q] = __float_as_uint(scores[row * E + e]);
+        const uint32_t cls = token_class ? (uint32_t)(token_class[row] & 3) << 30 : 0u;
+        const int dev = EXPANDED ? t / group_tokens : 0, g0 = dev * group_experts;
+        below[q] = listed[q] = 0;
+        bool cnd = EXPANDED && e >= g0 && e < g0 + group_experts;
+        const int32_t* list = topk_idx + row * k;
+        for (int j0 = 0; j0 < k; j0 += 8) {
+            int x[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) x[u] = list[j0 + u < k ? j0 + u : k - 1];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const bool counts = j0 + u < k && (!EXPANDED || x[u] < g0 || x[u] >= g0 + group_experts);
+                listed[q] += counts;
+                below[q] += counts && x[u] < e;
+                cnd = cnd || (counts && x[u] == e);
+            }
+        }
+        if (EXPANDED) {
+            const int lower = e - g0;  // experts of the token's device below e
+            below[q] += lower < 0 ? 0 : (lower > group_experts ? group_experts : lower);
+        }
+        uint32_t rank;
+        if (metric == MOE_METRIC_ORDER)
+            rank = (uint32_t)(seg_tokens - 1 - tl);
+        else if (metric == MOE_METRIC_REVERSE_ORDER)
+            rank = (uint32_t)tl;
+        else if (metric == MOE_METRIC_RANDOM)
+            rank = pair_hash(seed, (uint32_t)t * (uint32_t)E + (uint32_t)e) >> 3;
+        else
+            rank = bits[q];
+        key[q] = live && cnd ? rank + cls + 1u : 0u;
+        if (live && e == 0) {  // slots beyond the token's candidate count stay unused
+            const int n_c = listed[q] + (EXPANDED ? group_experts : 0);
+            for (int sl = n_c; sl < S; ++sl) pair_row[(size_t)t * S + sl] = -1;
+        }
+    }
+    __syncthreads();  // the counters are clear
+
+    // ---- candidates of every segment, from all lists (the experts of a token's own device are counted below) ----
+    const int entries = N * k;
+    for (int i0 = tid; i0 < entries; i0 += 256 * 4) {
+        int x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[u] = i0 + 256 * u < entries ? topk_idx[i0 + 256 * u] : -1;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (x[u] < 0) continue;
+            int at = x[u];
+            if (EXPANDED || n_blocks > 1) {
+                const int t = (i0 + 256 * u) / k;
+                if (EXPANDED) {
+                    const int g0 = t / group_tokens * group_experts;
+                    if (x[u] >= g0 && x[u] < g0 + group_experts) continue;
+                }
+                at += t / seg_tokens * E;
+            }
+            atomicAdd(&cand[at], 1);
+        }
+    }
+    __syncthreads();
+
+    // ---- kept rows of every segment: this one's first row, its expert's total ----
+    auto kept_of = [&](int i, int ee, int bb) {
+        int c = cand[i];
+        if (EXPANDED) {  // plus the tokens of block bb that sit on the expert's device
+            const int lo = (ee / group_experts) * group_tokens, hi = lo + group_tokens;
+            const int s0 = bb * seg_tokens, s1 = s0 + seg_tokens;
+            const int a = lo > s0 ? lo : s0, z = hi < s1 ? hi : s1;
+            c += z > a ? z - a : 0;
+        }
+        return c < cap ? c : cap;
+    };
+    if (scheduler) {
+        for (int i = tid; i < segs; i += 256) {
+            const int bb = i / E, ee = i - bb * E;
+            atomicAdd(&sched_tot[ee], kept_of(i, ee, bb));
+        }
+        __syncthreads();
+        build_schedule_from_totals(sched_tot, sched_off, sched);
+        return;
+    }
+    if (!mine) return;
+    int before = 0, own_total = 0;
+    for (int i = lane; i < segs; i += kWave) {
+        const int bb = i / E, ee = i - bb * E, kept = kept_of(i, ee, bb);
+        if (ee < e || (ee == e && bb < b)) before += kept;
+        if (ee == e) own_total += kept;
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        before += __shfl_xor(before, off, kWave);
+        own_total += __shfl_xor(own_total, off, kWave);
+    }
+    int n_cand = 0;
+#pragma unroll
+    for (int q = 0; q < HALVES; ++q) n_cand += __popcll(__ballot(key[q] != 0u));
+    if (lane == 0) {
+        seg_count[seg] = n_cand < cap ? n_cand : cap;
+        if (b == 0) {
+            expert_count[e] = own_total;
+            expert_offset[e] = before;
+            if (e == E - 1) expert_offset[E] = before + own_total;
+        }
+    }
+
+    // ---- a pair stays if fewer than cap pairs are ahead of it: larger keys, and equal keys of lower tokens ----
+    int ahead[HALVES];
+#pragma unroll
+    for (int q = 0; q < HALVES; ++q) ahead[q] = 0;
+    if (n_cand > cap) {
+        const int lanes = seg_tokens < kWave ? seg_tokens : kWave;
+        for (int j0 = 0; j0 < lanes; j0 += 8) {  // (past the segment keys are 0: ahead of no candidate)
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int j = j0 + u;
+                const uint32_t low = __builtin_amdgcn_readlane(key[0], j);
+                ahead[0] += low >= key[0] + (j < lane ? 0u : 1u);  // a lower token is ahead with an equal key
+                if (HALVES > 1) {
+                    const uint32_t high = __builtin_amdgcn_readlane(key[HALVES - 1], j);
+                    ahead[0] += high >= key[0] + 1u;
+                    ahead[HALVES - 1] += low >= key[HALVES - 1];
+                    ahead[HALVES - 1] += high >= key[HALVES - 1] + (j < lane ? 0u : 1u);
+                }
+            }
+        }
+    }
+    const uint64_t lower = (1ull << lane) - 1ull;
+    int base = before;
+#pragma unroll
+    for (int q = 0; q < HALVES; ++q) {
+        const bool keep = key[q] != 0u && (n_cand <= cap || ahead[q] < cap);
+        const uint64_t mask = __ballot(keep);
+        const int pos = base + __popcll(mask & lower), t = b * seg_tokens + lane + 64 * q;
+        base += __popcll(mask);
+        if (keep) {
+            row_token[pos] = t;
+            row_weight[pos] = __uint_as_float(bits[q]);  // the gating score, whatever ranked the pair
+        }
+        if (key[q] != 0u) pair_row[(size_t)t * S + below[q]] = keep ? pos : -1;
+    }
+}
+
 // keys are fetched four at a time: every run starts on a 16-byte boundary
 static bool select_by_four(const Sizes& s, int n_tokens) { return n_tokens % 4 == 0 && s.seg_tokens % 4 == 0; }
 
@@ -1337,6 +1521,23 @@ hipError_t launch_capacity_drop(const moe_desc_t& d, const Sizes& s, const DropW
         const bool fused = s.span == 1 && !(d.max_experts && s.slots > d.top_k) && N > 0 &&
                            s.seg_tokens <= kFusedMaxTokens && segs_all + 1 <= kFusedCounters &&
                            segs_all <= kFusedMaxSegs && (long long)segs_all * N * s.list_k <= kFusedMaxWork;
+        // (every block reads all lists and a wave ranks by comparing all pairs: hence the limits; 129 to 512 tokens of one segment and
+        // longer batches stay with the kernel below)
+        if (fused && s.seg_tokens <= kSmallSegTokens && N <= kSmallTokens && segs_all <= kSmallSegs) {
+            auto launch = [&](auto kern) {
+                ProfileScope prof(MOE_KERNEL_DROP_SELECT, st);
+                hipLaunchKernelGGL(kern, dim3((segs_all + 3) / 4 + (sched.enabled ? 1 : 0)), dim3(256), 0, st, scores, topk_idx,
+                                   token_class, seed, expert_count, seg_count, expert_offset, row_token, row_weight, pair_row, N, E,
+                                   s.list_k, s.slots, s.group_tokens, s.group_experts, d.metric, s.seg_tokens, s.n_blocks, s.cap,
+                                   sched);
+            };
+            const bool ex = d.mode == MOE_MODE_EXPANDED_DROP;
+            if (s.seg_tokens <= kWave)
+                launch(ex ? drop_small_kernel<true, 1> : drop_small_kernel<false, 1>);
+            else
+                launch(ex ? drop_small_kernel<true, 2> : drop_small_kernel<false, 2>);
+            return hipGetLastError();
+        }
         if (fused) {
             // every block reads all N lists: small blocks only where that is a single round for them too
             const bool small = s.seg_tokens <= 8 * kSmallBlock && N <= 8 * kSmallBlock;

@@ -163,3 +163,48 @@ def test_drop_threshold_of_key_ranges(n, groups, scope, width):
     np.testing.assert_array_equal(out["expert_count"].cpu().numpy(), counts)
     np.testing.assert_array_equal(out["row_token"].cpu().numpy()[: counts.sum()], tokens)
     assert np.array_equal(out["pair_row"].cpu().numpy() >= 0, keep)
+
+
+# ------------------------------------------------------------------------------------------------
+# the drop of a few tokens: a wave's lanes and halves filled, short by one and exceeded, the limits of its rule on both sides, blocks
+# with fewer segments than waves; through the one call that also builds the tile schedule, against the oracle's plan
+# ------------------------------------------------------------------------------------------------
+@pytest.mark.parametrize("n,e,k,groups", [(1, 1, 1, 1), (1, 64, 8, 1), (3, 5, 2, 1), (63, 8, 2, 1), (64, 8, 3, 1), (65, 7, 2, 1), (128, 8, 2, 1),
+                                          (129, 8, 2, 1), (512, 16, 6, 4), (513, 9, 2, 9), (512, 128, 9, 8), (512, 130, 4, 10),
+                                          (256, 64, 6, 8), (40, 256, 64, 4)])
+@pytest.mark.parametrize("mode,metric,classes", [(0, 0, False), (1, 0, False), (1, 1, True), (2, 3, False), (2, 2, True)])
+def test_drop_of_a_few_tokens(n, e, k, groups, mode, metric, classes):
+    from oracle import oracle
+
+    n, groups = (n, groups) if n % groups == 0 and e % groups == 0 else (n, 1)
+    d, h = 128, 128
+    rng = np.random.default_rng(n * e + mode)
+    logits = np.round(rng.standard_normal((n, e)) * 3).astype(np.float32)     # many equal scores
+    cls = rng.integers(0, 3, n).astype(np.uint8) if classes else None
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    for scope in (0, 1):
+        for gamma in (0.0, 0.4, 1.0):
+            desc = capmoe.make_desc(n, d, e, k, h, groups, mode, scope, gamma, capmoe.DTYPE_F32, metric)
+            ref = oracle.route_and_drop(logits, k, groups, mode, scope, gamma, metric=metric, token_class=cls, seed=5)
+            buf = capmoe.LayerBuffers(desc)
+            buf.logits.copy_(dev(logits))
+            capmoe.moe_route_topk(desc, None, None, None, True, buf.logits, buf.scores, buf.topk_idx, buf.topk_score, buf.workspace)
+            capmoe.moe_capacity_drop_ranked(desc, buf.scores, buf.topk_idx, None if cls is None else dev(cls), 5, buf.expert_count,
+                                            buf.seg_count, buf.expert_offset, buf.row_token, buf.row_weight, buf.pair_row,
+                                            buf.workspace)
+            torch.cuda.synchronize()
+            p = ref.plan
+            for got, want in ((buf.expert_count, p.expert_count), (buf.expert_offset, p.expert_offset), (buf.seg_count, p.seg_count),
+                              (buf.row_token[: p.rows], p.row_token), (buf.row_weight[: p.rows], p.row_weight),
+                              (buf.pair_row, p.pair_row)):
+                np.testing.assert_array_equal(got.cpu().numpy(), want)
+            # the layer in one call: the drop's last block builds the tile schedule
+            x = rng.standard_normal((n, d)).astype(np.float32)
+            w_router = (rng.standard_normal((e, d)) / 12).astype(np.float32)
+            ws = [dev((rng.standard_normal(s) / 12).astype(np.float32)) for s in ((e, h, d), (e, h, d), (e, d, h))] if e <= 16 else None
+            if ws and gamma == 0.4:
+                one, four = capmoe.LayerBuffers(desc), capmoe.LayerBuffers(desc)
+                capmoe.moe_layer_forward(desc, dev(x), dev(w_router), None, *ws, None if cls is None else dev(cls), 5, one)
+                capmoe.layer_forward(four, dev(x), dev(w_router), None, *ws, token_class=None if cls is None else dev(cls), seed=5)
+                torch.cuda.synchronize()
+                assert torch.equal(one.y, four.y) and torch.equal(one.pair_row, four.pair_row)
