@@ -891,39 +891,40 @@ __global__ __launch_bounds__(256) void drop_emit_kernel(const float* __restrict_
 // ---------------------------------------------------------------------------------------------
 // 4. at most k experts per token (optional; appendix "Maximum Number of Selected Experts")
 // ---------------------------------------------------------------------------------------------
-constexpr int kLimitTokens = 64;        // tokens of a block
-constexpr int kLimitPitch = kLimitTokens + 1;  // words per expert row of the block's key tile in LDS
-
 // Runs after a first emit.  For every token: its surviving pairs are listed, ranked by gating score
 // (equal scores: lower expert id first), and those ranked k-th or worse are removed.  Keys of every pair
 // that does not survive (dropped by capacity, or removed here) become 0, the per-segment counts are
 // lowered, and thresholds are reset so that a second emit keeps exactly the non-zero keys.
-// A block moves the keys of 64 tokens and all experts through LDS (the key matrix is expert-major: rows of
-// consecutive tokens go in and out as whole cache lines); then a wave takes a token at a time, lanes
+// A block moves the keys of TOKENS tokens and all experts through LDS (the key matrix is expert-major: rows of
+// consecutive tokens go in and out as whole sectors); then a wave takes a token at a time, lanes
 // over experts: the c-th candidate in ascending expert id owns slot c of the token (ballot prefix counts).
 // EPL = experts per lane (E <= 64 * EPL).  Nothing in the per-token loop waits for global memory: the
-// tokens' slot rows are staged in LDS beside the keys and their score rows are requested up front.
-template <int EPL>
+// tokens' slot rows are staged in LDS beside the keys and their score rows are requested up front.  A survivor is
+// ranked where it lies: the scores of the others come out of their lanes one after another (uniform).
+// Bound by latencies, a wave's tokens one after another, until its launch fills the chip: 3000 tokens x 64 experts 24.3 -> 9.7 us
+// against blocks of 64 tokens that fetched key by key, score row by token and ranked through a list in LDS (300 tokens 20.7 -> 6.7,
+// 32 768 25.5 -> 18.8, 16 384 x 256 48.4 -> 22.3).
+template <int EPL, int TOKENS>
 __global__ __launch_bounds__(256) void drop_limit_kernel(const float* __restrict__ scores, uint32_t* __restrict__ key_t,
                                                          int32_t* __restrict__ pair_row,
                                                          uint32_t* __restrict__ seg_tau, int32_t* __restrict__ seg_need,
                                                          int32_t* __restrict__ seg_count, int N, int E, int S, int k,
                                                          int seg_tokens, int segs) {
-    extern __shared__ uint32_t tile[];            // [E][kLimitPitch] keys, then [kLimitTokens][S] rows of pair_row
-    __shared__ uint2 survivors[4][256];           // per wave: (score bits, expert | slot << 16), ascending expert
+    constexpr int kPitch = TOKENS + 1;            // words per expert row of the block's key tile
+    extern __shared__ uint32_t tile[];            // [E][kPitch] keys, then [TOKENS][S] rows of pair_row
     __shared__ int removed[kMaxExperts];          // pairs this block removes per expert (one global atomic each at the end)
-    int32_t* rows = (int32_t*)(tile + (size_t)E * kLimitPitch);
+    int32_t* rows = (int32_t*)(tile + (size_t)E * kPitch);
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    constexpr int kPerWave = kLimitTokens / 4;    // tokens of a wave: wv, wv + 4, ...
-    const int t_first = blockIdx.x * kLimitTokens;
-    const int t_last = t_first + kLimitTokens - 1 < N ? t_first + kLimitTokens - 1 : N - 1;
+    constexpr int kPerWave = TOKENS / 4;    // tokens of a wave: wv, wv + 4, ...
+    const int t_first = blockIdx.x * TOKENS;
+    const int t_last = t_first + TOKENS - 1 < N ? t_first + TOKENS - 1 : N - 1;
     float sc[kPerWave][EPL];
 #pragma unroll
     for (int q = 0; q < kPerWave; ++q)
 #pragma unroll
         for (int i = 0; i < EPL; ++i) {
             const int t = t_first + wv + 4 * q, e = lane + kWave * i;
-            sc[q][i] = t < N && e < E ? scores[(size_t)t * E + e] : 0.0f;
+            sc[q][i] = scores[(size_t)(t < N ? t : N - 1) * E + (e < E ? e : E - 1)];  // (lanes past E keep nothing)
         }
     for (int i = blockIdx.x * 256 + tid; i < segs; i += gridDim.x * 256) {
         seg_tau[i] = 0u;
@@ -932,50 +933,83 @@ __global__ __launch_bounds__(256) void drop_limit_kernel(const float* __restrict
     for (int e = tid; e < E; e += 256) removed[e] = 0;
     // the block's tokens lie in one capacity block when its first and last do
     const bool one_block = t_first / seg_tokens == t_last / seg_tokens;
-    for (int i = tid; i < E * kLimitTokens; i += 256) {
-        const int e = i / kLimitTokens, tl = i - e * kLimitTokens;
-        tile[e * kLimitPitch + tl] = t_first + tl < N ? key_t[(size_t)e * N + t_first + tl] : 0u;
-    }
+    // both stagings request a batch before the first answer is stored (clamped addresses: a branch would serialise them)
+    constexpr int kBatch = 8;
     const int n_rows = (t_last - t_first + 1) * S;  // the block's rows of pair_row are consecutive in memory
-    for (int i = tid; i < n_rows; i += 256) rows[i] = pair_row[(size_t)t_first * S + i];
+    for (int base = tid; base < E * TOKENS; base += 256 * kBatch) {
+        uint32_t v[kBatch];
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) {
+            const int i = base + 256 * j, e = i / TOKENS < E ? i / TOKENS : E - 1, t = t_first + i % TOKENS;
+            v[j] = key_t[(size_t)e * N + (t < N ? t : N - 1)];
+        }
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) asm volatile("" : "+v"(v[j]));
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) {
+            const int i = base + 256 * j;
+            if (i < E * TOKENS) tile[i / TOKENS * kPitch + i % TOKENS] = v[j];  // (tokens from N up are not looked at)
+        }
+    }
+    for (int base = tid; base < n_rows; base += 256 * kBatch) {
+        int32_t v[kBatch];
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) {
+            const int i = base + 256 * j;
+            v[j] = pair_row[(size_t)t_first * S + (i < n_rows ? i : n_rows - 1)];
+        }
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) asm volatile("" : "+v"(v[j]));
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j)
+            if (base + 256 * j < n_rows) rows[base + 256 * j] = v[j];
+    }
+#pragma unroll
+    for (int q = 0; q < kPerWave; ++q)
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) asm volatile("" : "+v"(sc[q][i]));  // in flight since the start, not fetched per token
     __syncthreads();
     const uint64_t below = (1ull << lane) - 1ull;
-    uint2* list = &survivors[wv][0];
 #pragma unroll
     for (int q = 0; q < kPerWave; ++q) {
         const int tl = wv + 4 * q, t = t_first + tl;
         if (t >= N) break;  // wave-uniform
         int slot_base = 0, n = 0;
+        int slot[EPL];
+        uint64_t kept_mask[EPL];
 #pragma unroll
         for (int i = 0; i < EPL; ++i) {
             const int e = lane + kWave * i;
-            const uint32_t key = e < E ? tile[e * kLimitPitch + tl] : 0u;
+            const uint32_t key = e < E ? tile[e * kPitch + tl] : 0u;
             const bool cand = key != 0u;
             const uint64_t cand_mask = __ballot(cand);
-            const int slot = slot_base + __popcll(cand_mask & below);
+            slot[i] = slot_base + __popcll(cand_mask & below);
             slot_base += __popcll(cand_mask);
-            const bool kept = cand && rows[tl * S + slot] >= 0;  // survived the capacity
-            if (cand && !kept) tile[e * kLimitPitch + tl] = 0u;
-            const uint64_t kept_mask = __ballot(kept);
-            if (kept)
-                list[n + __popcll(kept_mask & below)] =
-                    make_uint2(__float_as_uint(sc[q][i]), (uint32_t)e | ((uint32_t)slot << 16));
-            n += __popcll(kept_mask);
+            const bool kept = cand && rows[tl * S + slot[i]] >= 0;  // survived the capacity
+            if (cand && !kept) tile[e * kPitch + tl] = 0u;
+            kept_mask[i] = __ballot(kept);
+            n += __popcll(kept_mask[i]);
         }
-        __builtin_amdgcn_wave_barrier();  // LDS operations of one wave complete in order
-        if (n > k) {
-            const int b = t / seg_tokens;
-            for (int j = lane; j < n; j += kWave) {
-                const uint2 mine = list[j];
-                int better = 0;  // survivors ahead of pair j: higher score, or equal score and lower expert id
-                for (int i = 0; i < n; ++i) {
-                    const uint32_t si = list[i].x;  // same address in every lane
-                    better += si > mine.x || (si == mine.x && i < j);
+        if (n > k) {  // wave-uniform
+            int better[EPL] = {};  // survivors ahead of mine: higher score, or equal score and lower expert id
+#pragma unroll
+            for (int i = 0; i < EPL; ++i)
+                for (uint64_t left = kept_mask[i]; left; left &= left - 1) {
+                    const int from = __builtin_ctzll(left);
+                    const uint32_t other = (uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(sc[q][i]), from);
+#pragma unroll
+                    for (int j = 0; j < EPL; ++j) {
+                        const uint32_t mine = __float_as_uint(sc[q][j]);
+                        better[j] += other > mine || (other == mine && from + kWave * i < lane + kWave * j);
+                    }
                 }
-                if (better >= k) {
-                    const int e = (int)(mine.y & 0xffffu), sl = (int)(mine.y >> 16);
-                    tile[e * kLimitPitch + tl] = 0u;
-                    pair_row[(size_t)t * S + sl] = -1;
+            const int b = t / seg_tokens;
+#pragma unroll
+            for (int i = 0; i < EPL; ++i) {
+                const int e = lane + kWave * i;
+                if ((kept_mask[i] >> lane & 1) && better[i] >= k) {
+                    tile[e * kPitch + tl] = 0u;
+                    pair_row[(size_t)t * S + slot[i]] = -1;
                     if (one_block)
                         atomicAdd(&removed[e], 1);
                     else
@@ -983,12 +1017,11 @@ __global__ __launch_bounds__(256) void drop_limit_kernel(const float* __restrict
                 }
             }
         }
-        __builtin_amdgcn_wave_barrier();  // the list is rewritten for the wave's next token only after these reads
     }
     __syncthreads();
-    for (int i = tid; i < E * kLimitTokens; i += 256) {
-        const int e = i / kLimitTokens, tl = i - e * kLimitTokens;
-        if (t_first + tl < N) key_t[(size_t)e * N + t_first + tl] = tile[e * kLimitPitch + tl];
+    for (int i = tid; i < E * TOKENS; i += 256) {
+        const int e = i / TOKENS, tl = i - e * TOKENS;
+        if (t_first + tl < N) key_t[(size_t)e * N + t_first + tl] = tile[e * kPitch + tl];
     }
     if (one_block)
         for (int e = tid; e < E; e += 256)
@@ -1647,14 +1680,19 @@ hipError_t launch_capacity_drop(const moe_desc_t& d, const Sizes& s, const DropW
     emit(!limit);
     if (limit) {
         // the first plan tells which pairs survive the capacity; trim every token to k of them, emit again
-        // the key tile of 64 tokens and their rows of pair_row: at most 256 * 65 + 64 * 255 words
-        const size_t lds = ((size_t)E * kLimitPitch + (size_t)kLimitTokens * s.slots) * 4;
-        auto kern = E <= 64 ? drop_limit_kernel<1> : (E <= 128 ? drop_limit_kernel<2> : drop_limit_kernel<4>);
+        // 16 tokens a block up to 16384 (32: 12.3 us against 9.7 at 3000, 23.9 against 22.3 at 16384 x 256); above, the blocks of
+        // 16 run in many rounds and move half lines of the key matrix (32 768 x 64: 21.8 against 18.8, 65 536: 47.4 against 28.1)
+        const int tokens = N <= 16384 ? 16 : 32;
+        // the key tile and the tokens' rows of pair_row: at most 256 * 33 + 32 * 255 words
+        const size_t lds = ((size_t)E * (tokens + 1) + (size_t)tokens * s.slots) * 4;
+        auto kern = tokens == 16
+                        ? (E <= 64 ? drop_limit_kernel<1, 16> : (E <= 128 ? drop_limit_kernel<2, 16> : drop_limit_kernel<4, 16>))
+                        : (E <= 64 ? drop_limit_kernel<1, 32> : (E <= 128 ? drop_limit_kernel<2, 32> : drop_limit_kernel<4, 32>));
         if (lds > 48 * 1024)
             (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         {
             ProfileScope prof(MOE_KERNEL_DROP_LIMIT, st);
-            hipLaunchKernelGGL(kern, dim3((N + kLimitTokens - 1) / kLimitTokens), dim3(256), lds, st, scores, ws.key_t,
+            hipLaunchKernelGGL(kern, dim3((N + tokens - 1) / tokens), dim3(256), lds, st, scores, ws.key_t,
                                pair_row, ws.seg_tau, ws.seg_need, seg_count, N, E, s.slots, d.top_k, s.seg_tokens, segs);
         }
         emit(true);

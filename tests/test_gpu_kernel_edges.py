@@ -208,3 +208,33 @@ def test_drop_of_a_few_tokens(n, e, k, groups, mode, metric, classes):
                 capmoe.layer_forward(four, dev(x), dev(w_router), None, *ws, token_class=None if cls is None else dev(cls), seed=5)
                 torch.cuda.synchronize()
                 assert torch.equal(one.y, four.y) and torch.equal(one.pair_row, four.pair_row)
+
+
+# ------------------------------------------------------------------------------------------------
+# at most k experts per token: blocks of tokens filled, short by one and exceeded, blocks that straddle two capacity blocks, one to four
+# experts per lane, more candidates than lanes, equal scores; against the oracle's plan
+# ------------------------------------------------------------------------------------------------
+@pytest.mark.parametrize("n,e,k,over,groups", [(1, 8, 2, 4, 1), (15, 8, 2, 4, 1), (16, 64, 8, 8, 1), (17, 64, 8, 8, 1), (63, 65, 4, 8, 1),
+                                               (65, 128, 8, 16, 4), (257, 130, 14, 50, 1), (120, 256, 8, 56, 8), (1030, 30, 4, 6, 2),
+                                               (16384, 8, 2, 3, 1), (16385, 16, 2, 3, 1), (16416, 70, 4, 4, 4),
+                                               (16400, 130, 3, 2, 1)])
+@pytest.mark.parametrize("mode,gamma", [(2, 1.0), (2, 3.0), (1, 1.0)])
+def test_limit_of_experts_per_token(n, e, k, over, groups, mode, gamma):
+    from oracle import oracle
+
+    n, groups = (n, groups) if n % groups == 0 and e % groups == 0 else (n, 1)
+    rng = np.random.default_rng(n * e + mode)
+    logits = np.round(rng.standard_normal((n, e)) * 3).astype(np.float32)     # many equal scores
+    desc = capmoe.make_desc(n, 128, e, k, 128, groups, mode, 0, gamma, capmoe.DTYPE_F32, 0, over, True)
+    ref = oracle.route_and_drop(logits, k, groups, mode, 0, gamma, metric=0, token_class=None, seed=5, overselect=over, max_experts=True)
+    buf = capmoe.LayerBuffers(desc)
+    buf.logits.copy_(torch.from_numpy(logits).cuda())
+    capmoe.moe_route_topk(desc, None, None, None, True, buf.logits, buf.scores, buf.topk_idx, buf.topk_score, buf.workspace)
+    capmoe.moe_capacity_drop_ranked(desc, buf.scores, buf.topk_idx, None, 5, buf.expert_count, buf.seg_count, buf.expert_offset,
+                                    buf.row_token, buf.row_weight, buf.pair_row, buf.workspace)
+    torch.cuda.synchronize()
+    p = ref.plan
+    assert (p.pair_row >= 0).sum(axis=1).max() <= k
+    for got, want in ((buf.expert_count, p.expert_count), (buf.expert_offset, p.expert_offset), (buf.seg_count, p.seg_count),
+                      (buf.row_token[: p.rows], p.row_token), (buf.row_weight[: p.rows], p.row_weight), (buf.pair_row, p.pair_row)):
+        np.testing.assert_array_equal(got.cpu().numpy(), want)
