@@ -1514,6 +1514,16 @@ __global__ __launch_bounds__(256) void drop_small_kernel(
     }
 }
 
+// The plan of a batch without tokens: every count is zero.
+__global__ __launch_bounds__(256) void drop_empty_kernel(int32_t* __restrict__ expert_count, int32_t* __restrict__ seg_count,
+                                                         int32_t* __restrict__ expert_offset, int E, int segs) {
+    for (int i = threadIdx.x; i < segs; i += 256) seg_count[i] = 0;
+    for (int i = threadIdx.x; i <= E; i += 256) {
+        expert_offset[i] = 0;
+        if (i < E) expert_count[i] = 0;
+    }
+}
+
 // keys are fetched four at a time: every run starts on a 16-byte boundary
 static bool select_by_four(const Sizes& s, int n_tokens) { return n_tokens % 4 == 0 && s.seg_tokens % 4 == 0; }
 
@@ -1548,10 +1558,15 @@ hipError_t launch_capacity_drop(const moe_desc_t& d, const Sizes& s, const DropW
     const int N = d.n_tokens, E = d.n_experts;
     FfnScheduleArgs no_schedule = {};  // enabled = 0
     const FfnScheduleArgs& sched = schedule ? *schedule : no_schedule;
+    if (N == 0) {  // scores, lists and pair_row may be null: no kernel that fetches from them is launched (and no row needs a schedule)
+        ProfileScope prof(MOE_KERNEL_DROP_EMIT, st);
+        hipLaunchKernelGGL(drop_empty_kernel, dim3(1), dim3(256), 0, st, expert_count, seg_count, expert_offset, E, s.n_blocks * E);
+        return hipGetLastError();
+    }
     {
         const int segs_all = s.n_blocks * E;
         constexpr int kSmallBlock = 256;  // threads of a block for short segments of short batches
-        const bool fused = s.span == 1 && !(d.max_experts && s.slots > d.top_k) && N > 0 &&
+        const bool fused = s.span == 1 && !(d.max_experts && s.slots > d.top_k) &&
                            s.seg_tokens <= kFusedMaxTokens && segs_all + 1 <= kFusedCounters &&
                            segs_all <= kFusedMaxSegs && (long long)segs_all * N * s.list_k <= kFusedMaxWork;
         // (every block reads all lists and a wave ranks by comparing all pairs: hence the limits; 129 to 512 tokens of one segment and
@@ -1613,7 +1628,7 @@ hipError_t launch_capacity_drop(const moe_desc_t& d, const Sizes& s, const DropW
     const bool many = form == Select::kShared || form == Select::kCount;  // blocks per segment
     const int segs = s.n_blocks * E, dsegs = segs / s.span;
     BigState* state = form == Select::kShared ? (BigState*)ws.big_state : nullptr;
-    if (N > 0) {
+    {
         const int grid = (N + kPrepTokens - 1) / kPrepTokens;
         const size_t lds = (size_t)kPrepTokens * (E | 1) * 5;
         if (lds > 64 * 1024)
@@ -1622,7 +1637,7 @@ hipError_t launch_capacity_drop(const moe_desc_t& d, const Sizes& s, const DropW
         ProfileScope prof(MOE_KERNEL_DROP_PREPARE, st);
         hipLaunchKernelGGL(drop_prepare_kernel, dim3(grid), dim3(256), lds, st, scores, topk_idx, ws.key_t, ws.slot_t,
                            pair_row, N, E, s.list_k, s.slots, d.mode == MOE_MODE_EXPANDED_DROP ? 1 : 0, s.group_tokens,
-                           s.group_experts, d.metric, s.seg_tokens > 0 ? s.seg_tokens : 1, token_class, seed,
+                           s.group_experts, d.metric, s.seg_tokens, token_class, seed,
                            (uint32_t*)state, state ? (long long)dsegs * (long long)(sizeof(BigState) / 4) : 0ll,
                            many ? seg_count : nullptr, ws.seg_need, segs);
     }
@@ -1676,7 +1691,7 @@ hipError_t launch_capacity_drop(const moe_desc_t& d, const Sizes& s, const DropW
                            s.n_blocks, s.seg_tokens, s.slots, d.metric == MOE_METRIC_SCORE && !token_class ? 1 : 0,
                            last ? sched : no_schedule);
     };
-    const bool limit = d.max_experts && s.slots > d.top_k && N > 0;
+    const bool limit = d.max_experts && s.slots > d.top_k;
     emit(!limit);
     if (limit) {
         // the first plan tells which pairs survive the capacity; trim every token to k of them, emit again

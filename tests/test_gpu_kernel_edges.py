@@ -238,3 +238,30 @@ def test_limit_of_experts_per_token(n, e, k, over, groups, mode, gamma):
     for got, want in ((buf.expert_count, p.expert_count), (buf.expert_offset, p.expert_offset), (buf.seg_count, p.seg_count),
                       (buf.row_token[: p.rows], p.row_token), (buf.row_weight[: p.rows], p.row_weight), (buf.pair_row, p.pair_row)):
         np.testing.assert_array_equal(got.cpu().numpy(), want)
+
+
+# ------------------------------------------------------------------------------------------------
+# a batch without tokens: its arrays are null, its plan is zeros, whatever ranks the pairs
+# ------------------------------------------------------------------------------------------------
+@pytest.mark.parametrize("metric", [capmoe.METRIC_SCORE, capmoe.METRIC_ORDER, capmoe.METRIC_REVERSE_ORDER, capmoe.METRIC_RANDOM])
+@pytest.mark.parametrize("classes", [False, True])
+@pytest.mark.parametrize("mode,scope,over,limit", [(0, 1, 0, False), (1, 0, 0, False), (1, 3, 2, True), (2, 2, 0, False), (2, 0, 3, True)])
+def test_empty_batch_of_every_metric(metric, classes, mode, scope, over, limit):
+    e, groups = 8, 4
+    desc = capmoe.make_desc(0, 128, e, 2, 128, groups, mode, scope, 1.0, capmoe.DTYPE_BF16, metric, over, limit)
+    cls = torch.ones(1, dtype=torch.uint8, device="cuda") if classes else None     # an array that is there, though nothing is in it
+    weights = [torch.zeros((e, 128, 128), dtype=torch.bfloat16, device="cuda") for _ in range(3)]
+    w_router = torch.zeros((e, 128), device="cuda")
+    for call in ("drop", "layer"):
+        buf = capmoe.LayerBuffers(desc)
+        assert buf.scores.data_ptr() == 0 and buf.topk_idx.data_ptr() == 0 and buf.pair_row.data_ptr() == 0
+        for a in (buf.expert_count, buf.seg_count, buf.expert_offset):
+            a.fill_(7)
+        if call == "drop":
+            capmoe.moe_capacity_drop_ranked(desc, buf.scores, buf.topk_idx, cls, 5, buf.expert_count, buf.seg_count,
+                                            buf.expert_offset, buf.row_token, buf.row_weight, buf.pair_row, buf.workspace)
+        else:
+            capmoe.moe_layer_forward(desc, buf.y, w_router, None, *weights, cls, 5, buf)
+        torch.cuda.synchronize()
+        for a in (buf.expert_count, buf.seg_count, buf.expert_offset):
+            assert bool((a == 0).all())
