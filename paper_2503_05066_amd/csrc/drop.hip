@@ -21,6 +21,7 @@
 
 #include "common.h"
 #include "schedule.h"
+#include "threshold.h"
 
 namespace capmoe {
 
@@ -172,62 +173,6 @@ __device__ __forceinline__ void static_for(F&& f) {
     if constexpr (I < N) {
         f(std::integral_constant<int, I>{});
         static_for<N, F, I + 1>(static_cast<F&&>(f));
-    }
-}
-
-// ---------------------------------------------------------------------------------------------
-// the threshold of a block's keys
-// ---------------------------------------------------------------------------------------------
-// The rem-th largest of the non-zero keys, which lie in [lo, hi]: kept are the keys above the threshold that is returned, and the
-// first `rem` (as it is left) of those equal to it.  Each step spreads what is left of the range over kBins bins, finds the bin
-// with that key and goes on inside it; it ends when the bin is one key wide or all of it is kept (no key equal to the threshold is, then).
-// The bins divide the range in which the keys lie: gating scores share a few exponents, and counted by fixed digits, most lanes of
-// a wave meet in one counter (us against four passes of eight bits: 64 segments of 65536 drawn ranks 34 -> 25, the whole drop by score
-// 90 -> 65; 1024 segments of 2048 keys 12.3 -> 9.3; the whole drop of 4096 tokens, 64 experts, all scores equal 30 -> 16).
-// walk(f) calls f(key) for every key of the calling thread; hist: kBins words of LDS, zero; sh: three.  Called by the whole block after a barrier.
-template <int NT>
-constexpr int kSelectBins = NT >= 1024 ? 2048 : 1024;
-template <int NT, class Walk>
-__device__ __forceinline__ uint32_t select_threshold(uint32_t lo, uint32_t hi, int& rem, int* hist, int* red, int* sh, Walk&& walk) {
-    constexpr int kBins = kSelectBins<NT>, kPer = kBins / NT;
-    const int tid = threadIdx.x;
-    for (;;) {
-        const uint32_t range = hi - lo;
-        if (range == 0u) return lo;
-        const int width = 32 - __clz(range), shift = width > __builtin_ctz(kBins) ? width - __builtin_ctz(kBins) : 0;
-        walk([&](uint32_t key) __attribute__((always_inline)) {
-            if (key - lo <= range) atomicAdd(&hist[(key - lo) >> shift], 1);  // (below lo wraps around; key 0 is below)
-        });
-        __syncthreads();
-        // thread i owns the bins from kBins - 1 - kPer * i downwards: a scan over the threads counts the keys of higher bins
-        int h[kPer], sum = 0, total;
-#pragma unroll
-        for (int j = 0; j < kPer; ++j) {
-            h[j] = hist[kBins - 1 - (tid * kPer + j)];
-            sum += h[j];
-        }
-        int above = block_exclusive_scan<NT>(sum, red, &total);
-#pragma unroll
-        for (int j = 0; j < kPer; ++j) {
-            if (above < rem && above + h[j] >= rem) {  // exactly one bin of one thread
-                sh[0] = kBins - 1 - (tid * kPer + j);
-                sh[1] = rem - above;
-                sh[2] = h[j];
-            }
-            above += h[j];
-            hist[kBins - 1 - (tid * kPer + j)] = 0;
-        }
-        __syncthreads();
-        lo += (uint32_t)sh[0] << shift;
-        rem = sh[1];
-        const bool all = sh[2] == rem;
-        if (shift == 0) return lo;
-        if (all) {
-            rem = 0;
-            return lo - 1u;
-        }
-        const uint32_t top = lo + ((1u << shift) - 1u);
-        hi = hi < top ? hi : top;
     }
 }
 

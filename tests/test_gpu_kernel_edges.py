@@ -165,6 +165,93 @@ def test_drop_threshold_of_key_ranges(n, groups, scope, width):
     assert np.array_equal(out["pair_row"].cpu().numpy() >= 0, keep)
 
 
+def _keys_of_pairs(scores, lists, metric, classes, seed, seg_tokens):
+    """(candidates [N,E], keys [N,E]) as the drop defines them: rank + 1 above the class's two bits, in 32-bit words; 0 without."""
+    n, e = scores.shape
+    token, expert = np.meshgrid(np.arange(n, dtype=np.uint32), np.arange(e, dtype=np.uint32), indexing="ij")
+    if metric == capmoe.METRIC_SCORE:
+        rank = scores.view(np.uint32)
+    elif metric == capmoe.METRIC_RANDOM:
+        x = token * np.uint32(e) + expert + np.uint32(seed * 0x9E3779B9 & 0xFFFFFFFF)
+        for shift, factor in ((16, 0x7FEB352D), (15, 0x846CA68B)):
+            x = (x ^ (x >> np.uint32(shift))) * np.uint32(factor)
+        rank = (x ^ (x >> np.uint32(16))) >> np.uint32(3)
+    else:
+        local = token % np.uint32(seg_tokens)
+        rank = np.uint32(seg_tokens - 1) - local if metric == capmoe.METRIC_ORDER else local
+    cand = np.zeros((n, e), bool)
+    np.put_along_axis(cand, lists, True, axis=1)
+    cls = np.zeros(n, np.uint32) if classes is None else classes.astype(np.uint32)
+    return cand, np.where(cand, rank + (cls << np.uint32(30))[:, None] + np.uint32(1), np.uint32(0))
+
+
+def _drop_against_sort(n, e, k, groups, scope, gamma, scores, lists, metric=0, classes=None, seed=3):
+    """Token Drop of given scores and lists: the whole plan against a sort of (key, token, expert), word for word."""
+    desc = capmoe.make_desc(n, 4, e, k, 8, groups, capmoe.MODE_TOKEN_DROP, scope, gamma, capmoe.DTYPE_F32, metric)
+    cap, slots, rows, workspace = capmoe.moe_query(desc)
+    blocks = groups if scope in (capmoe.SCOPE_LOCAL, capmoe.SCOPE_LOCAL_DEVICE) else 1
+    span = e // groups if scope in (capmoe.SCOPE_LOCAL_DEVICE, capmoe.SCOPE_GLOBAL_DEVICE) else 1
+    per = n // blocks
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    out = {name: torch.full(shape, -7, dtype=dt, device="cuda") for name, shape, dt in (
+        ("expert_count", (e,), torch.int32), ("seg_count", (blocks, e), torch.int32), ("expert_offset", (e + 1,), torch.int32),
+        ("row_token", (rows,), torch.int32), ("row_weight", (rows,), torch.float32), ("pair_row", (n, slots), torch.int32))}
+    ws = torch.empty(max(workspace, 256), dtype=torch.uint8, device="cuda")
+    capmoe.moe_capacity_drop_ranked(desc, dev(scores), dev(lists.astype(np.int32)), None if classes is None else dev(classes), seed,
+                                    out["expert_count"], out["seg_count"], out["expert_offset"], out["row_token"], out["row_weight"],
+                                    out["pair_row"], ws)
+    torch.cuda.synchronize()
+    cand, keys = _keys_of_pairs(scores, lists, metric, classes, seed, per)
+    keep = np.zeros((n, e), bool)
+    token, expert = np.meshgrid(np.arange(n), np.arange(e), indexing="ij")
+    for b in range(blocks):
+        for g in range(e // span):
+            part = (slice(b * per, (b + 1) * per), slice(g * span, (g + 1) * span))
+            t, x = token[part].ravel(), expert[part].ravel()
+            t, x = t[cand[t, x]], x[cand[t, x]]
+            best = np.lexsort((x, t, -keys[t, x].astype(np.int64)))[:cap]   # larger key, then lower token, then lower expert
+            keep[t[best], x[best]] = True
+    row_expert, row_token = np.nonzero(keep.T)                # rows are expert-major, ascending token
+    pair_row = np.full((n, slots), -1, np.int64)
+    pair_row[row_token, (np.cumsum(cand, axis=1) - 1)[row_token, row_expert]] = np.arange(len(row_token))
+    got = {name: a.cpu().numpy() for name, a in out.items()}
+    np.testing.assert_array_equal(got["expert_count"], keep.sum(axis=0))
+    np.testing.assert_array_equal(got["expert_offset"], np.concatenate([[0], np.cumsum(keep.sum(axis=0))]))
+    np.testing.assert_array_equal(got["seg_count"], keep.reshape(blocks, per, e).sum(axis=1))
+    np.testing.assert_array_equal(got["row_token"][: len(row_token)], row_token)
+    np.testing.assert_array_equal(got["row_weight"][: len(row_token)].view(np.uint32), scores.view(np.uint32)[row_token, row_expert])
+    np.testing.assert_array_equal(got["pair_row"], pair_row)
+    assert (got["row_token"][len(row_token):] == -7).all() and (got["row_weight"][len(row_token):] == -7).all()
+
+
+# a segment of a wave, of 256 and of 1024 threads in one launch; selected by 256 threads (by four, at odd addresses), by 1024, from L2
+# and by many blocks; one expert, and several under one budget
+FORMS = [(100, 1, 0), (300, 1, 0), (3000, 1, 0), (500, 1, 3), (1000, 1, 3), (999, 1, 3), (2001, 1, 3), (4096, 1, 3), (4099, 1, 3),
+         (12003, 1, 0), (16384, 1, 0), (32771, 1, 0), (65544, 1, 0), (65544, 2, 2)]
+
+
+def _lists(rng, n, e, k):
+    return np.sort(np.argsort(rng.random((n, e)), axis=1)[:, :k], axis=1)
+
+
+@pytest.mark.parametrize("n,groups,scope", FORMS)
+@pytest.mark.parametrize("bits,cls", [(0x7fc00000, 2), (0xffc00000, 0), (0xffe00000, 0), (0xfff00000, 0)])
+def test_drop_of_scores_that_are_no_numbers(n, groups, scope, bits, cls):
+    """More tokens without numbers than the capacity keeps, at the top of the 32-bit keys, above lower classes with scores of zero."""
+    n -= n % groups
+    e, k = 4, 2
+    rng = np.random.default_rng(n + cls)
+    scores = rng.random((n, e)).astype(np.float32)
+    scores[rng.random(n) < 0.3] = 0.0
+    classes = rng.integers(0, 2, n).astype(np.uint8) if cls else None
+    broken = rng.random(n) < 0.3
+    scores.view(np.uint32)[broken] = bits
+    if cls:
+        classes[broken] = cls
+    for gamma in (0.3, 0.8):
+        _drop_against_sort(n, e, k, groups, scope, gamma, scores, _lists(rng, n, e, k), classes=classes)
+
+
 # ------------------------------------------------------------------------------------------------
 # the drop of a few tokens: a wave's lanes and halves filled, short by one and exceeded, the limits of its rule on both sides, blocks
 # with fewer segments than waves; through the one call that also builds the tile schedule, against the oracle's plan
