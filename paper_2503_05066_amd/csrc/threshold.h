@@ -11,6 +11,7 @@ __device__ inline int block_exclusive_scan(int v, int* red, int* total);  // of 
 // The rem-th largest of the non-zero keys, which lie in [lo, hi]: kept are the keys above the threshold that is returned, and the
 // first `rem` (as it is left) of those equal to it.  Each step spreads what is left of the range over BINS bins, finds the bin
 // with that key and goes on inside it; it ends when the bin is one key wide or all of it is kept (no key equal to the threshold is, then).
+// It ends after four steps at most whatever the keys are: with fewer than `rem` of them (a caller's list that names an expert twice) all are kept.
 // The bins divide the range in which the keys lie: gating scores share a few exponents, and counted by fixed digits, most lanes of
 // a wave meet in one counter (us against four passes of eight bits: 64 segments of 65536 drawn ranks 34 -> 25, the whole drop by score
 // 90 -> 65; 1024 segments of 2048 keys 12.3 -> 9.3; the whole drop of 4096 tokens, 64 experts, all scores equal 30 -> 16).
@@ -22,8 +23,8 @@ __device__ __forceinline__ uint32_t select_threshold(uint32_t lo, uint32_t hi, i
     constexpr int kPer = BINS / NT;
     const int tid = threadIdx.x;
     for (;;) {
+        if (lo >= hi) return lo;  // one key is left (or there is none at all)
         const uint32_t range = hi - lo;
-        if (range == 0u) return lo;
         const int width = 32 - __clz(range), shift = width > __builtin_ctz(BINS) ? width - __builtin_ctz(BINS) : 0;
         walk([&](uint32_t key) __attribute__((always_inline)) {
             if (key - lo <= range) atomicAdd(&hist[(key - lo) >> shift], 1);  // (below lo wraps around; key 0 is below)
@@ -37,6 +38,10 @@ __device__ __forceinline__ uint32_t select_threshold(uint32_t lo, uint32_t hi, i
             sum += h[j];
         }
         int above = block_exclusive_scan<NT>(sum, red, &total);
+        if (total < rem) {  // fewer keys than that: they are all kept
+            rem = 0;
+            return lo - 1u;
+        }
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
             if (above < rem && above + h[j] >= rem) {  // exactly one bin of one thread

@@ -35,7 +35,7 @@ static void run(std::vector<uint32_t>& keys, int rem) {
     for (uint32_t k : keys)
         if (k) { lo = k < lo ? k : lo; hi = k > hi ? k : hi; }
     counters.assign(BINS, 0);
-    int sh[3] = {0, 0, 0};
+    int sh[3] = {BINS - 1, 1, 2};  // what LDS held before
     uint32_t tau = capmoe::select_threshold<1, BINS>(lo, hi, rem, counters.data(), nullptr, sh, [&](auto&& f) { for (uint32_t k : keys) f(k); });
     printf("%u %d\n", tau, rem);
 }
@@ -77,6 +77,7 @@ def _check(search, keys, cap):
     keys = np.asarray(keys, np.uint32)
     want = np.zeros(len(keys), bool)
     want[np.lexsort((np.arange(len(keys)), -keys.astype(np.int64)))[:cap]] = True
+    want &= keys != 0
     for bins in (1024, 2048):
         np.testing.assert_array_equal(_kept(keys, *search(keys, cap, bins)), want, err_msg=f"{bins} bins, capacity {cap}")
 
@@ -101,3 +102,12 @@ def test_threshold_in_the_last_bin_of_the_word(search, top):
     rng.shuffle(keys)
     for cap in (1, 8, 19, 20, 21, 52):
         _check(search, keys, cap)
+
+
+@pytest.mark.parametrize("keys", [[0, 0, 0], [5], [7, 0, 7, 7], [1, 0, 0x3f800001], [0xffffffff, 3, 0, 9, 9],
+                                  list(range(0x3d000001, 0x3d000001 + 50 * 4096, 4096))])
+def test_fewer_keys_than_the_capacity(search, keys):
+    """Lists that name an expert twice count more candidates than there are keys: the search ends, and keeps them all."""
+    keys = np.asarray(keys, np.uint32)
+    for more in (1, 2, 1000):
+        _check(search, keys, int((keys > 0).sum()) + more)
