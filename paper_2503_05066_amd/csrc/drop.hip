@@ -987,6 +987,8 @@ constexpr int kFusedMaxTokens = 8 * kFusedThreads;  // tokens of a segment: its 
 constexpr int kFusedMaxSegs = 2048;    // capacity segments (one candidate counter each)
 constexpr int kFusedCounters = 4096;   // counters in LDS: as many private copies of the segment counters as fit
 constexpr long long kFusedMaxWork = 8ll << 20;  // segments x top-k list entries: above it, three launches are cheaper
+constexpr int kFusedBins = 1024;       // counters of the threshold search
+static_assert(kFusedBins <= kFusedCounters && kFusedBins % kFusedThreads == 0, "they may lie in the candidate counters' place");
 
 // exclusive prefix sum of v over the block's NT threads; *total gets the block sum
 template <int NT>
@@ -1034,7 +1036,12 @@ __global__ __launch_bounds__(NT) void drop_fused_kernel(
     __shared__ uint32_t key_s[kMaxTok + kMaxTok / 16];
     __shared__ uint8_t slot_s[kMaxTok];
     __shared__ int cand[kFusedCounters];
-    __shared__ int hist[kSelectBins<NT>];
+    // The counters of the threshold search.  A small block, of which a compute unit holds several, has them in the place of the candidate
+    // counters, which are done with by then (its LDS decides how many: with 33 KB four fit, with 29 five; 500 tokens, 240 experts
+    // on 5 devices 18.1 and 14.0 us); a large one in a place of their own, that is cleared ahead of time.
+    constexpr bool kOwnBins = NT >= kFusedBins;
+    __shared__ int bins[kOwnBins ? kFusedBins : 1];
+    int* hist = kOwnBins ? bins : cand;
     __shared__ int red[kWaves], sh_bin[3];
     __shared__ uint32_t red5[kWaves][5];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -1050,7 +1057,8 @@ __global__ __launch_bounds__(NT) void drop_fused_kernel(
     auto pad = [](int i) { return i + (i >> 4); };
 
     for (int i = tid; i < copies * pitch; i += NT) cand[i] = 0;
-    for (int i = tid; i < kSelectBins<NT>; i += NT) hist[i] = 0;
+    if (kOwnBins)
+        for (int i = tid; i < kFusedBins; i += NT) hist[i] = 0;
     if (scheduler)
         for (int i = tid; i < kMaxExperts; i += NT) sched_tot[i] = 0;
     __syncthreads();
@@ -1232,7 +1240,11 @@ __global__ __launch_bounds__(NT) void drop_fused_kernel(
         tau = 0xffffffffu;  // nothing passes
     } else if (n_cand > cap) {
         need = cap;
-        tau = select_threshold<NT>(key_lo, key_hi, need, hist, red, sh_bin, [&](auto&& f) __attribute__((always_inline)) {
+        if (!kOwnBins) {
+            for (int i = tid; i < kFusedBins; i += NT) hist[i] = 0;
+            __syncthreads();
+        }
+        tau = select_threshold<NT, kFusedBins>(key_lo, key_hi, need, hist, red, sh_bin, [&](auto&& f) __attribute__((always_inline)) {
             for (int tl = tid; tl < seg_tokens; tl += NT) f(key_s[pad(tl)]);
         });
     }
