@@ -71,6 +71,7 @@ DropWorkspace drop_workspace(const moe_desc_t& d, const Sizes& s, void* base) {
     size_t off = 0;
     const size_t ne = (size_t)d.n_tokens * d.n_experts;
     const size_t segs = (size_t)s.n_blocks * d.n_experts;
+    // (drop_emit_kernel may fetch up to 60 bytes past the keys and 19 past the slots: what follows either is at least 256 bytes long)
     w.key_t = (uint32_t*)(p + off);
     off += align256(ne * 4);
     w.slot_t = (uint8_t*)(p + off);

@@ -651,8 +651,10 @@ constexpr int kEmitChunk = 256 * kEmitRun;  // tokens per pass of the block
 // everything it reads is requested in one batch, the gating scores of the kept pairs in a second.  Against keys and slots staged
 // through LDS a word and a byte at a time: 65536 tokens, 64 experts 36 -> 29 us, ranked by score 35 -> 25; 16384, 128 experts
 // (2048 tokens a segment) 24.9 -> 21.7.
-// VEC: runs start on 16-byte boundaries of keys and slots (N and seg_tokens are multiples of 16)
-template <bool VEC>
+// A run may start at any word of the keys and any byte of the slots and is fetched in pieces of 16 bytes all the same (24001 tokens, 250
+// experts without a capacity: the whole drop 75 us by words and bytes, 57 now; 250 experts on 25 devices, 4 tokens a segment, 73 and 63).
+// ALIGNED: runs start on 16-byte boundaries of keys and slots (N and seg_tokens are multiples of 16).
+template <bool ALIGNED>
 __global__ __launch_bounds__(256) void drop_emit_kernel(const float* __restrict__ scores,
                                                         const uint32_t* __restrict__ key_t,
                                                         const uint8_t* __restrict__ slot_t,
@@ -705,20 +707,28 @@ __global__ __launch_bounds__(256) void drop_emit_kernel(const float* __restrict_
     // ---- requested together: this run's keys and slots, threshold, the counts before it ----
     const uint32_t tau = seg_tau[seg];
     const int need = seg_need[seg];
+    // (a thread without a run fetches the first one; a run that is cut short by the segment's end is fetched whole: what follows either
+    // array in the workspace is longer than a run)
+    const int at = c0 + (i0 < n ? i0 : 0);
     uint32_t kx[kEmitRun];
     uint8_t sx[kEmitRun];
-    if (VEC) {  // n is a multiple of 16: a run is whole or past the end
-        const int at = c0 + (i0 < n ? i0 : 0);
+    if (ALIGNED) {
 #pragma unroll
         for (int j = 0; j < kEmitRun / 4; ++j) *(uint4*)&kx[4 * j] = *(const uint4*)(keys + at + 4 * j);
         *(uint4*)sx = *(const uint4*)(slots + at);
     } else {
+        struct alignas(4) Words {
+            uint32_t w[4];
+        };
 #pragma unroll
-        for (int j = 0; j < kEmitRun; ++j) {
-            const int at = c0 + (i0 + j < n ? i0 + j : n - 1);
-            kx[j] = keys[at];
-            sx[j] = slots[at];
-        }
+        for (int j = 0; j < kEmitRun / 4; ++j) *(Words*)&kx[4 * j] = *(const Words*)(keys + at + 4 * j);
+        const uint32_t odd = (uint32_t)(uintptr_t)(slots + at) & 3u;  // bytes past a word
+        const uint32_t* words = (const uint32_t*)(slots + at - odd);
+        uint32_t raw[kEmitRun / 4 + 1];
+        *(Words*)raw = *(const Words*)words;
+        raw[kEmitRun / 4] = words[kEmitRun / 4];
+#pragma unroll
+        for (int j = 0; j < kEmitRun / 4; ++j) *(uint32_t*)&sx[4 * j] = __builtin_amdgcn_alignbyte(raw[j + 1], raw[j], odd);
     }
     // first row of this segment: all segments of lower experts, then lower blocks of this expert
     int before = 0, own = 0;
