@@ -1455,12 +1455,12 @@ __global__ __launch_bounds__(256) void drop_small_kernel(
             for (int u = 0; u < 8; ++u) {
                 const int j = j0 + u;
                 const uint32_t low = __builtin_amdgcn_readlane(key[0], j);
-                ahead[0] += low >= key[0] + (j < lane ? 0u : 1u);  // a lower token is ahead with an equal key
+                ahead[0] += low > key[0] - (j < lane ? 1u : 0u);  // a lower token is ahead with an equal key (a candidate's is at least 1)
                 if (HALVES > 1) {
                     const uint32_t high = __builtin_amdgcn_readlane(key[HALVES - 1], j);
-                    ahead[0] += high >= key[0] + 1u;
+                    ahead[0] += high > key[0];
                     ahead[HALVES - 1] += low >= key[HALVES - 1];
-                    ahead[HALVES - 1] += high >= key[HALVES - 1] + (j < lane ? 0u : 1u);
+                    ahead[HALVES - 1] += high > key[HALVES - 1] - (j < lane ? 1u : 0u);
                 }
             }
         }

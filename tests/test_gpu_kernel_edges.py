@@ -226,7 +226,7 @@ def _drop_against_sort(n, e, k, groups, scope, gamma, scores, lists, metric=0, c
 
 # a segment of a wave, of 256 and of 1024 threads in one launch; selected by 256 threads (by four, at odd addresses), by 1024, from L2
 # and by many blocks; one expert, and several under one budget
-FORMS = [(100, 1, 0), (300, 1, 0), (3000, 1, 0), (500, 1, 3), (1000, 1, 3), (999, 1, 3), (2001, 1, 3), (4096, 1, 3), (4099, 1, 3),
+FORMS = [(40, 1, 0), (100, 1, 0), (300, 1, 0), (3000, 1, 0), (500, 1, 3), (1000, 1, 3), (999, 1, 3), (2001, 1, 3), (4096, 1, 3), (4099, 1, 3),
          (12003, 1, 0), (16384, 1, 0), (32771, 1, 0), (65544, 1, 0), (65544, 2, 2)]
 
 
@@ -235,7 +235,7 @@ def _lists(rng, n, e, k):
 
 
 @pytest.mark.parametrize("n,groups,scope", FORMS)
-@pytest.mark.parametrize("bits,cls", [(0x7fc00000, 2), (0xffc00000, 0), (0xffe00000, 0), (0xfff00000, 0)])
+@pytest.mark.parametrize("bits,cls", [(0x7fc00000, 2), (0xffc00000, 0), (0xffe00000, 0), (0xfff00000, 0), (0xfffffffe, 0)])
 def test_drop_of_scores_that_are_no_numbers(n, groups, scope, bits, cls):
     """More tokens without numbers than the capacity keeps, at the top of the 32-bit keys, above lower classes with scores of zero."""
     n -= n % groups
