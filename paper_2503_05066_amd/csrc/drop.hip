@@ -1300,17 +1300,20 @@ __global__ __launch_bounds__(NT) void drop_fused_kernel(
 // ---------------------------------------------------------------------------------------------
 // 6. the same for a few tokens: a wave per segment
 // ---------------------------------------------------------------------------------------------
-// Decoding steps: segments of at most 128 tokens.  What bounds them is the chain of steps, each a barrier or a latency of the
-// kernel above; here a wave holds its segment (lane l the tokens l and l + 64), ranks its keys against each other
+// Decoding steps: segments of at most 64 tokens.  What bounds them is the chain of steps, each a barrier or a latency of the
+// kernel above; here a wave holds its segment (a token per lane), ranks its keys against each other
 // instead of looking for a threshold, and the only thing the waves of a block share is the number of candidates of every segment.
 // us, alone: 1 token, 64 experts 6.8 -> 4.4; 16 tokens, 8 experts 8.8 -> 3.7; 37, 64 experts 9.1 -> 5.6; 256 on 8 devices, Expanded
-// Drop 12.3 -> 7.7; 128 tokens, 8 experts 8.8 -> 7.9.
-constexpr int kSmallSegTokens = 128;
-constexpr int kSmallTokens = 512;  // of the batch: every block reads all lists
+// Drop 12.3 -> 7.7.
+constexpr int kSmallSegTokens = kWave;
 constexpr int kSmallSegs = 1024;
+// What it costs is reading lists: its own tokens', each lane a list, and all of them, four entries a thread at a time; the kernel above
+// reads vectors, a thread per token and round.  The two times meet where k * (5 * seg_tokens + 2 * N) is about 12 288 (against the
+// kernel above, 64 experts: 64 tokens with lists of 16 0.82, of 32 1.02, of 64 1.26; 256 on 4 devices of 8 0.81, of 16 0.98, of 32
+// 1.26; 512 on 8 of 8 0.88, of 16 1.10, of 64 2.5).  Two tokens per lane, for up to 128 in a segment, took 0.9 to 2.6 of its time.
+constexpr int kSmallWork = 12288;
 
-// HALVES: tokens of a lane
-template <bool EXPANDED, int HALVES>
+template <bool EXPANDED>
 __global__ __launch_bounds__(256) void drop_small_kernel(
     const float* __restrict__ scores, const int32_t* __restrict__ topk_idx, const uint8_t* __restrict__ token_class,
     uint32_t seed, int32_t* __restrict__ expert_count, int32_t* __restrict__ seg_count,
@@ -1331,17 +1334,15 @@ __global__ __launch_bounds__(256) void drop_small_kernel(
 
     // ---- this segment's scores and lists: listed experts below e and in all, e itself (under Expanded Drop without the experts of the
     // token's own device, which are candidates anyway) ----
-    uint32_t bits[HALVES], key[HALVES];
-    int below[HALVES], listed[HALVES];
-#pragma unroll
-    for (int q = 0; q < HALVES; ++q) {
-        const int tl = lane + 64 * q, t = b * seg_tokens + tl;
-        const bool live = mine && tl < seg_tokens;
-        const size_t row = live ? t : 0;  // past the segment: the first token's, not used
-        bits[q] = __float_as_uint(scores[row * E + e]);
+    const int t = b * seg_tokens + lane;
+    const bool live = mine && lane < seg_tokens;
+    const size_t row = live ? t : 0;  // past the segment: the first token's, not used
+    const uint32_t bits = __float_as_uint(scores[row * E + e]);
+    uint32_t key;
+    int below = 0, listed = 0;
+    {
         const uint32_t cls = token_class ? (uint32_t)(token_class[row] & 3) << 30 : 0u;
         const int dev = EXPANDED ? t / group_tokens : 0, g0 = dev * group_experts;
-        below[q] = listed[q] = 0;
         bool cnd = EXPANDED && e >= g0 && e < g0 + group_experts;
         const int32_t* list = topk_idx + row * k;
         for (int j0 = 0; j0 < k; j0 += 8) {
@@ -1351,27 +1352,27 @@ __global__ __launch_bounds__(256) void drop_small_kernel(
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 const bool counts = j0 + u < k && (!EXPANDED || x[u] < g0 || x[u] >= g0 + group_experts);
-                listed[q] += counts;
-                below[q] += counts && x[u] < e;
+                listed += counts;
+                below += counts && x[u] < e;
                 cnd = cnd || (counts && x[u] == e);
             }
         }
         if (EXPANDED) {
             const int lower = e - g0;  // experts of the token's device below e
-            below[q] += lower < 0 ? 0 : (lower > group_experts ? group_experts : lower);
+            below += lower < 0 ? 0 : (lower > group_experts ? group_experts : lower);
         }
         uint32_t rank;
         if (metric == MOE_METRIC_ORDER)
-            rank = (uint32_t)(seg_tokens - 1 - tl);
+            rank = (uint32_t)(seg_tokens - 1 - lane);
         else if (metric == MOE_METRIC_REVERSE_ORDER)
-            rank = (uint32_t)tl;
+            rank = (uint32_t)lane;
         else if (metric == MOE_METRIC_RANDOM)
             rank = pair_hash(seed, (uint32_t)t * (uint32_t)E + (uint32_t)e) >> 3;
         else
-            rank = bits[q];
-        key[q] = live && cnd ? rank + cls + 1u : 0u;
+            rank = bits;
+        key = live && cnd ? rank + cls + 1u : 0u;
         if (live && e == 0) {  // slots beyond the token's candidate count stay unused
-            const int n_c = listed[q] + (EXPANDED ? group_experts : 0);
+            const int n_c = listed + (EXPANDED ? group_experts : 0);
             for (int sl = n_c; sl < S; ++sl) pair_row[(size_t)t * S + sl] = -1;
         }
     }
@@ -1432,9 +1433,7 @@ __global__ __launch_bounds__(256) void drop_small_kernel(
         before += __shfl_xor(before, off, kWave);
         own_total += __shfl_xor(own_total, off, kWave);
     }
-    int n_cand = 0;
-#pragma unroll
-    for (int q = 0; q < HALVES; ++q) n_cand += __popcll(__ballot(key[q] != 0u));
+    const int n_cand = __popcll(__ballot(key != 0u));
     if (lane == 0) {
         seg_count[seg] = n_cand < cap ? n_cand : cap;
         if (b == 0) {
@@ -1445,40 +1444,24 @@ __global__ __launch_bounds__(256) void drop_small_kernel(
     }
 
     // ---- a pair stays if fewer than cap pairs are ahead of it: larger keys, and equal keys of lower tokens ----
-    int ahead[HALVES];
-#pragma unroll
-    for (int q = 0; q < HALVES; ++q) ahead[q] = 0;
+    int ahead = 0;
     if (n_cand > cap) {
-        const int lanes = seg_tokens < kWave ? seg_tokens : kWave;
-        for (int j0 = 0; j0 < lanes; j0 += 8) {  // (past the segment keys are 0: ahead of no candidate)
+        for (int j0 = 0; j0 < seg_tokens; j0 += 8) {  // (past the segment keys are 0: ahead of no candidate)
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                const int j = j0 + u;
-                const uint32_t low = __builtin_amdgcn_readlane(key[0], j);
-                ahead[0] += low > key[0] - (j < lane ? 1u : 0u);  // a lower token is ahead with an equal key (a candidate's is at least 1)
-                if (HALVES > 1) {
-                    const uint32_t high = __builtin_amdgcn_readlane(key[HALVES - 1], j);
-                    ahead[0] += high > key[0];
-                    ahead[HALVES - 1] += low >= key[HALVES - 1];
-                    ahead[HALVES - 1] += high > key[HALVES - 1] - (j < lane ? 1u : 0u);
-                }
+                const uint32_t other = __builtin_amdgcn_readlane(key, j0 + u);
+                ahead += other > key - (j0 + u < lane ? 1u : 0u);  // (a candidate's key is at least 1)
             }
         }
     }
-    const uint64_t lower = (1ull << lane) - 1ull;
-    int base = before;
-#pragma unroll
-    for (int q = 0; q < HALVES; ++q) {
-        const bool keep = key[q] != 0u && (n_cand <= cap || ahead[q] < cap);
-        const uint64_t mask = __ballot(keep);
-        const int pos = base + __popcll(mask & lower), t = b * seg_tokens + lane + 64 * q;
-        base += __popcll(mask);
-        if (keep) {
-            row_token[pos] = t;
-            row_weight[pos] = __uint_as_float(bits[q]);  // the gating score, whatever ranked the pair
-        }
-        if (key[q] != 0u) pair_row[(size_t)t * S + below[q]] = keep ? pos : -1;
+    const bool keep = key != 0u && (n_cand <= cap || ahead < cap);
+    const uint64_t mask = __ballot(keep);
+    const int pos = before + __popcll(mask & ((1ull << lane) - 1ull));
+    if (keep) {
+        row_token[pos] = t;
+        row_weight[pos] = __uint_as_float(bits);  // the gating score, whatever ranked the pair
     }
+    if (key != 0u) pair_row[(size_t)t * S + below] = keep ? pos : -1;
 }
 
 // The plan of a batch without tokens: every count is zero.
@@ -1536,21 +1519,13 @@ hipError_t launch_capacity_drop(const moe_desc_t& d, const Sizes& s, const DropW
         const bool fused = s.span == 1 && !(d.max_experts && s.slots > d.top_k) &&
                            s.seg_tokens <= kFusedMaxTokens && segs_all + 1 <= kFusedCounters &&
                            segs_all <= kFusedMaxSegs && (long long)segs_all * N * s.list_k <= kFusedMaxWork;
-        // (every block reads all lists and a wave ranks by comparing all pairs: hence the limits; 129 to 512 tokens of one segment and
-        // longer batches stay with the kernel below)
-        if (fused && s.seg_tokens <= kSmallSegTokens && N <= kSmallTokens && segs_all <= kSmallSegs) {
-            auto launch = [&](auto kern) {
-                ProfileScope prof(MOE_KERNEL_DROP_SELECT, st);
-                hipLaunchKernelGGL(kern, dim3((segs_all + 3) / 4 + (sched.enabled ? 1 : 0)), dim3(256), 0, st, scores, topk_idx,
-                                   token_class, seed, expert_count, seg_count, expert_offset, row_token, row_weight, pair_row, N, E,
-                                   s.list_k, s.slots, s.group_tokens, s.group_experts, d.metric, s.seg_tokens, s.n_blocks, s.cap,
-                                   sched);
-            };
-            const bool ex = d.mode == MOE_MODE_EXPANDED_DROP;
-            if (s.seg_tokens <= kWave)
-                launch(ex ? drop_small_kernel<true, 1> : drop_small_kernel<false, 1>);
-            else
-                launch(ex ? drop_small_kernel<true, 2> : drop_small_kernel<false, 2>);
+        if (fused && s.seg_tokens <= kSmallSegTokens && segs_all <= kSmallSegs &&
+            (long long)s.list_k * (5 * s.seg_tokens + 2ll * N) <= kSmallWork) {
+            ProfileScope prof(MOE_KERNEL_DROP_SELECT, st);
+            auto kern = d.mode == MOE_MODE_EXPANDED_DROP ? drop_small_kernel<true> : drop_small_kernel<false>;
+            hipLaunchKernelGGL(kern, dim3((segs_all + 3) / 4 + (sched.enabled ? 1 : 0)), dim3(256), 0, st, scores, topk_idx,
+                               token_class, seed, expert_count, seg_count, expert_offset, row_token, row_weight, pair_row, N, E,
+                               s.list_k, s.slots, s.group_tokens, s.group_experts, d.metric, s.seg_tokens, s.n_blocks, s.cap, sched);
             return hipGetLastError();
         }
         if (fused) {
