@@ -643,15 +643,31 @@ static void launch_quad(float* logits, const float* partial, int ksplit, const f
                        topk_idx, topk_score, N, E, k);
 }
 
+// The tokens from which four lanes per token beat a wave per token, which is many rounds of waves by then; below, its shorter chain
+// wins.  us, wave -> four lanes: 64 experts top-8 12288 tokens 8.8 -> 7.5, 16384 11.7 -> 8.4, 65536 37.5 -> 15.5; 128 top-8 12288 13.9 -> 11.9;
+// 8 top-2 8192 1.2 times as fast, 12288 6.8 -> 4.4.  Quads that are not full walk the entries past E too (36 experts 1.0 to 1.08 of the
+// wave's time at 12288, 0.95 to 1.05 at 14336, 0.8 to 0.9 at 16384; 160 1.05 to 1.25, 0.9 to 1.1, 0.65 to 1.0: the more the shorter
+// the list).  Rows of experts that four does not divide are loaded by elements: 61 experts 1.06 to 1.15 at 12288, 0.85 to 0.95 at 16384;
+// 127 top-8 1.25, 1.00, 0.88 at 24576; above 128 the registers hold one wave per SIMD: 255 top-8 1.28 at 24576, 1.23 at 65536, only long
+// lists gain (top-33 1.02 at 40000, 0.90).  Every entry of a long list is ranked against all of it by the quad alone: 64 top-64 1.05 at
+// 16384, 1.10 at 20480, 0.93 at 24576.
+static int quad_tokens(int E, int k) {
+    if (E % 4 != 0) {
+        if (E <= 32) return 12288;
+        if (E <= 64) return k <= 32 ? 16384 : 24576;
+        if (E <= 128) return k < 16 ? 24576 : 16384;
+        return k <= 16 ? INT_MAX : 32768;
+    }
+    if (E <= 64 && k > 32) return k > 48 ? 24576 : 16384;
+    if (E <= 32 || E == 64 || E == 128) return 12288;
+    return k <= 2 ? 16384 : (E > 64 && k >= 16 ? 12288 : 14336);
+}
+
 hipError_t launch_softmax_topk(const moe_desc_t& d, float* logits, const float* partial, int ksplit, const float* bias,
                                float* scores, int32_t* topk_idx, float* topk_score, hipStream_t st) {
     ProfileScope prof(MOE_KERNEL_SOFTMAX_TOPK, st);
     const int N = d.n_tokens, E = d.n_experts, k = d.top_k + d.overselect;
-    // Four lanes per token from where a wave per token is many rounds of waves: below, the shorter chain of the wave per token
-    // wins (us, wave -> quad, 64 experts top-8: 8192 tokens 7.3 -> 7.6, 12288 9.2 -> 8.0, 16384 11.7 -> 8.4, 65536 37.5 -> 15.5;
-    // 128 top-8: 8192 10.6 -> 11.6, 12288 13.7 -> 11.6; 8 top-2: 4096 4.3 -> 4.6, 12288 7.4 -> 5.1; 64 top-64: 16384 17.3 -> 18.7,
-    // 32768 30.8 -> 23.3).
-    if (N >= (k <= 32 ? 12288 : 20480)) {
+    if (N >= quad_tokens(E, k)) {
         if (E <= 16)
             launch_quad<1>(logits, partial, ksplit, bias, scores, topk_idx, topk_score, N, E, k, st);
         else if (E <= 32)

@@ -72,7 +72,11 @@ def _assert_same_as_short_batches(logits, k, out):
 
 @pytest.mark.parametrize("n,e,k", [(12288, 1, 1), (12289, 8, 2), (12300, 16, 16), (12351, 17, 3), (12288, 30, 6), (12288, 32, 32),
                                    (20480, 33, 33), (12290, 60, 4), (12288, 61, 7), (12291, 64, 8), (20481, 64, 64),
-                                   (12288, 100, 5), (12288, 128, 8), (12288, 130, 9), (20480, 256, 64), (12289, 255, 1)])
+                                   (12288, 100, 5), (12288, 128, 8), (12288, 130, 9), (20480, 256, 64), (12289, 255, 1),
+                                   # where the rule goes over to four lanes, by experts and list length
+                                   (12287, 31, 4), (16383, 61, 7), (16384, 61, 7), (24576, 33, 33), (14335, 60, 4), (14336, 60, 4),
+                                   (16384, 60, 40), (24576, 64, 64), (16390, 65, 16), (24577, 127, 15), (14339, 100, 5), (16384, 100, 2),
+                                   (14336, 132, 9), (14341, 256, 64), (32767, 130, 17), (32768, 130, 17), (32769, 255, 64)])
 @pytest.mark.parametrize("kind", ["normal", "ties", "wide"])
 def test_softmax_topk_long_batches(n, e, k, kind):
     gen = torch.Generator(device="cuda").manual_seed(n + e)
