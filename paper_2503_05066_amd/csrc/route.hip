@@ -349,10 +349,7 @@ __global__ __launch_bounds__(256) void softmax_topk_kernel(float* __restrict__ l
         // Repeated wave-wide arg-max costs k rounds of cross-lane steps; this is a few ballots per bit.
         uint32_t bits[EPL];
 #pragma unroll
-        for (int i = 0; i < EPL; ++i) {
-            bits[i] = __float_as_uint(v[i] < 0.0f ? 0.0f : v[i]);
-            if (sum != sum) bits[i] = kNoNumber;  // a token without numbers: its scores are all the same
-        }
+        for (int i = 0; i < EPL; ++i) bits[i] = __float_as_uint(v[i] >= 0.0f ? v[i] : 0.0f);  // (a token without numbers: all the same)
         uint32_t tau = 0;
         for (int bit = 29; bit >= 0; --bit) {
             const uint32_t cand = tau | (1u << bit);
@@ -399,7 +396,7 @@ __global__ __launch_bounds__(256) void softmax_topk_kernel(float* __restrict__ l
         for (int i = 0; i < EPL; ++i)
             if (bits[i] != 0xffffffffu) {
                 topk_idx[(size_t)t * k + place[i]] = lane + kWave * i;
-                topk_score[(size_t)t * k + place[i]] = sum != sum ? sum : __uint_as_float(bits[i]);
+                topk_score[(size_t)t * k + place[i]] = v[i];
             }
         __builtin_amdgcn_wave_barrier();  // the list is rewritten for the wave's next token only after these reads
     }

@@ -105,14 +105,15 @@ def test_softmax_topk_long_batches_adds_router_slices(n, d, e, k):
     _assert_same_as_short_batches(logits, k, out)
 
 
-@pytest.mark.parametrize("n", [130, 12288])
-def test_tokens_without_numbers(n):
-    e, k = 64, 8
+@pytest.mark.parametrize("n,e,k", [(130, 64, 8), (12288, 64, 8), (130, 5, 5), (12288, 5, 3), (12290, 8, 8), (130, 61, 7), (16384, 61, 7),
+                                   (130, 130, 9), (14336, 132, 9), (24576, 127, 8), (16384, 256, 64), (130, 255, 64), (32768, 255, 20),
+                                   (70, 64, 64), (24576, 64, 64)])
+def test_tokens_without_numbers(n, e, k):
     logits = torch.randn((n, e), generator=torch.Generator(device="cuda").manual_seed(n), device="cuda")
     clean = _route(logits.clone(), k)
     broken = torch.zeros(n, dtype=torch.bool, device="cuda")
     broken[1::5] = True
-    logits[1::10, 3], logits[6::10] = float("nan"), float("-inf")
+    logits[1::10, min(3, e - 1)], logits[6::10] = float("nan"), float("-inf")
     scores, idx, score = _route(logits, k)
     assert bool(scores[broken].isnan().all()) and bool(score[broken].isnan().all())
     assert torch.equal(idx[broken], torch.arange(k, dtype=torch.int32, device="cuda").expand(int(broken.sum()), k))
