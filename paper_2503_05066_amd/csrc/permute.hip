@@ -42,16 +42,15 @@ __device__ inline uint32_t combine_pack(float lo, float hi) {
 // y[t,:] = sum over the token's slots (ascending) of row_weight[r] * yp[r,:], fp32 accumulation.
 //
 // A wave takes U pieces per lane (64 * U consecutive ones) of one token: lane s fetches slot s and its weight, a ballot
-// tells which slots hold a row, and the rows are then fetched eight pieces a lane at a time from wave-uniform addresses.
+// tells which slots hold a row, and ROWS rows at a time are then fetched from wave-uniform addresses.
 // The bytes bound it; what kept a thread per piece from them was three dependent loads per eight slots, taken or not, and
 // every slot's index in every lane.  16384 tokens of 24 slots, 46 k rows x 2048 62 -> 41 us (6.2 TB/s), 8192 x 4096 29 -> 23,
 // 4096 x 2048 15.1 -> 12.7, 3000 tokens of 32 slots 21 -> 17, 1 token 2.8 -> 2.2.
-template <bool BF16, int U>
+template <bool BF16, int U, int ROWS>
 __global__ __launch_bounds__(256) void combine_kernel(const uint4* __restrict__ yp,
                                                       const float* __restrict__ row_weight,
                                                       const int32_t* __restrict__ pair_row, uint4* __restrict__ y,
                                                       long long units, int parts, int pieces, int S) {
-    constexpr int kRows = U == 1 ? 8 : 4;  // rows in flight
     constexpr int kVals = BF16 ? 8 : 4;
     const int lane = threadIdx.x & 63;
     for (long long unit = (long long)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); unit < units;
@@ -71,11 +70,11 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint4* __restrict__ 
             const int w = r >= 0 ? __float_as_int(row_weight[r]) : 0;
             uint64_t left = __ballot(r >= 0);
             while (left) {
-                uint4 v[kRows][U];
-                float wj[kRows];
+                uint4 v[ROWS][U];
+                float wj[ROWS];
                 int n = 0, slot = 0;
 #pragma unroll
-                for (int j = 0; j < kRows; ++j) {
+                for (int j = 0; j < ROWS; ++j) {
                     if (left) {  // past the last row: that one again
                         slot = __builtin_ctzll(left);
                         left &= left - 1;
@@ -88,11 +87,11 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint4* __restrict__ 
                 }
                 // all of them are requested before any is used (the compiler otherwise moves each load behind the branch below)
 #pragma unroll
-                for (int j = 0; j < kRows; ++j)
+                for (int j = 0; j < ROWS; ++j)
 #pragma unroll
                     for (int u = 0; u < U; ++u) asm volatile("" : "+v"(v[j][u].x), "+v"(v[j][u].y), "+v"(v[j][u].z), "+v"(v[j][u].w));
 #pragma unroll
-                for (int j = 0; j < kRows; ++j) {
+                for (int j = 0; j < ROWS; ++j) {
                     if (j >= n) break;
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
@@ -193,12 +192,12 @@ hipError_t launch_dispatch(const moe_desc_t& d, const Sizes& s, const void* x, c
 
 constexpr long long kMaxBlocks = 1 << 22;  // a launch has fewer than 2^32 threads; the kernel strides over the rest
 
-template <bool BF16, int U>
+template <bool BF16, int U, int ROWS>
 static void launch_combine_units(const void* yp, const float* row_weight, const int32_t* pair_row, void* y, int tokens,
                                  int pieces, int slots, hipStream_t st) {
     const int parts = (pieces + 64 * U - 1) / (64 * U);
     const long long units = (long long)tokens * parts;
-    hipLaunchKernelGGL((combine_kernel<BF16, U>), dim3((unsigned)std::min<long long>((units + 3) / 4, kMaxBlocks)), dim3(256), 0,
+    hipLaunchKernelGGL((combine_kernel<BF16, U, ROWS>), dim3((unsigned)std::min<long long>((units + 3) / 4, kMaxBlocks)), dim3(256), 0,
                        st, (const uint4*)yp, row_weight, pair_row, (uint4*)y, units, parts, pieces, slots);
 }
 
@@ -206,19 +205,32 @@ template <bool BF16>
 static void choose_combine(const moe_desc_t& d, const Sizes& s, const void* yp, const float* row_weight, const int32_t* pair_row,
                            void* y, hipStream_t st) {
     const int pieces = (int)((size_t)d.d_model * s.elem / 16);
-    // Two pieces per lane from four rounds of waves on (a compute unit holds 32): their lists are fetched half as often.  One
-    // piece -> two: 65536 units 44 -> 41 and 35 -> 23 us; 16384 12.7 -> 13.0, 4 of them 2.2 -> 3.4 (four pieces: never better).
-    const long long units = (long long)d.n_tokens * ((pieces + 63) / 64);
-    // Short rows of many tokens: a wave for each token is many rounds of mostly idle lanes.  A wave per token -> a thread per
-    // piece, eight slots: 65536 tokens of 128 bytes 20 -> 7 us, of 256 22 -> 11, of 512 24 -> 17, of 1024 32 -> 31; 16384 of 256 equal.
-    if (pieces < 64 && d.n_tokens > 16384) {
-        const long long items = (long long)d.n_tokens * pieces;
+    const int n = d.n_tokens, slots = s.slots;
+    // Short rows of many tokens: a wave for each token is many rounds of waves with idle lanes, against which its list, fetched at once,
+    // weighs more the longer it is.  A wave per token against a thread per piece: rows of 8 pieces, 8 slots 1.04 times its time at 3000
+    // tokens, 1.44 at 8192, 3.1 at 65536; of 32 1.06, 1.27, 1.18; of 48 0.98, 1.07, 1.00; of 64 1.02, 1.00, 0.97; 16 slots, 16
+    // pieces 0.96 at 4096, 1.2 at 8192; of 40 0.94 and 0.99; 24 slots, 16 pieces 0.98 at 8192, 1.14 at 12000.
+    const int widest = slots <= 8 ? 48 : (slots <= 16 ? 32 : 16);
+    const int fewest = slots <= 8 ? 2048 : (slots <= 16 ? 256 : 400) * slots;
+    if (pieces <= widest && n > fewest) {
+        const long long items = (long long)n * pieces;
         hipLaunchKernelGGL((combine_narrow_kernel<BF16>), dim3(grid_for(items)), dim3(256), 0, st, (const uint4*)yp, row_weight,
-                           pair_row, (uint4*)y, items, pieces, s.slots);
-    } else if (units >= 32768 && pieces > 64)
-        launch_combine_units<BF16, 2>(yp, row_weight, pair_row, y, d.n_tokens, pieces, s.slots, st);
+                           pair_row, (uint4*)y, items, pieces, slots);
+        return;
+    }
+    // Two pieces per lane where the rows' last waves would be half idle, and for a round or two of waves (8192 fit the chip): the lists
+    // are fetched half as often.  One piece -> two, 6 slots: 96 pieces, 4096 tokens 5.4 -> 5.0 us, 256 pieces, 3000 tokens 8.5 -> 7.9; but
+    // 300 of 96 2.7 -> 3.0, 32768 of 256 0.88 of the old kernel's time and 0.92 (four pieces: never better).
+    const long long units = (long long)n * ((pieces + 63) / 64);
+    // As many rows in flight as short lists have: eight requests for one or two rows took 1.08 to 1.24 of the old kernel's time.
+    if (pieces > 64 && units >= 4000 && (pieces < 128 || units <= 16384))
+        launch_combine_units<BF16, 2, 4>(yp, row_weight, pair_row, y, n, pieces, slots, st);
+    else if (slots <= 2)
+        launch_combine_units<BF16, 1, 2>(yp, row_weight, pair_row, y, n, pieces, slots, st);
+    else if (slots <= 4)
+        launch_combine_units<BF16, 1, 4>(yp, row_weight, pair_row, y, n, pieces, slots, st);
     else
-        launch_combine_units<BF16, 1>(yp, row_weight, pair_row, y, d.n_tokens, pieces, s.slots, st);
+        launch_combine_units<BF16, 1, 8>(yp, row_weight, pair_row, y, n, pieces, slots, st);
 }
 
 hipError_t launch_combine(const moe_desc_t& d, const Sizes& s, const void* yp, const float* row_weight,

@@ -14,7 +14,10 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("n,d,slots,dtype", [
     (1, 8, 1, "bf16"), (3, 512, 8, "bf16"), (5, 520, 9, "bf16"), (16384, 64, 2, "bf16"), (16385, 64, 2, "bf16"),
     (16385, 504, 3, "bf16"), (16384, 1024, 5, "bf16"), (16383, 1032, 5, "bf16"), (700, 1024, 130, "bf16"),
-    (2, 4, 2, "f32"), (129, 260, 17, "f32"), (16385, 252, 3, "f32"), (16384, 512, 2, "f32"), (40, 256, 70, "f32")])
+    (2048, 64, 2, "bf16"), (2049, 64, 2, "bf16"), (2049, 384, 8, "bf16"), (2049, 392, 8, "bf16"), (3000, 256, 10, "bf16"),
+    (4097, 256, 16, "bf16"), (4097, 264, 16, "bf16"), (9601, 128, 24, "bf16"), (2000, 520, 3, "bf16"), (1999, 520, 3, "bf16"),
+    (2001, 1016, 4, "bf16"), (1025, 2048, 6, "bf16"), (4097, 2048, 6, "bf16"), (70, 2056, 1, "bf16"), (33, 1032, 4, "bf16"),
+    (2049, 188, 3, "f32"), (2, 4, 2, "f32"), (129, 260, 17, "f32"), (16385, 252, 3, "f32"), (16384, 512, 2, "f32"), (40, 256, 70, "f32")])
 def test_combine(n, d, slots, dtype):
     if slots <= 64:
         desc = capmoe.make_desc(n, d, 64, slots, 128, 1, capmoe.MODE_NONE, capmoe.SCOPE_LOCAL, 1.0,
