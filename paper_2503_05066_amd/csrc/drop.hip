@@ -373,7 +373,7 @@ __global__ __launch_bounds__(NT) void drop_select_kernel(const uint32_t* __restr
 // 2b. threshold of segments that one block would walk for long
 // ---------------------------------------------------------------------------------------------
 // A device budget makes one segment of all keys of a device's experts, a million and more with a single device.  One block
-// needs a pass over them per radix digit and another for the counts, at one compute unit's bandwidth.  Here many
+// needs several passes over them, at one compute unit's bandwidth.  Here many
 // blocks share a segment: three launches build the histograms of an 11, 11 and 10 bit digit (every block first picks the
 // digit before it from the histogram of the launch before), one counts per expert, one small one settles ties.  Integer
 // atomics throughout: the same numbers run to run.  Which segments come here: select_form.
@@ -1485,13 +1485,14 @@ static Select select_form(const moe_desc_t& d, const Sizes& s) {
     if (n_keys <= (select_by_four(s, d.n_tokens) ? 65536 : 32768) || s.cap == 0) return Select::kHeld;
     // Room for every key: there is no threshold to find.
     if (s.cap >= n_keys) return Select::kCount;
-    // One block reads its segment from L2 five times, however many others do; shared segments cost five launches and four
-    // passes over all keys at the chip's bandwidth.  One block -> shared: 4 segments of 262144 keys 100 -> 26 us, 64 of
-    // 65540 32 -> 31, of 262144 91 -> 64; but 128 of 65540 32 -> 40, of 131072 53 -> 60, 256 of 262144 132 -> 195; at an odd
-    // pitch 4 of 32771 30 -> 37, 64 of 40001 37 -> 43, of 50001 46 -> 41.  Budgets over several experts (the walk divides
-    // by the run length, and ties need a search): 256 of 66560 70 -> 67, 64 of 131104 198 -> 58.
+    // One block reads its segment from L2 once for the extent of its keys and once or twice more, however many others do; shared segments
+    // cost five launches and four passes over all keys at the chip's bandwidth.  A block each as a share of many blocks' time (the whole
+    // drop): 8 segments of 50001 keys 0.96, of 65540 0.90, of 80000 0.99, of 98304 1.03, of 131072 1.07, of 262144 1.25; 32 of them
+    // 0.91, 0.89, 0.97, 1.00, 1.02, 1.08; 48 of 131072 0.99, 64 of any 0.81 to 0.99; all scores equal 0.5 to 0.95.  Budgets over several
+    // experts (the walk divides by the run length, and ties need a search): 16384 tokens x 64 269 us and 38; 256 segments of
+    // 66560 keys 135 and 162, but up to a millisecond for ties.
     const int segs = s.n_blocks * (d.n_experts / s.span);
-    return s.span > 1 || (n_keys > 40960 && segs <= 64) ? Select::kShared : Select::kLoop;
+    return s.span > 1 || (n_keys > 98304 && segs < 48) ? Select::kShared : Select::kLoop;
 }
 
 size_t drop_big_state_bytes(const moe_desc_t& d, const Sizes& s) {

@@ -235,7 +235,7 @@ def _drop_against_sort(n, e, k, groups, scope, gamma, scores, lists, metric=0, c
 # a segment of a wave, of 256 and of 1024 threads in one launch; selected by 256 threads (by four, at odd addresses), by 1024, from L2
 # and by many blocks; one expert, and several under one budget
 FORMS = [(40, 1, 0), (100, 1, 0), (300, 1, 0), (3000, 1, 0), (500, 1, 3), (1000, 1, 3), (999, 1, 3), (2001, 1, 3), (4096, 1, 3), (4099, 1, 3),
-         (12003, 1, 0), (16384, 1, 0), (32771, 1, 0), (65544, 1, 0), (65544, 2, 2)]
+         (12003, 1, 0), (16384, 1, 0), (32771, 1, 0), (65544, 1, 0), (98304, 1, 0), (98305, 1, 0), (98308, 1, 0), (65544, 2, 2)]
 
 
 def _lists(rng, n, e, k):
