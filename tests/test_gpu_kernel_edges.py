@@ -133,46 +133,6 @@ def _scores_of_range(rng, n, e, width):
     return (base + rng.integers(0, width, (n, e)).astype(np.uint32)).view(np.float32)
 
 
-@pytest.mark.parametrize("n,groups,scope", [(63, 1, 0), (2048, 1, 0), (2049, 1, 0), (8192, 1, 0), (8196, 1, 0), (12003, 1, 0),
-                                            (2048, 2, 3), (24000, 4, 2), (65544, 1, 1), (30, 2, 2), (32, 2, 2), (34, 2, 2),
-                                            (8192, 2, 2), (8224, 2, 2), (8226, 2, 2)])
-@pytest.mark.parametrize("width", [1, 2, 1024, 2048, 2049, 1 << 21, 1 << 24])
-def test_drop_threshold_of_key_ranges(n, groups, scope, width):
-    """The kept pairs against a sort of (key, token, expert): expert-level and device-level capacities; runs of 16 tokens that are
-    whole, cut short and at odd addresses, segments of one, two and many chunks of 4096 tokens."""
-    n -= n % groups
-    e, k, gamma = 4, 4, 0.6
-    rng = np.random.default_rng(n + width)
-    scores = _scores_of_range(rng, n, e, width)
-    desc = capmoe.make_desc(n, 4, e, k, 8, groups, capmoe.MODE_TOKEN_DROP, scope, gamma, capmoe.DTYPE_F32)
-    cap, slots, rows, workspace = capmoe.moe_query(desc)
-    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
-    idx = np.broadcast_to(np.arange(e, dtype=np.int32), (n, e))
-    out = {name: torch.full(shape, -7, dtype=dt, device="cuda") for name, shape, dt in (
-        ("expert_count", (e,), torch.int32), ("seg_count", (groups * e,), torch.int32), ("expert_offset", (e + 1,), torch.int32),
-        ("row_token", (rows,), torch.int32), ("row_weight", (rows,), torch.float32), ("pair_row", (n, slots), torch.int32))}
-    ws = torch.empty(max(workspace, 256), dtype=torch.uint8, device="cuda")
-    capmoe.moe_capacity_drop(desc, dev(scores), dev(idx), out["expert_count"], out["seg_count"], out["expert_offset"],
-                             out["row_token"], out["row_weight"], out["pair_row"], ws)
-    torch.cuda.synchronize()
-    blocks = groups if scope in (0, 2) else 1
-    span = e // groups if scope in (2, 3) else 1
-    keep = np.zeros((n, e), bool)
-    per = n // blocks
-    bits = scores.view(np.uint32).astype(np.int64)
-    for b in range(blocks):
-        for g in range(e // span):
-            t, x = np.meshgrid(np.arange(b * per, (b + 1) * per), np.arange(g * span, (g + 1) * span), indexing="ij")
-            t, x = t.ravel(), x.ravel()
-            best = np.lexsort((x, t, -bits[t, x]))[:cap]   # larger score, then lower token, then lower expert
-            keep[t[best], x[best]] = True
-    tokens = np.concatenate([np.flatnonzero(keep[:, x]) for x in range(e)])
-    counts = keep.sum(axis=0)
-    np.testing.assert_array_equal(out["expert_count"].cpu().numpy(), counts)
-    np.testing.assert_array_equal(out["row_token"].cpu().numpy()[: counts.sum()], tokens)
-    assert np.array_equal(out["pair_row"].cpu().numpy() >= 0, keep)
-
-
 def _keys_of_pairs(scores, lists, metric, classes, seed, seg_tokens):
     """(candidates [N,E], keys [N,E]) as the drop defines them: rank + 1 above the class's two bits, in 32-bit words; 0 without."""
     n, e = scores.shape
@@ -240,6 +200,31 @@ FORMS = [(40, 1, 0), (100, 1, 0), (300, 1, 0), (3000, 1, 0), (500, 1, 3), (1000,
 
 def _lists(rng, n, e, k):
     return np.sort(np.argsort(rng.random((n, e)), axis=1)[:, :k], axis=1)
+
+
+@pytest.mark.parametrize("n,groups,scope", [(63, 1, 0), (2048, 1, 0), (2049, 1, 0), (8192, 1, 0), (8196, 1, 0), (12003, 1, 0),
+                                            (2048, 2, 3), (24000, 4, 2), (65544, 1, 1), (30, 2, 2), (32, 2, 2), (34, 2, 2),
+                                            (8192, 2, 2), (8224, 2, 2), (8226, 2, 2)])
+@pytest.mark.parametrize("width", [1, 2, 1024, 2048, 2049, 1 << 21, 1 << 24])
+def test_drop_threshold_of_key_ranges(n, groups, scope, width):
+    """Expert-level and device-level capacities; runs of 16 tokens that are whole, cut short and at odd addresses, segments of one, two
+    and many chunks of 4096 tokens."""
+    n -= n % groups
+    e = k = 4
+    rng = np.random.default_rng(n + width)
+    _drop_against_sort(n, e, k, groups, scope, 0.6, _scores_of_range(rng, n, e, width), _lists(rng, n, e, k))
+
+
+@pytest.mark.parametrize("n,groups,scope", FORMS)
+@pytest.mark.parametrize("metric", [capmoe.METRIC_SCORE, capmoe.METRIC_ORDER, capmoe.METRIC_REVERSE_ORDER, capmoe.METRIC_RANDOM])
+@pytest.mark.parametrize("gamma", [0.15, 0.7])
+def test_drop_threshold_of_classes(n, groups, scope, metric, gamma):
+    """Keys over the whole word: four classes above every metric (gathered weights), lists that name half of the experts."""
+    n -= n % groups
+    rng = np.random.default_rng(n + metric)
+    scores = rng.random((n, 4)).astype(np.float32)
+    scores[rng.random(n) < 0.2] = 0.0
+    _drop_against_sort(n, 4, 2, groups, scope, gamma, scores, _lists(rng, n, 4, 2), metric, rng.integers(0, 4, n).astype(np.uint8))
 
 
 @pytest.mark.parametrize("n,groups,scope", FORMS)

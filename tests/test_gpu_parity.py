@@ -365,11 +365,16 @@ def tied_logits(rng, n, e, ties):
     (5000, 32, 4, 1, ED, GLOBAL_DEV, 0.7, 1, None),       # Order: every key of a token is equal
     (70004, 3, 2, 1, TD, GLOBAL, 0.4, 0, "pad"),          # single experts: the first equal keys in token order
     (41001, 2, 1, 1, TD, GLOBAL, 0.4, 0, "flat"),
+    (98308, 3, 2, 1, TD, GLOBAL, 0.4, 0, "pad"),          # the same in segments that blocks share
+    (98305, 2, 1, 1, TD, GLOBAL, 0.4, 0, "flat"),
+    (98309, 47, 2, 1, TD, GLOBAL, 0.4, 0, "few"),
 ])
 def test_plan_ties_in_segments_of_many_blocks(orc, n, e, k, g, mode, scope, gamma, metric, ties):
     """More keys equal the threshold than a segment has room for, spread over all of it."""
     logits = tied_logits(np.random.default_rng(n + e), n, e, ties)
     check_route_and_plan(orc, logits, n, e, k, g, mode, scope, gamma, f"ties {n}x{e} {ties}", metric)
+    if n * e > 1 << 22:
+        return
     check_route_and_plan(orc, logits, n, e, k, g, mode, scope, gamma, f"ties {n}x{e} {ties}, at most k", metric, None, 0,
                          min(2, e - k), True)
 
@@ -392,9 +397,11 @@ def test_plan_long_segments_with_room_for_all(orc, n, e, k, g, mode, scope, gamm
     (65540, 66, 2, 1, TD, GLOBAL, 0.5, "few"),
     (131088, 34, 2, 2, ED, LOCAL, 0.5, "pad"),      # 68 of them in two blocks of tokens
     (32771, 3, 1, 1, TD, GLOBAL, 0.4, None),        # odd pitch: a few, just too long to be held
-    (40961, 2, 1, 1, TD, GLOBAL, 0.4, None),        # and either side of where blocks share them
+    (40961, 2, 1, 1, TD, GLOBAL, 0.4, None),
     (40959, 2, 1, 1, TD, GLOBAL, 0.4, "flat"),
     (41001, 65, 3, 1, TD, GLOBAL, 0.7, None),
+    (98304, 3, 1, 1, TD, GLOBAL, 0.4, "few"),       # the most keys that are not shared,
+    (98305, 48, 2, 1, TD, GLOBAL, 0.5, None),       # and the fewest segments of more
 ])
 def test_plan_segments_read_in_every_pass(orc, n, e, k, g, mode, scope, gamma, ties):
     """Long segments of single experts that one block each selects from."""
