@@ -39,6 +39,15 @@ __device__ inline uint32_t pair_hash(uint32_t seed, uint32_t counter) {
     return x;
 }
 
+// A pair's rank within its class, below 2^30: score bits (scores are in [0,1]), position in the segment, or a draw.
+template <class ScoreBits>
+__device__ __forceinline__ uint32_t pair_rank(int metric, int local, int seg_tokens, uint32_t seed, uint32_t pair, ScoreBits&& score_bits) {
+    if (metric == MOE_METRIC_ORDER) return (uint32_t)(seg_tokens - 1 - local);
+    if (metric == MOE_METRIC_REVERSE_ORDER) return (uint32_t)local;
+    if (metric == MOE_METRIC_RANDOM) return pair_hash(seed, pair) >> 3;
+    return score_bits();
+}
+
 // ---------------------------------------------------------------------------------------------
 // 1. candidate keys, transposed
 // ---------------------------------------------------------------------------------------------
@@ -94,16 +103,8 @@ __global__ __launch_bounds__(256) void drop_prepare_kernel(const float* __restri
             const bool c = e < E && slot_s[tl * ld + e] != 0;
             const uint64_t mask = __ballot(c);
             if (e < E) {
-                // rank within the class, below 2^30: score bits (scores are in [0,1]), position, or a draw
-                uint32_t rank;
-                if (metric == MOE_METRIC_ORDER)
-                    rank = (uint32_t)(seg_tokens - 1 - local);
-                else if (metric == MOE_METRIC_REVERSE_ORDER)
-                    rank = (uint32_t)local;
-                else if (metric == MOE_METRIC_RANDOM)
-                    rank = pair_hash(seed, (uint32_t)t * (uint32_t)E + (uint32_t)e) >> 3;
-                else
-                    rank = key_s[tl * ld + e];
+                const uint32_t rank = pair_rank(metric, local, seg_tokens, seed, (uint32_t)t * (uint32_t)E + (uint32_t)e,
+                                                [&] { return key_s[tl * ld + e]; });
                 key_s[tl * ld + e] = c ? cls + rank + 1u : 0u;
                 slot_s[tl * ld + e] = (uint8_t)(base + __popcll(mask & ((1ull << lane) - 1ull)));
             }
@@ -1000,30 +1001,6 @@ constexpr long long kFusedMaxWork = 8ll << 20;  // segments x top-k list entries
 constexpr int kFusedBins = 1024;       // counters of the threshold search
 static_assert(kFusedBins <= kFusedCounters && kFusedBins % kFusedThreads == 0, "they may lie in the candidate counters' place");
 
-// exclusive prefix sum of v over the block's NT threads; *total gets the block sum
-template <int NT>
-__device__ inline int fused_exclusive_scan(int v, int* red, int* total) {
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    int incl = v;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        const int o = __shfl_up(incl, off, kWave);
-        if (lane >= off) incl += o;
-    }
-    __syncthreads();
-    if (lane == 63) red[wv] = incl;
-    __syncthreads();
-    int before = 0, all = 0;
-#pragma unroll
-    for (int w = 0; w < NT / kWave; ++w) {
-        const int r = red[w];
-        before += w < wv ? r : 0;
-        all += r;
-    }
-    *total = all;
-    return before + incl - v;
-}
-
 // EXPANDED: Expanded Drop; ONE_BLOCK: a single capacity block (every token belongs to the block's segment
 // list); VW: entries of a top-k list fetched per load (divides k).  The pass over the lists is the bulk of
 // the kernel's instructions, so it is specialised.  NT: threads of the block, a segment holds at most 8 * NT
@@ -1143,17 +1120,10 @@ __global__ __launch_bounds__(NT) void drop_fused_kernel(
             const int t = b * seg_tokens + tl;
             info[j] = tl < seg_tokens ? key_s[pad(tl)] : 0u;
             c[j] = tl < seg_tokens && ((info[j] >> 20) != 0u || (EXPANDED && t / group_tokens == g_e));
-            // rank within the class, below 2^30: score bits (scores are in [0,1]), position, or a draw
             rank[j] = 0u;
             if (c[j]) {
-                if (metric == MOE_METRIC_ORDER)
-                    rank[j] = (uint32_t)(seg_tokens - 1 - tl);
-                else if (metric == MOE_METRIC_REVERSE_ORDER)
-                    rank[j] = (uint32_t)tl;
-                else if (metric == MOE_METRIC_RANDOM)
-                    rank[j] = pair_hash(seed, (uint32_t)t * (uint32_t)E + (uint32_t)e) >> 3;
-                else
-                    rank[j] = __float_as_uint(scores[(size_t)t * E + e]);
+                rank[j] = pair_rank(metric, tl, seg_tokens, seed, (uint32_t)t * (uint32_t)E + (uint32_t)e,
+                                    [&] { return __float_as_uint(scores[(size_t)t * E + e]); });
                 if (token_class) rank[j] += (uint32_t)(token_class[t] & 3) << 30;
             }
         }
@@ -1269,7 +1239,7 @@ __global__ __launch_bounds__(NT) void drop_fused_kernel(
         kx[j] = j < run && tb + j < seg_tokens ? key_s[pad(tb + j)] : 0u;
         eq_cnt += kx[j] != 0u && kx[j] == tau;
     }
-    int eq_rank = fused_exclusive_scan<NT>(eq_cnt, red, &total);
+    int eq_rank = block_exclusive_scan<NT>(eq_cnt, red, &total);
     uint32_t keep_bits = 0;
     int keep_cnt = 0;
 #pragma unroll
@@ -1281,7 +1251,7 @@ __global__ __launch_bounds__(NT) void drop_fused_kernel(
         keep_cnt += keep;
         keep_bits |= (uint32_t)keep << j;
     }
-    int pos = row0 + fused_exclusive_scan<NT>(keep_cnt, red, &total);
+    int pos = row0 + block_exclusive_scan<NT>(keep_cnt, red, &total);
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         if (kx[j] == 0u) continue;
@@ -1361,15 +1331,7 @@ __global__ __launch_bounds__(256) void drop_small_kernel(
             const int lower = e - g0;  // experts of the token's device below e
             below += lower < 0 ? 0 : (lower > group_experts ? group_experts : lower);
         }
-        uint32_t rank;
-        if (metric == MOE_METRIC_ORDER)
-            rank = (uint32_t)(seg_tokens - 1 - lane);
-        else if (metric == MOE_METRIC_REVERSE_ORDER)
-            rank = (uint32_t)lane;
-        else if (metric == MOE_METRIC_RANDOM)
-            rank = pair_hash(seed, (uint32_t)t * (uint32_t)E + (uint32_t)e) >> 3;
-        else
-            rank = bits;
+        const uint32_t rank = pair_rank(metric, lane, seg_tokens, seed, (uint32_t)t * (uint32_t)E + (uint32_t)e, [&] { return bits; });
         key = live && cnd ? rank + cls + 1u : 0u;
         if (live && e == 0) {  // slots beyond the token's candidate count stay unused
             const int n_c = listed + (EXPANDED ? group_experts : 0);
