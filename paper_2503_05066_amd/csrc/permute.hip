@@ -218,12 +218,17 @@ static void choose_combine(const moe_desc_t& d, const Sizes& s, const void* yp, 
                            pair_row, (uint4*)y, items, pieces, slots);
         return;
     }
-    // Two pieces per lane where the rows' last waves would be half idle, and for a round or two of waves (8192 fit the chip): the lists
-    // are fetched half as often.  One piece -> two, 6 slots: 96 pieces, 4096 tokens 5.4 -> 5.0 us, 256 pieces, 3000 tokens 8.5 -> 7.9; but
-    // 300 of 96 2.7 -> 3.0, 32768 of 256 0.88 of the old kernel's time and 0.92 (four pieces: never better).
+    // Two pieces per lane from four rounds of waves on (8192 fit the chip), and where the rows' last waves would be half idle: the lists
+    // are fetched half as often.  One piece -> two, in a layer: 65536 units of 24 slots 44 -> 41 us, of 2 26 -> 24, of 6 42 -> 34, of 8
+    // 48.4 -> 47.6; 32768 of 8 24.3 -> 24.0; but 16384 of 8 12.7 -> 12.9, 12000 of 32 16.7 -> 17.4.  By itself, 96 pieces: 4096
+    // tokens 5.4 -> 5.0, 300 2.7 -> 3.0.  Four pieces: never better.
     const long long units = (long long)n * ((pieces + 63) / 64);
-    // As many rows in flight as short lists have: eight requests for one or two rows took 1.08 to 1.24 of the old kernel's time.
-    if (pieces > 64 && units >= 4000 && (pieces < 128 || units <= 16384))
+    const bool two = pieces > 64 && (units >= 32768 || (pieces < 128 && units >= 4000));
+    // As many rows in flight as short lists have: eight requests for one or two rows took 1.08 to 1.24 of the old kernel's time, four in
+    // two pieces 25.2 us for 22.5 (8192 tokens of 512 pieces); and more of them where two pieces are fetched are no use (43 for 34).
+    if (two && slots <= 2)
+        launch_combine_units<BF16, 2, 2>(yp, row_weight, pair_row, y, n, pieces, slots, st);
+    else if (two)
         launch_combine_units<BF16, 2, 4>(yp, row_weight, pair_row, y, n, pieces, slots, st);
     else if (slots <= 2)
         launch_combine_units<BF16, 1, 2>(yp, row_weight, pair_row, y, n, pieces, slots, st);

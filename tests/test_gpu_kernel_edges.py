@@ -16,7 +16,8 @@ pytestmark = pytest.mark.gpu
     (16385, 504, 3, "bf16"), (16384, 1024, 5, "bf16"), (16383, 1032, 5, "bf16"), (700, 1024, 130, "bf16"),
     (2048, 64, 2, "bf16"), (2049, 64, 2, "bf16"), (2049, 384, 8, "bf16"), (2049, 392, 8, "bf16"), (3000, 256, 10, "bf16"),
     (4097, 256, 16, "bf16"), (4097, 264, 16, "bf16"), (9601, 128, 24, "bf16"), (2000, 520, 3, "bf16"), (1999, 520, 3, "bf16"),
-    (2001, 1016, 4, "bf16"), (1025, 2048, 6, "bf16"), (4097, 2048, 6, "bf16"), (70, 2056, 1, "bf16"), (33, 1032, 4, "bf16"),
+    (2001, 1016, 4, "bf16"), (1025, 2048, 6, "bf16"), (4097, 2048, 6, "bf16"), (70, 2056, 1, "bf16"), (33, 1032, 4, "bf16"), (16384, 1024, 2, "bf16"),
+    (8192, 2048, 9, "bf16"), (4097, 4096, 3, "bf16"),
     (2049, 188, 3, "f32"), (2, 4, 2, "f32"), (129, 260, 17, "f32"), (16385, 252, 3, "f32"), (16384, 512, 2, "f32"), (40, 256, 70, "f32")])
 def test_combine(n, d, slots, dtype):
     if slots <= 64:
