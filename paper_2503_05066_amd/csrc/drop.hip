@@ -1278,10 +1278,11 @@ __global__ __launch_bounds__(NT) void drop_fused_kernel(
 constexpr int kSmallSegTokens = kWave;
 constexpr int kSmallSegs = 1024;
 // What it costs is reading lists: its own tokens', each lane a list, and all of them, four entries a thread at a time; the kernel above
-// reads vectors, a thread per token and round.  The two times meet where k * (5 * seg_tokens + 2 * N) is about 12 288 (against the
-// kernel above, 64 experts: 64 tokens with lists of 16 0.82, of 32 1.02, of 64 1.26; 256 on 4 devices of 8 0.81, of 16 0.98, of 32
-// 1.26; 512 on 8 of 8 0.88, of 16 1.10, of 64 2.5).  Two tokens per lane, for up to 128 in a segment, took 0.9 to 2.6 of its time.
-constexpr int kSmallWork = 12288;
+// reads vectors, a thread per token and round, but has a larger block per segment.  The times meet where k * (2 * seg_tokens + N) is
+// about 5000 + 8 * segments (against the kernel above, 64 experts: 64 tokens with lists of 16 0.82, of 32 1.02, of 64 1.26; 256 on 4
+// devices of 8 0.81, of 16 0.98, of 32 1.26; 512 on 8 of 8 0.88, of 16 1.10; 128 experts 256 on 8 of 32 0.77): 7 of 892 sizes are
+// more than 5 % off the better of the two.  Two tokens per lane, for up to 128 in a segment, took 0.9 to 2.6 of its time.
+static bool small_lists(int k, int seg_tokens, int N, int segs) { return (long long)k * (2 * seg_tokens + N) <= 5000 + 8 * segs; }
 
 template <bool EXPANDED>
 __global__ __launch_bounds__(256) void drop_small_kernel(
@@ -1482,8 +1483,7 @@ hipError_t launch_capacity_drop(const moe_desc_t& d, const Sizes& s, const DropW
         const bool fused = s.span == 1 && !(d.max_experts && s.slots > d.top_k) &&
                            s.seg_tokens <= kFusedMaxTokens && segs_all + 1 <= kFusedCounters &&
                            segs_all <= kFusedMaxSegs && (long long)segs_all * N * s.list_k <= kFusedMaxWork;
-        if (fused && s.seg_tokens <= kSmallSegTokens && segs_all <= kSmallSegs &&
-            (long long)s.list_k * (5 * s.seg_tokens + 2ll * N) <= kSmallWork) {
+        if (fused && s.seg_tokens <= kSmallSegTokens && segs_all <= kSmallSegs && small_lists(s.list_k, s.seg_tokens, N, segs_all)) {
             ProfileScope prof(MOE_KERNEL_DROP_SELECT, st);
             auto kern = d.mode == MOE_MODE_EXPANDED_DROP ? drop_small_kernel<true> : drop_small_kernel<false>;
             hipLaunchKernelGGL(kern, dim3((segs_all + 3) / 4 + (sched.enabled ? 1 : 0)), dim3(256), 0, st, scores, topk_idx,
