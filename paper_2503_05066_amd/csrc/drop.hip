@@ -48,6 +48,19 @@ __device__ __forceinline__ uint32_t pair_rank(int metric, int local, int seg_tok
     return score_bits();
 }
 
+// Expanded Drop, in the one-launch kernels: the tokens of capacity block `block` that sit on the device of expert `e` (all of them have it as
+// a candidate), and the experts of a token's device (from g0 on) with a lower id than e (candidates below it, listed or not).
+__device__ __forceinline__ int tokens_on_device(int e, int block, int group_experts, int group_tokens, int seg_tokens) {
+    const int lo = e / group_experts * group_tokens, hi = lo + group_tokens;
+    const int s0 = block * seg_tokens, s1 = s0 + seg_tokens;
+    const int a = lo > s0 ? lo : s0, z = hi < s1 ? hi : s1;
+    return z > a ? z - a : 0;
+}
+__device__ __forceinline__ int device_experts_below(int e, int g0, int group_experts) {
+    const int lower = e - g0;
+    return lower < 0 ? 0 : (lower > group_experts ? group_experts : lower);
+}
+
 // ---------------------------------------------------------------------------------------------
 // 1. candidate keys, transposed
 // ---------------------------------------------------------------------------------------------
@@ -1134,10 +1147,7 @@ __global__ __launch_bounds__(NT) void drop_fused_kernel(
             const int t = b * seg_tokens + tl;
             int below = (int)(info[j] & 1023u);
             const int listed = (int)((info[j] >> 10) & 1023u);
-            if (EXPANDED) {
-                const int lower = e - (t / group_tokens) * group_experts;  // experts of the token's device below e
-                below += lower < 0 ? 0 : (lower > group_experts ? group_experts : lower);
-            }
+            if (EXPANDED) below += device_experts_below(e, t / group_tokens * group_experts, group_experts);
             const uint32_t key = c[j] ? rank[j] + 1u : 0u;
             if (c[j]) {
                 key_lo = key < key_lo ? key : key_lo;
@@ -1159,12 +1169,7 @@ __global__ __launch_bounds__(NT) void drop_fused_kernel(
         int c = 0;
         for (int r = 0; r < copies; ++r) c += cand[r * pitch + i];
         const int bb = i / E, ee = i - bb * E;
-        if (EXPANDED) {  // plus the tokens of block bb that sit on the expert's device
-            const int lo = (ee / group_experts) * group_tokens, hi = lo + group_tokens;
-            const int s0 = bb * seg_tokens, s1 = s0 + seg_tokens;
-            const int a = lo > s0 ? lo : s0, z = hi < s1 ? hi : s1;
-            c += z > a ? z - a : 0;
-        }
+        if (EXPANDED) c += tokens_on_device(ee, bb, group_experts, group_tokens, seg_tokens);
         const int kept = c < cap ? c : cap;
         if (scheduler) atomicAdd(&sched_tot[ee], kept);
         if (ee < e || (ee == e && bb < b)) before += kept;
@@ -1328,10 +1333,7 @@ __global__ __launch_bounds__(256) void drop_small_kernel(
                 cnd = cnd || (counts && x[u] == e);
             }
         }
-        if (EXPANDED) {
-            const int lower = e - g0;  // experts of the token's device below e
-            below += lower < 0 ? 0 : (lower > group_experts ? group_experts : lower);
-        }
+        if (EXPANDED) below += device_experts_below(e, g0, group_experts);
         const uint32_t rank = pair_rank(metric, lane, seg_tokens, seed, (uint32_t)t * (uint32_t)E + (uint32_t)e, [&] { return bits; });
         key = live && cnd ? rank + cls + 1u : 0u;
         if (live && e == 0) {  // slots beyond the token's candidate count stay unused
@@ -1367,12 +1369,7 @@ __global__ __launch_bounds__(256) void drop_small_kernel(
     // ---- kept rows of every segment: this one's first row, its expert's total ----
     auto kept_of = [&](int i, int ee, int bb) {
         int c = cand[i];
-        if (EXPANDED) {  // plus the tokens of block bb that sit on the expert's device
-            const int lo = (ee / group_experts) * group_tokens, hi = lo + group_tokens;
-            const int s0 = bb * seg_tokens, s1 = s0 + seg_tokens;
-            const int a = lo > s0 ? lo : s0, z = hi < s1 ? hi : s1;
-            c += z > a ? z - a : 0;
-        }
+        if (EXPANDED) c += tokens_on_device(ee, bb, group_experts, group_tokens, seg_tokens);
         return c < cap ? c : cap;
     };
     if (scheduler) {
