@@ -1285,8 +1285,8 @@ constexpr int kSmallSegs = 1024;
 // What it costs is reading lists: its own tokens', each lane a list, and all of them, four entries a thread at a time; the kernel above
 // reads vectors, a thread per token and round, but has a larger block per segment.  The times meet where k * (2 * seg_tokens + N) is
 // about 5000 + 8 * segments (against the kernel above, 64 experts: 64 tokens with lists of 16 0.82, of 32 1.02, of 64 1.26; 256 on 4
-// devices of 8 0.81, of 16 0.98, of 32 1.26; 512 on 8 of 8 0.88, of 16 1.10; 128 experts 256 on 8 of 32 0.77): 7 of 892 sizes are
-// more than 5 % off the better of the two.  Two tokens per lane, for up to 128 in a segment, took 0.9 to 2.6 of its time.
+// devices of 8 0.81, of 16 0.98, of 32 1.26; 512 on 8 of 8 0.88, of 16 1.10; 128 experts 256 on 8 of 32 0.77): 16 of 1354 sizes,
+// up to 2048 tokens in 1024 segments, are more than 5 % off the better of the two.  Two tokens per lane, for up to 128 in a segment, took 0.9 to 2.6 of its time.
 static bool small_lists(int k, int seg_tokens, int N, int segs) { return (long long)k * (2 * seg_tokens + N) <= 5000 + 8 * segs; }
 
 template <bool EXPANDED>

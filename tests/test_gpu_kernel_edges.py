@@ -254,7 +254,7 @@ def test_drop_of_scores_that_are_no_numbers(n, groups, scope, bits, cls):
 @pytest.mark.parametrize("n,e,k,groups", [(1, 1, 1, 1), (1, 64, 8, 1), (3, 5, 2, 1), (63, 8, 2, 1), (64, 8, 3, 1), (65, 7, 2, 1), (128, 8, 2, 1),
                                           (129, 8, 2, 1), (512, 16, 6, 4), (513, 9, 2, 9), (512, 128, 9, 8), (512, 130, 4, 10),
                                           (256, 64, 6, 8), (40, 256, 64, 4), (500, 240, 8, 5), (64, 64, 28, 1), (64, 64, 29, 1),
-                                          (512, 64, 14, 8), (512, 64, 15, 8), (96, 256, 3, 4), (96, 256, 3, 8)])
+                                          (512, 64, 14, 8), (512, 64, 15, 8), (96, 256, 3, 4), (96, 256, 3, 8), (2048, 32, 2, 32), (1023, 33, 5, 33)])
 @pytest.mark.parametrize("mode,metric,classes", [(0, 0, False), (1, 0, False), (1, 1, True), (2, 3, False), (2, 2, True)])
 def test_drop_of_a_few_tokens(n, e, k, groups, mode, metric, classes):
     from oracle import oracle
