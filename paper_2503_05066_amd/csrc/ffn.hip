@@ -97,10 +97,10 @@ __device__ __forceinline__ void mfma_16x16x32(f32x4& c, const bf16x8& a, const b
 //     k-step 1 of slab kt:  MFMAs  |  operand reads of slab kt+1 |  requests for the activations of slab kt+2
 // Loads complete in order, so "all but the last B_LOADS" at barrier kt means the activations and weights of
 // slab kt+1 have landed while the weights of slab kt+2 may still be in flight.  LIVE = number of 16-row
-// activation sub-tiles that are multiplied (the rest lie past the expert's last row).
+// activation sub-tiles per wave that are fetched and multiplied (the rest lie past the expert's last row).
 // STREAM: the walk over K starts at slab k0 + k_start and wraps around at the end of the block's share (see
 // TileConfig16); otherwise k_start is 0.
-template <int BM, int BN, int NW, int TM, int TN, int WTN, bool SWIGLU, int LOADS, bool STREAM, class FillsT>
+template <int BM, int BN, int NW, int WM, int TM, int TN, int WTN, bool SWIGLU, int LOADS, bool STREAM, class FillsT>
 struct PipelinedLoop16 {
     static constexpr int BK = 64;
     static constexpr int A_SLOT = BM * 128, B_SLOT = BN * 128, B_BASE = 2 * A_SLOT;
@@ -131,9 +131,10 @@ struct PipelinedLoop16 {
     __device__ __forceinline__ void fill_b(int i, int kt, int slot) const {
         fills.one(A_LOADS + i, smem + B_BASE + slot * B_SLOT + (wv + NW * i) * 1024, k_bytes(kt));
     }
+    template <int USED>
     __device__ __forceinline__ void fill_a_all(int kt) const {
 #pragma unroll
-        for (int i = 0; i < A_LOADS; ++i) fill_a(i, kt);
+        for (int i = 0; i < USED; ++i) fill_a(i, kt);
     }
     __device__ __forceinline__ void fill_b_all(int kt, int slot) const {
 #pragma unroll
@@ -147,38 +148,24 @@ struct PipelinedLoop16 {
     // instructions.
     template <int LIVE, int PHASE = 0>
     __device__ __forceinline__ void run(f32x4 (&acc)[TN][TM]) const {
-        fill_a_all(0);
+        constexpr int A_USED = (LIVE * WM * 16 + NW * 8 - 1) / (NW * 8);  // loads of 8 rows a wave that hold live rows
+        static_assert(A_USED <= A_LOADS, "live rows");
+        fill_a_all<A_USED>(0);
         fill_b_all(0, 0);
         __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
         __builtin_amdgcn_s_barrier();
-        if (1 < KT) fill_a_all(1);
+        if (1 < KT) fill_a_all<A_USED>(1);
         if (1 < KT) fill_b_all(1, 1);
-        if (LIVE == 0) {  // nothing to multiply in this wave: it only fills its share and keeps the barriers
-            int slot2 = 2;  // slot of slab kt + 2
-            for (int kt = 0; kt < KT; ++kt) {
-                // as in the waves that multiply: the weights of slab kt+2 may still fly at the barrier
-                if (kt + 2 < KT) {
-                    fill_b_all(kt + 2, slot2);
-                    __builtin_amdgcn_s_waitcnt(waitcnt_vm(B_LOADS));
-                } else {
-                    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
-                }
-                __builtin_amdgcn_s_barrier();
-                if (kt + 2 < KT) fill_a_all(kt + 2);
-                slot2 = slot2 == 2 ? 0 : slot2 + 1;
-            }
-            return;
-        }
-        constexpr int NL = LIVE > 0 ? LIVE : 1;
+        constexpr int NL = LIVE;
         constexpr int NMFMA = TN * NL, NREAD = NL + TN;
         // reads go out in the first half of a k-step, so that they have returned long before the barrier
         constexpr int READ_EVERY = NMFMA / 2 / NREAD > 0 ? NMFMA / 2 / NREAD : 1;
         constexpr int B_EVERY = NMFMA / B_LOADS > 0 ? NMFMA / B_LOADS : 1;
-        constexpr int A_EVERY = NMFMA / A_LOADS > 0 ? NMFMA / A_LOADS : 1;
+        constexpr int A_EVERY = NMFMA / A_USED;
         constexpr int B_OFF = PHASE * B_EVERY / 4 + (B_EVERY >= 8 ? B_EVERY / 8 : 0);
         constexpr int A_OFF = PHASE * A_EVERY / 4 + (A_EVERY >= 8 ? A_EVERY / 8 : 0);
         static_assert(B_OFF < B_EVERY && A_OFF < A_EVERY, "request placement");
-        static_assert(LIVE == 0 || (NMFMA >= NREAD * READ_EVERY && NMFMA >= B_LOADS && NMFMA >= A_LOADS * A_EVERY), "k-step too short");
+        static_assert(NMFMA >= NREAD * READ_EVERY && NMFMA >= B_LOADS * B_EVERY && A_EVERY > 0, "k-step too short");
         bf16x8 xa[2][NL], wb[2][TN];
 
         // r-th operand read of a k-step, in the order the MFMAs (activation sub-tile major) need them:
@@ -192,7 +179,7 @@ struct PipelinedLoop16 {
             else if (r <= TN)
                 wb[set][r - 1] = *(const bf16x8*)(pb + b_tile(r - 1));
             else
-                xa[set][r - TN] = *(const bf16x8*)(pa + (r - TN) * 16 * 128);
+                xa[set][r - TN] = *(const bf16x8*)(pa + (r - TN) * WM * 16 * 128);
         };
 #pragma unroll
         for (int r = 0; r < NREAD; ++r) read_item(r, 0, smem + a_lane, smem + B_BASE + b_lane);
@@ -233,7 +220,7 @@ struct PipelinedLoop16 {
                     const int j = q / TN, i = q % TN;
                     mfma_16x16x32(acc[i][j], wb[1][i], xa[1][j]);
                     if (MORE && q % READ_EVERY == 0 && q / READ_EVERY < NREAD) read_item(q / READ_EVERY, 0, pa, pb);
-                    if (REFILL && q % A_EVERY == A_OFF && q / A_EVERY < A_LOADS) fill_a(q / A_EVERY, kt + 2);
+                    if (REFILL && q % A_EVERY == A_OFF && q / A_EVERY < A_USED) fill_a(q / A_EVERY, kt + 2);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
@@ -348,7 +335,7 @@ struct TileConfig16 {
     // lane only and the sub-tiles differ by constant offsets
     const int lr = lane & 15, lk = lane >> 4;
     const int piece0 = (lk ^ ((lr >> 1) & 7)) << 4;
-    const int a_lane = (wm * WTM + lr) * 128 + piece0;
+    const int a_lane = (wm * 16 + lr) * 128 + piece0;
     const int b_lane = ((SWIGLU ? wn * (WTN / 2) : wn * WTN) + lr) * 128 + piece0;
 
     f32x4 acc[TN][TM];
@@ -359,12 +346,17 @@ struct TileConfig16 {
 #pragma unroll
             for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.f;
 
-    // 16-row sub-tiles of this wave that hold rows of the expert, in pairs (wave-uniform); the main loop
-    // is specialised on it so that the common full tile carries no conditionals
-    int live = (rows - wm * WTM + 31) / 32 * 2;
-    live = __builtin_amdgcn_readfirstlane(live < 0 ? 0 : (live > TM ? TM : live));
+    // The waves of a column of the block take its 16-row sub-tiles in turn, so that a partly filled tile keeps all of
+    // them multiplying: its time follows its rows in steps of 16 * WAVES_M.  `live` sub-tiles per wave hold rows of the
+    // expert (the same for the whole block; the one of the last wave may lie past the end); the main loop is specialised
+    // on it, so that the common full tile carries no conditionals, and fetches no others.
+    // (Halves of a tile as wave rows left two of four waves idle up to 128 rows: 128 x 2048 x 768 with 129 to 200 rows on
+    // most experts 638 -> 618 us a layer, 60 x 2048 x 1408 with at most 127 227 -> 224.)
+    int live = (rows + 16 * WAVES_M - 1) / (16 * WAVES_M);
+    if (WAVES_M == 1) live = (live + 1) & ~1;  // short tiles: memory binds, steps of 32 rows do
+    live = __builtin_amdgcn_readfirstlane(live);
 
-    using Loop = PipelinedLoop16<BM, BN, NW, TM, TN, WTN, SWIGLU, LOADS, STREAM, FillsT>;
+    using Loop = PipelinedLoop16<BM, BN, NW, WAVES_M, TM, TN, WTN, SWIGLU, LOADS, STREAM, FillsT>;
     static_assert(Loop::LDS_BYTES == kLdsBytes, "LDS size");
     // this block's share of the K slabs: all of them, or slice `split.slice` of `split.slices`
     const int slabs_all = K / 64;
@@ -382,14 +374,21 @@ struct TileConfig16 {
             case 2: loop.template run<TM, 2>(acc); break;
             default: loop.template run<TM, 3>(acc); break;
         }
-    } else if (TM > 6 && live == 6)
-        loop.template run<(TM > 6 ? 6 : TM)>(acc);
-    else if (TM > 4 && live == 4)
-        loop.template run<(TM > 4 ? 4 : TM)>(acc);
-    else if (TM > 2 && live == 2)
-        loop.template run<(TM > 2 ? 2 : TM)>(acc);
-    else
-        loop.template run<0>(acc);
+    } else if constexpr (WAVES_M == 1) {
+        loop.template run<2>(acc);
+    } else {
+        // (a remainder of fewer rows than LIVE = 3 holds is a short tile)
+        if (live == 7)
+            loop.template run<7>(acc);
+        else if (live == 6)
+            loop.template run<6>(acc);
+        else if (live == 5)
+            loop.template run<5>(acc);
+        else if (live == 4)
+            loop.template run<4>(acc);
+        else
+            loop.template run<3>(acc);
+    }
 
     // ---- an item cut along K: partial tiles through the workspace, the last unit to finish adds them ----
     // The units of an item may run on different XCDs, whose L2 caches do not see each other's lines.  A fence
@@ -465,7 +464,7 @@ struct TileConfig16 {
     static_assert((PIECES & (PIECES - 1)) == 0, "piece swizzle");
 #pragma unroll
     for (int j = 0; j < TM; ++j) {
-        const int r = wm * WTM + j * 16 + lr;
+        const int r = (j * WAVES_M + wm) * 16 + lr;
         uint8_t* lrow = smem + r * ROWB + (lk & 1) * 8;
         const int sw = r & (PIECES - 1);
 #pragma unroll

@@ -348,3 +348,40 @@ def test_empty_batch_of_every_metric(metric, classes, mode, scope, over, limit):
         torch.cuda.synchronize()
         for a in (buf.expert_count, buf.seg_count, buf.expert_offset):
             assert bool((a == 0).all())
+
+
+# ------------------------------------------------------------------------------------------------
+# expert products: row tiles filled to every step of 32 rows, and one row less and more
+# ------------------------------------------------------------------------------------------------
+def _ffn_against_fp64(d, h, counts, seed):
+    """moe_grouped_ffn over experts with these rows; every row against the product in 64 bits of the bf16 hidden activations."""
+    e, n = len(counts), sum(counts)
+    desc = capmoe.make_desc(n, d, e, 1, h, 1, capmoe.MODE_NONE, capmoe.SCOPE_GLOBAL, 1.0, capmoe.DTYPE_BF16)
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    act = {}
+    for name, shape, fan in (("x", (n, d), 1), ("g", (e, h, d), d), ("u", (e, h, d), d), ("w", (e, d, h), h)):
+        act[name] = (torch.randn(shape, generator=gen, device="cuda") * fan ** -0.5).to(torch.bfloat16)
+    offset = torch.tensor(np.concatenate([[0], np.cumsum(counts)]), dtype=torch.int32, device="cuda")
+    ws = torch.empty(capmoe.moe_query(desc)[3], dtype=torch.uint8, device="cuda")
+    yp = torch.full((n + 1, d), 7.0, dtype=torch.bfloat16, device="cuda")
+    capmoe.moe_grouped_ffn(desc, act["x"], offset, act["g"], act["u"], act["w"], yp, ws)
+    torch.cuda.synchronize()
+    at = 0
+    for j, c in enumerate(counts):
+        rows = slice(at, at + c)
+        x = act["x"][rows].double()
+        g, u = x @ act["g"][j].double().T, x @ act["u"][j].double().T
+        hidden = g * torch.sigmoid(g) * u
+        ref, mass = hidden @ act["w"][j].double().T, hidden.abs() @ act["w"][j].double().abs().T
+        # every hidden value and the output are rounded to bf16 once (2^-9 each); fp32 sums of d and h products add (d + h) 2^-24
+        # of the mass, and the fp32 silu a few 2^-24
+        bound = (2.0 ** -8 + (2 * d + h + 64) * 2.0 ** -24) * mass + 2.0 ** -8 * ref.abs() + 1e-6
+        assert bool(((yp[rows].double() - ref).abs() <= bound).all()), (j, c)
+        at += c
+    assert bool((yp[n:] == 7.0).all())
+    return yp
+
+
+@pytest.mark.parametrize("d,h", [(128, 128), (256, 384), (384, 256)])
+def test_ffn_partly_filled_tiles(d, h):
+    _ffn_against_fp64(d, h, [65, 95, 96, 97, 128, 129, 160, 161, 191, 192, 193, 224, 225, 255, 256 + 66, 512 + 127], d + h)
