@@ -5,16 +5,16 @@
 //
 // Rows per expert are only known on the device, so one wave (a kernel of its own, or the tail of the
 // capacity drop's last launch) first turns expert_offset into lists of row tiles (expert, first row,
-// valid rows); the GEMM grids are sized for the static upper bound and surplus blocks exit at once.
+// valid rows); the GEMM kernels run one block per compute unit, which takes items off these lists until none is left.
 //
 // bf16: both operands are K-contiguous ("NT" GEMM), staged through LDS in 16-byte pieces with an
-// XOR swizzle and multiplied on the matrix cores with fp32 accumulation (v_mfma_f32_16x16x32_bf16 in
-// both tile shapes): 256 x 256 blocks of 2 x 2 waves with 128 x 128 wave tiles for full-height row
-// tiles (the bulk of the flops), 64 x 256 blocks of 1 x 4 waves with 64 x 64 wave tiles for the short
-// remainders (weight streaming).  The weight rows feed the MFMA's first operand and the activation
+// XOR swizzle and multiplied on the matrix cores with fp32 accumulation (v_mfma_f32_16x16x32_bf16):
+// 256 x 256 blocks of 2 x 2 waves with 128 x 128 wave tiles, of which a block with fewer rows fetches and
+// multiplies what is filled.  The weight rows feed the MFMA's first operand and the activation
 // rows the second, so a lane ends up with 4 consecutive output columns of one row.
 // The fp32 kernels are in ffn_f32.hip, those of the smallest bf16 batches in ffn_thin.hip.
 #include <type_traits>
+#include <utility>
 
 #include "common.h"
 #include "schedule.h"
@@ -48,28 +48,6 @@ typedef __attribute__((address_space(3))) void* lptr_t;
 // at zero" (gfx9 encoding: vmcnt in bits 3:0 and 15:14, expcnt 6:4 left at 7, lgkmcnt 11:8).
 __host__ __device__ constexpr int waitcnt_vm(int n) { return (n & 15) | (7 << 4) | ((n >> 4) << 14); }
 
-// What a wave needs to request its pieces of a K slab: one buffer descriptor per operand tensor (the
-// block's activation rows, its weight rows, and for SwiGLU tiles the up-projection rows) and one 32-bit
-// byte offset per wave-wide load.  Load i uses the activations for i < A_LOADS, the second weight tensor
-// from B1_FROM on.  The loads are MUBUF loads with an LDS destination: unlike the global (FLAT-encoded)
-// form, the compiler does not count them against the LDS counter, so the operand reads of the matrix
-// loop keep fine-grained waits; the K advance goes into the scalar offset.
-// B_POLICY: cache policy of the weight loads.
-template <int LOADS, int A_LOADS, int B1_FROM, int B_POLICY>
-struct Fills {
-    static constexpr int kALoads = A_LOADS;
-    __amdgpu_buffer_rsrc_t a, b0, b1;
-    uint32_t voff[LOADS];
-    __device__ __forceinline__ void one(int i, uint8_t* lds_dst, uint32_t k_bytes) const {
-        // i is a compile-time constant after unrolling
-        const __amdgpu_buffer_rsrc_t r = i < A_LOADS ? a : (i >= B1_FROM ? b1 : b0);
-        if (i < A_LOADS)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lptr_t)lds_dst, 16, voff[i], k_bytes, 0, 0);
-        else
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lptr_t)lds_dst, 16, voff[i], k_bytes, 0, B_POLICY);
-    }
-};
-
 // ---------------------------------------------------------------------------------------------
 // tiles on 16x16x32 matrix instructions, four waves
 // ---------------------------------------------------------------------------------------------
@@ -80,14 +58,165 @@ struct Fills {
 // instruction, so the requests for the next slabs are spread over the whole slab (a burst of fills from
 // every wave right after the barrier backs up the address unit and stalls the matrix pipe behind it).
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 
-// c += a x b with the accumulator pinned to the accumulation registers: a wave of these tiles holds 256
-// accumulator values, exactly the accumulation half of its register budget, and must never shuffle them
-// through the other half.  The compiler does not see the instruction inside the statement, so the code
-// that reads the accumulators after the last one waits out its latency itself.
-__device__ __forceinline__ void mfma_16x16x32(f32x4& c, const bf16x8& a, const bf16x8& b) {
-    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+constexpr int kRsrcFlags = 0x00020000;  // raw buffer of 32-bit words, no swizzle (gfx9 descriptor word 3)
+constexpr int kDeviceScope = 16;        // cache policy bit sc1 of the buffer instructions
+
+// f(0), f(1), .. f(N - 1) with compile-time arguments
+template <class F, int... Is>
+__device__ __forceinline__ void each_of(std::integer_sequence<int, Is...>, F&& f) {
+    (f(std::integral_constant<int, Is>{}), ...);
 }
+template <int N, class F>
+__device__ __forceinline__ void each(F&& f) {
+    each_of(std::make_integer_sequence<int, N>{}, f);
+}
+
+// The accumulators: a wave of the 256-wide tiles holds 256 values, exactly the accumulation half of its register budget, and must
+// never move them.  As variables they leave that to the compiler, whose allocator, with no register to spare, moved hundreds of
+// them between the loops for the different tile heights (and knows neither the instruction inside an asm statement nor the
+// wait states it asks for).  So they have fixed places, named in the statements: fragment F in a[4F .. 4F+3].  The compiler
+// itself uses none of these registers (it has 256 others, and the kernels need no more; the kernel's first statement
+// makes it count them).  The code that reads them after the last matrix instruction waits out its latency itself.
+template <int F>
+__device__ __forceinline__ void acc_mfma(const bf16x8& a, const bf16x8& b) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 a[%0:%1], %2, %3, a[%0:%1]" ::"n"(4 * F), "n"(4 * F + 3), "v"(a), "v"(b));
+}
+template <int F>
+__device__ __forceinline__ void acc_zero() {
+    asm volatile(
+        "v_accvgpr_write_b32 a[%0], 0\n\tv_accvgpr_write_b32 a[%1], 0\n\t"
+        "v_accvgpr_write_b32 a[%2], 0\n\tv_accvgpr_write_b32 a[%3], 0" ::"n"(4 * F), "n"(4 * F + 1), "n"(4 * F + 2), "n"(4 * F + 3));
+}
+template <int F>
+__device__ __forceinline__ f32x4 acc_read() {
+    f32x4 c;
+    asm volatile("v_accvgpr_read_b32 %0, a[%1]" : "=v"(c[0]) : "n"(4 * F));
+    asm volatile("v_accvgpr_read_b32 %0, a[%1]" : "=v"(c[1]) : "n"(4 * F + 1));
+    asm volatile("v_accvgpr_read_b32 %0, a[%1]" : "=v"(c[2]) : "n"(4 * F + 2));
+    asm volatile("v_accvgpr_read_b32 %0, a[%1]" : "=v"(c[3]) : "n"(4 * F + 3));
+    return c;
+}
+
+// The block tile: 256 activation rows x BN weight rows over 64-wide K slabs, 2 x 2 waves.
+//
+// LDS rows are 128 bytes (64 bf16).  They are filled by direct global->LDS loads: one wave-wide load writes
+// 1 KB of consecutive LDS (64 lanes x 16 bytes = 8 rows), and each lane chooses WHICH 16-byte piece of its
+// row it fetches, so that piece kc of row r lands at position kc ^ ((r >> 1) & 7): with the 64 LDS banks of
+// this chip, the 16 lanes that a 16-byte read serves per cycle then fall into 16 different bank groups, for
+// the fill as well as for the operand reads.  Lane l reads row (l & 15), piece (l >> 4) of a k-step and ends
+// with output columns 4*(l >> 4) .. +3 of activation row (l & 15) of each 16 x 16 sub-tile.
+//
+// The waves of a column take the 16-row activation sub-tiles in turn, so that a partly filled tile keeps all four waves
+// multiplying: its time follows its rows in steps of 32.  (With halves of a tile instead, 128 x 2048 x 768 with 129 to 200
+// rows on most experts 638 -> 618 us a layer, 60 x 2048 x 1408 with at most 127 227 -> 224.)
+//
+// SWIGLU: weight rows [0,BN/2) of the tile come from W_gate, [BN/2,BN) from W_up, for the same BN/2 hidden
+// columns; a wave holds matching gate and up columns and applies silu(g)*u itself.
+template <int BN_, bool SWIGLU_>
+struct Shape {
+    static constexpr int BM = kFfnTileM, BN = BN_, NW = 4, BK = 64;
+    static constexpr bool SWIGLU = SWIGLU_;
+    static constexpr int kThreads = 64 * NW;
+    static constexpr int kNCols = SWIGLU ? BN / 2 : BN;  // output columns of a block
+    static constexpr int TM = BM / 2 / 16, TN = BN / 2 / 16;
+    static constexpr int A_LOADS = BM / 8 / NW, B_LOADS = BN / 8 / NW;  // wave-wide loads of eight 128-byte rows per slab
+    static constexpr int A_SLOT = BM * 128, B_SLOT = BN * 128, B_BASE = 2 * A_SLOT;
+    static constexpr int kLdsBytes = 2 * A_SLOT + 3 * B_SLOT;
+    static constexpr int TNO = SWIGLU ? TN / 2 : TN;  // 16-column output sub-tiles of a wave
+    static constexpr int fragment(int i, int j) { return i * TM + j; }  // of weight sub-tile i, activation sub-tile j
+    static_assert(TNO % 2 == 0 && B_LOADS % 2 == 0, "sub-tiles leave in pairs; a load must not straddle two tensors");
+};
+
+// Which part of the product a block does next (uniform over the block).
+struct WorkItem {
+    int valid;
+    int e, row0, rows, n0;  // output rows [row0, row0 + rows) of expert e, output columns from n0
+    int first, slabs;       // its K slabs (all of them unless the item is cut along K)
+    int turn;               // the slab of these that the walk begins with (it wraps around)
+    int once;               // the weights are fetched with the non-temporal policy
+    int slices, slice;      // units of an item that is cut along K (1: not cut)
+    int unit, stride;       // where this unit's partial tile lies: unit of slice 0, units between slices
+    int ticket;             // index of the item's ticket
+    int short_unit;         // its partial tiles are in the region of the short items
+};
+
+// What a wave needs to request its pieces of a K slab: one buffer descriptor per operand tensor (the
+// block's activation rows, its weight rows, and for SwiGLU tiles the up-projection rows) and one 32-bit
+// byte offset per wave-wide load.  The loads are MUBUF loads with an LDS destination: unlike the global
+// (FLAT-encoded) form, the compiler does not count them against the LDS counter, so the operand reads of the
+// matrix loop keep fine-grained waits; the K advance goes into the scalar offset.
+// Each descriptor opens the block's own window of a tensor (its activation rows, its weight rows), so
+// 32-bit byte offsets suffice whatever the tensor size; with a gather list the window is the whole
+// unpermuted input, whose size the host checks.
+template <class S>
+struct Fills {
+    __amdgpu_buffer_rsrc_t a, b0, b1;
+    uint32_t va[S::A_LOADS], vb[S::B_LOADS];
+    int first, slabs, turn;
+    uint8_t* smem;
+    int wv;
+
+    __device__ __forceinline__ void weights_of_lane(int lane, int K) {  // the same for every item
+#pragma unroll
+        for (int i = 0; i < S::B_LOADS; ++i) {
+            const int r = (wv + S::NW * i) * 8 + lane / 8, kc = (lane % 8) ^ ((r >> 1) & 7);
+            const int rb = S::SWIGLU && r >= S::BN / 2 ? r - S::BN / 2 : r;  // the up-projection rows of the same hidden columns
+            vb[i] = ((uint32_t)rb * (uint32_t)K + kc * 8) * 2u;
+        }
+    }
+    __device__ __forceinline__ void aim(const WorkItem& w, const uint16_t* A, const uint16_t* B0, const uint16_t* B1,
+                                        const int32_t* gather, int lane, int K, int Nout) {
+        a = __builtin_amdgcn_make_buffer_rsrc((void*)(gather ? A : A + (size_t)w.row0 * K), 0, -1, kRsrcFlags);
+        b0 = __builtin_amdgcn_make_buffer_rsrc((void*)(B0 + ((size_t)w.e * Nout + w.n0) * K), 0, -1, kRsrcFlags);
+        b1 = S::SWIGLU ? __builtin_amdgcn_make_buffer_rsrc((void*)(B1 + ((size_t)w.e * Nout + w.n0) * K), 0, -1, kRsrcFlags) : b0;
+        first = w.first;
+        slabs = w.slabs;
+        turn = w.turn;
+        uint32_t row[S::A_LOADS];
+#pragma unroll
+        for (int i = 0; i < S::A_LOADS; ++i) {
+            const int r = (wv + S::NW * i) * 8 + lane / 8;
+            const int rr = r < w.rows ? r : w.rows - 1;  // rows past the expert's end repeat its last row
+            row[i] = gather ? (uint32_t)gather[w.row0 + rr] : (uint32_t)rr;
+        }
+#pragma unroll
+        for (int i = 0; i < S::A_LOADS; ++i) {
+            const int r = (wv + S::NW * i) * 8 + lane / 8, kc = (lane % 8) ^ ((r >> 1) & 7);
+            va[i] = (row[i] * (uint32_t)K + kc * 8) * 2u;
+        }
+    }
+    __device__ __forceinline__ uint32_t k_bytes(int kt) const {
+        kt += turn;
+        kt = kt < slabs ? kt : kt - slabs;
+        return (uint32_t)(kt + first) * (S::BK * 2);
+    }
+    __device__ __forceinline__ void one_a(int i, int kt) const {
+        uint8_t* dst = smem + (kt & 1) * S::A_SLOT + (wv + S::NW * i) * 1024;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(a, (lptr_t)dst, 16, va[i], k_bytes(kt), 0, 0);
+    }
+    __device__ __forceinline__ void one_b(int i, int kt, int slot, bool once) const {
+        // i and once are compile-time constants after unrolling
+        uint8_t* dst = smem + S::B_BASE + slot * S::B_SLOT + (wv + S::NW * i) * 1024;
+        const __amdgpu_buffer_rsrc_t r = S::SWIGLU && i >= S::B_LOADS / 2 ? b1 : b0;
+        if (once)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lptr_t)dst, 16, vb[i], k_bytes(kt), 0, 2);  // bit 1: non-temporal
+        else
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lptr_t)dst, 16, vb[i], k_bytes(kt), 0, 0);
+    }
+    // the first two slabs of an item, always whole (a fixed number of requests: see wait_for_first_slab)
+    __device__ __forceinline__ void first_two(bool once) const {
+#pragma unroll
+        for (int kt = 0; kt < 2; ++kt) {
+#pragma unroll
+            for (int i = 0; i < S::B_LOADS; ++i) one_b(i, kt, kt, once);
+#pragma unroll
+            for (int i = 0; i < S::A_LOADS; ++i) one_a(i, kt);
+            __builtin_amdgcn_sched_barrier(0);  // their order is what the wait counts
+        }
+    }
+};
 
 // K loop of a wave.  LDS: two slots of activation rows, then a ring of three slots of weight rows (the
 // operand that streams from HBM gets a window of up to two slabs to land).  A slab is two 32-wide k-steps;
@@ -98,47 +227,29 @@ __device__ __forceinline__ void mfma_16x16x32(f32x4& c, const bf16x8& a, const b
 // Loads complete in order, so "all but the last B_LOADS" at barrier kt means the activations and weights of
 // slab kt+1 have landed while the weights of slab kt+2 may still be in flight.  LIVE = number of 16-row
 // activation sub-tiles per wave that are fetched and multiplied (the rest lie past the expert's last row).
-// STREAM: the walk over K starts at slab k0 + k_start and wraps around at the end of the block's share (see
-// TileConfig16); otherwise k_start is 0.
-template <int BM, int BN, int NW, int WM, int TM, int TN, int WTN, bool SWIGLU, int LOADS, bool STREAM, class FillsT>
-struct PipelinedLoop16 {
-    static constexpr int BK = 64;
-    static constexpr int A_SLOT = BM * 128, B_SLOT = BN * 128, B_BASE = 2 * A_SLOT;
-    static constexpr int LDS_BYTES = 2 * A_SLOT + 3 * B_SLOT;
-    static constexpr int A_LOADS = FillsT::kALoads, B_LOADS = LOADS - A_LOADS;
-    uint8_t* smem;
-    const FillsT& fills;
+// The caller has requested the first two slabs and waited for the first.
+//
+// ONCE (layers whose weights the memory-side cache does not keep, see ffn_weights_stream): an expert's only row tile, short
+// or partly filled, whose weight rows no other block reads, and the short tiles, row pieces and cut short items that run
+// after the big ones.  Two things bound such a stream, measured
+// on a read-only kernel with the same fills (256 rows of 128 bytes per slab, 3 GiB):
+//   - blocks that walk K in step all read at the same offset of a power-of-two row pitch, i.e. from a few memory
+//     channels: 4.9 TB/s at K = 4096, 5.0 at 2048; with the walk of the blocks starting at different slabs 6.3, 6.0;
+//   - keeping lines that nobody reads again: with the non-temporal policy on top 7.0, 6.9 (K = 1408, whose pitch
+//     spreads over the channels by itself: 6.3 -> 7.1).
+// Whole layers, before -> after: 64 experts x 4096 x 1408 with 37 tokens 392 -> 346 us, with 256 tokens 431 -> 380;
+// 8 experts x 4096 x 14336 with 16 tokens 503 -> 445; 60 x 2048 x 1408 with 1531 tokens 253 -> 228.
+// Other tiles share their weight rows with the blocks that run beside them at the same K: neither applies (the
+// policy on the short tiles of the joint list, whose experts' big tiles run beside them: 1 % slower).
+template <class S, bool ONCE>
+struct MatrixLoop {
+    const Fills<S>& fills;
     int a_lane, b_lane;  // byte offset, inside a slot, of this lane's piece of the wave's first row (k-step 0)
-    int KT, wv;  // slabs this block multiplies, wave index
-    int k0;      // first of them (0 unless the item is cut along K)
-    int k_start;  // STREAM: slab of the share the walk begins with, below KT
 
     // byte offset of weight sub-tile i relative to the wave's first weight row: with SwiGLU the second half
     // of the sub-tiles are the up-projection rows of the same hidden columns
     static __device__ __forceinline__ constexpr int b_tile(int i) {
-        return SWIGLU ? ((i / (TN / 2)) * (BN / 2) + (i % (TN / 2)) * 16) * 128 : i * 16 * 128;
-    }
-    __device__ __forceinline__ uint32_t k_bytes(int kt) const {
-        if (STREAM) {
-            kt += k_start;
-            kt = kt < KT ? kt : kt - KT;
-        }
-        return (uint32_t)(kt + k0) * (BK * 2);
-    }
-    __device__ __forceinline__ void fill_a(int i, int kt) const {
-        fills.one(i, smem + (kt & 1) * A_SLOT + (wv + NW * i) * 1024, k_bytes(kt));
-    }
-    __device__ __forceinline__ void fill_b(int i, int kt, int slot) const {
-        fills.one(A_LOADS + i, smem + B_BASE + slot * B_SLOT + (wv + NW * i) * 1024, k_bytes(kt));
-    }
-    template <int USED>
-    __device__ __forceinline__ void fill_a_all(int kt) const {
-#pragma unroll
-        for (int i = 0; i < USED; ++i) fill_a(i, kt);
-    }
-    __device__ __forceinline__ void fill_b_all(int kt, int slot) const {
-#pragma unroll
-        for (int i = 0; i < B_LOADS; ++i) fill_b(i, kt, slot);
+        return S::SWIGLU ? ((i / (S::TN / 2)) * (S::BN / 2) + (i % (S::TN / 2)) * 16) * 128 : i * 16 * 128;
     }
 
     // PHASE (0..3): where in a k-step this wave places its fill requests.  The four waves leave every barrier
@@ -146,27 +257,29 @@ struct PipelinedLoop16 {
     // the address unit in the same few cycles, its queue fills, and the waves that wait cannot issue their
     // next matrix instruction.  Each wave therefore shifts its requests by a different number of matrix
     // instructions.
-    template <int LIVE, int PHASE = 0>
-    __device__ __forceinline__ void run(f32x4 (&acc)[TN][TM]) const {
-        constexpr int A_USED = (LIVE * WM * 16 + NW * 8 - 1) / (NW * 8);  // loads of 8 rows a wave that hold live rows
-        static_assert(A_USED <= A_LOADS, "live rows");
-        fill_a_all<A_USED>(0);
-        fill_b_all(0, 0);
-        __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
-        __builtin_amdgcn_s_barrier();
-        if (1 < KT) fill_a_all<A_USED>(1);
-        if (1 < KT) fill_b_all(1, 1);
-        constexpr int NL = LIVE;
-        constexpr int NMFMA = TN * NL, NREAD = NL + TN;
+    // before_last(): called between the last two slabs; what it writes to this wave's LDS in the activation slot of the last
+    // slab but one is seen by the whole block when run() returns.
+    template <int LIVE, int PHASE, class F>
+    __device__ __forceinline__ void run(F&& before_last) const {
+        constexpr int TN = S::TN, A_LOADS = S::A_LOADS, B_LOADS = S::B_LOADS;
+        constexpr int NMFMA = TN * LIVE, NREAD = LIVE + TN;
+        // loads of eight rows a wave that hold live rows
+        constexpr int A_USED = LIVE * 2 * 16 / (S::NW * 8);
+        static_assert(A_USED >= 1 && A_USED <= A_LOADS, "live rows");
         // reads go out in the first half of a k-step, so that they have returned long before the barrier
-        constexpr int READ_EVERY = NMFMA / 2 / NREAD > 0 ? NMFMA / 2 / NREAD : 1;
-        constexpr int B_EVERY = NMFMA / B_LOADS > 0 ? NMFMA / B_LOADS : 1;
+        constexpr int READ_PER = NMFMA >= 2 * NREAD ? 1 : (2 * NREAD + NMFMA - 1) / NMFMA;  // reads per MFMA that has some
+        constexpr int READ_EVERY = READ_PER > 1 ? 1 : NMFMA / 2 / NREAD;
+        constexpr int B_EVERY = NMFMA / B_LOADS;
         constexpr int A_EVERY = NMFMA / A_USED;
         constexpr int B_OFF = PHASE * B_EVERY / 4 + (B_EVERY >= 8 ? B_EVERY / 8 : 0);
         constexpr int A_OFF = PHASE * A_EVERY / 4 + (A_EVERY >= 8 ? A_EVERY / 8 : 0);
-        static_assert(B_OFF < B_EVERY && A_OFF < A_EVERY, "request placement");
-        static_assert(NMFMA >= NREAD * READ_EVERY && NMFMA >= B_LOADS * B_EVERY && A_EVERY > 0, "k-step too short");
-        bf16x8 xa[2][NL], wb[2][TN];
+        static_assert(B_EVERY > 0 && A_EVERY > 0 && B_OFF < B_EVERY && A_OFF < A_EVERY, "request placement");
+        static_assert(NMFMA * READ_PER >= NREAD * READ_EVERY, "k-step too short");
+        bf16x8 xa[2][LIVE], wb[2][TN];
+        uint8_t* const smem = fills.smem;
+        const int KT = fills.slabs;
+        int a_lane = this->a_lane, b_lane = this->b_lane;
+        asm volatile("" : "+v"(a_lane), "+v"(b_lane));  // the first operand reads stay here, not ahead of all instances
 
         // r-th operand read of a k-step, in the order the MFMAs (activation sub-tile major) need them:
         // weight 0, activation 0, weights 1.., activations 1..  pa / pb: this lane's piece of the wave's first
@@ -179,10 +292,16 @@ struct PipelinedLoop16 {
             else if (r <= TN)
                 wb[set][r - 1] = *(const bf16x8*)(pb + b_tile(r - 1));
             else
-                xa[set][r - TN] = *(const bf16x8*)(pa + (r - TN) * WM * 16 * 128);
+                xa[set][r - TN] = *(const bf16x8*)(pa + (r - TN) * 2 * 16 * 128);
+        };
+        auto reads_at = [&](int q, int set, const uint8_t* pa, const uint8_t* pb) {
+            if (q % READ_EVERY != 0) return;
+#pragma unroll
+            for (int r = q / READ_EVERY * READ_PER; r < q / READ_EVERY * READ_PER + READ_PER; ++r)
+                if (r < NREAD) read_item(r, set, pa, pb);
         };
 #pragma unroll
-        for (int r = 0; r < NREAD; ++r) read_item(r, 0, smem + a_lane, smem + B_BASE + b_lane);
+        for (int r = 0; r < NREAD; ++r) read_item(r, 0, smem + a_lane, smem + S::B_BASE + b_lane);
 
         // One slab.  MORE: there is a next slab to read operands of; REFILL: slab kt+2 exists and is
         // requested.  Compile-time, so that the steady state carries no branches between its matrix
@@ -193,16 +312,16 @@ struct PipelinedLoop16 {
             const int next_slot = slot == 2 ? 0 : slot + 1;
             {
                 // the second k-step's pieces sit four pieces further: bit 6 of the byte offset
-                const uint8_t* pa = smem + (kt & 1) * A_SLOT + (a_lane ^ 64);
-                const uint8_t* pb = smem + B_BASE + slot * B_SLOT + (b_lane ^ 64);
-#pragma unroll
-                for (int q = 0; q < NMFMA; ++q) {
-                    const int j = q / TN, i = q % TN;
-                    mfma_16x16x32(acc[i][j], wb[0][i], xa[0][j]);
-                    if (q % READ_EVERY == 0 && q / READ_EVERY < NREAD) read_item(q / READ_EVERY, 1, pa, pb);
-                    if (REFILL && q % B_EVERY == B_OFF && q / B_EVERY < B_LOADS) fill_b(q / B_EVERY, kt + 2, slot2);
+                const uint8_t* pa = smem + (kt & 1) * S::A_SLOT + (a_lane ^ 64);
+                const uint8_t* pb = smem + S::B_BASE + slot * S::B_SLOT + (b_lane ^ 64);
+                each<NMFMA>([&](auto q_c) {
+                    constexpr int q = decltype(q_c)::value, j = q / TN, i = q % TN;
+                    acc_mfma<S::fragment(i, j)>(wb[0][i], xa[0][j]);
+                    reads_at(q, 1, pa, pb);
+                    if (REFILL && q % B_EVERY == B_OFF && q / B_EVERY < B_LOADS)
+                        fills.one_b(q / B_EVERY, kt + 2, slot2, ONCE);
                     __builtin_amdgcn_sched_barrier(0);
-                }
+                });
             }
             // slab kt+1 has landed for this wave (the younger weight requests may still fly), this wave's
             // operand reads of slab kt have returned (the LDS counter is part of the wait)
@@ -213,16 +332,15 @@ struct PipelinedLoop16 {
             __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_sched_barrier(0);
             {
-                const uint8_t* pa = smem + ((kt + 1) & 1) * A_SLOT + a_lane;
-                const uint8_t* pb = smem + B_BASE + next_slot * B_SLOT + b_lane;
-#pragma unroll
-                for (int q = 0; q < NMFMA; ++q) {
-                    const int j = q / TN, i = q % TN;
-                    mfma_16x16x32(acc[i][j], wb[1][i], xa[1][j]);
-                    if (MORE && q % READ_EVERY == 0 && q / READ_EVERY < NREAD) read_item(q / READ_EVERY, 0, pa, pb);
-                    if (REFILL && q % A_EVERY == A_OFF && q / A_EVERY < A_USED) fill_a(q / A_EVERY, kt + 2);
+                const uint8_t* pa = smem + ((kt + 1) & 1) * S::A_SLOT + a_lane;
+                const uint8_t* pb = smem + S::B_BASE + next_slot * S::B_SLOT + b_lane;
+                each<NMFMA>([&](auto q_c) {
+                    constexpr int q = decltype(q_c)::value, j = q / TN, i = q % TN;
+                    acc_mfma<S::fragment(i, j)>(wb[1][i], xa[1][j]);
+                    if (MORE) reads_at(q, 0, pa, pb);
+                    if (REFILL && q % A_EVERY == A_OFF && q / A_EVERY < A_USED) fills.one_a(q / A_EVERY, kt + 2);
                     __builtin_amdgcn_sched_barrier(0);
-                }
+                });
             }
         };
         int kt = 0, slot = 0;
@@ -232,271 +350,20 @@ struct PipelinedLoop16 {
             slab(kt, slot, yes, yes);
             slot = slot == 2 ? 0 : slot + 1;
         }
-        if (kt + 1 < KT) {
-            slab(kt++, slot, yes, no);
-            slot = slot == 2 ? 0 : slot + 1;
-        }
+        slab(kt++, slot, yes, no);  // (an item has two slabs at least)
+        slot = slot == 2 ? 0 : slot + 1;
+        before_last(kt);
+        __builtin_amdgcn_sched_barrier(0);
         slab(kt, slot, no, no);
         // the last matrix instructions retire before anything else reads the accumulators
         asm volatile("s_nop 15\n\ts_nop 15");
     }
 };
 
-// A block's place among the units of an item that is cut along K (slices == 1: the whole item).
-struct SplitUnit {
-    int slices, slice;
-    int stride;      // units between consecutive slices of one item
-    float* partial;  // slice 0 of this item
-    int* counter;    // this item's ticket
-};
-
-// Block tile of BM activation rows x BN weight rows over 64-wide K slabs, WAVES_M x WAVES_N waves, on the
-// loop above.  One output tile: rows [row0, row0+rows) of expert e times kNCols output columns from n0.
-//
-// LDS rows are 128 bytes (64 bf16).  They are filled by direct global->LDS loads: one wave-wide load writes
-// 1 KB of consecutive LDS (64 lanes x 16 bytes = 8 rows), and each lane chooses WHICH 16-byte piece of its
-// row it fetches, so that piece kc of row r lands at position kc ^ ((r >> 1) & 7): with the 64 LDS banks of
-// this chip, the 16 lanes that a 16-byte read serves per cycle then fall into 16 different bank groups, for
-// the fill as well as for the operand reads.  Lane l reads row (l & 15), piece (l >> 4) of a k-step and ends
-// with output columns 4*(l >> 4) .. +3 of activation row (l & 15) of each 16 x 16 sub-tile.
-//
-// SWIGLU: weight rows [0,BN/2) of the tile come from W_gate, [BN/2,BN) from W_up, for the same BN/2 hidden
-// columns; a wave holds matching gate and up columns and applies silu(g)*u itself.
-//
-// Two shapes are used: 256 x 256 with 2 x 2 waves (128 x 128 per wave) for full-height row tiles, and
-// 64 x 256 with 1 x 4 waves (64 x 64 per wave) for the short remainders, where the work is weight streaming.
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool SWIGLU, bool STREAM>
-struct TileConfig16 {
-    static constexpr int kBM = BM, kBN = BN;
-    static constexpr int kNCols = SWIGLU ? BN / 2 : BN;
-    static constexpr int kThreads = 64 * WAVES_M * WAVES_N;
-    static constexpr int kLdsBytes = 2 * BM * 128 + 3 * BN * 128;
-    // STREAM (layers whose weights the memory-side cache does not keep, see ffn_weights_stream): an expert's only row tile, short
-    // or partly filled, whose weight rows no other block reads, and the short tiles, row pieces and cut short items that run
-    // after the big ones.  Two things bound such a stream, measured
-    // on a read-only kernel with the same fills (256 rows of 128 bytes per slab, 3 GiB):
-    //   - blocks that walk K in step all read at the same offset of a power-of-two row pitch, i.e. from a few memory
-    //     channels: 4.9 TB/s at K = 4096, 5.0 at 2048; with the walk of the blocks starting at different slabs 6.3, 6.0;
-    //   - keeping lines that nobody reads again: with the non-temporal policy on top 7.0, 6.9 (K = 1408, whose pitch
-    //     spreads over the channels by itself: 6.3 -> 7.1).
-    // Whole layers, before -> after: 64 experts x 4096 x 1408 with 37 tokens 392 -> 346 us, with 256 tokens 431 -> 380;
-    // 8 experts x 4096 x 14336 with 16 tokens 503 -> 445; 60 x 2048 x 1408 with 1531 tokens 253 -> 228.
-    // Other tiles share their weight rows with the blocks that run beside them at the same K: neither applies (the
-    // policy on the short tiles of the joint list, whose experts' big tiles run beside them: 1 % slower).
-    static constexpr int kWeightPolicy = STREAM ? 2 : 0;  // bit 1: non-temporal
-
-    static __device__ __forceinline__ void run(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B0,
-                                               const uint16_t* __restrict__ B1, uint16_t* __restrict__ C,
-                                               const int32_t* __restrict__ gather, int e, int row0, int rows, int n0,
-                                               int K, int Nout, bool alone, uint8_t* smem, const SplitUnit& split) {
-    constexpr int NW = WAVES_M * WAVES_N;
-    constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;
-    constexpr int TM = WTM / 16, TN = WTN / 16;
-    constexpr int A_GROUPS = BM / 8, GROUPS = (BM + BN) / 8;  // eight 128-byte rows per wave-wide load
-    constexpr int LOADS = GROUPS / NW, A_LOADS = A_GROUPS / NW, B_LOADS = LOADS - A_LOADS;
-    constexpr int B1_FROM = SWIGLU ? A_LOADS + B_LOADS / 2 : LOADS;
-    static_assert(GROUPS % NW == 0 && A_GROUPS % NW == 0 && (!SWIGLU || B_LOADS % 2 == 0),
-                  "a wave-wide load must not straddle two tensors");
-    static_assert(WTM % 32 == 0 && WTN % 16 == 0 && (!SWIGLU || TN % 2 == 0), "wave tile");
-    static_assert(B_LOADS < 64, "vmcnt range");
-
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int wm = wv / WAVES_N, wn = wv % WAVES_N;
-
-    // ---- sources of this lane's pieces ----
-    // Each descriptor opens the block's own window of a tensor (its activation rows, its weight rows), so
-    // 32-bit byte offsets suffice whatever the tensor size; with a gather list the window is the whole
-    // unpermuted input, whose size the host checks.
-    constexpr int kRsrcFlags = 0x00020000;  // raw buffer of 32-bit words, no swizzle (gfx9 descriptor word 3)
-    using FillsT = Fills<LOADS, A_LOADS, B1_FROM, kWeightPolicy>;
-    FillsT fills;
-    fills.a = __builtin_amdgcn_make_buffer_rsrc((void*)(gather ? A : A + (size_t)row0 * K), 0, -1, kRsrcFlags);
-    fills.b0 = __builtin_amdgcn_make_buffer_rsrc((void*)(B0 + ((size_t)e * Nout + n0) * K), 0, -1, kRsrcFlags);
-    fills.b1 = SWIGLU ? __builtin_amdgcn_make_buffer_rsrc((void*)(B1 + ((size_t)e * Nout + n0) * K), 0, -1, kRsrcFlags)
-                      : fills.b0;
-#pragma unroll
-    for (int i = 0; i < LOADS; ++i) {
-        const int g = wv + NW * i;          // row group: activation rows first, then weight rows
-        const int r = g * 8 + lane / 8;
-        const int kc = (lane % 8) ^ ((r >> 1) & 7);
-        if (i < A_LOADS) {
-            const int rr = r < rows ? r : rows - 1;  // rows past the expert's end repeat its last row
-            const uint32_t arow = gather ? (uint32_t)gather[row0 + rr] : (uint32_t)rr;
-            fills.voff[i] = (arow * (uint32_t)K + kc * 8) * 2u;
-        } else {
-            int rb = r - BM;
-            if (SWIGLU && rb >= BN / 2) rb -= BN / 2;  // the up-projection rows of the same hidden columns
-            fills.voff[i] = ((uint32_t)rb * (uint32_t)K + kc * 8) * 2u;
-        }
-    }
-
-    // ---- this lane's operand pieces: row (lane & 15) of a sub-tile, piece (lane >> 4) of a k-step ----
-    // every sub-tile starts at a multiple of 16 rows, so the piece swizzle (row >> 1) & 7 depends on the
-    // lane only and the sub-tiles differ by constant offsets
-    const int lr = lane & 15, lk = lane >> 4;
-    const int piece0 = (lk ^ ((lr >> 1) & 7)) << 4;
-    const int a_lane = (wm * 16 + lr) * 128 + piece0;
-    const int b_lane = ((SWIGLU ? wn * (WTN / 2) : wn * WTN) + lr) * 128 + piece0;
-
-    f32x4 acc[TN][TM];
-#pragma unroll
-    for (int i = 0; i < TN; ++i)
-#pragma unroll
-        for (int j = 0; j < TM; ++j)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.f;
-
-    // The waves of a column of the block take its 16-row sub-tiles in turn, so that a partly filled tile keeps all of
-    // them multiplying: its time follows its rows in steps of 16 * WAVES_M.  `live` sub-tiles per wave hold rows of the
-    // expert (the same for the whole block; the one of the last wave may lie past the end); the main loop is specialised
-    // on it, so that the common full tile carries no conditionals, and fetches no others.
-    // (Halves of a tile as wave rows left two of four waves idle up to 128 rows: 128 x 2048 x 768 with 129 to 200 rows on
-    // most experts 638 -> 618 us a layer, 60 x 2048 x 1408 with at most 127 227 -> 224.)
-    int live = (rows + 16 * WAVES_M - 1) / (16 * WAVES_M);
-    if (WAVES_M == 1) live = (live + 1) & ~1;  // short tiles: memory binds, steps of 32 rows do
-    live = __builtin_amdgcn_readfirstlane(live);
-
-    using Loop = PipelinedLoop16<BM, BN, NW, WAVES_M, TM, TN, WTN, SWIGLU, LOADS, STREAM, FillsT>;
-    static_assert(Loop::LDS_BYTES == kLdsBytes, "LDS size");
-    // this block's share of the K slabs: all of them, or slice `split.slice` of `split.slices`
-    const int slabs_all = K / 64;
-    const int k_first = split.slices > 1 ? (int)((long long)split.slice * slabs_all / split.slices) : 0;
-    const int k_end = split.slices > 1 ? (int)((long long)(split.slice + 1) * slabs_all / split.slices) : slabs_all;
-    // The start of the walk depends on the output columns alone and only moves where the expert has a single tile: in a
-    // GEMM that is not cut along K a row's sums run in the same order whatever other experts share the launch.  (Which
-    // items are cut follows from the tiles of all experts.)
-    const int k_start = STREAM && alone ? (int)((long long)n0 * (k_end - k_first) / Nout) : 0;
-    Loop loop{smem, fills, a_lane, b_lane, k_end - k_first, __builtin_amdgcn_readfirstlane(wv), k_first, k_start};
-    if (live == TM) {
-        switch (loop.wv & 3) {
-            case 0: loop.template run<TM, 0>(acc); break;
-            case 1: loop.template run<TM, 1>(acc); break;
-            case 2: loop.template run<TM, 2>(acc); break;
-            default: loop.template run<TM, 3>(acc); break;
-        }
-    } else if constexpr (WAVES_M == 1) {
-        loop.template run<2>(acc);
-    } else {
-        // (a remainder of fewer rows than LIVE = 3 holds is a short tile)
-        if (live == 7)
-            loop.template run<7>(acc);
-        else if (live == 6)
-            loop.template run<6>(acc);
-        else if (live == 5)
-            loop.template run<5>(acc);
-        else if (live == 4)
-            loop.template run<4>(acc);
-        else
-            loop.template run<3>(acc);
-    }
-
-    // ---- an item cut along K: partial tiles through the workspace, the last unit to finish adds them ----
-    // The units of an item may run on different XCDs, whose L2 caches do not see each other's lines.  A fence
-    // that writes back and invalidates a whole L2 per unit costs more than the cut saves, so the partial tiles
-    // are stored and loaded with device-scope cache policy instead (written through to memory, read around
-    // caches that may be stale), each store is acknowledged before the ticket is taken, and the ticket is a
-    // device-scope atomic.
-    if (split.slices > 1) {
-        // a unit's partial tile is stored in register order (fragment, lane): whole 1 KB lines per wave store
-        constexpr int FRAGS = TN * TM;
-        constexpr int kDeviceScope = 16;  // cache policy bit sc1 of the buffer instructions
-        const size_t unit_floats = (size_t)BM * BN;
-        typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
-        const uint32_t at = (uint32_t)((wv * FRAGS * 64 + lane) * 16);  // + fragment * 1024 bytes
-        {
-            const __amdgpu_buffer_rsrc_t mine = __builtin_amdgcn_make_buffer_rsrc(
-                (void*)(split.partial + (size_t)(split.slice * split.stride) * unit_floats), 0, -1, kRsrcFlags);
-#pragma unroll
-            for (int i = 0; i < TN; ++i)
-#pragma unroll
-                for (int j = 0; j < TM; ++j) {
-                    const f32x4 v = acc[i][j];
-                    __builtin_amdgcn_raw_buffer_store_b128(*(const u32x4*)&v, mine, at + (i * TM + j) * 1024, 0, kDeviceScope);
-                }
-        }
-        __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));  // every store of this lane has been acknowledged
-        __syncthreads();
-        int* ticket = (int*)smem;  // the operand slots are free: the loop's last barrier follows its last read
-        if (tid == 0) *ticket = __hip_atomic_fetch_add(split.counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __syncthreads();
-        const int order = *ticket;
-        __syncthreads();
-        if (order != split.slices - 1) return;  // another unit of this item finishes later and does the sum
-#pragma unroll
-        for (int i = 0; i < TN; ++i)
-#pragma unroll
-            for (int j = 0; j < TM; ++j)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.f;
-        for (int sl = 0; sl < split.slices; ++sl) {  // slice order, whichever unit does it: the same sum every run
-            const __amdgpu_buffer_rsrc_t theirs = __builtin_amdgcn_make_buffer_rsrc(
-                (void*)(split.partial + (size_t)(sl * split.stride) * unit_floats), 0, -1, kRsrcFlags);
-            // up to 32 loads in flight at a time: a load that goes around the caches takes microseconds
-            constexpr int BATCH = FRAGS < 32 ? FRAGS : 32;
-            static_assert(FRAGS % BATCH == 0, "fragment batches");
-#pragma unroll
-            for (int g = 0; g < FRAGS; g += BATCH) {
-                u32x4 q[BATCH];
-#pragma unroll
-                for (int t = 0; t < BATCH; ++t)
-                    q[t] = __builtin_amdgcn_raw_buffer_load_b128(theirs, at + (g + t) * 1024, 0, kDeviceScope);
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int t = 0; t < BATCH; ++t) {
-                    const f32x4 p = *(const f32x4*)&q[t];
-                    const int i = (g + t) / TM, j = (g + t) % TM;
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) acc[i][j][v] += p[v];
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-    }
-
-    // ---- epilogue ----
-    // The tile is transposed through LDS (free after the K loop: its last barrier follows the last operand
-    // read), because a lane holds 8-byte runs scattered over 16 rows and a wave store of those touches 64
-    // cache lines: bf16 rows of OUT_COLS columns, 16-byte piece p of row r at position
-    // p ^ (r mod PIECES), then every row leaves as consecutive 16-byte pieces of consecutive lanes.
-    constexpr int TNO = SWIGLU ? TN / 2 : TN;
-    constexpr int OUT_COLS = kNCols, ROWB = OUT_COLS * 2, PIECES = ROWB / 16;
-    static_assert(BM * ROWB <= kLdsBytes, "the output tile must fit in the operand slots");
-    static_assert((PIECES & (PIECES - 1)) == 0, "piece swizzle");
-#pragma unroll
-    for (int j = 0; j < TM; ++j) {
-        const int r = (j * WAVES_M + wm) * 16 + lr;
-        uint8_t* lrow = smem + r * ROWB + (lk & 1) * 8;
-        const int sw = r & (PIECES - 1);
-#pragma unroll
-        for (int i = 0; i < TNO; ++i) {
-            const int piece = ((SWIGLU ? wn * (WTN / 2) : wn * WTN) + i * 16) / 8 + (lk >> 1);
-            float o[4];
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const float g = acc[i][j][v];
-                if (SWIGLU) {
-                    const float u = acc[i + TN / 2][j][v];
-                    o[v] = g * u * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(g * -1.4426950408889634f));
-                } else {
-                    o[v] = g;
-                }
-            }
-            uint2 pk;
-            pk.x = pack_bf16x2(o[0], o[1]);
-            pk.y = pack_bf16x2(o[2], o[3]);
-            *(uint2*)(lrow + ((piece ^ sw) << 4)) = pk;
-        }
-    }
-    __syncthreads();
-    for (int idx = tid; idx < BM * PIECES; idx += kThreads) {
-        const int r = idx / PIECES, pc = idx % PIECES;
-        if (r < rows) {
-            const uint4 v = *(const uint4*)(smem + r * ROWB + ((pc ^ (r & (PIECES - 1))) << 4));
-            *(uint4*)(C + (size_t)(row0 + r) * Nout + n0 + pc * 8) = v;
-        }
-    }
+// a read-only word that is the same for the whole wave, through the scalar cache (written by earlier kernels only)
+__device__ __forceinline__ int scalar_word(const int32_t* p, int i) {
+    return ((const __attribute__((address_space(4))) int32_t*)(uintptr_t)p)[i];
 }
-};
 
 // Decode a block's position in a list of `total` = tiles x column blocks work items, ordered
 // [column group][row tile][column in group].
@@ -507,159 +374,385 @@ __device__ inline void decode_item(int logical, int nt, int col_group, int& tile
     nb = cg * col_group + (rem - tile * col_group);
 }
 
-// One launch serves both kinds of tile.  Every XCD (block id mod 8) gets a contiguous eighth of the work, and
-// blocks that run together on an XCD share row and weight tiles in its L2.
+// The order of the work.  Every XCD (block id mod 8) gets a contiguous eighth of it, so that blocks that run together on an
+// XCD share row and weight tiles in its L2, and its blocks take the next position of that eighth as they get free.
 //
 // split_hdr[4] set (see the tile schedule: a long launch that is never cut along K): the blocks walk the list
 // that holds both kinds expert by expert, so the short tiles of an expert run next to its big tiles and their
-// weight streaming overlaps matrix work.
+// weight streaming overlaps matrix work.  The last split_hdr[5] items of the order are not dealt out in eighths: whichever
+// XCD has a compute unit free takes the next one, so that an XCD that runs a few per cent slower than the others
+// (they differ) does not end the launch alone.
 //
 // Otherwise the two lists one after the other: the XCD's eighth of the big items, then its eighth of the short
 // ones (longest first).  The last split_hdr[0] big items of an XCD's share run as split_hdr[1] units each; the
-// units follow the XCD's whole items in launch order, slice by slice, so that the units that run together read
-// the same K range of the tiles they share.
-//
-// Big, Small: tiles whose weight rows other blocks read beside them; BigStream, SmallStream: tiles that stream them (the same
-// two classes where the weights are to stay in the caches, see ffn_weights_stream).
-template <class Big, class BigStream, class Small, class SmallStream, bool SWIGLU>
-__global__ __launch_bounds__(Big::kThreads) void ffn_gemm_bf16_kernel(
+// units follow the XCD's whole items, slice by slice, so that the units that run together read
+// the same K range of the tiles they share.  A GEMM too short in K to be cut there runs the few big items left over
+// after the XCD's last full round (split_hdr[6]) as kFfnRowPieces quarters of their rows each: twice the compute-unit time,
+// on compute units that would have idled, in half the item's time.
+template <class S>
+struct WorkOrder {
+    const TileListArgs& L;
+    int slabs, Nout, group_big, group_short, xcd;
+    bool stream;
+    bool joint;
+    int nt_big, nt_short;        // row tiles (joint: all of them in nt_big)
+    int base_big, base_short;    // first item of this XCD's eighth
+    int whole, pieces, whole_s, units, units_s;  // positions of each kind, in this order
+    int cut, cut_here, slices, cut_s, cut_s_here, slices_s;
+    int fixed, pool;             // joint: items dealt out in eighths, items shared at the end
+    int few_big;                 // less than a round of big items
+
+    __device__ __forceinline__ WorkOrder(const TileListArgs& lists, const int32_t* hdr, int K, int Nout_, int gb, int gs, bool stream_)
+        : L(lists), slabs(K / S::BK), Nout(Nout_), group_big(gb), group_short(gs), xcd(blockIdx.x & 7), stream(stream_) {
+        const int ncol = Nout / S::kNCols;
+        joint = scalar_word(hdr, 4);
+        pieces = whole_s = units = units_s = 0;
+        cut = cut_here = cut_s = cut_s_here = 0;
+        slices = slices_s = 1;
+        nt_short = base_short = fixed = pool = few_big = 0;
+        if (joint) {
+            nt_big = scalar_word(L.u_count, 0);
+            pool = scalar_word(hdr, 5);
+            fixed = nt_big * ncol - pool;
+            const int chunk = (fixed + 7) >> 3;
+            base_big = xcd * chunk;
+            whole = max(0, min(chunk, fixed - base_big));
+        } else {
+            nt_big = scalar_word(L.b_count, 0);
+            nt_short = scalar_word(L.s_count, 0);
+            cut = scalar_word(hdr, 0), slices = scalar_word(hdr, 1);
+            cut_s = scalar_word(hdr, 2), slices_s = scalar_word(hdr, 3);
+            const int in_rows = scalar_word(hdr, 6);
+            const int total_b = nt_big * ncol, total_s = nt_short * ncol;
+            const int chunk_b = (total_b + 7) >> 3, chunk_s = (total_s + 7) >> 3;
+            few_big = chunk_b <= kFfnSplitUnits / 8;
+            base_big = xcd * chunk_b, base_short = xcd * chunk_s;
+            const int mine = max(0, min(chunk_b, total_b - base_big)), mine_s = max(0, min(chunk_s, total_s - base_short));
+            whole = min(mine, chunk_b - cut - in_rows);
+            whole_s = min(mine_s, chunk_s - cut_s);
+            pieces = in_rows > 0 ? (mine - whole) * kFfnRowPieces : 0;
+            cut_here = cut > 0 ? mine - whole : 0, cut_s_here = mine_s - whole_s;
+            units = cut_here * slices, units_s = cut_s_here * slices_s;
+        }
+    }
+    __device__ __forceinline__ int positions() const { return whole + pieces + whole_s + units + units_s; }
+
+    // position p of this XCD's share, or item p - kPoolItem of the shared end of the joint order
+    static constexpr int kPoolItem = 1 << 30;
+    __device__ __forceinline__ WorkItem at(int p) const {
+        WorkItem w;
+        w.valid = 0;
+        int logical, rows_word, tile, nb, quarter = -1, alone;
+        w.slices = 1, w.slice = w.unit = w.stride = w.ticket = w.short_unit = 0;
+        bool is_short = false;
+        if (p >= kPoolItem) {
+            if (p - kPoolItem >= pool) return w;
+            logical = fixed + p - kPoolItem;
+        } else if (p < whole) {
+            logical = base_big + p;
+        } else if ((p -= whole) < pieces) {
+            logical = base_big + whole + p / kFfnRowPieces;
+            quarter = p % kFfnRowPieces;
+        } else if ((p -= pieces) < whole_s) {
+            logical = base_short + p;
+            is_short = true;
+        } else if ((p -= whole_s) < units) {
+            w.slices = slices, w.stride = cut;
+            w.slice = p / cut_here;
+            const int idx = p - w.slice * cut_here;
+            logical = base_big + whole + idx;
+            w.unit = w.ticket = xcd * (kFfnSplitUnits / 8) + idx;
+        } else if ((p -= units) < units_s) {
+            w.slices = slices_s, w.stride = cut_s;
+            w.slice = p / cut_s_here;
+            const int idx = p - w.slice * cut_s_here;
+            logical = base_short + whole_s + idx;
+            w.unit = xcd * (kFfnSplitUnits / 8) + idx;
+            w.ticket = kFfnSplitUnits + w.unit;
+            is_short = true, w.short_unit = 1;
+        } else {
+            return w;
+        }
+        if (is_short)
+            decode_item(logical, nt_short, group_short, tile, nb);
+        else
+            decode_item(logical, nt_big, group_big, tile, nb);
+        // uniform, also where the divisions ran on the vector unit
+        tile = __builtin_amdgcn_readfirstlane(tile), nb = __builtin_amdgcn_readfirstlane(nb);
+        w.valid = 1;
+        w.n0 = nb * S::kNCols;
+        w.e = scalar_word(is_short ? L.s_expert : (joint ? L.u_expert : L.b_expert), tile);
+        w.row0 = scalar_word(is_short ? L.s_row0 : (joint ? L.u_row0 : L.b_row0), tile);
+        rows_word = scalar_word(is_short ? L.s_rows : (joint ? L.u_rows : L.b_rows), tile);
+        w.rows = rows_word & kTileRowsMask;
+        alone = stream && (rows_word & kAloneTileFlag);
+        if (is_short)
+            // with less than a round of big items those of the same expert run beside it and read the same weights (314 tokens,
+            // all at 8 experts x 3840 x 640: 169 -> 155 us)
+            w.once = stream && (alone || !few_big || w.slices > 1);
+        else
+            w.once = w.slices > 1 ? 0 : (quarter >= 0 ? stream : alone);
+        if (quarter >= 0) {  // a big tile has more than 64 rows: no quarter is empty
+            const int from = quarter * w.rows / kFfnRowPieces, to = (quarter + 1) * w.rows / kFfnRowPieces;
+            w.row0 += from;
+            w.rows = to - from;
+        }
+        w.first = w.slice * slabs / w.slices;
+        w.slabs = (w.slice + 1) * slabs / w.slices - w.first;
+        // The start of the walk depends on the output columns alone and only moves where the expert has a single tile: in a
+        // GEMM that is not cut along K a row's sums run in the same order whatever other experts share the launch.  (Which
+        // items are cut follows from the tiles of all experts.)
+        w.turn = alone && w.once ? (int)((long long)w.n0 * w.slabs / Nout) : 0;
+        return w;
+    }
+};
+
+// Writes sub-tile row j (16 rows of this wave) of a block's output tile: a lane holds 4 consecutive columns of a row in each
+// sub-tile; the lanes exchange halves between two sub-tiles (v_permlane16_swap), hold 16 bytes each, and a wave's store writes
+// 64 consecutive bytes of 16 rows.  Nothing passes through LDS, which by then receives the next item's first slabs.  Rows past
+// the tile's end lie past the end of the descriptor's window and are not written: the number of stores is the same for all.
+template <class S>
+struct TileWriter {
+    __amdgpu_buffer_rsrc_t c;
+    uint32_t at;      // byte offset of this lane's first column in row 0
+    uint32_t pitch;   // bytes of a row
+    __device__ __forceinline__ TileWriter(uint16_t* C, const WorkItem& w, int Nout, int wm, int wn, int lane) {
+        c = __builtin_amdgcn_make_buffer_rsrc((void*)(C + (size_t)w.row0 * Nout + w.n0), 0,
+                                              ((w.rows - 1) * Nout + S::kNCols) * 2, kRsrcFlags);
+        const int lr = lane & 15, lk = lane >> 4;
+        pitch = (uint32_t)Nout * 2u;
+        at = (uint32_t)(wm * 16 + lr) * pitch + (uint32_t)(wn * (S::kNCols / 2) + (lk & 1) * 16 + (lk >> 1) * 8) * 2u;
+    }
+    template <class Frag>
+    __device__ __forceinline__ void rows(int j, Frag&& frag) const {  // frag(i): sub-tile i's values, i a compile-time argument
+        each<S::TNO / 2>([&](auto pair_c) {
+            constexpr int i = 2 * decltype(pair_c)::value;
+            uint32_t half[2][2];
+            each<2>([&](auto s_c) {
+                constexpr int s = decltype(s_c)::value;
+                const f32x4 g = frag(std::integral_constant<int, i + s>{});
+                float o[4];
+                if constexpr (S::SWIGLU) {
+                    const f32x4 u = frag(std::integral_constant<int, i + s + S::TNO>{});
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        o[v] = g[v] * u[v] * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(g[v] * -1.4426950408889634f));
+                } else {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) o[v] = g[v];
+                }
+                half[s][0] = pack_bf16x2(o[0], o[1]);
+                half[s][1] = pack_bf16x2(o[2], o[3]);
+            });
+            const auto lo = __builtin_amdgcn_permlane16_swap(half[0][0], half[1][0], false, false);
+            const auto hi = __builtin_amdgcn_permlane16_swap(half[0][1], half[1][1], false, false);
+            const u32x4 out = {lo[0], hi[0], lo[1], hi[1]};
+            __builtin_amdgcn_raw_buffer_store_b128(out, c, at + (uint32_t)(j * 32) * pitch + i * 32, 0, 0);
+        });
+    }
+};
+
+// An item cut along K: partial tiles through the workspace; of the waves that hold the same part of the item's units, the last
+// one to finish adds them and writes the output.
+// The units of an item may run on different XCDs, whose L2 caches do not see each other's lines.  A fence
+// that writes back and invalidates a whole L2 per unit costs more than the cut saves, so the partial tiles
+// are stored and loaded with device-scope cache policy instead (written through to memory, read around
+// caches that may be stale), each store is acknowledged before the ticket is taken, and the ticket is a
+// device-scope atomic (a byte of it for each of the four waves).
+template <class S>
+__device__ __forceinline__ void finish_unit(const WorkItem& w, const TileWriter<S>& out,
+                                            float* split_partial, int32_t* split_counter, int wv, int lane, int live) {
+    constexpr int TN = S::TN, TM = S::TM;
+    // a unit's partial tile is stored in register order (fragment, lane): whole 1 KB lines per wave store
+    const size_t unit_floats = (size_t)(w.short_unit ? kFfnTileSmall : S::BM) * S::BN;
+    float* item = split_partial + (w.short_unit ? (size_t)kFfnSplitUnits * kFfnTileM * 256 : 0) + (size_t)w.unit * unit_floats;
+    // (a short item has two live sub-tiles at most: its fragments are packed)
+    const int height = w.short_unit ? kFfnTileSmall / 32 : TM;
+    const uint32_t at = (uint32_t)((wv * TN * height * 64 + lane) * 16);  // + fragment * 1024 bytes
+    {
+        const __amdgpu_buffer_rsrc_t mine = __builtin_amdgcn_make_buffer_rsrc(
+            (void*)(item + (size_t)(w.slice * w.stride) * unit_floats), 0, -1, kRsrcFlags);
+        each<TM>([&](auto j_c) {
+            constexpr int j = decltype(j_c)::value;
+            if (j < live)
+                each<TN>([&](auto i_c) {
+                    constexpr int i = decltype(i_c)::value;
+                    const f32x4 v = acc_read<S::fragment(i, j)>();
+                    __builtin_amdgcn_raw_buffer_store_b128(*(const u32x4*)&v, mine, at + (j * TN + i) * 1024, 0, kDeviceScope);
+                });
+        });
+    }
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));  // every store of this lane has been acknowledged
+    int order = 0;
+    if (lane == 0) order = __hip_atomic_fetch_add(split_counter + w.ticket, 1 << (8 * wv), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    order = (__builtin_amdgcn_readfirstlane(order) >> (8 * wv)) & 255;
+    if (order != w.slices - 1) return;  // another unit of this item finishes later and does the sum
+    const __amdgpu_buffer_rsrc_t all = __builtin_amdgcn_make_buffer_rsrc((void*)item, 0, -1, kRsrcFlags);
+    const uint32_t unit_bytes = (uint32_t)(w.stride * unit_floats * 4);
+#pragma unroll 1
+    for (int j = 0; j < live; ++j) {
+        f32x4 sum[TN];
+#pragma unroll
+        for (int i = 0; i < TN; ++i) sum[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+        for (int s0 = 0; s0 < w.slices; s0 += 4) {  // slice order, whichever unit does it: the same sum every run
+            // four slices in flight at a time: a load that goes around the caches takes microseconds
+            u32x4 q[4][TN];
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int i = 0; i < TN; ++i)
+                    q[t][i] = __builtin_amdgcn_raw_buffer_load_b128(
+                        all, at + (j * TN + i) * 1024, (uint32_t)(s0 + t < w.slices ? s0 + t : s0) * unit_bytes, kDeviceScope);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                if (s0 + t < w.slices) {
+#pragma unroll
+                    for (int i = 0; i < TN; ++i) sum[i] += *(const f32x4*)&q[t][i];
+                }
+        }
+        out.rows(j, [&](auto i_c) { return sum[decltype(i_c)::value]; });
+    }
+}
+
+// Waits until the first slab of an item has landed, for this wave: its requests are older than those of the second slab and
+// than the `stores` output stores of the item before, and memory operations complete in order.
+template <class S>
+__device__ __forceinline__ void wait_for_first_slab(int live_stored) {
+    constexpr int second = S::A_LOADS + S::B_LOADS, per = S::TNO / 2;
+    static_assert(second + per * S::TM < 64, "vmcnt range");
+    switch (live_stored) {
+        case 8: __builtin_amdgcn_s_waitcnt(waitcnt_vm(second + per * 8)); break;
+        case 7: __builtin_amdgcn_s_waitcnt(waitcnt_vm(second + per * 7)); break;
+        case 6: __builtin_amdgcn_s_waitcnt(waitcnt_vm(second + per * 6)); break;
+        case 5: __builtin_amdgcn_s_waitcnt(waitcnt_vm(second + per * 5)); break;
+        case 4: __builtin_amdgcn_s_waitcnt(waitcnt_vm(second + per * 4)); break;
+        case 3: __builtin_amdgcn_s_waitcnt(waitcnt_vm(second + per * 3)); break;
+        case 2: __builtin_amdgcn_s_waitcnt(waitcnt_vm(second + per * 2)); break;
+        case 1: __builtin_amdgcn_s_waitcnt(waitcnt_vm(second + per * 1)); break;
+        default: __builtin_amdgcn_s_waitcnt(waitcnt_vm(second)); break;
+    }
+}
+
+// Tickets of the blocks of an XCD lie in the last of its split units' tickets, that of the shared end in the last ticket of
+// the short items: at most kFfnSplitUnits / 8 - 1 items of an XCD are cut (what is left after full rounds).
+constexpr int kXcdTicket = kFfnSplitUnits / 8 - 1, kPoolTicket = kFfnSplitUnits + kFfnSplitUnits / 8 - 1;
+
+// One block per compute unit, for the whole launch: it requests the first two slabs of its next item before it writes the
+// output of the last, so that an item's start (its tile's description, then the first slabs: two to four microseconds in which
+// a block of its own would only wait) hides behind the output of the one before, and no blocks without work have to be
+// started and ended on every compute unit.  With a block per item and the output through LDS an item of 256 rows and 32 slabs
+// took 46 us of loop, 5 of output and 4 between it and the next; now 45, 3.5 and 3.  Layers of 60 x 2048 x 1408 with 1531
+// tokens 222 -> 219 us, 64 x 2048 x 1024 with 4096 285 -> 283 and with 3000 in separate calls 430 -> 419, 128 x 2048 x 768 with
+// 16384 596 -> 580.
+template <class S>
+__global__ __launch_bounds__(S::kThreads) void ffn_gemm_bf16_kernel(
     const uint16_t* __restrict__ A, const uint16_t* __restrict__ B0, const uint16_t* __restrict__ B1,
     uint16_t* __restrict__ C, const int32_t* __restrict__ gather, const TileListArgs L, int K, int Nout,
     int col_group_big, int col_group_small, const int32_t* __restrict__ split_hdr, float* split_partial,
-    int32_t* split_counter) {
-    static_assert(Big::kThreads == Small::kThreads, "one block size");
-    static_assert(Big::kNCols == Small::kNCols, "one column-block width: the joint list is decoded with it");
-    constexpr bool kStream = !std::is_same_v<Big, BigStream>;
+    int32_t* split_counter, int stream) {
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
-    const int32_t* __restrict__ b_expert = L.b_expert;
-    const int32_t* __restrict__ b_row0 = L.b_row0;
-    const int32_t* __restrict__ b_rows = L.b_rows;
-    const int32_t* __restrict__ s_expert = L.s_expert;
-    const int32_t* __restrict__ s_row0 = L.s_row0;
-    const int32_t* __restrict__ s_rows = L.s_rows;
-    const int cut = split_hdr ? split_hdr[0] : 0, slices = split_hdr ? split_hdr[1] : 1;
-    const int cut_s = split_hdr ? split_hdr[2] : 0, slices_s = split_hdr ? split_hdr[3] : 1;
-    const int xcd = blockIdx.x & 7;
-    int slot = blockIdx.x >> 3;
-    int tile, nb;
-    const SplitUnit one{1, 0, 0, nullptr, nullptr};
-    if (split_hdr && split_hdr[4]) {
-        const int nt = *L.u_count;
-        const int total = nt * (Nout / Big::kNCols);
-        // The last split_hdr[5] items of the order are not dealt out in eighths: whichever XCD has a compute
-        // unit free takes the next one (a counter), so that an XCD that runs a few per cent slower than the others
-        // (they differ) does not end the launch alone.  Every XCD brings blocks for a quarter of that pool, twice
-        // its even share; the ones that find the pool empty leave.
-        const int pool = split_hdr[5], fixed = total - pool, chunk = (fixed + 7) >> 3;
-        int logical = xcd * chunk + slot;
-        if (slot >= chunk) {
-            if (slot - chunk >= (pool + 3) >> 2) return;
-            int* next = (int*)smem;
-            if (threadIdx.x == 0)
-                *next = __hip_atomic_fetch_add(split_counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __syncthreads();
-            const int taken = *next;
-            __syncthreads();
-            if (taken >= pool) return;
-            logical = fixed + taken;
-        } else if (logical >= fixed) {
-            return;
+    if constexpr (S::TN * S::TM == 64)
+        asm volatile("" ::: "a255");  // the kernel has all accumulation registers
+    else
+        asm volatile("" ::: "a127");
+    static_assert(S::TN * S::TM == 64 || S::TN * S::TM == 32, "accumulators");
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wv >> 1, wn = wv & 1;
+    const WorkOrder<S> order(L, split_hdr, K, Nout, col_group_big, col_group_small, stream);
+    WorkItem cur = order.at(blockIdx.x >> 3);
+    if (!cur.valid) return;
+
+    // ---- this lane's operand pieces: row (lane & 15) of a sub-tile, piece (lane >> 4) of a k-step ----
+    // every sub-tile starts at a multiple of 16 rows, so the piece swizzle (row >> 1) & 7 depends on the
+    // lane only and the sub-tiles differ by constant offsets
+    const int lr = lane & 15, lk = lane >> 4;
+    const int piece0 = (lk ^ ((lr >> 1) & 7)) << 4;
+    const int a_lane = (wm * 16 + lr) * 128 + piece0;
+    const int b_lane = ((S::SWIGLU ? wn * (S::BN / 4) : wn * (S::BN / 2)) + lr) * 128 + piece0;
+
+    Fills<S> fills;
+    fills.smem = smem;
+    fills.wv = wv;
+    fills.weights_of_lane(lane, K);
+    fills.aim(cur, A, B0, B1, gather, lane, K, Nout);
+    if (cur.once)
+        fills.first_two(true);
+    else
+        fills.first_two(false);
+    int live_stored = 0;
+    for (;;) {
+        each<S::TN * S::TM>([](auto f_c) { acc_zero<decltype(f_c)::value>(); });
+        __builtin_amdgcn_sched_barrier(0);
+        wait_for_first_slab<S>(live_stored);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        // the block's next position: taken now, needed at the end of this item
+        int next = 0;
+        if (tid == 0) {
+            next = (gridDim.x >> 3) +
+                   __hip_atomic_fetch_add(split_counter + (blockIdx.x & 7) * (kFfnSplitUnits / 8) + kXcdTicket, 1, __ATOMIC_RELAXED,
+                                          __HIP_MEMORY_SCOPE_AGENT);
+            if (order.pool > 0 && next >= order.positions())
+                next = WorkOrder<S>::kPoolItem + __hip_atomic_fetch_add(split_counter + kPoolTicket, 1, __ATOMIC_RELAXED,
+                                                                        __HIP_MEMORY_SCOPE_AGENT);
         }
-        decode_item(logical, nt, col_group_big, tile, nb);
-        const int rows = L.u_rows[tile];
-        const int e = L.u_expert[tile], row0 = L.u_row0[tile], n0 = nb * Big::kNCols, n_rows = rows & kTileRowsMask;
-        const bool is_short = rows & kShortTileFlag, alone = kStream && (rows & kAloneTileFlag);
-        if (is_short && alone)
-            SmallStream::run(A, B0, B1, C, gather, e, row0, n_rows, n0, K, Nout, true, smem, one);
-        else if (is_short)  // its expert's big tiles run beside it and read the same weights
-            Small::run(A, B0, B1, C, gather, e, row0, n_rows, n0, K, Nout, false, smem, one);
-        else if (alone)
-            BigStream::run(A, B0, B1, C, gather, e, row0, n_rows, n0, K, Nout, true, smem, one);
+        // every wave gets a copy of it in a place that only its own requests fill
+        auto hand_over = [&](int kt) {
+            if (wv == 0) {
+                const int n = __builtin_amdgcn_readfirstlane(next);
+                if (lane < S::NW) *(volatile int*)(smem + ((kt + 1) & 1) * S::A_SLOT + lane * 1024) = n;
+            }
+        };
+        const int live = (cur.rows + 31) >> 5;
+        auto loop = [&](auto once_c) {
+            const MatrixLoop<S, decltype(once_c)::value> m{fills, a_lane, b_lane};
+            switch (live) {
+                case 8:
+                    switch (wv) {
+                        case 0: m.template run<8, 0>(hand_over); break;
+                        case 1: m.template run<8, 1>(hand_over); break;
+                        case 2: m.template run<8, 2>(hand_over); break;
+                        default: m.template run<8, 3>(hand_over); break;
+                    }
+                    break;
+                case 7: m.template run<7, 0>(hand_over); break;
+                case 6: m.template run<6, 0>(hand_over); break;
+                case 5: m.template run<5, 0>(hand_over); break;
+                case 4: m.template run<4, 0>(hand_over); break;
+                case 3: m.template run<3, 0>(hand_over); break;
+                case 2: m.template run<2, 0>(hand_over); break;
+                default: m.template run<1, 0>(hand_over); break;
+            }
+        };
+        if (cur.once)
+            loop(std::true_type{});
         else
-            Big::run(A, B0, B1, C, gather, e, row0, n_rows, n0, K, Nout, false, smem, one);
-        return;
-    }
-    const int nt_b = *L.b_count, nt_s = *L.s_count;
-    const int total_b = nt_b * (Nout / Big::kNCols), total_s = nt_s * (Nout / Small::kNCols);
-    const int chunk_b = (total_b + 7) >> 3, chunk_s = (total_s + 7) >> 3;
-    // per XCD: whole big items, the row pieces of big items (see below), whole short items, then the units of the cut
-    // big items and of the cut short ones (longest work first, the shortest pieces fill the end)
-    const int in_rows = split_hdr ? split_hdr[6] : 0;
-    constexpr int per_xcd = kFfnSplitUnits / 8;
-    const int whole = chunk_b - cut - in_rows, units = cut * slices, whole_s = chunk_s - cut_s, units_s = cut_s * slices_s;
-    if (slot < whole) {
-        const int logical = xcd * chunk_b + slot;
-        if (logical >= total_b) return;
-        decode_item(logical, nt_b, col_group_big, tile, nb);
-        const int rows = b_rows[tile];
-        if (kStream && (rows & kAloneTileFlag))
-            BigStream::run(A, B0, B1, C, gather, b_expert[tile], b_row0[tile], rows & kTileRowsMask, nb * Big::kNCols, K, Nout,
-                           true, smem, one);
-        else
-            Big::run(A, B0, B1, C, gather, b_expert[tile], b_row0[tile], rows & kTileRowsMask, nb * Big::kNCols, K, Nout, false,
-                     smem, one);
-        return;
-    }
-    slot -= whole;
-    // A GEMM too short in K to be cut there runs the few big items left over after the XCD's last full round as
-    // kRowPieces short-tile blocks each (rows 0-63, 64-127, ... of the item): twice the compute-unit time, on
-    // compute units that would have idled, in half the item's time.
-    constexpr int kRowPieces = Big::kBM / Small::kBM;
-    static_assert(Big::kBM % Small::kBM == 0, "a big tile is a whole number of short tiles");
-    if (slot < in_rows * kRowPieces) {
-        const int idx = slot / kRowPieces, piece = slot - idx * kRowPieces;
-        const int logical = xcd * chunk_b + whole + idx;
-        if (logical >= total_b) return;
-        decode_item(logical, nt_b, col_group_big, tile, nb);
-        const int first = piece * Small::kBM, left = (b_rows[tile] & kTileRowsMask) - first;
-        if (left <= 0) return;
-        SmallStream::run(A, B0, B1, C, gather, b_expert[tile], b_row0[tile] + first, left < Small::kBM ? left : Small::kBM,
-                         nb * Small::kNCols, K, Nout, b_rows[tile] & kAloneTileFlag, smem, one);
-        return;
-    }
-    slot -= in_rows * kRowPieces;
-    if (slot < whole_s) {
-        const int logical = xcd * chunk_s + slot;
-        if (logical >= total_s) return;
-        decode_item(logical, nt_s, col_group_small, tile, nb);
-        const bool alone = kStream && (s_rows[tile] & kAloneTileFlag);
-        // with less than a round of big items those of the same expert run beside it and read the same weights (314 tokens,
-        // all at 8 experts x 3840 x 640: 169 -> 155 us)
-        if (!kStream || (!alone && chunk_b <= per_xcd))
-            Small::run(A, B0, B1, C, gather, s_expert[tile], s_row0[tile], s_rows[tile] & kTileRowsMask, nb * Small::kNCols,
-                       K, Nout, false, smem, one);
-        else
-            SmallStream::run(A, B0, B1, C, gather, s_expert[tile], s_row0[tile], s_rows[tile] & kTileRowsMask,
-                             nb * Small::kNCols, K, Nout, alone, smem, one);
-        return;
-    }
-    slot -= whole_s;
-    if (slot < units) {
-        // unit (xcd, slice, idx) keeps its partial tile at unit index xcd * units-per-XCD + slice * cut + idx
-        const int slice = slot / cut, idx = slot - slice * cut;
-        const int logical = xcd * chunk_b + whole + idx;
-        if (logical >= total_b) return;
-        decode_item(logical, nt_b, col_group_big, tile, nb);
-        const SplitUnit su{slices, slice, cut,
-                           split_partial + (size_t)(xcd * per_xcd + idx) * ((size_t)Big::kBM * Big::kBN),
-                           split_counter + xcd * per_xcd + idx};
-        Big::run(A, B0, B1, C, gather, b_expert[tile], b_row0[tile], b_rows[tile] & kTileRowsMask, nb * Big::kNCols, K,
-                 Nout, false, smem, su);
-        return;
-    }
-    slot -= units;
-    if (slot < units_s) {
-        const int slice = slot / cut_s, idx = slot - slice * cut_s;
-        const int logical = xcd * chunk_s + whole_s + idx;
-        if (logical >= total_s) return;
-        decode_item(logical, nt_s, col_group_small, tile, nb);
-        // the short items' partial tiles follow those of the big items
-        float* region = split_partial + (size_t)kFfnSplitUnits * kFfnTileM * 256;
-        const SplitUnit su{slices_s, slice, cut_s,
-                           region + (size_t)(xcd * per_xcd + idx) * ((size_t)Small::kBM * Small::kBN),
-                           split_counter + kFfnSplitUnits + xcd * per_xcd + idx};
-        SmallStream::run(A, B0, B1, C, gather, s_expert[tile], s_row0[tile], s_rows[tile] & kTileRowsMask, nb * Small::kNCols,
-                         K, Nout, s_rows[tile] & kAloneTileFlag, smem, su);
+            loop(std::false_type{});
+        const int p = __builtin_amdgcn_readfirstlane(*(volatile int*)(smem + (cur.slabs & 1) * S::A_SLOT + wv * 1024));
+        const WorkItem nxt = order.at(p);
+        if (nxt.valid) {
+            fills.aim(nxt, A, B0, B1, gather, lane, K, Nout);
+            if (nxt.once)
+                fills.first_two(true);
+            else
+                fills.first_two(false);
+        }
+        const TileWriter<S> out(C, cur, Nout, wm, wn, lane);
+        if (cur.slices > 1) {
+            finish_unit<S>(cur, out, split_partial, split_counter, wv, lane, live);
+            live_stored = 0;
+        } else {
+            each<S::TM>([&](auto j_c) {
+                constexpr int j = decltype(j_c)::value;
+                if (j < live)
+                    out.rows(j, [&](auto i_c) { return acc_read<S::fragment(decltype(i_c)::value, j)>(); });
+            });
+            live_stored = live;
+        }
+        if (!nxt.valid) return;
+        cur = nxt;
     }
 }
 
@@ -677,43 +770,27 @@ static int column_group(int nb_total) {
     return 1;
 }
 
-template <class Big, class BigStream, class Small, class SmallStream, bool SWIGLU>
-static void launch_bf16_tiles(const void* A, const void* B0, const void* B1, void* C, const int32_t* gather,
-                        const FfnWorkspace& ws, int K, int Nout, const int32_t* split_hdr, int32_t* split_counter,
-                        hipStream_t st) {
-    constexpr int lds = Big::kLdsBytes > Small::kLdsBytes ? Big::kLdsBytes : Small::kLdsBytes;
-    auto kern = ffn_gemm_bf16_kernel<Big, BigStream, Small, SmallStream, SWIGLU>;
-    static std::atomic<uint64_t> configured{0};
-    once_per_device(configured, [&] {
-        (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    });
-    const int nb_b = Nout / Big::kNCols, nb_s = Nout / Small::kNCols;
-    // items cut along K (or into row pieces) add at most kFfnSplitUnits blocks per list, the pool at the end of the
-    // joint order as many blocks as it has items; + 16: both lists are cut into eight whole chunks
-    const long long grid =
-        (long long)nb_b * ws.big.max_launch + (long long)nb_s * ws.small.max_launch +
-        std::max(2 * kFfnSplitUnits, kFfnJointPoolRounds * compute_units()) + 16;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(Big::kThreads), lds, st, (const uint16_t*)A,
-                       (const uint16_t*)B0, (const uint16_t*)B1, (uint16_t*)C, gather, tile_list_args(ws, true), K, Nout,
-                       // short items that stream: all column blocks of a tile in a row, so that those that run together
-                       // start their walks over K at different slabs (they share activation rows only)
-                       column_group(nb_b), std::is_same_v<Big, BigStream> ? column_group(nb_s) : nb_s, split_hdr,
-                       ws.split_partial, split_counter);
-}
-
-// BN: weight rows of a block
 template <int BN, bool SWIGLU>
 static void launch_bf16(bool stream, const void* A, const void* B0, const void* B1, void* C, const int32_t* gather,
                         const FfnWorkspace& ws, int K, int Nout, const int32_t* split_hdr, int32_t* split_counter,
                         hipStream_t st) {
-    using Big = TileConfig16<kFfnTileM, BN, 2, 2, SWIGLU, false>;
-    using Small = TileConfig16<kFfnTileSmall, BN, 1, 4, SWIGLU, false>;
-    if (stream)
-        launch_bf16_tiles<Big, TileConfig16<kFfnTileM, BN, 2, 2, SWIGLU, true>, Small,
-                          TileConfig16<kFfnTileSmall, BN, 1, 4, SWIGLU, true>, SWIGLU>(A, B0, B1, C, gather, ws, K, Nout,
-                                                                                       split_hdr, split_counter, st);
-    else
-        launch_bf16_tiles<Big, Big, Small, Small, SWIGLU>(A, B0, B1, C, gather, ws, K, Nout, split_hdr, split_counter, st);
+    using S = Shape<BN, SWIGLU>;
+    auto kern = ffn_gemm_bf16_kernel<S>;
+    static std::atomic<uint64_t> configured{0};
+    once_per_device(configured, [&] {
+        (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, S::kLdsBytes);
+    });
+    const int nb = Nout / S::kNCols;
+    // a block per compute unit, the same number on every XCD; fewer where the plan cannot hold as many items (an item cut
+    // along K or into row pieces is eight at most)
+    const int per_xcd = std::max(1, compute_units() / 8);
+    const long long items = (long long)kFfnSplitMaxSlices * nb * ((long long)ws.big.max_launch + ws.small.max_launch);
+    const int grid = 8 * (int)std::min<long long>(per_xcd, (items + 7) / 8);
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(S::kThreads), S::kLdsBytes, st, (const uint16_t*)A,
+                       (const uint16_t*)B0, (const uint16_t*)B1, (uint16_t*)C, gather, tile_list_args(ws, true), K, Nout,
+                       // short items that stream: all column blocks of a tile in a row, so that those that run together
+                       // start their walks over K at different slabs (they share activation rows only)
+                       column_group(nb), stream ? nb : column_group(nb), split_hdr, ws.split_partial, split_counter, (int)stream);
 }
 
 // The arguments of the tile schedule for a descriptor and its workspace layout (host side).
