@@ -124,6 +124,14 @@ struct Shape {
     static constexpr int A_LOADS = BM / 8 / NW, B_LOADS = BN / 8 / NW;  // wave-wide loads of eight 128-byte rows per slab
     static constexpr int A_SLOT = BM * 128, B_SLOT = BN * 128, B_BASE = 2 * A_SLOT;
     static constexpr int kLdsBytes = 2 * A_SLOT + 3 * B_SLOT;
+    // Slabs in LDS for a tile of `live` x 32 rows: up to five of these, activations and weights of a slab lie side by side in a
+    // ring of three slots, up to two in a ring of four; above, two slots of activations and three of weights.
+    static constexpr int kRingLive = 5;
+    static __host__ __device__ constexpr int ring(int live) { return live <= 2 ? 4 : (live <= kRingLive ? 3 : 2); }
+    static __host__ __device__ constexpr int a_stride(int live) { return live <= kRingLive ? live * 4096 + B_SLOT : A_SLOT; }
+    static __host__ __device__ constexpr int b_stride(int live) { return live <= kRingLive ? live * 4096 + B_SLOT : B_SLOT; }
+    static __host__ __device__ constexpr int b_base(int live) { return live <= kRingLive ? live * 4096 : B_BASE; }
+    static_assert(4 * (2 * 4096 + B_SLOT) <= kLdsBytes && 3 * (kRingLive * 4096 + B_SLOT) <= kLdsBytes, "rings");
     static constexpr int TNO = SWIGLU ? TN / 2 : TN;  // 16-column output sub-tiles of a wave
     static constexpr int fragment(int i, int j) { return i * TM + j; }  // of weight sub-tile i, activation sub-tile j
     static_assert(TNO % 2 == 0 && B_LOADS % 2 == 0, "sub-tiles leave in pairs; a load must not straddle two tensors");
@@ -192,42 +200,61 @@ struct Fills {
         kt = kt < slabs ? kt : kt - slabs;
         return (uint32_t)(kt + first) * (S::BK * 2);
     }
-    __device__ __forceinline__ void one_a(int i, int kt) const {
-        uint8_t* dst = smem + (kt & 1) * S::A_SLOT + (wv + S::NW * i) * 1024;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(a, (lptr_t)dst, 16, va[i], k_bytes(kt), 0, 0);
+    // load i of slab kt's activations / weights into the slot that begins at byte `slot` of LDS
+    __device__ __forceinline__ void one_a(int i, int kt, int slot) const {
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(a, (lptr_t)(smem + slot + (wv + S::NW * i) * 1024), 16, va[i], k_bytes(kt), 0, 0);
     }
     __device__ __forceinline__ void one_b(int i, int kt, int slot, bool once) const {
         // i and once are compile-time constants after unrolling
-        uint8_t* dst = smem + S::B_BASE + slot * S::B_SLOT + (wv + S::NW * i) * 1024;
+        uint8_t* dst = smem + slot + (wv + S::NW * i) * 1024;
         const __amdgpu_buffer_rsrc_t r = S::SWIGLU && i >= S::B_LOADS / 2 ? b1 : b0;
         if (once)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lptr_t)dst, 16, vb[i], k_bytes(kt), 0, 2);  // bit 1: non-temporal
         else
             __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lptr_t)dst, 16, vb[i], k_bytes(kt), 0, 0);
     }
-    // the first two slabs of an item, always whole (a fixed number of requests: see wait_for_first_slab)
-    __device__ __forceinline__ void first_two(bool once) const {
+    // The first slabs of an item, as many as its loop keeps in LDS.  Returns how many requests are younger than those of the
+    // first slab.
+    __device__ __forceinline__ int start(int live, bool once) const {
+        const int n = min(S::ring(live), slabs);
+        for (int kt = 0; kt < n; ++kt) {
+            const int sa = kt * S::a_stride(live), sb = S::b_base(live) + kt * S::b_stride(live);
+            if (once) {
 #pragma unroll
-        for (int kt = 0; kt < 2; ++kt) {
+                for (int i = 0; i < S::B_LOADS; ++i) one_b(i, kt, sb, true);
+            } else {
 #pragma unroll
-            for (int i = 0; i < S::B_LOADS; ++i) one_b(i, kt, kt, once);
+                for (int i = 0; i < S::B_LOADS; ++i) one_b(i, kt, sb, false);
+            }
 #pragma unroll
-            for (int i = 0; i < S::A_LOADS; ++i) one_a(i, kt);
-            __builtin_amdgcn_sched_barrier(0);  // their order is what the wait counts
+            for (int i = 0; i < S::A_LOADS; ++i)
+                if (i < live) one_a(i, kt, sa);
+            __builtin_amdgcn_sched_barrier(0);  // their order is what the waits count
         }
+        return (n - 1) * (S::B_LOADS + live);
     }
 };
 
-// K loop of a wave.  LDS: two slots of activation rows, then a ring of three slots of weight rows (the
-// operand that streams from HBM gets a window of up to two slabs to land).  A slab is two 32-wide k-steps;
-// matrix instructions lag the operand reads by one k-step:
+// K loop of a wave.  A slab is two 32-wide k-steps; matrix instructions lag the operand reads by one k-step.  LIVE = number of
+// 16-row activation sub-tiles per wave that are fetched and multiplied (the rest lie past the expert's last row).
+//
+// High tiles (LIVE above kRingLive).  LDS: two slots of activation rows, then a ring of three slots of weight rows (the
+// operand that streams from HBM gets a window of up to two slabs to land):
 //     k-step 0 of slab kt:  MFMAs  |  operand reads of k-step 1  |  requests for the weights of slab kt+2
 //     barrier kt (slab kt+1 landed, slab kt no longer read)
 //     k-step 1 of slab kt:  MFMAs  |  operand reads of slab kt+1 |  requests for the activations of slab kt+2
 // Loads complete in order, so "all but the last B_LOADS" at barrier kt means the activations and weights of
-// slab kt+1 have landed while the weights of slab kt+2 may still be in flight.  LIVE = number of 16-row
-// activation sub-tiles per wave that are fetched and multiplied (the rest lie past the expert's last row).
-// The caller has requested the first two slabs and waited for the first.
+// slab kt+1 have landed while the weights of slab kt+2 may still be in flight.
+//
+// Low tiles.  A slab takes 0.2 to 0.9 us of matrix instructions, less than a fetch takes, so what bounds them is how much a
+// compute unit has in flight.  LDS: a ring of R slots (three; four up to two live sub-tiles) that hold activations and weights
+// of a slab:
+//     k-step 0 of slab kt:  MFMAs  |  operand reads of k-step 1
+//     barrier kt (slab kt+1 landed, slabs kt+2 .. kt+R-1 may fly, slab kt no longer read)
+//     k-step 1 of slab kt:  MFMAs  |  operand reads of slab kt+1 |  requests for slab kt+R
+// (with the slots of the high tiles 32 rows took 33.8 us over 32 slabs, with four 29.8: 1531 tokens of 60 x 2048 x 1408)
+//
+// The caller has requested the first slabs (Fills::start) and waited for the first one.
 //
 // ONCE (layers whose weights the memory-side cache does not keep, see ffn_weights_stream): an expert's only row tile, short
 // or partly filled, whose weight rows no other block reads, and the short tiles, row pieces and cut short items that run
@@ -259,13 +286,18 @@ struct MatrixLoop {
     // instructions.
     // before_last(): called between the last two slabs; what it writes to this wave's LDS in the activation slot of the last
     // slab but one is seen by the whole block when run() returns.
-    template <int LIVE, int PHASE, class F>
-    __device__ __forceinline__ void run(F&& before_last) const {
-        constexpr int TN = S::TN, A_LOADS = S::A_LOADS, B_LOADS = S::B_LOADS;
+    // draw(): called with two to four slabs left.  before_last(at): called between the last two slabs; what it writes to this
+    // wave's LDS from byte `at` (of a slot that is read no more) is seen by the whole block when run() returns.
+    template <int LIVE, int PHASE, class D, class F>
+    __device__ __forceinline__ void run(D&& draw, F&& before_last) const {
+        constexpr int TN = S::TN, B_LOADS = S::B_LOADS;
         constexpr int NMFMA = TN * LIVE, NREAD = LIVE + TN;
-        // loads of eight rows a wave that hold live rows
-        constexpr int A_USED = LIVE * 2 * 16 / (S::NW * 8);
-        static_assert(A_USED >= 1 && A_USED <= A_LOADS, "live rows");
+        constexpr int R = S::ring(LIVE);
+        constexpr bool RING = LIVE <= S::kRingLive;
+        constexpr int A_USED = LIVE * 2 * 16 / (S::NW * 8);  // loads of eight rows a wave that hold live rows
+        static_assert(A_USED == LIVE && LIVE <= S::A_LOADS, "live rows");
+        constexpr int PER = B_LOADS + A_USED;  // requests per slab
+        constexpr int A_STRIDE = S::a_stride(LIVE), B_STRIDE = S::b_stride(LIVE), B_BASE = S::b_base(LIVE);
         // reads go out in the first half of a k-step, so that they have returned long before the barrier
         constexpr int READ_PER = NMFMA >= 2 * NREAD ? 1 : (2 * NREAD + NMFMA - 1) / NMFMA;  // reads per MFMA that has some
         constexpr int READ_EVERY = READ_PER > 1 ? 1 : NMFMA / 2 / NREAD;
@@ -274,6 +306,7 @@ struct MatrixLoop {
         constexpr int B_OFF = PHASE * B_EVERY / 4 + (B_EVERY >= 8 ? B_EVERY / 8 : 0);
         constexpr int A_OFF = PHASE * A_EVERY / 4 + (A_EVERY >= 8 ? A_EVERY / 8 : 0);
         static_assert(B_EVERY > 0 && A_EVERY > 0 && B_OFF < B_EVERY && A_OFF < A_EVERY, "request placement");
+        constexpr int F_EVERY = NMFMA >= PER ? NMFMA / PER : 1, F_PER = (PER + NMFMA - 1) / NMFMA;  // low tiles
         static_assert(NMFMA * READ_PER >= NREAD * READ_EVERY, "k-step too short");
         bf16x8 xa[2][LIVE], wb[2][TN];
         uint8_t* const smem = fills.smem;
@@ -301,60 +334,87 @@ struct MatrixLoop {
                 if (r < NREAD) read_item(r, set, pa, pb);
         };
 #pragma unroll
-        for (int r = 0; r < NREAD; ++r) read_item(r, 0, smem + a_lane, smem + S::B_BASE + b_lane);
+        for (int r = 0; r < NREAD; ++r) read_item(r, 0, smem + a_lane, smem + B_BASE + b_lane);
 
-        // One slab.  MORE: there is a next slab to read operands of; REFILL: slab kt+2 exists and is
-        // requested.  Compile-time, so that the steady state carries no branches between its matrix
-        // instructions; the last two slabs run the other instances.  slot = kt mod 3.
-        auto slab = [&](int kt, int slot, auto more_c, auto refill_c) {
+        // One slab.  MORE: there is a next slab to read operands of; REFILL: slab kt+2 (low tiles: kt+R) exists and is
+        // requested.  Compile-time, so that the steady state carries no branches between its matrix instructions; the last
+        // slabs run the other instances.  sa, sb: slots of the slab's activations and weights.
+        auto slab = [&](int kt, int sa, int sb, auto more_c, auto refill_c) {
             constexpr bool MORE = decltype(more_c)::value, REFILL = decltype(refill_c)::value;
-            const int slot2 = slot == 0 ? 2 : slot - 1;  // (kt + 2) mod 3
-            const int next_slot = slot == 2 ? 0 : slot + 1;
+            constexpr int SA = RING ? R : 2, SB = RING ? R : 3;  // slots
+            const int sa1 = sa == SA - 1 ? 0 : sa + 1, sb1 = sb == SB - 1 ? 0 : sb + 1;
+            const int sb2 = sb1 == SB - 1 ? 0 : sb1 + 1;
             {
                 // the second k-step's pieces sit four pieces further: bit 6 of the byte offset
-                const uint8_t* pa = smem + (kt & 1) * S::A_SLOT + (a_lane ^ 64);
-                const uint8_t* pb = smem + S::B_BASE + slot * S::B_SLOT + (b_lane ^ 64);
+                const uint8_t* pa = smem + sa * A_STRIDE + (a_lane ^ 64);
+                const uint8_t* pb = smem + B_BASE + sb * B_STRIDE + (b_lane ^ 64);
                 each<NMFMA>([&](auto q_c) {
                     constexpr int q = decltype(q_c)::value, j = q / TN, i = q % TN;
                     acc_mfma<S::fragment(i, j)>(wb[0][i], xa[0][j]);
                     reads_at(q, 1, pa, pb);
-                    if (REFILL && q % B_EVERY == B_OFF && q / B_EVERY < B_LOADS)
-                        fills.one_b(q / B_EVERY, kt + 2, slot2, ONCE);
+                    if (!RING && REFILL && q % B_EVERY == B_OFF && q / B_EVERY < B_LOADS)
+                        fills.one_b(q / B_EVERY, kt + 2, B_BASE + sb2 * B_STRIDE, ONCE);
                     __builtin_amdgcn_sched_barrier(0);
                 });
             }
-            // slab kt+1 has landed for this wave (the younger weight requests may still fly), this wave's
+            // slab kt+1 has landed for this wave (younger requests may still fly), this wave's
             // operand reads of slab kt have returned (the LDS counter is part of the wait)
             if (REFILL)
-                __builtin_amdgcn_s_waitcnt(waitcnt_vm(B_LOADS));
+                __builtin_amdgcn_s_waitcnt(waitcnt_vm(RING ? (R - 2) * PER : B_LOADS));
+            else if (R > 3 && kt + 3 < KT)  // slabs kt+2 and kt+3 are the last
+                __builtin_amdgcn_s_waitcnt(waitcnt_vm(2 * PER));
+            else if (R > 2 && kt + 2 < KT)
+                __builtin_amdgcn_s_waitcnt(waitcnt_vm(PER));
             else
                 __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
             __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_sched_barrier(0);
             {
-                const uint8_t* pa = smem + ((kt + 1) & 1) * S::A_SLOT + a_lane;
-                const uint8_t* pb = smem + S::B_BASE + next_slot * S::B_SLOT + b_lane;
+                const uint8_t* pa = smem + sa1 * A_STRIDE + a_lane;
+                const uint8_t* pb = smem + B_BASE + sb1 * B_STRIDE + b_lane;
                 each<NMFMA>([&](auto q_c) {
                     constexpr int q = decltype(q_c)::value, j = q / TN, i = q % TN;
                     acc_mfma<S::fragment(i, j)>(wb[1][i], xa[1][j]);
                     if (MORE) reads_at(q, 0, pa, pb);
-                    if (REFILL && q % A_EVERY == A_OFF && q / A_EVERY < A_USED) fills.one_a(q / A_EVERY, kt + 2);
+                    if (!RING && REFILL && q % A_EVERY == A_OFF && q / A_EVERY < A_USED) fills.one_a(q / A_EVERY, kt + 2, sa * A_STRIDE);
+                    if (RING && REFILL && q % F_EVERY == 0)
+#pragma unroll
+                        for (int f = q / F_EVERY * F_PER; f < q / F_EVERY * F_PER + F_PER; ++f) {
+                            if (f < B_LOADS)
+                                fills.one_b(f, kt + R, B_BASE + sb * B_STRIDE, ONCE);
+                            else if (f < PER)
+                                fills.one_a(f - B_LOADS, kt + R, sa * A_STRIDE);
+                        }
                     __builtin_amdgcn_sched_barrier(0);
                 });
             }
         };
-        int kt = 0, slot = 0;
+        int kt = 0, sa = 0, sb = 0;
         const std::true_type yes{};
         const std::false_type no{};
-        for (; kt + 2 < KT; ++kt) {
-            slab(kt, slot, yes, yes);
-            slot = slot == 2 ? 0 : slot + 1;
+        auto advance = [&]() {
+            ++kt;
+            if (RING) {
+                sa = sb = sb == R - 1 ? 0 : sb + 1;
+            } else {
+                sa ^= 1;
+                sb = sb == 2 ? 0 : sb + 1;
+            }
+        };
+        while (kt + R < KT) {
+            slab(kt, sa, sb, yes, yes);
+            advance();
         }
-        slab(kt++, slot, yes, no);  // (an item has two slabs at least)
-        slot = slot == 2 ? 0 : slot + 1;
-        before_last(kt);
+        draw();
+        int at = 0;
+        do {  // (an item has two slabs at least)
+            slab(kt, sa, sb, yes, no);
+            at = sa * A_STRIDE;
+            advance();
+        } while (R > 2 && kt + 1 < KT);
+        before_last(at);
         __builtin_amdgcn_sched_barrier(0);
-        slab(kt, slot, no, no);
+        slab(kt, sa, sb, no, no);
         // the last matrix instructions retire before anything else reads the accumulators
         asm volatile("s_nop 15\n\ts_nop 15");
     }
@@ -405,24 +465,28 @@ struct WorkOrder {
     __device__ __forceinline__ WorkOrder(const TileListArgs& lists, const int32_t* hdr, int K, int Nout_, int gb, int gs, bool stream_)
         : L(lists), slabs(K / S::BK), Nout(Nout_), group_big(gb), group_short(gs), xcd(blockIdx.x & 7), stream(stream_) {
         const int ncol = Nout / S::kNCols;
-        joint = scalar_word(hdr, 4);
+        // everything at once: a block that starts waits for one fetch, not for one after the other
+        int h[7];
+#pragma unroll
+        for (int i = 0; i < 7; ++i) h[i] = scalar_word(hdr, i);
+        const int n_all = scalar_word(L.u_count, 0), n_big = scalar_word(L.b_count, 0), n_short = scalar_word(L.s_count, 0);
+        joint = h[4];
         pieces = whole_s = units = units_s = 0;
         cut = cut_here = cut_s = cut_s_here = 0;
         slices = slices_s = 1;
         nt_short = base_short = fixed = pool = few_big = 0;
         if (joint) {
-            nt_big = scalar_word(L.u_count, 0);
-            pool = scalar_word(hdr, 5);
+            nt_big = n_all;
+            pool = h[5];
             fixed = nt_big * ncol - pool;
             const int chunk = (fixed + 7) >> 3;
             base_big = xcd * chunk;
             whole = max(0, min(chunk, fixed - base_big));
         } else {
-            nt_big = scalar_word(L.b_count, 0);
-            nt_short = scalar_word(L.s_count, 0);
-            cut = scalar_word(hdr, 0), slices = scalar_word(hdr, 1);
-            cut_s = scalar_word(hdr, 2), slices_s = scalar_word(hdr, 3);
-            const int in_rows = scalar_word(hdr, 6);
+            nt_big = n_big, nt_short = n_short;
+            cut = h[0], slices = h[1];
+            cut_s = h[2], slices_s = h[3];
+            const int in_rows = h[6];
             const int total_b = nt_big * ncol, total_s = nt_short * ncol;
             const int chunk_b = (total_b + 7) >> 3, chunk_s = (total_s + 7) >> 3;
             few_big = chunk_b <= kFfnSplitUnits / 8;
@@ -616,22 +680,19 @@ __device__ __forceinline__ void finish_unit(const WorkItem& w, const TileWriter<
     }
 }
 
-// Waits until the first slab of an item has landed, for this wave: its requests are older than those of the second slab and
-// than the `stores` output stores of the item before, and memory operations complete in order.
-template <class S>
-__device__ __forceinline__ void wait_for_first_slab(int live_stored) {
-    constexpr int second = S::A_LOADS + S::B_LOADS, per = S::TNO / 2;
-    static_assert(second + per * S::TM < 64, "vmcnt range");
-    switch (live_stored) {
-        case 8: __builtin_amdgcn_s_waitcnt(waitcnt_vm(second + per * 8)); break;
-        case 7: __builtin_amdgcn_s_waitcnt(waitcnt_vm(second + per * 7)); break;
-        case 6: __builtin_amdgcn_s_waitcnt(waitcnt_vm(second + per * 6)); break;
-        case 5: __builtin_amdgcn_s_waitcnt(waitcnt_vm(second + per * 5)); break;
-        case 4: __builtin_amdgcn_s_waitcnt(waitcnt_vm(second + per * 4)); break;
-        case 3: __builtin_amdgcn_s_waitcnt(waitcnt_vm(second + per * 3)); break;
-        case 2: __builtin_amdgcn_s_waitcnt(waitcnt_vm(second + per * 2)); break;
-        case 1: __builtin_amdgcn_s_waitcnt(waitcnt_vm(second + per * 1)); break;
-        default: __builtin_amdgcn_s_waitcnt(waitcnt_vm(second)); break;
+// Waits until at most n memory operations of this wave are outstanding (the instruction takes a constant).
+__device__ __forceinline__ void wait_for_all_but(int n) {
+    switch (n) {
+#define CAPMOE_WAIT(k) \
+    case k: __builtin_amdgcn_s_waitcnt(waitcnt_vm(k)); break;
+#define CAPMOE_WAIT8(k) \
+    CAPMOE_WAIT(k) CAPMOE_WAIT(k + 1) CAPMOE_WAIT(k + 2) CAPMOE_WAIT(k + 3) CAPMOE_WAIT(k + 4) CAPMOE_WAIT(k + 5) \
+    CAPMOE_WAIT(k + 6) CAPMOE_WAIT(k + 7)
+        CAPMOE_WAIT8(0) CAPMOE_WAIT8(8) CAPMOE_WAIT8(16) CAPMOE_WAIT8(24) CAPMOE_WAIT8(32) CAPMOE_WAIT8(40) CAPMOE_WAIT8(48)
+        CAPMOE_WAIT8(56)
+#undef CAPMOE_WAIT8
+#undef CAPMOE_WAIT
+        default: __builtin_amdgcn_s_waitcnt(waitcnt_vm(0)); break;
     }
 }
 
@@ -660,8 +721,10 @@ __global__ __launch_bounds__(S::kThreads) void ffn_gemm_bf16_kernel(
     static_assert(S::TN * S::TM == 64 || S::TN * S::TM == 32, "accumulators");
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wv >> 1, wn = wv & 1;
+    int per_xcd = gridDim.x >> 3;
+    asm volatile("" : "+s"(per_xcd));  // kept, not fetched again with every ticket
     const WorkOrder<S> order(L, split_hdr, K, Nout, col_group_big, col_group_small, stream);
-    WorkItem cur = order.at(blockIdx.x >> 3);
+    WorkItem cur = order.at((int)(blockIdx.x >> 3));
     if (!cur.valid) return;
 
     // ---- this lane's operand pieces: row (lane & 15) of a sub-tile, piece (lane >> 4) of a k-step ----
@@ -677,79 +740,85 @@ __global__ __launch_bounds__(S::kThreads) void ffn_gemm_bf16_kernel(
     fills.wv = wv;
     fills.weights_of_lane(lane, K);
     fills.aim(cur, A, B0, B1, gather, lane, K, Nout);
-    if (cur.once)
-        fills.first_two(true);
-    else
-        fills.first_two(false);
-    int live_stored = 0;
+    // memory operations of this wave that are younger than the requests for the item's first slab: those for the slabs after it,
+    // and the stores of the item before; they complete in order
+    int younger = fills.start((cur.rows + 31) >> 5, cur.once);
     for (;;) {
-        each<S::TN * S::TM>([](auto f_c) { acc_zero<decltype(f_c)::value>(); });
+        const int live = (cur.rows + 31) >> 5;
+        each<S::TM>([&](auto j_c) {
+            if (decltype(j_c)::value < live)
+                each<S::TN>([](auto i_c) { acc_zero<S::fragment(decltype(i_c)::value, decltype(j_c)::value)>(); });
+        });
         __builtin_amdgcn_sched_barrier(0);
-        wait_for_first_slab<S>(live_stored);
+        wait_for_all_but(younger);
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
-        // the block's next position: taken now, needed at the end of this item
-        int next = 0;
-        if (tid == 0) {
-            next = (gridDim.x >> 3) +
-                   __hip_atomic_fetch_add(split_counter + (blockIdx.x & 7) * (kFfnSplitUnits / 8) + kXcdTicket, 1, __ATOMIC_RELAXED,
-                                          __HIP_MEMORY_SCOPE_AGENT);
-            if (order.pool > 0 && next >= order.positions())
-                next = WorkOrder<S>::kPoolItem + __hip_atomic_fetch_add(split_counter + kPoolTicket, 1, __ATOMIC_RELAXED,
-                                                                        __HIP_MEMORY_SCOPE_AGENT);
-        }
-        // every wave gets a copy of it in a place that only its own requests fill
-        auto hand_over = [&](int kt) {
+        // The block's next position.  (The offset of zero is one that the compiler takes for a value per lane: with an address
+        // that is the same in all lanes it would wait for the ticket at once, to hand it to the whole wave.)
+        int next = __builtin_nondeterministic_value(0), none = 0, handed = 0;
+        asm volatile("" : "+v"(none));
+        auto draw = [&]() {
+            if (tid == 0)
+                next = __hip_atomic_fetch_add(split_counter + (blockIdx.x & 7) * (kFfnSplitUnits / 8) + kXcdTicket + none, 1,
+                                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        };
+        // Every wave gets a copy of it.  Slots begin at multiples of 4 KB, of which wave w's own requests fill the w-th quarter:
+        // no other wave's requests for the next item overwrite what this one has not read yet.
+        auto hand_over = [&](int at) {
+            handed = at + wv * 1024;
             if (wv == 0) {
-                const int n = __builtin_amdgcn_readfirstlane(next);
-                if (lane < S::NW) *(volatile int*)(smem + ((kt + 1) & 1) * S::A_SLOT + lane * 1024) = n;
+                int n = 0;
+                if (lane == 0) {
+                    n = next + per_xcd;
+                    if (order.pool > 0 && n >= order.positions())
+                        n = WorkOrder<S>::kPoolItem + __hip_atomic_fetch_add(split_counter + kPoolTicket, 1, __ATOMIC_RELAXED,
+                                                                             __HIP_MEMORY_SCOPE_AGENT);
+                }
+                n = __builtin_amdgcn_readfirstlane(n);
+                if (lane < S::NW) *(volatile int*)(smem + at + lane * 1024) = n;
             }
         };
-        const int live = (cur.rows + 31) >> 5;
         auto loop = [&](auto once_c) {
             const MatrixLoop<S, decltype(once_c)::value> m{fills, a_lane, b_lane};
             switch (live) {
                 case 8:
                     switch (wv) {
-                        case 0: m.template run<8, 0>(hand_over); break;
-                        case 1: m.template run<8, 1>(hand_over); break;
-                        case 2: m.template run<8, 2>(hand_over); break;
-                        default: m.template run<8, 3>(hand_over); break;
+                        case 0: m.template run<8, 0>(draw, hand_over); break;
+                        case 1: m.template run<8, 1>(draw, hand_over); break;
+                        case 2: m.template run<8, 2>(draw, hand_over); break;
+                        default: m.template run<8, 3>(draw, hand_over); break;
                     }
                     break;
-                case 7: m.template run<7, 0>(hand_over); break;
-                case 6: m.template run<6, 0>(hand_over); break;
-                case 5: m.template run<5, 0>(hand_over); break;
-                case 4: m.template run<4, 0>(hand_over); break;
-                case 3: m.template run<3, 0>(hand_over); break;
-                case 2: m.template run<2, 0>(hand_over); break;
-                default: m.template run<1, 0>(hand_over); break;
+                case 7: m.template run<7, 0>(draw, hand_over); break;
+                case 6: m.template run<6, 0>(draw, hand_over); break;
+                case 5: m.template run<5, 0>(draw, hand_over); break;
+                case 4: m.template run<4, 0>(draw, hand_over); break;
+                case 3: m.template run<3, 0>(draw, hand_over); break;
+                case 2: m.template run<2, 0>(draw, hand_over); break;
+                default: m.template run<1, 0>(draw, hand_over); break;
             }
         };
         if (cur.once)
             loop(std::true_type{});
         else
             loop(std::false_type{});
-        const int p = __builtin_amdgcn_readfirstlane(*(volatile int*)(smem + (cur.slabs & 1) * S::A_SLOT + wv * 1024));
+        const int p = __builtin_amdgcn_readfirstlane(*(volatile int*)(smem + handed));
         const WorkItem nxt = order.at(p);
+        younger = 0;
         if (nxt.valid) {
             fills.aim(nxt, A, B0, B1, gather, lane, K, Nout);
-            if (nxt.once)
-                fills.first_two(true);
-            else
-                fills.first_two(false);
+            younger = fills.start((nxt.rows + 31) >> 5, nxt.once);
         }
         const TileWriter<S> out(C, cur, Nout, wm, wn, lane);
         if (cur.slices > 1) {
-            finish_unit<S>(cur, out, split_partial, split_counter, wv, lane, live);
-            live_stored = 0;
+            finish_unit<S>(cur, out, split_partial, split_counter, wv, lane, live);  // (its stores, if any, are not counted)
         } else {
             each<S::TM>([&](auto j_c) {
                 constexpr int j = decltype(j_c)::value;
                 if (j < live)
                     out.rows(j, [&](auto i_c) { return acc_read<S::fragment(decltype(i_c)::value, j)>(); });
             });
-            live_stored = live;
+            younger += live * (S::TNO / 2);
         }
         if (!nxt.valid) return;
         cur = nxt;

@@ -385,3 +385,9 @@ def _ffn_against_fp64(d, h, counts, seed):
 @pytest.mark.parametrize("d,h", [(128, 128), (256, 384), (384, 256)])
 def test_ffn_partly_filled_tiles(d, h):
     _ffn_against_fp64(d, h, [65, 95, 96, 97, 128, 129, 160, 161, 191, 192, 193, 224, 225, 255, 256 + 66, 512 + 127], d + h)
+
+
+@pytest.mark.parametrize("slabs_up,slabs_down", [(2, 4), (4, 6), (6, 8), (8, 2)])
+def test_ffn_short_walks_of_low_tiles(slabs_up, slabs_down):
+    """Fewer slabs of K than the rings of low tiles hold, as many, and more; every height a ring serves."""
+    _ffn_against_fp64(64 * slabs_up, 64 * slabs_down, [1, 32, 33, 64, 65, 96, 128, 129, 160, 161, 5, 256 + 20], slabs_up)
