@@ -1,4 +1,4 @@
-// The bf16 expert products of batches whose experts have few rows, 64 at most (see ffn.hip for the tile schedule and
+// The bf16 expert products of batches whose experts have few rows (see ffn.hip for the tile schedule and
 // the other kernels): decoding steps, and any batch with a small capacity.
 //
 // The work is streaming weights.  The blocks of ffn.hip take 256 weight rows each: with few experts or narrow ones
@@ -196,9 +196,8 @@ struct ThinTile {
     }
 };
 
-// expert_offset is the caller's: an expert of a plan from elsewhere may have more rows than the capacity leaves it, and then
-// has big tiles too.  So the blocks walk the joint list, as often around as it takes: with the plans of this library's own
-// drop once, because no expert has a second tile there.  A tile of more than 32 rows is done in passes of its blocks over
+// An expert may have more than 64 rows (see ffn_is_thin; and expert_offset is the caller's: in a plan from elsewhere also more
+// than the capacity leaves it), and then has big tiles too.  So the blocks walk the joint list, as often around as it takes.  A tile of more than 32 rows is done in passes of its blocks over
 // the same weights, which stay in the L2 for them (64 tokens top-6, 64 x 4096 x 1408, 56 rows on one expert 210 -> 187 us,
 // 64 top-2, 8 x 4096 x 1024, 53 rows 53 -> 47).
 template <bool SWIGLU, bool STREAM>
@@ -238,8 +237,14 @@ static long long rows_bound(const moe_desc_t& d, const Sizes& s) {
 // With more rows a block fetches as many activations as weights and loses (256 tokens, 24 rows per expert 382 -> 393),
 // except where the wide blocks are too few to fill half the chip: 64 tokens, 16 x 4096 x 512, 24 rows 90 -> 77 us, but
 // 8 x 4096 x 1024, 64 rows 97 -> 101 and x 2048 126 -> 176.
+// Where the capacity lets an expert have more than 64 rows, what it gets is not known here.  With 8 rows on average or fewer
+// most experts still have few and the others take several passes: 70 tokens top-1, 32 x 1792 x 2304, even and skewed,
+// 115 -> 83 and 80 -> 54 us, 160, all on one expert, 97 -> 54, 256 top-1, 64 x 2048 x 1408 97 -> 81, top-2 140 -> 134, 200 top-2,
+// 48 x 4096 x 2048 256 -> 251, 256 top-1, 32 x 3072 x 3072 215 -> 218; with more rows or tokens they lose (320 top-2, 60 x 2048 x
+// 1408 120 -> 132, 128 top-6, 64 x 4096 x 1408 338 -> 349, 512 top-2, 128 x 1024 x 768 82 -> 90).
 bool ffn_is_thin(const moe_desc_t& d, const Sizes& s) {
-    if (d.dtype != MOE_DTYPE_BF16 || rows_bound(d, s) > kFfnTileSmall) return false;
+    if (d.dtype != MOE_DTYPE_BF16) return false;
+    if (rows_bound(d, s) > kFfnTileSmall) return d.n_tokens <= 256 && s.max_rows <= 8ll * d.n_experts;
     if (s.max_rows <= 16ll * d.n_experts) return true;
     return s.max_rows <= 24ll * d.n_experts && (long long)d.n_experts * (d.d_hidden / 128) <= 128;
 }

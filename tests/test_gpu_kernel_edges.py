@@ -391,3 +391,10 @@ def test_ffn_partly_filled_tiles(d, h):
 def test_ffn_short_walks_of_low_tiles(slabs_up, slabs_down):
     """Fewer slabs of K than the rings of low tiles hold, as many, and more; every height a ring serves."""
     _ffn_against_fp64(64 * slabs_up, 64 * slabs_down, [1, 32, 33, 64, 65, 96, 128, 129, 160, 161, 5, 256 + 20], slabs_up)
+
+
+@pytest.mark.parametrize("counts", [[70], [0, 129, 0, 33], [200, 1, 17], [256], [1, 16, 17, 100, 65], [257], [3] * 32, [9] * 29])
+def test_ffn_few_tokens_on_experts_without_a_bound(counts):
+    """Up to 256 tokens and 8 per expert on average the few-row kernels run whatever the plan puts on one expert, above them the
+    others."""
+    _ffn_against_fp64(256, 384, counts + [0] * (32 - len(counts)), sum(counts))
