@@ -16,7 +16,7 @@ SOURCES = ["api.hip", "route.hip", "router_mfma.hip", "drop.hip", "permute.hip",
 # the packed-fp32 feature is switched off for all device code; the router file must not contract
 # multiplies and adds (its softmax is a fixed sequence of individually rounded operations)
 COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
-          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall", "-Wno-unused-command-line-argument"]
+          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-mllvm", "-amdgpu-kernarg-preload-count=16", "-Wall", "-Wno-unused-command-line-argument"]
 PER_FILE = {"route.hip": ["-ffp-contract=off", "-fhip-fp32-correctly-rounded-divide-sqrt"]}
 
 
