@@ -398,3 +398,10 @@ def test_ffn_few_tokens_on_experts_without_a_bound(counts):
     """Up to 256 tokens and 8 per expert on average the few-row kernels run whatever the plan puts on one expert, above them the
     others."""
     _ffn_against_fp64(256, 384, counts + [0] * (32 - len(counts)), sum(counts))
+
+
+@pytest.mark.parametrize("counts", [[276] * 66, [256] * 64 + [1], [256, 40] * 64 + [33] * 12, [257] * 63])
+def test_ffn_shared_last_round(counts):
+    """Short items after a round of big ones (four column blocks, 256 compute units), which all XCDs share at the end: as many as
+    a round, one tile, more, and just under a round of big items."""
+    _ffn_against_fp64(1024, 512, counts, len(counts))
