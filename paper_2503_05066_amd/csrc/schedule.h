@@ -9,8 +9,8 @@
 namespace capmoe {
 
 // Expert e with c rows gets floor(c / big) full tiles; a remainder above small_max rows becomes one
-// more (partly filled) big tile, a smaller one is cut into ceil(remainder / small) short tiles, which
-// run the same loop on 64-row blocks (few rows per weight byte: memory-bound work).
+// more (partly filled) big tile, a smaller one is cut into ceil(remainder / small) short tiles
+// (few rows per weight byte: memory-bound work).
 //
 // A GEMM runs its big work items (row tiles x column blocks) in rounds of one item per compute unit, and
 // every XCD (an eighth of the compute units with an L2 of its own) gets a contiguous eighth of them.  The
@@ -29,7 +29,7 @@ namespace capmoe {
 struct SplitArgs {
     int32_t* hdr;      // [kFfnSplitHdr]: big items per XCD that are cut (taken from the end of the XCD's share) and
                        // units per item, then the same for the short items, then 1 if the GEMM walks the joint list,
-                       // then how many items at the end of that list the XCDs share out by a counter (counter[0]),
+                       // then how many items at the end of that list the XCDs share out by a ticket of their own,
                        // then how many big items at the end of an XCD's share run as row pieces
     int32_t* counter;  // [2 * kFfnSplitUnits] tickets (big, short), zeroed here before every launch
     int ncol_big;      // column blocks of the GEMM's big items; 0: never cut
@@ -126,7 +126,7 @@ __host__ __device__ inline void ffn_schedule_header(int nb, int ns, int ncol_big
     // the end of the joint order that the XCDs share out among themselves as they get free
     hdr[5] = hdr[4] ? kFfnJointPoolRounds * cus : 0;
     // Big items left over after the XCD's last full round, in a GEMM too short in K to be cut there: run
-    // as row pieces (four short-tile blocks each) when those and the XCD's short items fit in one round
+    // as row pieces (four items of a quarter of the rows each) when those and the XCD's short items fit in one round
     // together, which then takes half an item's time instead of a whole one.
     const int left_over = per_xcd > 0 && chunk[0] > per_xcd ? chunk[0] % per_xcd : 0;
     hdr[6] = !hdr[4] && slabs < kFfnSplitMinK && short_tiles && left_over > 0 &&
