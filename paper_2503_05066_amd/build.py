@@ -13,7 +13,8 @@ OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libcapmoe.so")
 
 SOURCES = ["api.hip", "route.hip", "router_mfma.hip", "drop.hip", "permute.hip", "ffn.hip", "ffn_f32.hip", "ffn_thin.hip", "probe.hip"]
-# the packed-fp32 feature is switched off for all device code; the router file must not contract
+# the packed-fp32 feature is switched off for all device code; the first sixteen words of a kernel's arguments arrive in
+# registers (a token through 64 experts x 2048 x 1024: 38.3 -> 37.7 us); the router file must not contract
 # multiplies and adds (its softmax is a fixed sequence of individually rounded operations)
 COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-mllvm", "-amdgpu-kernarg-preload-count=16", "-Wall", "-Wno-unused-command-line-argument"]
