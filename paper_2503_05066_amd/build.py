@@ -1,12 +1,19 @@
 """Build libcapmoe.so (the HIP kernels and their C ABI) for gfx950 with hipcc, in-tree."""
 from __future__ import annotations
 
+import glob
 import os
+import shutil
 import subprocess
 import sys
+import tempfile
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
+if not __package__:  # run as a file
+    sys.path.insert(0, os.path.dirname(PKG))
+from paper_2503_05066_amd import accumulators  # noqa: E402
+
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
@@ -17,8 +24,11 @@ SOURCES = ["api.hip", "route.hip", "router_mfma.hip", "drop.hip", "permute.hip",
 # registers (a token through 64 experts x 2048 x 1024: 38.3 -> 37.7 us); the router file must not contract
 # multiplies and adds (its softmax is a fixed sequence of individually rounded operations)
 COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
-          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-mllvm", "-amdgpu-kernarg-preload-count=16", "-Wall", "-Wno-unused-command-line-argument"]
+          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-mllvm", "-amdgpu-kernarg-preload-count=16", "-Wall",
+          "-Wno-unused-command-line-argument"]
 PER_FILE = {"route.hip": ["-ffp-contract=off", "-fhip-fp32-correctly-rounded-divide-sqrt"]}
+# sources whose asm statements name accumulation registers: the assembly of the same compilation is checked
+NAMED_ACCUMULATORS = {"ffn.hip"}
 
 
 def _hipcc() -> str:
@@ -28,23 +38,34 @@ def _hipcc() -> str:
     raise RuntimeError("hipcc not found")
 
 
-def build(verbose: bool = False) -> str:
-    os.makedirs(OBJ, exist_ok=True)
-    hipcc = _hipcc()
-
-    def compile_one(src):
-        obj = os.path.join(OBJ, src.replace(".hip", ".o"))
-        cmd = [hipcc, *COMMON, *PER_FILE.get(src, []), "-c", os.path.join(CSRC, src), "-o", obj]
+def compile_source(source: str, obj: str, flags=(), named_accumulators: bool = False, verbose: bool = False) -> None:
+    with tempfile.TemporaryDirectory(prefix="capmoe_") as tmp:
+        # the intermediate files of a compilation lie beside its object
+        out = os.path.join(tmp, os.path.basename(obj)) if named_accumulators else obj
+        cmd = [_hipcc(), *COMMON, *flags, *(["-save-temps=obj"] if named_accumulators else []), "-c", source, "-o", out]
         r = subprocess.run(cmd, capture_output=True, text=True)
         if r.returncode != 0 or verbose:
             sys.stderr.write(r.stdout + r.stderr)
         if r.returncode != 0:
-            raise RuntimeError("hipcc failed on " + src)
+            raise RuntimeError("hipcc failed on " + os.path.basename(source))
+        if named_accumulators:
+            written, = glob.glob(os.path.join(tmp, "*amdgcn*gfx950*.s"))
+            with open(written) as f:
+                accumulators.check(f.read())
+            shutil.move(out, obj)
+
+
+def build(verbose: bool = False) -> str:
+    os.makedirs(OBJ, exist_ok=True)
+
+    def compile_one(src):
+        obj = os.path.join(OBJ, src.replace(".hip", ".o"))
+        compile_source(os.path.join(CSRC, src), obj, PER_FILE.get(src, []), src in NAMED_ACCUMULATORS, verbose)
         return obj
 
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
         objs = list(ex.map(compile_one, SOURCES))
-    r = subprocess.run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs],
+    r = subprocess.run([_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs],
                        capture_output=True, text=True)
     if r.returncode != 0:
         sys.stderr.write(r.stdout + r.stderr)
