@@ -280,7 +280,8 @@ int moe_profile_attach(moe_profile_t* table);
  *   header          host [2][8], out: for the gate/up GEMM, then the down GEMM:
  *                   [0] big work items per XCD that are cut along K, [1] units per such item,
  *                   [2], [3] the same for the short items, [4] 1 if the GEMM walks the joint tile list,
- *                   [5] work items at the end of that list that the XCDs share out by a counter,
+ *                   [5] work items at the end of the order (of the joint list, or of the short items)
+ *                   that the XCDs share out by a counter,
  *                   [6] big work items per XCD that run as four items of a quarter of the rows, [7] 0.
  *                   All zero for desc->dtype == fp32, whose kernels use none of this; the kernels of bf16 batches
  *                   with few rows per expert use the tiles but not the header.

@@ -439,9 +439,7 @@ __device__ inline void decode_item(int logical, int nt, int col_group, int& tile
 //
 // split_hdr[4] set (see the tile schedule: a long launch that is never cut along K): the blocks walk the list
 // that holds both kinds expert by expert, so the short tiles of an expert run next to its big tiles and their
-// weight streaming overlaps matrix work.  The last split_hdr[5] items of the order are not dealt out in eighths: whichever
-// XCD has a compute unit free takes the next one, so that an XCD that runs a few per cent slower than the others
-// (they differ) does not end the launch alone.
+// weight streaming overlaps matrix work.
 //
 // Otherwise the two lists one after the other: the XCD's eighth of the big items, then its eighth of the short
 // ones (longest first; ordered by height instead, with an eighth of every height for each XCD, the items that stream weights
@@ -450,6 +448,10 @@ __device__ inline void decode_item(int logical, int nt, int col_group, int& tile
 // the same K range of the tiles they share.  A GEMM too short in K to be cut there runs the few big items left over
 // after the XCD's last full round (split_hdr[6]) as kFfnRowPieces quarters of their rows each: twice the compute-unit time,
 // on compute units that would have idled, in half the item's time.
+//
+// The last split_hdr[5] items of the order (of the joint list, or of the short items) are not dealt out in eighths: whichever
+// XCD has a compute unit free takes the next one, so that an XCD that runs a few per cent slower than the others
+// (they differ) does not end the launch alone.
 template <class S>
 struct WorkOrder {
     const TileListArgs& L;
@@ -472,13 +474,13 @@ struct WorkOrder {
         for (int i = 0; i < 7; ++i) h[i] = scalar_word(hdr, i);
         const int n_all = scalar_word(L.u_count, 0), n_big = scalar_word(L.b_count, 0), n_short = scalar_word(L.s_count, 0);
         joint = h[4];
+        pool = h[5];
         pieces = whole_s = units = units_s = 0;
         cut = cut_here = cut_s = cut_s_here = 0;
         slices = slices_s = 1;
-        nt_short = base_short = fixed = pool = few_big = 0;
+        nt_short = base_short = fixed = few_big = 0;
         if (joint) {
             nt_big = n_all;
-            pool = h[5];
             fixed = nt_big * ncol - pool;
             const int chunk = (fixed + 7) >> 3;
             base_big = xcd * chunk;
@@ -489,10 +491,6 @@ struct WorkOrder {
             cut_s = h[2], slices_s = h[3];
             const int in_rows = h[6];
             const int total_b = nt_big * ncol, total_s = nt_short * ncol;
-            // After a round of big items or more the last round of short ones goes to whichever XCD has a compute unit free: their
-            // eighths end up to 15 us apart (4096 tokens of 64 x 2048 x 1024 277 -> 273 us a layer, 9400 of 96 x 1024 x 4480 946 -> 918;
-            // with short items alone the second ticket costs more: 1531 of 60 x 2048 x 1408 216 -> 218).
-            if (cut == 0 && cut_s == 0 && in_rows == 0 && total_b >= (int)gridDim.x) pool = min(total_s, (int)gridDim.x);
             fixed = total_s - pool;
             const int chunk_b = (total_b + 7) >> 3, chunk_s = (fixed + 7) >> 3;
             few_big = chunk_b <= kFfnSplitUnits / 8;
@@ -507,7 +505,7 @@ struct WorkOrder {
     }
     __device__ __forceinline__ int positions() const { return whole + pieces + whole_s + units + units_s; }
 
-    // position p of this XCD's share, or item p - kPoolItem of the shared end of the joint order
+    // position p of this XCD's share, or item p - kPoolItem of the shared end of the order
     static constexpr int kPoolItem = 1 << 30;
     __device__ __forceinline__ WorkItem at(int p) const {
         WorkItem w;

@@ -29,7 +29,8 @@ namespace capmoe {
 struct SplitArgs {
     int32_t* hdr;      // [kFfnSplitHdr]: big items per XCD that are cut (taken from the end of the XCD's share) and
                        // units per item, then the same for the short items, then 1 if the GEMM walks the joint list,
-                       // then how many items at the end of that list the XCDs share out by a ticket of their own,
+                       // then how many items at the end of the order (of the joint list, or of the short items) the
+                       // XCDs share out by a ticket of their own,
                        // then how many big items at the end of an XCD's share run as row pieces
     int32_t* counter;  // [2 * kFfnSplitUnits] tickets (big, short), zeroed here before every launch
     int ncol_big;      // column blocks of the GEMM's big items; 0: never cut
@@ -123,8 +124,6 @@ __host__ __device__ inline void ffn_schedule_header(int nb, int ns, int ncol_big
     }
     const long long joint_items = (long long)(nb + ns) * ncol_big;
     hdr[4] = joint_list && ns > 0 && slabs < kFfnSplitMinK && joint_items >= (long long)kFfnJointMinRounds * cus;
-    // the end of the joint order that the XCDs share out among themselves as they get free
-    hdr[5] = hdr[4] ? kFfnJointPoolRounds * cus : 0;
     // Big items left over after the XCD's last full round, in a GEMM too short in K to be cut there: run
     // as row pieces (four items of a quarter of the rows each) when those and the XCD's short items fit in one round
     // together, which then takes half an item's time instead of a whole one.
@@ -133,6 +132,15 @@ __host__ __device__ inline void ffn_schedule_header(int nb, int ns, int ncol_big
                      left_over * kFfnRowPieces + chunk[1] <= per_xcd
                  ? left_over
                  : 0;
+    // The end of the order that the XCDs share out among themselves as they get free.  After a round of big items or more
+    // that is the last round of short ones: their eighths end up to 15 us apart (4096 tokens of 64 x 2048 x 1024 277 -> 273 us
+    // a layer, 9400 of 96 x 1024 x 4480 946 -> 918; with short items alone the second ticket costs more: 1531 of
+    // 60 x 2048 x 1408 216 -> 218).
+    hdr[5] = 0;
+    if (hdr[4])
+        hdr[5] = kFfnJointPoolRounds * cus;
+    else if (hdr[0] == 0 && hdr[2] == 0 && hdr[6] == 0 && per_xcd > 0 && items[0] >= 8 * per_xcd)
+        hdr[5] = (int)(items[1] < 8 * per_xcd ? items[1] : 8 * per_xcd);
     hdr[7] = 0;
 }
 

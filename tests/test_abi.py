@@ -96,10 +96,12 @@ MODES = {"none": 0, "token": 1, "expanded": 2}
     ("mixtral", "none", (65, 4), [0, 1, 0, 1, 1, 256, 0, 0], [2, 5, 8, 4, 0, 0, 0, 0]),
     # Expanded Drop: 86 big items per XCD leave 22, too many to cut; the 4 short ones run as 8 units each
     ("mixtral", "expanded", (43, 2), [0, 1, 0, 1, 1, 256, 0, 0], [0, 1, 4, 8, 0, 0, 0, 0]),
-    # OLMoE shape: 2.7 rounds of items, K too short to cut, exactly two rounds of big items: nothing special
-    ("olmoe", "token", (64, 22), [0, 1, 0, 1, 0, 0, 0, 0], [0, 1, 0, 1, 0, 0, 0, 0]),
-    # fine-grained, Expanded Drop: gate/up has 161.25 big items per XCD, the 2 after the fifth round run as row pieces
-    ("finegrained", "expanded", (215, 11), [0, 1, 0, 1, 0, 0, 2, 0], [0, 1, 0, 1, 0, 0, 0, 0]),
+    # OLMoE shape: 2.7 rounds of items, K too short to cut, exactly two rounds of big items: the 176 short items after
+    # them are shared
+    ("olmoe", "token", (64, 22), [0, 1, 0, 1, 0, 176, 0, 0], [0, 1, 0, 1, 0, 176, 0, 0]),
+    # fine-grained, Expanded Drop: gate/up has 161.25 big items per XCD, the 2 after the fifth round run as row pieces;
+    # down has 215 and shares its 88 short ones
+    ("finegrained", "expanded", (215, 11), [0, 1, 0, 1, 0, 0, 2, 0], [0, 1, 0, 1, 0, 88, 0, 0]),
     # decode shape: short tiles only
     ("decode", "token", (0, 64), [0, 1, 0, 1, 0, 0, 0, 0], [0, 1, 0, 1, 0, 0, 0, 0]),
 ])
@@ -114,6 +116,25 @@ def test_tile_schedule_decisions_on_the_named_workloads(orc, name, mode, tiles, 
     got_tiles, (got_gate_up, got_down) = capmoe.moe_ffn_schedule_query(d, ref.plan.expert_count, 256)
     assert got_tiles == tiles
     assert got_gate_up == gate_up and got_down == down
+
+
+@pytest.mark.parametrize("big,short,shared,in_rows", [
+    (63, 80, 0, 0),      # 252 big items: less than a round of them, each XCD keeps its eighth of the short ones
+    (64, 0, 0, 0),       # nothing to share
+    (64, 1, 4, 0),
+    (64, 63, 252, 0),
+    (64, 64, 256, 0),    # exactly a round
+    (64, 76, 256, 0),    # the rest is dealt out in eighths
+    (65, 64, 256, 0),    # 33 big items per XCD, 29 on the last
+    (65, 10, 0, 1),      # the one left over and the short ones fit a round: row pieces, nothing is shared
+])
+def test_tile_schedule_shares_the_last_round_of_short_items(big, short, shared, in_rows):
+    """Four column blocks, K too short to cut, 256 compute units."""
+    d = capmoe.make_desc(1 << 15, 1024, 160, 1, 512, 1, capmoe.MODE_NONE, capmoe.SCOPE_GLOBAL, 1.0, capmoe.DTYPE_BF16)
+    counts = [256] * big + [1] * short
+    tiles, headers = capmoe.moe_ffn_schedule_query(d, counts + [0] * (160 - len(counts)), 256)
+    assert tiles == (big, short)
+    assert headers == [[0, 1, 0, 1, 0, shared, in_rows, 0]] * 2
 
 
 def test_tile_schedule_query_edge_cases():
