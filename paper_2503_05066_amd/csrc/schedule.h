@@ -116,31 +116,30 @@ __host__ __device__ inline void ffn_schedule_header(int nb, int ns, int ncol_big
     // so that short items start at once on the other compute units and both kinds end together.
     const int left_big = per_xcd > 0 ? chunk[0] % per_xcd : 0;
     const int big_cus = chunk[1] > 0 ? per_xcd * 2 * left_big / (2 * left_big + chunk[1]) : per_xcd;
-    for (int which = 0; which < 2; ++which) {
-        int cut = 0, slices = 1;
-        split_rule(chunk[which], per_xcd, which == 0 ? big_cus : per_xcd, slabs, cut, slices);
-        hdr[2 * which] = cut;
-        hdr[2 * which + 1] = slices;
-    }
+    int cut[2], slices[2];
+    for (int which = 0; which < 2; ++which)
+        split_rule(chunk[which], per_xcd, which == 0 ? big_cus : per_xcd, slabs, cut[which], slices[which]);
     const long long joint_items = (long long)(nb + ns) * ncol_big;
-    hdr[4] = joint_list && ns > 0 && slabs < kFfnSplitMinK && joint_items >= (long long)kFfnJointMinRounds * cus;
+    const bool joint = joint_list && ns > 0 && slabs < kFfnSplitMinK && joint_items >= (long long)kFfnJointMinRounds * cus;
     // Big items left over after the XCD's last full round, in a GEMM too short in K to be cut there: run
     // as row pieces (four items of a quarter of the rows each) when those and the XCD's short items fit in one round
     // together, which then takes half an item's time instead of a whole one.
-    const int left_over = per_xcd > 0 && chunk[0] > per_xcd ? chunk[0] % per_xcd : 0;
-    hdr[6] = !hdr[4] && slabs < kFfnSplitMinK && short_tiles && left_over > 0 &&
-                     left_over * kFfnRowPieces + chunk[1] <= per_xcd
-                 ? left_over
-                 : 0;
+    const int left_over = chunk[0] > per_xcd ? left_big : 0;
+    const int in_rows =
+        !joint && slabs < kFfnSplitMinK && short_tiles && left_over > 0 && left_over * kFfnRowPieces + chunk[1] <= per_xcd
+            ? left_over
+            : 0;
     // The end of the order that the XCDs share out among themselves as they get free.  After a round of big items or more
     // that is the last round of short ones: their eighths end up to 15 us apart (4096 tokens of 64 x 2048 x 1024 277 -> 273 us
     // a layer, 9400 of 96 x 1024 x 4480 946 -> 918; with short items alone the second ticket costs more: 1531 of
     // 60 x 2048 x 1408 216 -> 218).
-    hdr[5] = 0;
-    if (hdr[4])
-        hdr[5] = kFfnJointPoolRounds * cus;
-    else if (hdr[0] == 0 && hdr[2] == 0 && hdr[6] == 0 && per_xcd > 0 && items[0] >= 8 * per_xcd)
-        hdr[5] = (int)(items[1] < 8 * per_xcd ? items[1] : 8 * per_xcd);
+    int shared = 0;
+    if (joint)
+        shared = kFfnJointPoolRounds * cus;
+    else if (cut[0] == 0 && cut[1] == 0 && in_rows == 0 && chunk[0] > 0 && items[0] >= 8 * per_xcd)
+        shared = items[1] < 8 * per_xcd ? (int)items[1] : 8 * per_xcd;
+    hdr[0] = cut[0], hdr[1] = slices[0], hdr[2] = cut[1], hdr[3] = slices[1];
+    hdr[4] = joint, hdr[5] = shared, hdr[6] = in_rows;
     hdr[7] = 0;
 }
 
