@@ -284,8 +284,6 @@ struct MatrixLoop {
     // the address unit in the same few cycles, its queue fills, and the waves that wait cannot issue their
     // next matrix instruction.  Each wave therefore shifts its requests by a different number of matrix
     // instructions.
-    // before_last(): called between the last two slabs; what it writes to this wave's LDS in the activation slot of the last
-    // slab but one is seen by the whole block when run() returns.
     // draw(): called with two to four slabs left.  before_last(at): called between the last two slabs; what it writes to this
     // wave's LDS from byte `at` (of a slot that is read no more) is seen by the whole block when run() returns.
     template <int LIVE, int PHASE, class D, class F>
@@ -424,6 +422,11 @@ struct MatrixLoop {
 __device__ __forceinline__ int scalar_word(const int32_t* p, int i) {
     return ((const __attribute__((address_space(4))) int32_t*)(uintptr_t)p)[i];
 }
+
+// A word of LDS for another wave or from one.  (Through a generic pointer it would be a FLAT access, which waits for the
+// vector-memory counter as well: the whole round trip and all younger requests, with nothing else on the SIMD to run.)
+typedef __attribute__((address_space(3))) volatile int* lds_int_t;
+__device__ __forceinline__ lds_int_t lds_word(uint8_t* smem, int at) { return (lds_int_t)(smem + at); }
 
 // Decode a block's position in a list of `total` = tiles x column blocks work items, ordered
 // [column group][row tile][column in group].
@@ -780,7 +783,7 @@ __global__ __launch_bounds__(S::kThreads) void ffn_gemm_bf16_kernel(
                                                                              __HIP_MEMORY_SCOPE_AGENT);
                 }
                 n = __builtin_amdgcn_readfirstlane(n);
-                if (lane < S::NW) *(volatile int*)(smem + at + lane * 1024) = n;
+                if (lane < S::NW) *lds_word(smem, at + lane * 1024) = n;
             }
         };
         auto loop = [&](auto once_c) {
@@ -807,7 +810,7 @@ __global__ __launch_bounds__(S::kThreads) void ffn_gemm_bf16_kernel(
             loop(std::true_type{});
         else
             loop(std::false_type{});
-        const int p = __builtin_amdgcn_readfirstlane(*(volatile int*)(smem + handed));
+        const int p = __builtin_amdgcn_readfirstlane(*lds_word(smem, handed));
         const WorkItem nxt = order.at(p);
         younger = 0;
         if (nxt.valid) {

@@ -32,6 +32,8 @@ def test_accumulators_belong_to_the_asm_statements(hipcc, tmp_path):
                    check=True, capture_output=True, timeout=600)
     # every height of a tile, twice (how its weights are fetched), in three kernels
     assert accumulators.check(out.read_text()) > 5000
+    # FLAT accesses wait for every request in flight; LDS and global memory are told apart everywhere
+    assert not [line for line in out.read_text().splitlines() if line.strip().startswith("flat_")]
 
 
 def test_the_build_refuses_accumulators_that_the_compiler_uses(hipcc, tmp_path):
