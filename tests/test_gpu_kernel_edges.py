@@ -405,3 +405,9 @@ def test_ffn_shared_last_round(counts):
     """Short items after a round of big ones (four column blocks, 256 compute units), which all XCDs share at the end: as many as
     a round, one tile, more, and just under a round of big items."""
     _ffn_against_fp64(1024, 512, counts, len(counts))
+
+
+@pytest.mark.parametrize("counts", [[256] * 64, [256] * 65, [256] * 32 + [64] * 32, [256] * 32 + [64] * 33, [33] * 64, [200] * 63])
+def test_ffn_about_an_item_per_compute_unit(counts):
+    """Four column blocks: as many items as compute units, after which no block looks for another one, a few less and more."""
+    _ffn_against_fp64(1024, 512, counts, len(counts))
