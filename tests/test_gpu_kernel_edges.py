@@ -400,11 +400,21 @@ def test_ffn_few_tokens_on_experts_without_a_bound(counts):
     _ffn_against_fp64(256, 384, counts + [0] * (32 - len(counts)), sum(counts))
 
 
-@pytest.mark.parametrize("counts", [[276] * 66, [256] * 64 + [1], [256, 40] * 64 + [33] * 12, [257] * 63])
+@pytest.mark.parametrize("counts", [[276] * 66, [256] * 64 + [1], [256, 40] * 64, [256, 40] * 64 + [33] * 12, [257] * 63])
 def test_ffn_shared_last_round(counts):
-    """Short items after a round of big ones (four column blocks, 256 compute units), which all XCDs share at the end: as many as
-    a round, one tile, more, and just under a round of big items."""
+    """Short items after a round of big ones (four column blocks, 256 compute units), which all XCDs share at the end: eight more
+    than a round, one tile, exactly a round, more, and just under a round of big items, where none are shared."""
     _ffn_against_fp64(1024, 512, counts, len(counts))
+
+
+@pytest.mark.parametrize("d,h,counts", [
+    (768, 384, [256] * 86 + [21] * 40), (768, 384, [256] * 86 + [64]), (768, 384, [256] * 86 + [33] * 90),
+    (1280, 640, [256, 21] * 52), (256, 128, [512] * 57 + [256] * 143 + [64] * 56),
+])
+def test_ffn_blocks_that_start_in_the_shared_round(d, h, counts):
+    """257 to 260 big items: 33 per XCD leave the last one with fewer positions than compute units, and its other blocks begin
+    with shared items: fewer of these than such blocks, fewer than a round, and more."""
+    _ffn_against_fp64(d, h, counts, len(counts))
 
 
 @pytest.mark.parametrize("counts", [[256] * 64, [256] * 65, [256] * 32 + [64] * 32, [256] * 32 + [64] * 33, [33] * 64, [200] * 63])
