@@ -6,6 +6,7 @@
 // Here a block has 32 weight rows, and two blocks of four independent waves share a compute unit: 8 x 2048 x 1024, one
 // row each, gate/up 24.4 -> 11.1 us, down 14.9 -> 7.2 us; 64 x 4096 x 1408, 16 tokens, 205 -> 179 and 107 -> 88 us
 // (7.0 TB/s; without the non-temporal policy on the weights 201 and 101).
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -197,9 +198,11 @@ struct ThinTile {
 };
 
 // An expert may have more than 64 rows (see ffn_is_thin; and expert_offset is the caller's: in a plan from elsewhere also more
-// than the capacity leaves it), and then has big tiles too.  So the blocks walk the joint list, as often around as it takes.  A tile of more than 32 rows is done in passes of its blocks over
-// the same weights, which stay in the L2 for them (64 tokens top-6, 64 x 4096 x 1408, 56 rows on one expert 210 -> 187 us,
-// 64 top-2, 8 x 4096 x 1024, 53 rows 53 -> 47).
+// than the capacity leaves it), and then has big tiles too.  So the blocks walk the joint list, as often around as it takes.
+// A tile of more than 32 rows is done in passes of its blocks over the same weights, which are fetched to be kept: the passes
+// after the first find them in the L2 or, where the blocks that run together have more of them than its 4 MB, in the
+// memory-side cache (64 tokens top-6, 64 x 4096 x 1408, 56 rows on one expert 210 -> 187 us, 64 top-2, 8 x 4096 x 1024, 53 rows
+// 53 -> 47).
 template <bool SWIGLU, bool STREAM>
 __global__ __launch_bounds__(64 * kThinWaves, 2) void ffn_thin_kernel(
     const uint16_t* __restrict__ A, const uint16_t* __restrict__ B0, const uint16_t* __restrict__ B1,
@@ -237,14 +240,22 @@ static long long rows_bound(const moe_desc_t& d, const Sizes& s) {
 // With more rows a block fetches as many activations as weights and loses (256 tokens, 24 rows per expert 382 -> 393),
 // except where the wide blocks are too few to fill half the chip: 64 tokens, 16 x 4096 x 512, 24 rows 90 -> 77 us, but
 // 8 x 4096 x 1024, 64 rows 97 -> 101 and x 2048 126 -> 176.
-// Where the capacity lets an expert have more than 64 rows, what it gets is not known here.  With 8 rows on average or fewer
-// most experts still have few and the others take several passes: 70 tokens top-1, 32 x 1792 x 2304, even and skewed,
-// 115 -> 83 and 80 -> 54 us, 160, all on one expert, 97 -> 54, 256 top-1, 64 x 2048 x 1408 97 -> 81, top-2 140 -> 134, 200 top-2,
-// 48 x 4096 x 2048 256 -> 251, 256 top-1, 32 x 3072 x 3072 215 -> 218; with more rows or tokens they lose (320 top-2, 60 x 2048 x
-// 1408 120 -> 132, 128 top-6, 64 x 4096 x 1408 338 -> 349, 512 top-2, 128 x 1024 x 768 82 -> 90).
+// Where the capacity lets an expert have more than 64 rows, what it gets is not known here, and a tile of 256 rows is eight
+// passes over the expert's weights.  With at most 256 rows in all, 8 on average, this is faster however they lie, as long as the
+// weights that all tokens may share stay below 48 MB (the passes after the first then come from the caches) and the wide blocks
+// do not split K either: tokens dealt evenly, half of them on one expert, all on one: 72 top-1, 16 x 4096 x 2048, 173, 155, 82 ->
+// 125, 128, 37 us for both products; 256 top-1, 32 x 4096 x 2048, 276, 275, 119 -> 248, 270, 88, 128 x 4096 x 2048, 901, 633, 120 ->
+// 840, 630, 88, 256 x 2048 x 768, 258, 162, 66 -> 252, 146, 46; 128 top-2, 64 x 2048 x 2048, 248, 233, 65 -> 237, 226, 41.
+// Above each bound some plan loses: 256 top-1, 32 x 4096 x 4096, half on one 524 -> 557, 32 x 4096 x 14336, all on one
+// 149 -> 474; 256 top-2, 96 x 2048 x 1024, 181 -> 192, 160 top-3, 64 x 2048 x 1024, over twelve experts 53 -> 57;
+// 256 top-1, 32 x 8192 x 1024, all on one 82 -> 118, 32 x 1024 x 8192 72 -> 99.
 bool ffn_is_thin(const moe_desc_t& d, const Sizes& s) {
     if (d.dtype != MOE_DTYPE_BF16) return false;
-    if (rows_bound(d, s) > kFfnTileSmall) return d.n_tokens <= 256 && s.max_rows <= 8ll * d.n_experts;
+    if (rows_bound(d, s) > kFfnTileSmall) {
+        const long long n = d.n_tokens, rows = std::max<long long>(s.max_rows, n);
+        return rows <= 256 && s.max_rows <= 8ll * d.n_experts && d.d_model / 64 < kFfnSplitMinK && d.d_hidden / 64 < kFfnSplitMinK &&
+               rows * d.d_model * d.d_hidden <= n << 23;
+    }
     if (s.max_rows <= 16ll * d.n_experts) return true;
     return s.max_rows <= 24ll * d.n_experts && (long long)d.n_experts * (d.d_hidden / 128) <= 128;
 }
