@@ -67,7 +67,9 @@ constexpr int kFfnSplitUnits = 256;      // most units of cut items in one launc
 constexpr int kFfnSplitMaxSlices = 8;    // most units per item
 constexpr int kFfnSplitMinSlabs = 16;    // fewest 64-wide K slabs per unit
 constexpr int kFfnSplitMinK = 128;       // GEMMs with fewer K slabs are never cut: a unit costs a fixed ~30 us on top of
-                                         // its slabs (partial tile out, ticket, the sum), an item of 64 slabs only 100 us
+                                         // its slabs (partial tile out, ticket, the sum), an item of 64 slabs only 100 us.
+                                         // (Drawn with a block per item.  With blocks that stay a full tile's unit takes 11 us
+                                         // on average for that, the one that adds 27 to 49; the line was not drawn again.)
 constexpr int kFfnSplitHdr = 8;          // ints per GEMM in the schedule's header
 constexpr int kFfnJointMinRounds = 8;    // work items per compute unit from which an uncut GEMM walks the joint tile
                                          // list (measured: 16 and 20 rounds gain 2 %, 3 rounds lose 7 %, 5 neither)
@@ -79,7 +81,6 @@ struct TileList {
     int32_t* rows;    // [max_tiles] valid rows in the tile
     int32_t* count;   // [1]
     int max_tiles;    // capacity of the arrays
-    int max_launch;   // most tiles a launch can find in the list, per column block
     int tile_m;
 };
 struct FfnWorkspace {

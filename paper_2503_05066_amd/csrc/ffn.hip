@@ -446,11 +446,11 @@ __device__ inline void decode_item(int logical, int nt, int col_group, int& tile
 //
 // Otherwise the two lists one after the other: the XCD's eighth of the big items, then its eighth of the short
 // ones (longest first; ordered by height instead, with an eighth of every height for each XCD, the items that stream weights
-// no longer ran beside those that multiply: 279 -> 297 and 419 -> 456 us).  The last split_hdr[0] big items of an XCD's share run as split_hdr[1] units each; the
-// units follow the XCD's whole items, slice by slice, so that the units that run together read
-// the same K range of the tiles they share.  A GEMM too short in K to be cut there runs the few big items left over
-// after the XCD's last full round (split_hdr[6]) as kFfnRowPieces quarters of their rows each: twice the compute-unit time,
-// on compute units that would have idled, in half the item's time.
+// no longer ran beside those that multiply: 279 -> 297 and 419 -> 456 us).  The last split_hdr[0] big items of an XCD's
+// share run as split_hdr[1] units each; the units follow the XCD's whole items, slice by slice, so that the units that run
+// together read the same K range of the tiles they share.  A GEMM too short in K to be cut there runs the few big items left
+// over after the XCD's last full round (split_hdr[6]) as kFfnRowPieces quarters of their rows each: twice the compute-unit
+// time, on compute units that would have idled, in half the item's time.
 //
 // The last split_hdr[5] items of the order (of the joint list, or of the short items) are not dealt out in eighths: whichever
 // XCD has a compute unit free takes the next one, so that an XCD that runs a few per cent slower than the others
@@ -712,7 +712,7 @@ __device__ __forceinline__ void wait_for_all_but(int n) {
 // the short items: at most kFfnSplitUnits / 8 - 1 items of an XCD are cut (what is left after full rounds).
 constexpr int kXcdTicket = kFfnSplitUnits / 8 - 1, kPoolTicket = kFfnSplitUnits + kFfnSplitUnits / 8 - 1;
 
-// One block per compute unit, for the whole launch: it requests the first two slabs of its next item before it writes the
+// One block per compute unit, for the whole launch: it requests the first slabs of its next item before it writes the
 // output of the last, so that an item's start (its tile's description, then the first slabs: two to four microseconds in which
 // a block of its own would only wait) hides behind the output of the one before, and no blocks without work have to be
 // started and ended on every compute unit.  With a block per item and the output through LDS an item of 256 rows and 32 slabs
@@ -884,7 +884,7 @@ static void launch_bf16(bool stream, const void* A, const void* B0, const void* 
     // a block per compute unit, the same number on every XCD; fewer where the plan cannot hold as many items (an item cut
     // along K or into row pieces is eight at most)
     const int per_xcd = std::max(1, compute_units() / 8);
-    const long long items = (long long)kFfnSplitMaxSlices * nb * ((long long)ws.big.max_launch + ws.small.max_launch);
+    const long long items = (long long)kFfnSplitMaxSlices * nb * ((long long)ws.big.max_tiles + ws.small.max_tiles);
     const int grid = 8 * (int)std::min<long long>(per_xcd, (items + 7) / 8);
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(S::kThreads), S::kLdsBytes, st, (const uint16_t*)A,
                        (const uint16_t*)B0, (const uint16_t*)B1, (uint16_t*)C, gather, tile_list_args(ws, true), K, Nout,

@@ -40,15 +40,13 @@ struct SplitArgs {
 struct TileListArgs {
     int32_t *b_expert, *b_row0, *b_rows, *b_count, *s_expert, *s_row0, *s_rows, *s_count;
     int b_max, s_max;
-    // both kinds in one list, expert by expert (an expert's big tiles, then its short ones); a short tile's row
-    // count carries kShortTileFlag.  u_max == 0: not written.
+    // both kinds in one list, expert by expert (an expert's big tiles, then its short ones).  u_max == 0: not written.
     int32_t *u_expert, *u_row0, *u_rows, *u_count;
     int u_max;
 };
-// Flags beside a tile's row count (tile heights are far below them).
-constexpr int kShortTileFlag = 1 << 16;  // joint list: a short tile
+// A flag beside a tile's row count (tile heights are far below it).
 constexpr int kAloneTileFlag = 1 << 17;  // its expert's only tile
-constexpr int kTileRowsMask = kShortTileFlag - 1;
+constexpr int kTileRowsMask = kAloneTileFlag - 1;
 
 struct ExpertTiles {
     int lo, rows, nb, ns;
@@ -215,7 +213,7 @@ __device__ inline void build_ffn_schedule(const int32_t* expert_offset, const Ff
                 L.u_expert[ui] = e;
                 L.u_row0[ui] = x.lo + full * big + i * small;
                 const int left = rem - i * small;
-                L.u_rows[ui] = (left < small ? left : small) | kShortTileFlag | flag;
+                L.u_rows[ui] = (left < small ? left : small) | flag;
             }
         }
     }
