@@ -78,7 +78,8 @@ __device__ __forceinline__ void each(F&& f) {
 // them between the loops for the different tile heights (and knows neither the instruction inside an asm statement nor the
 // wait states it asks for).  So they have fixed places, named in the statements: fragment F in a[4F .. 4F+3].  The compiler
 // itself uses none of these registers (it has 256 others, and the kernels need no more; the kernel's first statement
-// makes it count them; the build ends if its output shows otherwise, see accumulators.py).  The code that reads them after the last matrix instruction waits out its latency itself.
+// makes it count them; the build ends if its output shows otherwise, see accumulators.py).  The code that reads them after
+// the last matrix instruction waits out its latency itself.
 template <int F>
 __device__ __forceinline__ void acc_mfma(const bf16x8& a, const bf16x8& b) {
     asm volatile("v_mfma_f32_16x16x32_bf16 a[%0:%1], %2, %3, a[%0:%1]" ::"n"(4 * F), "n"(4 * F + 3), "v"(a), "v"(b));
